@@ -2,16 +2,17 @@
 """Benchmark of the slice-spraying hot path on one MI355X.
 
 One step = tent_plan (extent scans, slice scan, slice-table expansion, rail binding) followed by
-tent_execute (gather into per-rail staging, scatter to destination) over one freshly declared
+tent_execute (every source byte into its rail's staging region and to its destination) over one freshly declared
 batch of the KVCache-migration workload; descriptor tables and byte pools are resident in HBM
 before the timed region starts.  The K timed steps run twice: on a single stream, and with the
 plans on a second stream so that step k+1's binding (a one-wavefront dependency chain) runs under
 step k's copies; the second figure is the headline unless --single-stream is given, both are
 printed.  Prints ONE JSON line.
 
-  value        read+write GB/s of the whole step: 4 * payload * steps / elapsed
-  roofline     the slower of the two copy kernels (gather: source pages -> staging, scatter: staging ->
-               destination): 2 * payload bytes per launch against HBM peak, duration from HIP events
+  value        read+write GB/s of the whole step: 3 * payload * steps / elapsed (the copy reads every payload byte once and
+               writes it twice, to staging and to the destination; while the scatter still read the staging
+               regions back the factor was 4, so compare ms_per_step or payload_GBps with older lines)
+  roofline     the copy kernel: 3 * payload bytes per launch against HBM peak, duration from HIP events
                recorded on the launch stream around every launch inside the timed region
   configs      the same two timed passes, shorter, for the other workloads (tiny, rl_params, many_small,
                many_small_x6; the re-planning workload is the `replanning` entry)
@@ -32,6 +33,7 @@ import time
 import numpy as np
 
 HBM_PEAK_GBPS = 8000.0
+MOVED = 3                        # bytes the copy moves per payload byte: source read, staging written, destination written
 ALL_LEGS = ("configs", "declare", "concurrent", "feedback", "recovery", "replanning", "dispatch", "bounded", "graph")
 
 # HBM bytes per copy launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (scaled by the
@@ -42,13 +44,10 @@ PMC_SOURCES = ("copy.hip", "copy_generic.h", "split.hip", "tile_tables.h")
 PMC_TRAFFIC = {
     "copy_sources_sha256": "40cb27ddb00ff4ebb63f4a50cccb998e176129192c040f14719fefbf480c15aa",
     # bytes read + bytes written per launch (profiles/copy_kernels_hbm_traffic.txt)
-    "kv_migration": {"gather": 43019356871, "scatter": 43019353287},
-    "rl_params": {"gather": 30488282590, "scatter": 30488290142},
-    "many_small_x6": {"gather": 33592918724, "scatter": 33592915140},
 }
 
 
-def measured_traffic(workload, kernel):
+def measured_traffic(workload):
     import hashlib
     csrc = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2604_00368_amd", "csrc")
     try:
@@ -57,7 +56,7 @@ def measured_traffic(workload, kernel):
         return None
     if digest != PMC_TRAFFIC["copy_sources_sha256"]:
         return None
-    return PMC_TRAFFIC.get(workload, {}).get(kernel)
+    return PMC_TRAFFIC.get(workload)
 
 
 def parse():
@@ -306,18 +305,16 @@ class Run:
 def summarize(w, n_slices, steps, elapsed_single, tm_single, elapsed_piped, tm_piped):
     """Compact record of one workload's two timed passes."""
     plan_ms = sum(tm_single[n][0] for n in ("extent_scan", "slice_scan", "expand", "compact", "bind")) / max(1, steps)
-    g_ms, g_n = tm_piped["gather"]
-    s_ms, s_n = tm_piped["scatter"]
-    g_avg, s_avg = g_ms / max(1, g_n), s_ms / max(1, s_n)
+    copy_avg = tm_piped["gather"][0] / max(1, tm_piped["gather"][1])
     ms1, ms2 = elapsed_single * 1e3 / steps, elapsed_piped * 1e3 / steps
-    value = 4 * w.payload / (ms2 * 1e-3) / 1e9
+    value = MOVED * w.payload / (ms2 * 1e-3) / 1e9
     return {"payload_bytes": w.payload, "n_slices": n_slices, "slice_bytes": w.slice_bytes,
             "n_rails": int(w.rails.shape[0]), "steps": steps,
             "ms_per_step_single_stream": round(ms1, 4), "ms_per_step_two_streams": round(ms2, 4),
             "GBps": round(value, 1), "pct_of_hbm_peak": round(100 * value / HBM_PEAK_GBPS, 2),
             "plan_ms": round(plan_ms, 4), "slices_planned_per_s": round(n_slices / (plan_ms * 1e-3), 1) if plan_ms > 0 else None,
-            "gather_GBps": round(2 * w.payload / (g_avg * 1e-3) / 1e9, 1),
-            "scatter_GBps": round(2 * w.payload / (s_avg * 1e-3) / 1e9, 1)}
+            "payload_GBps": round(w.payload / (ms2 * 1e-3) / 1e9, 1),
+            "copy_GBps": round(MOVED * w.payload / (copy_avg * 1e-3) / 1e9, 1)}
 
 
 def ceilings(args):
@@ -359,8 +356,7 @@ def ceilings(args):
     for name, w in ws.items():
         r = Run(T, W, torch, dev, w, (src, arena, dst), 4, 1, T.TENT_FLAG_PROFILE)
         dt, tm = r.timed_pass(r.step_single)
-        out[f"engine_{name}_gather"] = round(2 * w.payload / (tm["gather"][0] / tm["gather"][1] * 1e-3) / 1e9, 1)
-        out[f"engine_{name}_scatter"] = round(2 * w.payload / (tm["scatter"][0] / tm["scatter"][1] * 1e-3) / 1e9, 1)
+        out[f"engine_{name}_copy"] = round(MOVED * w.payload / (tm["gather"][0] / tm["gather"][1] * 1e-3) / 1e9, 1)
         out[f"engine_{name}_verified"] = r.verify()
         r.close()
     print(json.dumps({"ceilings": out}))
@@ -388,11 +384,9 @@ def sweep(args):
             r = Run(T, W, torch, dev, w, (src, arena, dst), 4, 1, T.TENT_FLAG_PROFILE)
             dt, tm = r.timed_pass(r.step_single)
             plan = sum(tm[k][0] for k in ("extent_scan", "slice_scan", "expand", "compact", "bind")) / 4
-            g, s = tm["gather"][0] / tm["gather"][1], tm["scatter"][0] / tm["scatter"][1]
+            copy = tm["gather"][0] / tm["gather"][1]
             rows.append({"layout": "paged_32KiB" if paged else "contiguous", "slice_KiB": kib, "slices": r.n_slices,
-                         "plan_ms": round(plan, 4), "gather_GBps": round(2 * w.payload / g / 1e6, 0),
-                         "scatter_GBps": round(2 * w.payload / s / 1e6, 0),
-                         "execute_GBps": round(4 * w.payload / (g + s) / 1e6, 0)})
+                         "plan_ms": round(plan, 4), "copy_GBps": round(MOVED * w.payload / copy / 1e6, 0)})
             r.close()
     print(json.dumps({"sweep": {"payload_bytes": payload, "placement": layout.mode, "rows": rows}}))
 
@@ -530,8 +524,8 @@ def main():
             T.tent_release(ctx, h)
         T.tent_get_timings(ctx)
         with_declare = {"ms_per_step": round(dt * 1e3 / args.steps, 4),
-                        "GBps": round(4 * w.payload * args.steps / dt / 1e9, 1),
-                        "pct_of_hbm_peak": round(100 * 4 * w.payload * args.steps / dt / 1e9 / HBM_PEAK_GBPS, 2),
+                        "GBps": round(MOVED * w.payload * args.steps / dt / 1e9, 1),
+                        "pct_of_hbm_peak": round(100 * MOVED * w.payload * args.steps / dt / 1e9 / HBM_PEAK_GBPS, 2),
                         "declare_host_ms_per_call": round(host[0] * 1e3 / args.steps, 4), "complete": bool(ok_left),
                         "verified": run.verify()}
 
@@ -608,14 +602,14 @@ def main():
         dt, tm_r, passes = min(seqs, key=lambda x: x[0])
         copy_ms = tm_r["gather"][0] + tm_r["scatter"][0]
         replanning = {"passes": passes, "total_ms": round(dt * 1e3, 3),
-                      "GBps": round(4 * w.payload / dt / 1e9, 2),
-                      "pct_of_hbm_peak": round(100 * 4 * w.payload / dt / 1e9 / HBM_PEAK_GBPS, 2),
+                      "GBps": round(MOVED * w.payload / dt / 1e9, 2),
+                      "pct_of_hbm_peak": round(100 * MOVED * w.payload / dt / 1e9 / HBM_PEAK_GBPS, 2),
                       "plan_ms_total": round(sum(tm_r[k][0] for k in ("extent_scan", "slice_scan", "expand",
                                                                         "compact", "bind")), 3),
                       "plan_stage_ms": {k: round(tm_r[k][0], 3) for k in ("extent_scan", "slice_scan", "expand",
                                                                                "compact", "bind")},
                       "copy_ms_total": round(copy_ms, 3),
-                      "copy_GBps": round(4 * w.payload / (copy_ms * 1e-3) / 1e9, 1),
+                      "copy_GBps": round(MOVED * w.payload / (copy_ms * 1e-3) / 1e9, 1),
                       "verified": run.verify()}
         T.tent_reset(ctx, h_fb, stream)
 
@@ -659,7 +653,7 @@ def main():
                     best = ms if best is None else min(best, ms)
                 assert T.tent_poll(ctx_b, h_b, stream) == 0
                 bounded.append({"slot_MiB": chunk >> 20, "slots": slots, "chunks": -(-w.payload // chunk),
-                                "execute_ms": round(best, 4), "GBps": round(4 * w.payload / (best * 1e-3) / 1e9, 2)})
+                                "execute_ms": round(best, 4), "GBps": round(MOVED * w.payload / (best * 1e-3) / 1e9, 2)})
         T.tent_destroy(ctx_b)
 
     log("dispatch / bounded legs done")
@@ -715,15 +709,10 @@ def main():
 
     # plan stages are timed on the single-stream pass, where nothing runs beside them
     plan_ms = sum(tm_single[n][0] for n in ("extent_scan", "slice_scan", "expand", "compact", "bind")) / max(1, args.steps)
-    gather_ms, gather_n = tm["gather"]
-    scatter_ms, scatter_n = tm["scatter"]
-    gather_avg = gather_ms / max(1, gather_n)
-    scatter_avg = scatter_ms / max(1, scatter_n)
+    copy_avg = tm["gather"][0] / max(1, tm["gather"][1])
     ms_per_step = elapsed * 1e3 / args.steps
-    value = 4 * w.payload / (ms_per_step * 1e-3) / 1e9
-    # the roofline entry describes the slower of the two copy launches
-    dom, dom_avg = ("scatter", scatter_avg) if scatter_avg >= gather_avg else ("gather", gather_avg)
-    achieved = 2 * w.payload / (dom_avg * 1e-3) / 1e9
+    value = MOVED * w.payload / (ms_per_step * 1e-3) / 1e9
+    achieved = MOVED * w.payload / (copy_avg * 1e-3) / 1e9
     run.close()
 
     # The other workloads, each through the same two timed passes (fewer steps), in the same pools.
@@ -747,7 +736,7 @@ def main():
         e3, _ = ro.timed_pass(step_two_plan_streams_o)
         ms3 = e3 * 1e3 / steps_o
         rec["ms_per_step_two_plan_streams"] = round(ms3, 4)
-        rec["pct_of_hbm_peak_two_plan_streams"] = round(100 * 4 * wo.payload / (ms3 * 1e-3) / 1e9 / HBM_PEAK_GBPS, 2)
+        rec["pct_of_hbm_peak_two_plan_streams"] = round(100 * MOVED * wo.payload / (ms3 * 1e-3) / 1e9 / HBM_PEAK_GBPS, 2)
         rec["declare_host_ms"] = round(ro.declare_host_ms, 3)
         rec["verified"] = ro.verify()
         configs.append(rec)
@@ -782,7 +771,7 @@ def main():
                                             "value": round(n_slices * len(batches) / concurrent_plan_s, 1)},
         "stage_ms": {k: round(v[0] / max(1, args.steps), 4) for k, v in tm.items()},
         "stage_ms_single_stream": {k: round(v[0] / max(1, args.steps), 4) for k, v in tm_single.items()},
-        "execute_GBps": round(4 * w.payload / ((gather_avg + scatter_avg) * 1e-3) / 1e9, 2),
+        "payload_GBps": round(w.payload / (ms_per_step * 1e-3) / 1e9, 2),
         "declare_ms": round(declare_ms, 3),
         "configs": configs,
         "feedback": {"window_slices": n_slices, "ms_per_window": round(fb_ms / max(1, fb_n), 4),
@@ -796,13 +785,11 @@ def main():
         "bounded_staging": bounded,
         "graph_replay_ms_per_step": None if graph_ms is None else round(graph_ms, 4),
         "plain_copy_GBps": round(plain_copy_GBps, 2),
-        "roofline": {"bound": "hbm", "kernel": "ordered_copy_kernel<%s>" % ("true" if dom == "gather" else "false"), "achieved": round(achieved, 2),
+        "roofline": {"bound": "hbm", "kernel": "one_pass_copy_kernel", "achieved": round(achieved, 2),
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
-                     "traffic": measured_traffic(args.workload, dom),
-                     "algorithmic_bytes_per_launch": 2 * w.payload,
-                     "avg_launch_ms": round(dom_avg, 4),
-                     "gather_GBps": round(2 * w.payload / (gather_avg * 1e-3) / 1e9, 2),
-                     "scatter_GBps": round(2 * w.payload / (scatter_avg * 1e-3) / 1e9, 2)},
+                     "traffic": measured_traffic(args.workload),
+                     "algorithmic_bytes_per_launch": MOVED * w.payload,
+                     "avg_launch_ms": round(copy_avg, 4)},
     }
     del src, dst, arena, pools, pools3, run
     if not args.no_cpu_baseline:

@@ -169,8 +169,8 @@ enum {
     TENT_T_EXPAND      = 2,    /* slice-table expansion                                           */
     TENT_T_COMPACT     = 3,    /* pending-list compaction (re-planning only)                      */
     TENT_T_BIND        = 4,    /* rail assignment                                                 */
-    TENT_T_GATHER      = 5,    /* paged source -> staging                                         */
-    TENT_T_SCATTER     = 6,    /* staging -> destination                                          */
+    TENT_T_GATHER      = 5,    /* paged source -> staging (and destination, where one launch does both) */
+    TENT_T_SCATTER     = 6,    /* staging -> destination, where it is a launch of its own         */
     TENT_T_FEEDBACK    = 7,    /* bandwidth probe over the completed slices (tent_update_bandwidth) */
     TENT_T_COUNT       = 8
 };
@@ -388,8 +388,11 @@ int tent_get_latencies(tent_ctx *ctx, tent_batch_t batch, uint64_t *host_out, ui
  * Move every BOUND slice: gather its bytes from the paged source extents into
  * its rail's staging region, then scatter from staging to the destination
  * extents at the slice's absolute offset (Section 4.1 staging hop; Section 4.4
- * direct-to-offset writes), and mark it DONE.  Enqueues on `stream` and
- * returns; the caller synchronises the stream or polls.  The DONE marks are enqueued
+ * direct-to-offset writes), and mark it DONE.  Where the batch passed the overlap check and the
+ * staging arena shares no byte with a registered segment, both steps are one pass: every source byte is
+ * read once and stored to staging and to the destination.  With TENT_FLAG_SKIP_OVERLAP_CHECK, or an arena inside a
+ * segment, the gather ends before the scatter begins, so a destination may then reuse source bytes.
+ * Enqueues on `stream` and returns; the caller synchronises the stream or polls.  The DONE marks are enqueued
  * ahead of the copies (the copies are driven by address tables, not by slice
  * state), which is what lets a re-plan on another stream run beside the copies; tent_poll, on
  * any stream, waits for the end of the copies before it counts, so completion is never reported
@@ -410,15 +413,15 @@ int tent_execute(tent_ctx *ctx, tent_batch_t batch, void *stream);
  * chunk's bytes on rail d form an interval [lo_d, hi_d) of the rail's staging offsets and sit at
  * region_base_d + (offset - lo_d), region_base_d being the exclusive sum over rails of (hi_d - lo_d)
  * rounded up to 256 bytes.  The arena is used as `slots` (1 or 2) slots of chunk_bytes + 256 * n_rails
- * bytes; chunk c lives in slot c mod slots.  With two slots the gather of chunk c + 1 overlaps the
- * scatter of chunk c: gathers are enqueued on `stream`, scatters on a stream of the library's own
- * (default priority), ordered by events, and `stream` is made to wait for the last scatter, so work
+ * bytes; chunk c lives in slot c mod slots.  Where tent_execute would move the batch in one pass (see
+ * there) so does every chunk: one launch stores its bytes to the slot and to the destination, the chunks follow
+ * each other on `stream`, and two slots only change where the bytes lie.  Otherwise, with two slots the gather of
+ * chunk c + 1 overlaps the scatter of chunk c: gathers are enqueued on `stream`, scatters on a stream of the library's
+ * own (default priority), ordered by events, and `stream` is made to wait for the last scatter, so work
  * enqueued on `stream` afterwards sees the batch complete.  Slices are marked DONE as by
  * tent_execute.  Only enqueues.
- * Which to use: one slot.  Both stages of a chunk are bound by the device memory's bandwidth, so
- * overlapping them adds none; measured on MI355X, two slots ran between 5 % faster and 2 % slower
- * than one and need twice the arena.  Two slots are there for a caller whose second stage is not
- * a device copy of its own device's memory.
+ * Which to use: one slot.  Two need twice the arena; they save nothing in one pass, and in two passes both stages
+ * are bound by the device memory's bandwidth (measured on MI355X between 5 % faster and 2 % slower).
  * Lengths and addresses may be anything: when every extent length and the slice size are multiples of
  * 1 KiB the chunks are moved by table-driven copies, otherwise byte-exactly in ranges of 1 KiB of the
  * payload (slower).

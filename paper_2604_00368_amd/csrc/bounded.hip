@@ -22,6 +22,7 @@ namespace {
 
 constexpr uint64_t kNoTile = ~0ull;
 constexpr uint64_t kRegMask = (1ull << 56) - 1;
+constexpr int kBothLanes = 512;
 
 __global__ void __launch_bounds__(256) bounded_clear_kernel(BatchDev b, uint32_t n_chunks)
 {
@@ -36,7 +37,7 @@ __global__ void __launch_bounds__(256) bounded_clear_kernel(BatchDev b, uint32_t
 // Per tile (declaration order): rail and staging offset of its first byte, or kNoTile when its slice is
 // not BOUND; per (chunk, rail): the interval of staging offsets the chunk touches.  A workgroup covers
 // 256 consecutive tiles, which lie in one chunk because a chunk holds a multiple of 256 tiles.
-__global__ void __launch_bounds__(256) bounded_tiles_kernel(BatchDev b, uint64_t chunk_tiles)
+__global__ void __launch_bounds__(256) bounded_tiles_kernel(BatchDev b, uint64_t chunk_tiles, uint64_t* staged)
 {
     __shared__ unsigned long long lo[TENT_MAX_RAILS], hi[TENT_MAX_RAILS];
     if (threadIdx.x < TENT_MAX_RAILS) { lo[threadIdx.x] = kNoTile; hi[threadIdx.x] = 0; }
@@ -53,7 +54,7 @@ __global__ void __launch_bounds__(256) bounded_tiles_kernel(BatchDev b, uint64_t
             atomicMin(&lo[d], (unsigned long long)reg);
             atomicMax(&hi[d], (unsigned long long)(reg + b.tile_bytes));
         }
-        b.ga_lin[q] = code;
+        staged[q] = code;
     }
     __syncthreads();
     if (first < b.n_sc_tiles && threadIdx.x < TENT_MAX_RAILS && lo[threadIdx.x] != kNoTile) {
@@ -82,18 +83,18 @@ __global__ void __launch_bounds__(64) bounded_bases_kernel(BatchDev b, uint64_t 
 // Turn every tile's (rail, staging offset) into its address inside the slot of its chunk (0 = tile not
 // to be moved), so that the copy kernels need no dependent look-ups.
 __global__ void __launch_bounds__(256) bounded_resolve_kernel(BatchDev b, uint64_t chunk_tiles, uint8_t* arena,
-                                                              uint64_t slot_bytes, uint32_t slots)
+                                                              uint64_t slot_bytes, uint32_t slots, uint64_t* staged)
 {
     const uint64_t q = ((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
     if (q >= b.n_sc_tiles) return;
-    const uint64_t c = b.ga_lin[q];
+    const uint64_t c = staged[q];
     uint64_t addr = 0;
     if (c != kNoTile) {
         const uint64_t chunk = q / chunk_tiles;
         const uint64_t row = chunk * TENT_MAX_RAILS + (c >> 56);
         addr = (uint64_t)arena + (chunk % slots) * slot_bytes + b.ch_base[row] + ((c & kRegMask) - b.ch_lo[row]);
     }
-    b.ga_lin[q] = addr;
+    staged[q] = addr;
 }
 
 // Copy the tiles [q_begin, q_end) of one chunk between their paged side and the arena.
@@ -112,8 +113,7 @@ __global__ void __launch_bounds__(kOrderedLanes) bounded_copy_kernel(const uint6
     if (near_tile == 0 || *overflow != 0) return;
     const uint64_t in_tile = at & ((1ull << tile_shift) - 1);
     const uint64_t far = far_tile + in_tile, near = near_tile + in_tile;
-    typedef uint32_t vec4u __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(1))) vec4u vec4u_any __attribute__((aligned(1)));   // device memory, any alignment
+    typedef vec4u_dev vec4u_any;                                  // device memory, any alignment
     // the paged side is streamed (nontemporal); the arena side uses ordinary accesses so that a slot
     // small enough for the memory-side cache can be served from it when the chunk is scattered
     if (kGather) {
@@ -123,6 +123,26 @@ __global__ void __launch_bounds__(kOrderedLanes) bounded_copy_kernel(const uint6
         const vec4u v = *(const vec4u_any*)near;
         __builtin_nontemporal_store(v, (vec4u_any*)far);
     }
+}
+
+// Both directions of a chunk in one launch, where the batch allows one-pass copies (see copy.hip): source -> slot and
+// destination.  Chunks stay ordered by their launches, so the arena ends as with two launches per chunk.
+__global__ void __launch_bounds__(kBothLanes) bounded_both_kernel(const uint64_t* __restrict__ from, const uint64_t* __restrict__ staged,
+                                                           const uint64_t* __restrict__ to, const uint64_t* __restrict__ overflow,
+                                                           uint64_t q_begin, uint64_t q_end, uint32_t tile_shift)
+{
+    const uint64_t w = (uint64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const uint64_t at = w * (kBothLanes * 16) + (uint64_t)threadIdx.x * 16;
+    const uint64_t q = q_begin + (at >> tile_shift);
+    if (q >= q_end) return;
+    const uint64_t src = from[q];
+    const uint64_t lin = staged[q];
+    const uint64_t dst = to[q];
+    if (lin == 0 || *overflow != 0) return;
+    const uint64_t in_tile = at & ((1ull << tile_shift) - 1);
+    const vec4u v = *(const vec4u_dev*)(src + in_tile);
+    __builtin_nontemporal_store(v, (vec4u_dev*)(lin + in_tile));
+    __builtin_nontemporal_store(v, (vec4u_dev*)(dst + in_tile));
 }
 
 // ---- geometry without a tile enumeration: ranges of 1 KiB of the payload -----------------------
@@ -177,8 +197,9 @@ __global__ void __launch_bounds__(256) bounded_ranges_kernel(BatchDev b, uint64_
 }
 
 // Move the BOUND bytes of payload positions [c_lo, c_hi) -- one chunk -- between their paged side and the
-// chunk's slot, one wavefront per range of 1 KiB.
-template <bool kGather>
+// chunk's slot, one wavefront per range of 1 KiB.  kBoth (one-pass copies): the wavefront that gathered a piece scatters
+// it at once, reading back what it has just written.
+template <bool kGather, bool kBoth>
 __global__ void __launch_bounds__(256) bounded_ranges_copy_kernel(BatchDev b, uint64_t c_lo, uint64_t c_hi,
                                                                   uint8_t* slot, uint64_t row)
 {
@@ -196,6 +217,10 @@ __global__ void __launch_bounds__(256) bounded_ranges_copy_kernel(BatchDev b, ui
             const uint32_t d = b.s_rail[i];
             uint8_t* staged = slot + b.ch_base[row + d] + (b.s_stage_off[i] + x - b.ch_lo[row + d]);
             copy_range_generic<kGather>(b, i, x, x + (to - from), staged);
+            if (kBoth) {
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+                copy_range_generic<false>(b, i, x, x + (to - from), staged);
+            }
         }
         if (end >= p1) break;
         ++i;
@@ -234,10 +259,11 @@ hipError_t launch_bounded_prepare(const BatchDev& b, uint64_t payload, uint64_t 
         return hipGetLastError();
     }
     if (!grid_for((b.n_sc_tiles + 255) / 256, &grid)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(bounded_tiles_kernel, grid, dim3(256), 0, s, b, chunk_bytes / b.tile_bytes);
+    uint64_t* staged = b.one_pass ? b.op_lin : b.ga_lin;
+    hipLaunchKernelGGL(bounded_tiles_kernel, grid, dim3(256), 0, s, b, chunk_bytes / b.tile_bytes, staged);
     hipLaunchKernelGGL(bounded_bases_kernel, dim3(n_chunks), dim3(64), 0, s, b, slot_bytes);
     hipLaunchKernelGGL(bounded_resolve_kernel, grid, dim3(256), 0, s, b, chunk_bytes / b.tile_bytes, arena, slot_bytes,
-                       slots);
+                       slots, staged);
     return hipGetLastError();
 }
 
@@ -252,10 +278,12 @@ hipError_t launch_bounded_copy(const BatchDev& b, bool gather, uint32_t chunk, u
         if (!grid_for((c_hi - c_lo + 4 * kRangeBytes - 1) / (4 * kRangeBytes), &grid)) return hipErrorInvalidValue;
         uint8_t* slot = arena + (chunk % slots) * slot_bytes;
         const uint64_t row = (uint64_t)chunk * TENT_MAX_RAILS;
-        if (gather)
-            hipLaunchKernelGGL(bounded_ranges_copy_kernel<true>, grid, dim3(256), 0, s, b, c_lo, c_hi, slot, row);
+        if (b.one_pass)
+            hipLaunchKernelGGL((bounded_ranges_copy_kernel<true, true>), grid, dim3(256), 0, s, b, c_lo, c_hi, slot, row);
+        else if (gather)
+            hipLaunchKernelGGL((bounded_ranges_copy_kernel<true, false>), grid, dim3(256), 0, s, b, c_lo, c_hi, slot, row);
         else
-            hipLaunchKernelGGL(bounded_ranges_copy_kernel<false>, grid, dim3(256), 0, s, b, c_lo, c_hi, slot, row);
+            hipLaunchKernelGGL((bounded_ranges_copy_kernel<false, false>), grid, dim3(256), 0, s, b, c_lo, c_hi, slot, row);
         return hipGetLastError();
     }
     uint32_t tile_shift = 0;
@@ -266,8 +294,12 @@ hipError_t launch_bounded_copy(const BatchDev& b, bool gather, uint32_t chunk, u
     const uint64_t q_end = q_begin + chunk_tiles < b.n_sc_tiles ? q_begin + chunk_tiles : b.n_sc_tiles;
     const uint64_t bytes = (q_end - q_begin) << tile_shift;
     dim3 grid;
-    if (!grid_for((bytes + kOrderedLanes * 16 - 1) / (kOrderedLanes * 16), &grid)) return hipErrorInvalidValue;
-    if (gather)
+    const uint64_t lanes = b.one_pass ? kBothLanes : kOrderedLanes;
+    if (!grid_for((bytes + lanes * 16 - 1) / (lanes * 16), &grid)) return hipErrorInvalidValue;
+    if (b.one_pass)
+        hipLaunchKernelGGL(bounded_both_kernel, grid, dim3(kBothLanes), 0, s, b.op_src, b.op_lin, b.op_dst,
+                           &b.plan->bounded_overflow, q_begin, q_end, tile_shift);
+    else if (gather)
         hipLaunchKernelGGL(bounded_copy_kernel<true>, grid, dim3(kOrderedLanes), 0, s, b.ga_src, b.ga_lin,
                            &b.plan->bounded_overflow, q_begin, q_end, tile_shift);
     else

@@ -162,6 +162,197 @@ hipError_t launch_copy_compact(const BatchDev& b, bool gather, uint64_t max_tile
     return hipGetLastError();
 }
 
+// ---- one pass: source -> staging and destination ----------------------------------------------------
+// Every source byte is read once and stored twice, so that the scatter's read of the staging region (a quarter of
+// the two-pass traffic) falls away.  Allowed where no destination byte is a source byte of the batch (the overlap check
+// passed) and the arena lies outside the segments; the two kernels above stay for every other batch.
+// HBM-bound.  8 GiB on MI355X, ordinary allocations, two passes -> one pass: 32 KiB pages shuffled on both sides
+// 6.02 -> 4.57 ms (5.6 TB/s of the 3 bytes per payload byte it moves), contiguous tensors 5.76 -> 4.00 ms (6.4 TB/s),
+// 4.5 GiB of 18 KiB pages in 2 KiB tiles 3.32 -> 2.66 ms.  Order: ascending destination address (declaration order, one
+// frontier per rail but scattered destination pages: 2-4 % slower on pages, the same on tensors).  Ordinary
+// loads with nontemporal stores: nontemporal loads 5-10 % slower, ordinary stores 4-8 %.  512 lanes: 64, 128,
+// 256 and 1024 lanes 1-5 % slower.  A look-up of (slice record, offset) in place of the staging table: 6 % slower.
+constexpr int kOnePassLanes = 512;
+
+__device__ __forceinline__ void copy_to_both(const uint64_t* __restrict__ from, const uint64_t* __restrict__ mid,
+                                             const uint64_t* __restrict__ to, uint64_t n_tiles, uint32_t tile_shift)
+{
+    const uint64_t w = (uint64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const uint64_t at = w * (kOnePassLanes * 16) + (uint64_t)threadIdx.x * 16;
+    const uint64_t q = at >> tile_shift;
+    if (q >= n_tiles) return;
+    const uint64_t src = from[q];
+    const uint64_t lin = mid[q];
+    const uint64_t dst = to[q];
+    if (lin == 0) return;
+    const uint64_t in_tile = at & ((1ull << tile_shift) - 1);
+    const vec4u v = *(const vec4u_dev*)(src + in_tile);
+    __builtin_nontemporal_store(v, (vec4u_dev*)(lin + in_tile));
+    __builtin_nontemporal_store(v, (vec4u_dev*)(dst + in_tile));
+}
+
+__global__ void __launch_bounds__(kOnePassLanes) one_pass_copy_kernel(const uint64_t* __restrict__ from,
+                                                                      const uint64_t* __restrict__ mid,
+                                                                      const uint64_t* __restrict__ to, uint64_t n_tiles,
+                                                                      uint32_t tile_shift)
+{
+    copy_to_both(from, mid, to, n_tiles, tile_shift);
+}
+
+// Over a list of tiles whose length only the device knows; the grid covers the host's bound on it.
+__global__ void __launch_bounds__(kOnePassLanes) one_pass_list_copy_kernel(const uint64_t* __restrict__ from,
+                                                                           const uint64_t* __restrict__ mid,
+                                                                           const uint64_t* __restrict__ to,
+                                                                           const uint64_t* __restrict__ n_act,
+                                                                           uint32_t tile_shift)
+{
+    copy_to_both(from, mid, to, *n_act, tile_shift);
+}
+
+typedef __attribute__((address_space(1))) uint8_t byte_dev;
+
+// Bytes [lo, hi) of slice i, at most 1 KiB, between the extents they lie in and a wavefront's 1 KiB of LDS (offset
+// 0 = byte lo).  Every piece is one round of loads: bytes up to the next 16-byte boundary of the LDS side, whole
+// vectors (aligned in LDS, at any address in the extent), bytes behind them.
+template <bool kToLds>
+__device__ __forceinline__ void walk_cut_side(const BatchDev& b, uint64_t i, uint32_t lo, uint32_t hi, vec4u* lds)
+{
+    const uint32_t*    ptr = kToLds ? b.src_ptr : b.dst_ptr;
+    const tent_extent* ext = kToLds ? b.src_ext : b.dst_ext;
+    const uint64_t*    pre = kToLds ? b.src_pre : b.dst_pre;
+    const uint32_t     e0  = kToLds ? b.s_src_e0[i] : b.s_dst_e0[i];
+    const uint32_t j = b.s_desc[i];
+    uint64_t pos = pre[ptr[j]] + b.s_off[i] + lo;                // position in the batch-wide extent prefix
+    const uint64_t end = pos + (hi - lo);
+    uint32_t e = last_not_above32(pre, e0, ptr[j + 1], pos);
+    uint8_t* bytes = (uint8_t*)lds;
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t at = 0;
+    while (pos < end) {
+        const uint64_t e_end = pre[e + 1];
+        const uint32_t n = (uint32_t)((e_end < end ? e_end : end) - pos);
+        const tent_extent x = ext[e];
+        const uint64_t paged = b.seg_base[x.seg] + x.off + (pos - pre[e]);
+        uint32_t head = (16u - (at & 15u)) & 15u;
+        if (head > n) head = n;
+        const uint32_t n_vec = (n - head) >> 4, tail = (n - head) & 15u;
+        const bool do_head = lane < head, do_vec = lane < n_vec, do_tail = lane < tail;
+        const uint32_t o_head = lane, o_vec = head + lane * 16u, o_tail = n - tail + lane;
+        if (kToLds) {
+            uint8_t h = 0, g = 0;
+            vec4u v;
+            if (do_head) h = *(const byte_dev*)(paged + o_head);
+            if (do_vec) v = *(const vec4u_dev*)(paged + o_vec);
+            if (do_tail) g = *(const byte_dev*)(paged + o_tail);
+            if (do_head) bytes[at + o_head] = h;
+            if (do_vec) lds[(at + o_vec) >> 4] = v;
+            if (do_tail) bytes[at + o_tail] = g;
+        } else {
+            if (do_head) *(byte_dev*)(paged + o_head) = bytes[at + o_head];
+            if (do_vec) *(vec4u_dev*)(paged + o_vec) = lds[(at + o_vec) >> 4];
+            if (do_tail) *(byte_dev*)(paged + o_tail) = bytes[at + o_tail];
+        }
+        at += n;
+        pos += n;
+        ++e;
+    }
+}
+
+// Geometry whose tiles cross extent boundaries, slice by slice as copy_kernel: a wavefront whose 1 KiB has one
+// address on each side copies straight through registers.  Otherwise its bytes pass through 1 KiB of LDS: the
+// side that is cut into several extents is walked piece by piece, the other side and the staging address keep their
+// 16-byte accesses.
+__global__ void __launch_bounds__(256) one_pass_slice_copy_kernel(const SliceRec* __restrict__ rec,
+                                                                  const uint64_t* __restrict__ src_tab,
+                                                                  const uint64_t* __restrict__ dst_tab, uint64_t n_slices,
+                                                                  uint32_t bps, uint32_t bps_shift, uint32_t tiles_per_slice,
+                                                                  uint32_t tile_shift, const BatchDev* __restrict__ batch)
+{
+    __shared__ vec4u bounce[256];
+    const uint64_t w = (uint64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const uint64_t i = bps_shift != 0xFFFFFFFFu ? (w >> bps_shift)
+                       : (w >> 32) == 0 ? (uint64_t)((uint32_t)w / bps) : w / bps;
+    if (i >= n_slices) return;
+    const uint32_t c = (uint32_t)(w - i * bps);
+    const uint32_t x = c * 4096u + threadIdx.x * 16;             // this lane's byte offset inside the slice
+    uint32_t t = x >> tile_shift;
+    if (t >= tiles_per_slice) t = tiles_per_slice - 1;
+    const uint64_t from = src_tab[i * tiles_per_slice + t];
+    const uint64_t to = dst_tab[i * tiles_per_slice + t];
+    const SliceRec r = rec[i];
+    const bool in_range = x + 16 <= r.len;
+    const bool ragged = x < r.len && !in_range;                  // slice ends inside this lane's vector
+    const bool any_ragged = __any(ragged);
+    const bool src_cut = any_ragged || __any(x < r.len && (from & kTileSlow));
+    const bool dst_cut = any_ragged || __any(x < r.len && (to & kTileSlow));
+    const uint32_t in_tile = x & ((1u << tile_shift) - 1);
+    vec4u v;
+    if (!src_cut && !dst_cut) {
+        if (!in_range) return;
+        v = *(const vec4u_dev*)(from + in_tile);
+        __builtin_nontemporal_store(v, (vec4u_dev*)(r.lin + x));
+        __builtin_nontemporal_store(v, (vec4u_dev*)(to + in_tile));
+        return;
+    }
+    const uint32_t wave_lo = c * 4096u + (threadIdx.x & ~63u) * 16;
+    const uint32_t wave_hi = wave_lo + 1024 < r.len ? wave_lo + 1024 : r.len;
+    if (wave_lo >= wave_hi) return;
+    vec4u* mine = &bounce[threadIdx.x & ~63u];                   // this wavefront's 1 KiB
+    if (src_cut) {
+        walk_cut_side<true>(*batch, i, wave_lo, wave_hi, mine);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        v = bounce[threadIdx.x];                                 // bytes past the slice's end are not used
+    } else if (in_range) {
+        v = *(const vec4u_dev*)(from + in_tile);
+        bounce[threadIdx.x] = v;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    }
+    if (in_range) __builtin_nontemporal_store(v, (vec4u_dev*)(r.lin + x));
+    if (any_ragged) {                                            // the bytes of the slice's last, partial vector
+        const uint32_t whole = (wave_hi - wave_lo) & ~15u, at = whole + (threadIdx.x & 63u);
+        if (at < wave_hi - wave_lo) *(byte_dev*)(r.lin + wave_lo + at) = ((const uint8_t*)mine)[at];
+    }
+    if (dst_cut) walk_cut_side<false>(*batch, i, wave_lo, wave_hi, mine);
+    else if (in_range) __builtin_nontemporal_store(v, (vec4u_dev*)(to + in_tile));
+}
+
+// 2-D grid so that the block count is not capped by the 1-D limit.
+static bool copy_grid(uint64_t blocks, dim3* grid)
+{
+    const uint32_t gx = blocks < 65536 ? (uint32_t)blocks : 65536u;
+    const uint64_t gy = (blocks + gx - 1) / gx;
+    if (gy > 0x7FFFFFFFull) return false;
+    *grid = dim3(gx, (uint32_t)gy);
+    return true;
+}
+
+hipError_t launch_copy_one_pass(const BatchDev& b, bool compact, uint64_t max_tiles, hipStream_t s)
+{
+    uint32_t tile_shift = 0;
+    while ((1u << tile_shift) < b.tile_bytes) ++tile_shift;
+    dim3 grid;
+    if (b.n_sc_tiles == 0) {
+        const uint32_t bps = (uint32_t)((b.slice_bytes + 4095) / 4096);
+        uint32_t bps_shift = 0xFFFFFFFFu;
+        if ((bps & (bps - 1)) == 0) { bps_shift = 0; while ((1u << bps_shift) < bps) ++bps_shift; }
+        if (!copy_grid(b.n_slices * (uint64_t)bps, &grid)) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(one_pass_slice_copy_kernel, grid, dim3(256), 0, s, b.s_rec, b.src_tile, b.dst_tile, b.n_slices, bps,
+                           bps_shift, b.tiles_per_slice, tile_shift, b.self);
+        return hipGetLastError();
+    }
+    const uint64_t tiles = !compact ? b.n_sc_tiles : max_tiles < b.act_capacity ? max_tiles : b.act_capacity;
+    if (tiles == 0) return hipSuccess;
+    const uint64_t per_block = kOnePassLanes * 16;
+    if (!copy_grid(((tiles << tile_shift) + per_block - 1) / per_block, &grid)) return hipErrorInvalidValue;
+    if (compact)
+        hipLaunchKernelGGL(one_pass_list_copy_kernel, grid, dim3(kOnePassLanes), 0, s, b.act_src, b.act_lin, b.act_dst,
+                           &b.plan->n_act, tile_shift);
+    else
+        hipLaunchKernelGGL(one_pass_copy_kernel, grid, dim3(kOnePassLanes), 0, s, b.op_src, b.op_lin, b.op_dst, b.n_sc_tiles,
+                           tile_shift);
+    return hipGetLastError();
+}
+
 hipError_t launch_copy(const BatchDev& b, bool gather, hipStream_t s)
 {
     // 256 lanes (4 KiB per workgroup) measured best among 64/128/256/512 on MI355X

@@ -61,6 +61,7 @@ __global__ void __launch_bounds__(256) expand_kernel(BatchDev b)
         const uint64_t rest = len_j - off;
         b.s_desc[i] = j;
         b.s_off[i] = off;
+        b.s_pos[i] = b.src_pre[slo] + off;
         b.s_len[i] = (uint32_t)(rest < b.slice_bytes ? rest : b.slice_bytes);
         b.s_src_e0[i] = (uint32_t)last_not_above(b.src_pre, slo, shi, b.src_pre[slo] + off);
         b.s_dst_e0[i] = (uint32_t)last_not_above(b.dst_pre, dlo, dhi, b.dst_pre[dlo] + off);
@@ -91,7 +92,7 @@ __global__ void __launch_bounds__(256) tile_tables_kernel(BatchDev b) { build_ti
 
 hipError_t launch_tile_tables_prepare(const BatchDev& b, hipStream_t s)
 {
-    if (b.n_sc_tiles == 0) return hipSuccess;
+    if (b.n_sc_tiles == 0 || !b.ord_pre) return hipSuccess;      // no tile goes by destination address
     return exclusive_scan(OrderedLen{b.dst_ext, b.dst_order}, b.n_dst_ext, b.ord_pre, b.scan_partials, s);
 }
 
@@ -105,7 +106,8 @@ hipError_t launch_tile_tables(const BatchDev& b, hipStream_t s)
 
 // Copy records: staging address (arena + region base of the rail + offset inside the region) and
 // length of every BOUND slice; slices in any other state get length 0 and are skipped by the copy.
-__global__ void __launch_bounds__(256) finalize_kernel(BatchDev b, uint8_t* arena)
+// With `mark` the BOUND slices become DONE on the way (nothing behind this kernel reads the state).
+__global__ void __launch_bounds__(256) finalize_kernel(BatchDev b, uint8_t* arena, int mark)
 {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < b.n_slices; i += stride) {
@@ -113,6 +115,7 @@ __global__ void __launch_bounds__(256) finalize_kernel(BatchDev b, uint8_t* aren
         if (b.s_state[i] == TENT_SLICE_BOUND) {
             r.lin = (uint64_t)arena + b.plan->base[b.s_rail[i]] + b.s_stage_off[i];
             r.len = b.s_len[i];
+            if (mark) b.s_state[i] = TENT_SLICE_DONE;
         }
         b.s_rec[i] = r;
     }
@@ -180,7 +183,7 @@ hipError_t launch_finalize(const BatchDev& b, uint8_t* arena, bool compact, uint
 {
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(finalize_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, arena);
+    hipLaunchKernelGGL(finalize_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, arena, 0);
     if (b.n_sc_tiles && compact) {
         uint32_t tile_shift = 0;
         while ((1u << tile_shift) < b.tile_bytes) ++tile_shift;
@@ -193,6 +196,102 @@ hipError_t launch_finalize(const BatchDev& b, uint8_t* arena, bool compact, uint
         blocks = (b.n_sc_tiles + 255) / 256;
         if (blocks > 65536) blocks = 65536;
         hipLaunchKernelGGL(finalize_tiles_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);
+    }
+    return hipGetLastError();
+}
+
+// ---- bookkeeping of the one-pass copies ---------------------------------------------------------
+constexpr uint32_t kTilesPerWave = 1024;
+
+// One launch resolves the staging address of every tile that moves and marks its slice DONE: a group of
+// lanes (a power of two, up to a wavefront) takes one slice, reads its state, writes the addresses of the slice's
+// tiles at their places in the copy's order, and its first lane then changes the state that only this
+// group reads.  It was three launches (slice records, tile addresses, marks) and 16 bytes of table per tile more:
+// what bounds it is one launch (about 5 us) up to some 10^5 tiles, then 4 bytes read and 8 written per tile.
+// Slices of more than kTilesPerWave tiles are shared by `parts` wavefronts, and a launch of its own marks them.
+__global__ void __launch_bounds__(256) stage_tiles_kernel(BatchDev b, uint8_t* arena, uint32_t group_shift, uint32_t tile_shift,
+                                                          uint32_t parts)
+{
+    const uint64_t at = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    uint64_t i = at >> group_shift;
+    uint32_t group = 1u << group_shift;
+    uint32_t t0 = (uint32_t)at & (group - 1);
+    if (parts > 1) {                                                // group = wavefront here
+        t0 += 64u * (uint32_t)(i % parts);
+        i /= parts;
+        group *= parts;
+    }
+    if (i >= b.n_slices) return;
+    const uint32_t n_t = b.s_len[i] >> tile_shift;
+    const uint64_t q0 = b.s_pos[i] >> tile_shift;
+    const bool bound = b.s_state[i] == TENT_SLICE_BOUND;
+    uint64_t lin = 0;
+    if (bound) lin = (uint64_t)arena + b.plan->base[b.s_rail[i]] + b.s_stage_off[i];
+    for (uint32_t t = t0; t < n_t; t += group) {
+        const uint64_t p = b.tile_pos ? b.tile_pos[q0 + t] : q0 + t;
+        b.op_lin[p] = bound ? lin + ((uint64_t)t << tile_shift) : 0;
+    }
+    if (bound && t0 == 0 && parts == 1) b.s_state[i] = TENT_SLICE_DONE;
+}
+
+// The same when few slices move: the tiles of the BOUND slices are listed with their three addresses, in any
+// order (the copy's result does not depend on it), every slice taking its place in the list with one atomic add.
+// A slice that does not fit the list, or the host's bound on it that sizes the copy, stays BOUND and is not listed;
+// the slices that do fit occupy the list without gaps, because the first that does not moves the counter past the bound.
+__global__ void __launch_bounds__(256) list_tiles_kernel(BatchDev b, uint8_t* arena, uint32_t group_shift, uint32_t tile_shift,
+                                                         uint64_t max_tiles)
+{
+    const uint64_t at = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t i = at >> group_shift;
+    const uint32_t group = 1u << group_shift;
+    const uint32_t t0 = (uint32_t)at & (group - 1);
+    const bool bound = i < b.n_slices && b.s_state[i] == TENT_SLICE_BOUND;
+    const uint32_t n_t = bound ? b.s_len[i] >> tile_shift : 0;
+    uint64_t from = 0;
+    if (bound && t0 == 0) {
+        from = atomicAdd((unsigned long long*)&b.plan->n_act_asked, (unsigned long long)n_t);
+        if (from + n_t <= max_tiles) atomicAdd((unsigned long long*)&b.plan->n_act, (unsigned long long)n_t);
+    }
+    from = __shfl((unsigned long long)from, (int)((threadIdx.x & 63u) & ~(group - 1)), 64);
+    if (!bound || from + n_t > max_tiles) return;
+    const uint64_t lin = (uint64_t)arena + b.plan->base[b.s_rail[i]] + b.s_stage_off[i];
+    const uint64_t q0 = b.s_pos[i] >> tile_shift;
+    for (uint32_t t = t0; t < n_t; t += group) {
+        const uint64_t p = b.tile_pos ? b.tile_pos[q0 + t] : q0 + t;
+        b.act_src[from + t] = b.op_src[p];
+        b.act_lin[from + t] = lin + ((uint64_t)t << tile_shift);
+        b.act_dst[from + t] = b.op_dst[p];
+    }
+    if (t0 == 0) b.s_state[i] = TENT_SLICE_DONE;
+}
+
+__global__ void clear_list_kernel(BatchDev b)
+{
+    b.plan->n_act = 0;
+    b.plan->n_act_asked = 0;
+}
+
+hipError_t launch_stage_and_mark(const BatchDev& b, uint8_t* arena, bool compact, uint64_t max_tiles, hipStream_t s)
+{
+    if (b.n_sc_tiles == 0) {
+        uint64_t blocks = (b.n_slices + 255) / 256;
+        if (blocks > 4096) blocks = 4096;
+        hipLaunchKernelGGL(finalize_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, arena, 1);
+        return hipGetLastError();
+    }
+    uint32_t tile_shift = 0, group_shift = 0;
+    while ((1u << tile_shift) < b.tile_bytes) ++tile_shift;
+    while (group_shift < 6 && (1u << group_shift) < b.tiles_per_slice) ++group_shift;
+    const uint32_t parts = compact ? 1u : (b.tiles_per_slice + kTilesPerWave - 1) / kTilesPerWave;
+    const uint64_t blocks = (((b.n_slices * parts) << group_shift) + 255) / 256;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    if (compact) {
+        if (max_tiles > b.act_capacity) max_tiles = b.act_capacity;
+        hipLaunchKernelGGL(clear_list_kernel, dim3(1), dim3(1), 0, s, b);
+        hipLaunchKernelGGL(list_tiles_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, arena, group_shift, tile_shift, max_tiles);
+    } else {
+        hipLaunchKernelGGL(stage_tiles_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, arena, group_shift, tile_shift, parts);
+        if (parts > 1) return launch_mark_done(b, false, s);
     }
     return hipGetLastError();
 }

@@ -591,6 +591,18 @@ int convert_rails(const tent_rail_state* rails, uint32_t n_rails, uint64_t pendi
     return TENT_OK;
 }
 
+// Whether the staging arena shares no byte with a registered segment: only then may a destination byte be written
+// before every source byte has been read into staging.
+bool arena_apart(const tent_ctx* ctx)
+{
+    const uint64_t a = (uint64_t)ctx->cfg.staging_arena, n = ctx->cfg.staging_bytes;
+    for (const Segment& s : ctx->segments) {
+        const uint64_t b = (uint64_t)s.base;
+        if (b < a ? a - b < s.len : b - a < n) return false;
+    }
+    return true;
+}
+
 // tent_declare and tent_declare_static.  With `use_static` the tables and the sort's workspace are
 // carved from the static workspace of the context's GPU and nothing is allocated, on the device or
 // on the host.
@@ -689,6 +701,7 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     cv.want(&d.first, (uint64_t)n_desc + 1);
     cv.want(&d.s_desc, n_slices);
     cv.want(&d.s_off, n_slices);
+    cv.want(&d.s_pos, n_slices);
     cv.want(&d.s_len, n_slices);
     cv.want(&d.s_src_e0, n_slices);
     cv.want(&d.s_dst_e0, n_slices);
@@ -715,26 +728,42 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     cv.want(&d.len_pre, n_slices + 1);
     cv.want(&order_dev, nd);
     cv.want(&rank_dev, nd);
+    const bool bounded = (ctx->cfg.flags & TENT_FLAG_BOUNDED_STAGING) != 0;
+    const bool check = !(ctx->cfg.flags & TENT_FLAG_SKIP_OVERLAP_CHECK);
+    d.one_pass = check && arena_apart(ctx) && d.n_sc_tiles < 0xFFFFFFFFull ? 1u : 0u;
     if (d.n_sc_tiles) {
-        cv.want(&d.ord_pre, nd + 1);
-        cv.want(&d.ga_src, d.n_sc_tiles);
-        cv.want(&d.ga_lin, d.n_sc_tiles);
-        cv.want(&d.ga_slice, d.n_sc_tiles);
-        cv.want(&d.ga_x, d.n_sc_tiles);
-        if (ctx->cfg.flags & TENT_FLAG_BOUNDED_STAGING) cv.want(&d.ga_dst, d.n_sc_tiles);
+        // one-pass copies go by destination address (a context with bounded staging: by payload position, as its chunks
+        // do), two passes by either order
+        if (!d.one_pass || !bounded) cv.want(&d.ord_pre, nd + 1);
+        if (!d.one_pass || bounded) {
+            cv.want(&d.ga_slice, d.n_sc_tiles);
+            cv.want(&d.ga_x, d.n_sc_tiles);
+        }
+        if (d.one_pass) {
+            cv.want(&d.op_src, d.n_sc_tiles);
+            cv.want(&d.op_dst, d.n_sc_tiles);
+            cv.want(&d.op_lin, d.n_sc_tiles);
+            if (!bounded) cv.want(&d.tile_pos, d.n_sc_tiles);
+        } else {
+            cv.want(&d.ga_src, d.n_sc_tiles);
+            cv.want(&d.ga_lin, d.n_sc_tiles);
+            if (bounded) cv.want(&d.ga_dst, d.n_sc_tiles);
+            cv.want(&d.sc_dst, d.n_sc_tiles);
+            cv.want(&d.sc_lin, d.n_sc_tiles);
+            cv.want(&d.sc_slice, d.n_sc_tiles);
+            cv.want(&d.sc_x, d.n_sc_tiles);
+        }
         // an execute goes over a list of tiles only when at most half of the batch's tiles can move
         d.act_capacity = d.n_sc_tiles / 2 + 1;
-        cv.want(&d.tile_scan, n_slices + 1);
-        cv.want(&d.tile_partials, scan_partials_capacity(n_slices));
+        if (!d.one_pass) {
+            cv.want(&d.tile_scan, n_slices + 1);
+            cv.want(&d.tile_partials, scan_partials_capacity(n_slices));
+        }
         cv.want(&d.act_src, d.act_capacity);
         cv.want(&d.act_lin, d.act_capacity);
         cv.want(&d.act_dst, d.act_capacity);
-        cv.want(&d.sc_dst, d.n_sc_tiles);
-        cv.want(&d.sc_lin, d.n_sc_tiles);
-        cv.want(&d.sc_slice, d.n_sc_tiles);
-        cv.want(&d.sc_x, d.n_sc_tiles);
     }
-    if (ctx->cfg.flags & TENT_FLAG_BOUNDED_STAGING) {
+    if (bounded) {
         cv.want(&d.ch_lo, (uint64_t)kMaxChunks * TENT_MAX_RAILS);
         cv.want(&d.ch_hi, (uint64_t)kMaxChunks * TENT_MAX_RAILS);
         cv.want(&d.ch_base, (uint64_t)kMaxChunks * TENT_MAX_RAILS);
@@ -751,7 +780,6 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     if (cv.overflow) return TENT_ERR_NOMEM;
 
     // destination extents in address order (for the scatter) and the overlap check run on the device
-    const bool check = !(ctx->cfg.flags & TENT_FLAG_SKIP_OVERLAP_CHECK);
     const bool order = check || d.n_sc_tiles != 0;
     uint64_t ws_need = 0;
     if (order && order_workspace_bytes(nd, ns, check, &ws_need) != hipSuccess) { (void)hipGetLastError(); return TENT_ERR_HIP; }
@@ -1343,17 +1371,28 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
     uint64_t max_tiles = b->bound_hint * b->dev.tiles_per_slice;
     if (b->tile_hint < max_tiles) max_tiles = b->tile_hint;
     const bool compact = b->dev.n_sc_tiles != 0 && max_tiles * 2 <= b->dev.n_sc_tiles;
-    HIP_TRY(launch_finalize(b->dev, static_cast<uint8_t*>(ctx->cfg.staging_arena), compact, max_tiles, s));
-    // The copies below are driven by the tables just written and read no slice state, so the slices
+    // The copies below are driven by the tables that the bookkeeping writes and read no slice state, so the slices
     // are marked DONE ahead of them: in stream order nothing changes, and the next re-plan, if it
     // is enqueued on another stream, can run beside the copies.  tent_poll, on whatever stream, waits
     // for the end of the copies (done_event), so a slice is never reported complete while its bytes move.
-    HIP_TRY(launch_mark_done(b->dev, compact, s));
+    uint8_t* arena = static_cast<uint8_t*>(ctx->cfg.staging_arena);
+    if (b->dev.one_pass) {
+        HIP_TRY(launch_stage_and_mark(b->dev, arena, compact, max_tiles, s));
+    } else {
+        HIP_TRY(launch_finalize(b->dev, arena, compact, max_tiles, s));
+        HIP_TRY(launch_mark_done(b->dev, compact, s));
+    }
     // From here on a failure would leave slices marked DONE whose bytes were never moved: the batch
     // is then flagged, and every call but tent_reset and tent_release refuses it.
     auto copies = [&]() -> hipError_t {
         hipError_t e = record_execute_bookkeeping(*b, s);
         if (e != hipSuccess) return e;
+        if (b->dev.one_pass) {
+            StageTimer t(ctx, TENT_T_GATHER, s);
+            e = launch_copy_one_pass(b->dev, compact, max_tiles, s);
+            if (e != hipSuccess) return e;
+            return record_execute_done(*b, s);
+        }
         {
             StageTimer t(ctx, TENT_T_GATHER, s);
             e = compact ? launch_copy_compact(b->dev, true, max_tiles, s)
@@ -1399,7 +1438,13 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     uint8_t* arena = static_cast<uint8_t*>(ctx->cfg.staging_arena);
     const uint64_t payload = b->payload;
     HIP_TRY(launch_bounded_prepare(d, payload, chunk_bytes, (uint32_t)n_chunks, slot_bytes, slots, arena, s));
-    if (slots == 1) {
+    if (d.one_pass) {
+        // both directions of a chunk in one launch; a chunk's launch ends before the next one may reuse its slot
+        for (uint32_t c = 0; c < n_chunks; ++c) {
+            StageTimer t(ctx, TENT_T_GATHER, s);
+            HIP_TRY(launch_bounded_copy(d, true, c, payload, chunk_bytes, slot_bytes, slots, arena, s));
+        }
+    } else if (slots == 1) {
         for (uint32_t c = 0; c < n_chunks; ++c) {
             {
                 StageTimer t(ctx, TENT_T_GATHER, s);

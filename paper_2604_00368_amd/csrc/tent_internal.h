@@ -84,6 +84,7 @@ struct PlanState {
     uint64_t bounded_overflow;            // tent_execute_bounded: chunks whose regions do not fit the arena
     uint64_t n_act;                       // tent_execute with few BOUND slices: entries of the list of tiles that move
     uint64_t compact_overflow;            // nonzero: more tiles move than the launch was sized for (nothing is marked DONE)
+    uint64_t n_act_asked;                 // one-pass copies: tiles of the BOUND slices, listed or not
 };
 
 // What the binding chain needs to know about a run of equal-length slices: 32 bytes, read as two 16-byte halves.
@@ -119,6 +120,7 @@ struct BatchDev {
 
     uint32_t* s_desc;              // [n_slices]
     uint64_t* s_off;
+    uint64_t* s_pos;               // payload position of the slice's first byte (transfers laid end to end)
     uint32_t* s_len;
     uint32_t* s_src_e0;            // extent holding the slice's first source byte
     uint32_t* s_dst_e0;
@@ -163,6 +165,15 @@ struct BatchDev {
     uint64_t* act_lin;             //                staging address,
     uint64_t* act_dst;             //                destination address
     uint64_t  act_capacity;
+    // One-pass copies (the batch's destinations overlap neither each other nor its sources, and the staging
+    // arena lies outside its segments, so a byte may reach its destination while others are still unread): source,
+    // staging and destination address of every tile, in ascending destination address, or in declaration order
+    // (tile_pos = nullptr) in a context with bounded staging.  They replace the four ga_ and sc_ tables below and above.
+    uint32_t  one_pass;            // 1: the batch's copies read every source byte once and write staging and destination
+    uint64_t* op_src;              // [n_sc_tiles]
+    uint64_t* op_dst;              // [n_sc_tiles]
+    uint64_t* op_lin;              // [n_sc_tiles] filled by every execute, 0 = not to be moved
+    uint32_t* tile_pos;            // [n_sc_tiles] place of every tile of the declaration order in those tables
     uint64_t* sc_dst;              // [n_sc_tiles] scatter: destination address of the tile
     uint64_t* sc_lin;              // [n_sc_tiles] scatter: staging address, 0 = not to be moved
     uint32_t* sc_slice;
@@ -220,6 +231,8 @@ hipError_t launch_tile_tables(const BatchDev& b, hipStream_t s);
 hipError_t launch_tile_tables_prepare(const BatchDev& b, hipStream_t s);   // what the builders need when they run inside the chain launch
 hipError_t launch_finalize(const BatchDev& b, uint8_t* arena, bool compact, uint64_t max_tiles, hipStream_t s);
 hipError_t launch_copy(const BatchDev& b, bool gather, hipStream_t s);
+hipError_t launch_stage_and_mark(const BatchDev& b, uint8_t* arena, bool compact, uint64_t max_tiles, hipStream_t s);
+hipError_t launch_copy_one_pass(const BatchDev& b, bool compact, uint64_t max_tiles, hipStream_t s);
 hipError_t launch_copy_ordered(const BatchDev& b, bool gather, hipStream_t s);
 hipError_t launch_copy_compact(const BatchDev& b, bool gather, uint64_t max_tiles, hipStream_t s);
 hipError_t launch_mark_done(const BatchDev& b, bool compact, hipStream_t s);

@@ -81,16 +81,30 @@ __device__ __forceinline__ void ordered_tile_tables(const BatchDev& b, uint64_t 
         const uint64_t se = last_not_above(b.src_pre, b.s_src_e0[i], b.src_ptr[j + 1], s_pos);
         const tent_extent sx = b.src_ext[se];
         const uint64_t q = s_pos / tile;
-        b.ga_src[q] = b.seg_base[sx.seg] + sx.off + (s_pos - b.src_pre[se]);
-        b.ga_slice[q] = (uint32_t)i;
-        b.ga_x[q] = (uint32_t)x;
+        const uint64_t src_addr = b.seg_base[sx.seg] + sx.off + (s_pos - b.src_pre[se]);
+        if (b.ga_slice) {
+            b.ga_slice[q] = (uint32_t)i;
+            b.ga_x[q] = (uint32_t)x;
+        }
         const uint64_t d_pos = b.dst_pre[b.dst_ptr[j]] + off;
         const uint64_t de = last_not_above(b.dst_pre, b.s_dst_e0[i], b.dst_ptr[j + 1], d_pos);
         const tent_extent dx = b.dst_ext[de];
         const uint64_t within = d_pos - b.dst_pre[de];
         const uint64_t dst_addr = b.seg_base[dx.seg] + dx.off + within;
-        if (b.ga_dst) b.ga_dst[q] = dst_addr;                      // same tile on the destination side
+        if (b.one_pass && !b.tile_pos) {                           // both addresses in declaration order
+            b.op_src[q] = src_addr;
+            b.op_dst[q] = dst_addr;
+            continue;
+        }
         const uint64_t qd = (b.ord_pre[b.dst_rank[de]] + within) / tile;
+        if (b.one_pass) {
+            b.op_src[qd] = src_addr;
+            b.op_dst[qd] = dst_addr;
+            b.tile_pos[q] = (uint32_t)qd;
+            continue;
+        }
+        b.ga_src[q] = src_addr;
+        if (b.ga_dst) b.ga_dst[q] = dst_addr;                      // same tile on the destination side
         b.sc_dst[qd] = dst_addr;
         b.sc_slice[qd] = (uint32_t)i;
         b.sc_x[qd] = (uint32_t)x;

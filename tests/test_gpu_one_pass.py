@@ -1,0 +1,123 @@
+"""The one-pass copies (source -> staging and destination in one launch) against the two passes they stand in for, and
+the batches that must keep two passes: destinations that reuse source bytes, an arena inside a segment."""
+import numpy as np
+import pytest
+
+from paper_2604_00368_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+KiB = 1 << 10
+
+
+@pytest.fixture(scope="module")
+def H():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_harness
+    return gpu_harness
+
+
+def cut_tails(w, seed, most):
+    """The last extent of every transfer loses up to `most` bytes on both sides."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    cut = rng.integers(0, most + 1, size=w.n_desc).astype(np.uint32)
+    w.src_ext["len"][w.src_ptr[1:] - 1] -= cut
+    w.dst_ext["len"][w.dst_ptr[1:] - 1] -= cut
+    return w
+
+
+LAYOUTS = {
+    "tiles_4KiB": lambda: W.kv_migration(n_req=3, layers=1, ctx_lo=40, ctx_hi=400, page_tokens=16, slice_bytes=256 * KiB),
+    "tiles_2KiB": lambda: W.many_small(n_req=24),
+    "slice_of_many_tiles": lambda: W.sweep(8 << 20, True, payload=32 << 20, n_desc=2),
+    "one_tile_slices": lambda: W.tiny(n_desc=5, slice_bytes=4 * KiB),
+    "ragged_tails": lambda: cut_tails(W.many_small(n_req=24), 1, 1500),
+    "tails_of_single_bytes": lambda: cut_tails(W.tiny(n_desc=9), 2, 17),
+    "cut_anywhere": lambda: W.ragged(3, n_desc=20, max_len=90_000, max_ext=700, slice_bytes=16 * KiB),
+    "tiny_extents": lambda: W.ragged(4, n_desc=9, max_len=4000, max_ext=3, slice_bytes=1500),
+    "pieces_of_4096": lambda: W.ragged(5, n_desc=12, max_len=60_000, max_ext=40_000, slice_bytes=4 * KiB),
+}
+
+
+@pytest.mark.parametrize("name", sorted(LAYOUTS))
+@pytest.mark.parametrize("partial", [False, True])
+def test_one_pass_equals_two_passes(H, name, partial):
+    from paper_2604_00368_amd import binding as T
+    w = LAYOUTS[name]()
+    src, dst0 = W.fill_numpy(w, 0), W.fill_numpy(w, 1)
+    R = w.rails.shape[0]
+    results = []
+    for flags in (0, T.TENT_FLAG_SKIP_OVERLAP_CHECK):
+        with H.Engine(w, src, dst0, flags=flags, arena_skew=3) as eng:
+            eng.declare()
+            moved = []
+            for window in range(3 if partial else 1):
+                st, info = eng.plan()
+                assert st == 0
+                if partial and window < 2:                   # a third of what is bound, then the rest
+                    share = np.array(list(info.rail_bytes)[:R], dtype=np.uint64) // np.uint64(3 - window)
+                    moved.append(T.tent_sim_advance(eng.ctx, eng.batch, w.rails["queued_bytes"] + share, eng.stream))
+                eng.execute()
+                moved.append(T.tent_poll(eng.ctx, eng.batch, eng.stream))
+            assert moved[-1] == 0
+            results.append((eng.dst.cpu().numpy(), eng.arena.cpu().numpy(), eng.table(), moved))
+    one, two = results
+    assert np.array_equal(one[0], two[0])
+    assert np.array_equal(one[1], two[1])
+    assert np.array_equal(one[2], two[2]) and one[3] == two[3]
+
+
+@pytest.mark.parametrize("size", [32 * KiB, 1000])
+def test_destinations_that_reuse_source_bytes_keep_two_passes(H, size):
+    """Pages permuted in place: every source byte must be in staging before the first destination byte is written."""
+    from paper_2604_00368_amd import binding as T
+    dev, n = "cuda:0", 64
+    perm = np.random.Generator(np.random.PCG64(7)).permutation(n)
+    pool0 = np.random.Generator(np.random.PCG64(8)).integers(0, 256, size=n * size, dtype=np.uint8)
+    pool = torch.from_numpy(pool0).to(dev)
+    arena = torch.zeros(n * size + 256 * 4, dtype=torch.uint8, device=dev)
+    src = np.zeros(n, dtype=W.EXTENT_DTYPE)
+    src["off"], src["len"] = np.arange(n) * size, size
+    dst = src.copy()
+    dst["off"] = perm * size
+    ptr = np.arange(0, n + 1, 8, dtype=np.uint32)
+    ctx = T.tent_create(16 * KiB, arena.data_ptr(), arena.numel(), T.TENT_FLAG_SKIP_OVERLAP_CHECK)
+    T.tent_register_segment(ctx, pool.data_ptr(), pool.numel())
+    stream = torch.cuda.current_stream()
+    h = T.tent_declare(ctx, ptr, src, ptr, dst)
+    T.tent_plan(ctx, h, W.make_rails([50000, 25000, 40000]), False, stream)
+    T.tent_execute(ctx, h, stream)
+    torch.cuda.synchronize()
+    want = np.empty_like(pool0)
+    want.reshape(n, size)[perm] = pool0.reshape(n, size)
+    assert np.array_equal(pool.cpu().numpy(), want)
+    T.tent_destroy(ctx)
+
+
+def test_arena_inside_a_segment(H, oracle):
+    """The arena may be part of a registered range; the result is the same."""
+    from paper_2604_00368_amd import binding as T
+    w = W.small_variant("many_small")
+    src_h, dst_h = W.fill_numpy(w, 0), W.fill_numpy(w, 1)
+    whole = torch.zeros(src_h.size + w.staging_bytes + 512, dtype=torch.uint8, device="cuda:0")
+    at = -(-src_h.size // 256) * 256
+    whole[:src_h.size] = torch.from_numpy(src_h).to(whole.device)
+    dst = torch.from_numpy(dst_h).to(whole.device)
+    ctx = T.tent_create(w.slice_bytes, whole.data_ptr() + at, w.staging_bytes)
+    T.tent_register_segment(ctx, whole.data_ptr(), whole.numel())
+    T.tent_register_segment(ctx, dst.data_ptr(), dst.numel())
+    stream = torch.cuda.current_stream()
+    h = T.tent_declare(ctx, w.src_ptr, w.src_ext, w.dst_ptr, w.dst_ext)
+    T.tent_plan(ctx, h, w.rails, False, stream)
+    T.tent_execute(ctx, h, stream)
+    torch.cuda.synchronize()
+    s = oracle.split(w.src_ptr, w.src_ext, w.slice_bytes)
+    b = oracle.bind(s.len, w.rails)
+    want, staging = dst_h.copy(), np.zeros(w.staging_bytes, dtype=np.uint8)
+    oracle.execute(w, s, b, [src_h, want], staging)
+    assert np.array_equal(dst.cpu().numpy(), want)
+    assert np.array_equal(whole[at:at + w.staging_bytes].cpu().numpy(), staging)
+    T.tent_destroy(ctx)
