@@ -8,18 +8,16 @@
 // are nondecreasing in k, so picking the cheapest rail m times is a merge of R sorted sequences: the
 // run takes the m smallest triples (f_d(k), d, k) in lexicographic order, and the slice at position
 // p of the run gets the triple of rank p.  Three steps follow from that:
-//   1. run table     maximal runs of equal-length pending slices (flag heads, exclusive scan), and one record
-//                    per run with everything that does not depend on the rails' state, among it the cost level
-//                    at which the run will end according to a floating-point water-filling model;
+//   1. run table     maximal runs of equal-length pending slices (flag heads, exclusive scan);
 //   2. chain         one wavefront, lane = rail, walks the runs in order and finds, per run, how many
-//                    slots k_d each rail takes.  The split is found from the record's level (slot count per
-//                    rail from a floating-point estimate, confirmed against the integer costs of the two
-//                    neighbouring slots) and repaired one slot at a time (add the cheapest free slot / drop
-//                    the dearest taken slot) until exactly m slots are taken; where the estimate does not
-//                    hold, count_d(v) = #{k : f_d(k) <= v} (closed form, two integer divisions) is evaluated
-//                    at bracketed levels instead.  Floating point only steers the guess; the counts and
-//                    repairs are integer and exact.  Runs of one slice (tails) are a plain argmin.  A second
-//                    wavefront feeds the run records to the chain through a ring in LDS.
+//                    slots k_d each rail takes.  A second wavefront, the feeder, goes ahead of it and hands it one record
+//                    per run with everything that does not depend on the rails' state, among it the cost level at
+//                    which the run will end according to a floating-point water-filling model.  The split is found
+//                    from that level (slots at or below it, per rail) and repaired one slot at a time (add the
+//                    cheapest free slot / drop the dearest taken slot) until exactly m slots are taken; where
+//                    the level does not serve, count_d(v) = #{k : f_d(k) <= v} (closed form, two integer
+//                    divisions) is evaluated at bracketed levels instead.  The level only steers the guess; the
+//                    counts and repairs are exact.  Runs of one slice (tails) are a plain argmin.
 //   3. emit          one lane per slot (d, k): its rank in the run is
 //                    k + sum_{d' < d} count_d'(f) + sum_{d' > d} count_d'(f - 1),  f = f_d(k),
 //                    which gives the slice it belongs to; staging offset = T_d at run start + k l.
@@ -98,6 +96,17 @@ struct RunHead {
     }
 };
 
+struct PendingLen {
+    const uint32_t* s_len;
+    const uint32_t* pending;      // nullptr: position = slice index
+    const uint64_t* n_pending;
+    __device__ uint64_t operator()(uint64_t q) const
+    {
+        if (q >= *n_pending) return 0;
+        return s_len[pending ? pending[q] : (uint32_t)q];
+    }
+};
+
 __global__ void __launch_bounds__(256) run_table_kernel(BatchDev b, int use_pending)
 {
     const uint64_t n = b.plan->n_pending;
@@ -144,53 +153,22 @@ __device__ __forceinline__ uint32_t slots_upto_fast(const Rail& r, uint64_t A, u
     return k;
 }
 
-// Smallest 32-bit key over the wavefront (keys carry a lane in their low 6 bits), as a uniform value.
-template <int R>
-__device__ __forceinline__ uint32_t wave_min_key(uint32_t key)
-{
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_reduce32(key, R, Min32{}));
-}
-
-// Costs within 2^25 ps of the level are compared as 32-bit keys (offset << 6 | lane, below 2^31); a cost farther
-// on the harmless side (a free slot far above the level, a taken slot far below it) gets the key kFarKey | lane,
-// which loses against every near key; a winner at or above kFarKey means "no near candidate" and is never used.
-constexpr uint32_t kRelBits = 25;
-constexpr uint64_t kRelSpan = 1ull << kRelBits;
-constexpr uint32_t kFarKey = 0x80000000u;
-constexpr uint32_t kNoKey = 0xFFFFFFFFu;
-constexpr uint64_t kNoLevel = ~0ull;
-// The lean path sums slot counts in 32 bits: runs stay below 2^24 slices and a lane whose estimate cannot be
-// used adds 2^25 instead of its count, so that with up to 64 lanes the sum neither wraps nor comes near m.
-constexpr uint32_t kLeanRunMax = 1u << 24;
-constexpr uint32_t kOffMark = 1u << 25;
-
-// ---- step 1b: one record per run ---------------------------------------------------------------
-// Everything the chain needs to know about a run that does not depend on the rails' state, computed
-// in parallel before the chain starts; the chain fetches the records a block at a time.  The cost
-// level comes from the water-filling model: the rails that take part end a run at a common cost level,
-// level(bytes) = (bytes + sum_d h_d G_d) / sum_d G_d over those rails, with G_d = 65536 / c1_d bytes per
-// picosecond and h_d the rail's head cost; a rail takes part once the level has passed its head cost.  The
-// bytes bound before a run are known in advance (a prefix sum of the pending lengths), so the level after
-// every run is too.  It is an estimate: the chain verifies what it derives from it in integers.
-struct PendingLen {
-    const uint32_t* s_len;
-    const uint32_t* pending;      // nullptr: position = slice index
-    const uint64_t* n_pending;
-    __device__ uint64_t operator()(uint64_t q) const
-    {
-        if (q >= *n_pending) return 0;
-        return s_len[pending ? pending[q] : (uint32_t)q];
-    }
+// ---- the feeder: one record per run ------------------------------------------------------------
+// Cost level at which a run ends, from the water-filling model: the rails that take part end a run at a common cost
+// level, level(bytes) = (bytes + sum_d h_d G_d) / sum_d G_d over those rails, with G_d = 65536 / c1_d bytes per picosecond and
+// h_d the rail's head cost; a rail takes part once the level has passed its head cost.  The bytes bound
+// before a run are known in advance (a prefix sum of the pending lengths), so the level after every run is too.
+struct LevelModel {
+    // admitted rails in ascending order of their head cost h_d = c0_d + A_d c1_d / 65536 (what the rail's next byte
+    // would cost): h[j] the j-th smallest, G[j] and hG[j] the sums of G_d and of h_d G_d over the first j + 1
+    double h[TENT_MAX_RAILS], G[TENT_MAX_RAILS], hG[TENT_MAX_RAILS];
+    uint32_t live;
+    double max_c1;
 };
 
-__global__ void __launch_bounds__(256) run_records_kernel(BatchDev b, RailParams rp, int mode)
+// By a whole workgroup (at least 64 threads), with barriers.
+__device__ __forceinline__ void build_level_model(LevelModel& lm, const BatchDev& b, const RailParams& rp, int mode)
 {
-    // Admitted rails in ascending order of their head cost h_d = c0_d + A_d c1_d / 65536 (what the rail's next byte
-    // would cost): sh_h[j] the j-th smallest, sh_G[j] and sh_hG[j] the sums of G_d and of h_d G_d over the first j + 1.
-    // At cost level v the rails with h_d < v hold sum (v - h_d) G_d bytes, so the level that holds B bytes is
-    // (B + sh_hG[j]) / sh_G[j] for the first j at which it does not reach the next rail's head cost.
-    __shared__ double sh_h[TENT_MAX_RAILS], sh_G[TENT_MAX_RAILS], sh_hG[TENT_MAX_RAILS];
-    __shared__ uint32_t sh_live;
     const uint32_t t = threadIdx.x;
     if (t < TENT_MAX_RAILS) {
         auto head = [&](uint32_t d, double* G) -> double {
@@ -203,87 +181,173 @@ __global__ void __launch_bounds__(256) run_records_kernel(BatchDev b, RailParams
         double G = 0.0;
         const double h = live ? head(t, &G) : 0.0;
         uint32_t rank = 0, n_live = 0;
+        double max_c1 = 0.0;
         for (uint32_t d = 0; d < rp.n_rails; ++d) {
             if (!((rp.admitted >> d) & 1)) continue;
             ++n_live;
             double Gd;
             const double hd = head(d, &Gd);
+            const double c1 = (double)(uint32_t)rp.c1[d];
+            max_c1 = c1 > max_c1 ? c1 : max_c1;
             rank += (hd < h || (hd == h && d < t)) ? 1u : 0u;
         }
-        if (live) { sh_h[rank] = h; sh_G[rank] = G; sh_hG[rank] = h * G; }
-        if (t == 0) sh_live = n_live;
+        if (live) { lm.h[rank] = h; lm.G[rank] = G; lm.hG[rank] = h * G; }
+        if (t == 0) { lm.live = n_live; lm.max_c1 = max_c1; }
     }
     __syncthreads();
     if (t == 0) {
-        for (uint32_t j = 1; j < sh_live; ++j) { sh_G[j] += sh_G[j - 1]; sh_hG[j] += sh_hG[j - 1]; }
+        for (uint32_t j = 1; j < lm.live; ++j) { lm.G[j] += lm.G[j - 1]; lm.hG[j] += lm.hG[j - 1]; }
     }
     __syncthreads();
-    const uint64_t n_runs = b.plan->n_runs;
-    const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r > n_runs) return;
-    RunRec rec{0, 0, kNoLevel, 0.0, 0.0};
-    if (r < n_runs) {
-        const uint32_t start = b.run_start[r];
-        const uint32_t id = (mode & kBindUsePending) ? b.pending[start] : start;
-        rec.len = b.s_len[id];
-        rec.m = b.run_start[r + 1] - start;
-        rec.inv_len = 1.0 / (double)rec.len;
-        const double bytes = (double)rec.m * (double)rec.len + (double)b.len_pre[start];
-        const uint32_t n_live = sh_live;
-        double v = -1.0;
-        for (uint32_t j = 0; j < n_live; ++j) {
-            // half a slice per participating rail on top: the slot counts are rounded down
-            v = (bytes + 0.5 * (double)(j + 1) * (double)rec.len + sh_hG[j]) / sh_G[j];
-            if (j + 1 == n_live || v <= sh_h[j + 1]) break;
-        }
-        // no level (the chain then takes its general path) for runs too short to gain from one or too long for
-        // the short path's 32-bit slot sums
-        if (v >= 0.0 && v < 1.0e14 && rec.m > (uint32_t)kTol && rec.m < kLeanRunMax) {
-            rec.level = (uint64_t)v;
-            rec.level_f = (double)rec.level;
-        }
+}
+
+// Half a slice per participating rail comes on top of the bytes: the slot counts are rounded down.
+__device__ __forceinline__ double level_at(const LevelModel& lm, double bytes, double half_slice)
+{
+    double v = -1.0;
+    for (uint32_t j = 0; j < lm.live; ++j) {
+        v = (bytes + half_slice * (double)(j + 1) + lm.hG[j]) / lm.G[j];
+        if (j + 1 == lm.live || v <= lm.h[j + 1]) break;
     }
-    b.run_rec[r] = rec;
+    return v;
+}
+
+// A record is four 16-byte quads, read by every lane of the chain at one address; the short path reads the first two:
+//   {slices m, flags, X shift}  {length of the single slice behind the run, run index}  {level, slice length l, that length}  {1 / l}
+// A run of one slice that does not stand behind a longer run has m = 0 and is the single slice itself.
+typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+constexpr uint32_t kRecTail = 1u;          // a single slice follows the run and is bound with it
+constexpr uint32_t kRecSingle = 2u;        // there is no run, only a single slice
+constexpr uint32_t kRecNoLevel = 4u;       // the level does not serve: general path
+constexpr uint32_t kRecRebase = 8u;        // the chain takes its relative state afresh from the integers first
+constexpr uint32_t kRecSame = 16u;         // the run's slices are as long as those of the run before
+constexpr uint32_t kRecEnd = 32u;          // behind the last run
+constexpr uint32_t kRecShort = kRecTail | kRecSame;   // what nearly every record of a long batch is: the short path
+constexpr uint32_t kFeedBlock = 64;        // runs the feeder looks at a time, one per lane
+constexpr uint32_t kRingRecords = 256;
+
+// The chain keeps costs relative to the level in units of 2^-16 ps, as doubles that hold whole numbers below 2^53
+// exactly.  A rail 2^kFarBits ps or more above the level counts as infinitely far until the state is rebased, which
+// happens at least once while the level rises by 2^kStepBits ps; a run that lifts the level by more than that, or whose single
+// slot costs more, goes the general way.
+constexpr int kFarBits = 36, kStepBits = 34;
+constexpr double kMaxLevel = 4.0e15;       // ps; levels are whole numbers, exact as doubles
+constexpr uint32_t kLevelRunMax = 1u << 25;   // slices: slot counts of up to 64 rails are summed in 32 bits
+constexpr double kUnit = 65536.0;
+
+struct RecordRing {
+    Quad rec[kRingRecords][4];
+    uint32_t filled;                       // records written
+    uint32_t taken;                        // records read
+};
+
+__device__ __forceinline__ double join_f64(uint32_t lo, uint32_t hi) { return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo)); }
+__device__ __forceinline__ uint32_t low_f64(double x) { return (uint32_t)(uint64_t)__double_as_longlong(x); }
+__device__ __forceinline__ uint32_t high_f64(double x) { return (uint32_t)((uint64_t)__double_as_longlong(x) >> 32); }
+
+// Run records reach the chain through a ring in LDS.  A load that the chain issued itself would have to be
+// awaited through the counter its row stores also use, that is, at once and at full memory latency, which is
+// long while another batch's copies saturate the memory.  The feeder stays at most kRingRecords ahead, the chain
+// waits only for a record that is not there yet.  Neither wait depends on the waiting wavefront itself, and both
+// loops end with the run table (the chain at the record behind it).
+__device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const LevelModel& lm, RecordRing& ring, uint32_t lane)
+{
+    const uint32_t n_runs = (uint32_t)b.plan->n_runs;
+    const bool pending = (mode & kBindUsePending) != 0;
+    const double step = (double)(1ull << kStepBits);
+    uint32_t written = 0;
+    // of the last record written: its level, whether it served, and the slice length of the last run of several slices
+    double last_level = 0.0;
+    bool last_served = false;
+    uint32_t last_len = 0;
+    auto wait_for_room = [&](uint32_t count) {
+        while (written + count - __hip_atomic_load(&ring.taken, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) > kRingRecords)
+            __builtin_amdgcn_s_sleep(4);
+    };
+    auto from_lane = [](double x, int at) -> double { return __shfl(x, at, 64); };
+    for (uint32_t at = 0; at < n_runs; at += kFeedBlock) {
+        const bool here = at + lane < n_runs;
+        const uint32_t r = here ? at + lane : n_runs - 1;
+        const uint32_t start = b.run_start[r], end = b.run_start[r + 1];
+        const uint32_t after = r + 1 < n_runs ? b.run_start[r + 2] : end;
+        const uint32_t before = r > 0 ? b.run_start[r - 1] : start;
+        const uint32_t len = b.s_len[pending ? b.pending[start] : start];
+        const uint32_t len_after = after > end ? b.s_len[pending ? b.pending[end] : end] : 0;
+        const double bytes = (double)b.len_pre[start];
+        const uint32_t m = end - start;
+        const bool single = m == 1;
+        const bool joined = single && start - before > 1;            // bound together with the run before it
+        const bool has_tail = !single && after - end == 1;
+        const uint32_t tail = single ? len : has_tail ? len_after : 0;
+        const double l_f = (double)len;
+        const double v = level_at(lm, bytes + (double)m * l_f, 0.5 * l_f), v_before = level_at(lm, bytes, 0.0);
+        const bool valid = v >= 0.0 && v < kMaxLevel;
+        const bool serves = valid && v - v_before < step && m < kLevelRunMax && l_f * lm.max_c1 < step * kUnit;
+        const double level = valid ? __builtin_floor(v) : 0.0;
+        // the records written before this one: the lane below among those that are written, or the last block's last
+        const uint64_t written_mask = __ballot(here && !joined), run_mask = __ballot(here && !single);
+        const uint64_t served_mask = __ballot(serves);
+        const uint64_t below = (1ull << lane) - 1;
+        const uint64_t prev_mask = written_mask & below, prev_run_mask = run_mask & below;
+        const int prev = prev_mask ? 63 - __clzll((long long)prev_mask) : -1;
+        const int prev_run = prev_run_mask ? 63 - __clzll((long long)prev_run_mask) : -1;
+        const double level_there = from_lane(level, prev < 0 ? 0 : prev);
+        const uint32_t len_there = __shfl(len, prev_run < 0 ? 0 : prev_run, 64);
+        const double prev_level = prev < 0 ? last_level : level_there;
+        const bool prev_served = prev < 0 ? last_served : ((served_mask >> (prev < 0 ? 0 : prev)) & 1) != 0;
+        const uint32_t prev_len = prev_run < 0 ? last_len : len_there;
+        // a block over which the level rises far is rebased record by record, any other at its start
+        const double v_first = from_lane(v_before, 0), v_last = from_lane(v, 63);
+        uint32_t flags = (single ? kRecSingle : 0u) | (has_tail ? kRecTail : 0u) | (serves ? 0u : kRecNoLevel);
+        if (prev < 0 || !prev_served || !(v_last - v_first < step)) flags |= kRecRebase;
+        if (!single && prev_len == len) flags |= kRecSame;
+        const double shift = (prev_level - level) * kUnit;
+        wait_for_room(kFeedBlock);
+        if (here && !joined) {
+            Quad* out = ring.rec[(written + (uint32_t)__popcll(prev_mask)) % kRingRecords];
+            const double tail_f = (double)tail, inv = 1.0 / l_f;
+            out[0] = Quad{single ? 0u : m, flags, low_f64(shift), high_f64(shift)};
+            out[1] = Quad{low_f64(tail_f), high_f64(tail_f), r, 0u};
+            out[2] = Quad{low_f64(level), high_f64(level), len, tail};
+            out[3] = Quad{low_f64(inv), high_f64(inv), 0u, 0u};
+        }
+        written += (uint32_t)__popcll(written_mask);
+        if (written_mask) {
+            const int last = 63 - __clzll((long long)written_mask);
+            last_level = from_lane(level, last);
+            last_served = ((served_mask >> last) & 1) != 0;
+        }
+        if (run_mask) last_len = __shfl(len, 63 - __clzll((long long)run_mask), 64);
+        __hip_atomic_store(&ring.filled, written, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    wait_for_room(1);
+    if (lane == 0) {
+        Quad* out = ring.rec[written % kRingRecords];
+        out[0] = Quad{0u, kRecEnd, 0u, 0u};
+        out[1] = out[2] = out[3] = Quad{0u, 0u, 0u, 0u};
+    }
+    __hip_atomic_store(&ring.filled, written + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // ---- step 2: chain over runs ------------------------------------------------------------------
-// kWide = 16, 32 or 64: lanes that can hold a rail; with 16 every reduction stays inside one DPP row.
-// Runs in lanes 0 .. kWide-1 of the first wavefront of a workgroup; the other lanes leave at once.
-//
-// Per rail the chain keeps the exact product P = A * c1 of the bytes in flight (so that a slot's cost
-// is c0 + ((P + j * l * c1) >> 16) with additions only), the bytes bound T, and a floating-point
-// shadow of A for the estimates.  The loop is a chain of dependent instructions on one wavefront,
-// so what counts is how few it issues per run and that it never waits for memory: run records come
-// kWide at a time, one per lane, out of a ring in LDS that a second wavefront fills ahead of their use,
-// and are handed out with readlane; results leave as one row of K and one of T per run.  The general path sits in a function of
-// its own: inlined, its code and registers made the loop's short paths measurably slower.
-
-// State of one lane of the chain that a run may change, and the slots the lane takes in the run.
-struct ChainVars {
-    uint64_t P, T;
-    double Bd;
-    uint64_t ref_level;
-    uint32_t cnt, all_proven, k;
-};
-
 // A run of m slices of l bytes from any state and with any (or no) level estimate: the level is searched
 // with exact slot counts (bracket, interpolation, bisection) and the split repaired slot by slot.  Kept
-// out of line: the chain's loop calls it only where its short path does not apply.
+// out of line: the chain's loop calls it only where its short path does not apply.  Returns the lane's slot count.
 template <int kWide>
-__device__ __attribute__((noinline)) uint64_t bind_run_general(ChainVars cv, Rail rail, double G, double g, bool live,
-                                                               uint64_t live_mask, uint64_t A_less_T, int lane, uint32_t l,
-                                                               uint32_t m, uint64_t vi, double level_f, double inv_l)
+__device__ __attribute__((noinline)) uint32_t bind_run_general(uint64_t T, uint32_t cnt, Rail rail, bool live, uint64_t A_less_T,
+                                                               int lane, uint32_t l, uint32_t m, bool has_level, double level_f,
+                                                               double inv_l)
 {
     constexpr int R = kWide;
-    const uint64_t T = cv.T;
-    const uint32_t cnt = cv.cnt;
-    bool all_proven = cv.all_proven != 0;
+    const uint64_t live_mask = __ballot(live);
+    const double G = live ? 65536.0 * rail.inv_c1 : 0.0;      // bytes the rail absorbs per picosecond
+    const double g = (double)rail.c0 * G;                     // its fixed latency expressed in bytes
     uint32_t k = 0, taken = 0;
     const uint64_t A = A_less_T + T;
-    if (!all_proven) all_proven = __ballot(live && cnt > 0) == live_mask;
+    const bool all_proven = __ballot(live && cnt > 0) == live_mask;   // every admitted rail has received a slot
     if (m > (uint32_t)kTol) {
         double v;
-        if (vi != kNoLevel && all_proven) {
+        if (has_level && all_proven) {
             v = level_f;
         } else {
             // rails whose next slot already costs more than the level stay out of the pool
@@ -367,274 +431,249 @@ __device__ __attribute__((noinline)) uint64_t bind_run_general(ChainVars cv, Rai
         k -= lane == win;
         --taken;
     }
-    // only the slot count (low half) and the "every rail has a slot" flag (bit 32) go back: the caller derives its
-    // state from the count, so that the loop's registers are not tied to those of the calling convention
-    return (uint64_t)k | ((uint64_t)(all_proven ? 1u : 0u) << 32);
+    return k;
 }
 
-// Run records reach the chain through a ring of blocks in LDS, kWide records a block, one per lane, each as
-// two 16-byte halves {len, m, level} and {level_f, inv_len}.  A second wavefront of the workgroup, the feeder,
-// copies them there from global memory several blocks ahead.  A load that the chain issued itself would have to
-// be awaited through the counter its row stores also use, that is, at once and at full memory latency per block,
-// which is long while another batch's copies saturate the memory.  `filled` counts the blocks the feeder has
-// written, `taken` those the chain has read; the feeder stays at most kRingBlocks ahead, the chain waits only
-// for a block that is not there yet.  Neither wait depends on the waiting wavefront itself, and both loops end
-// with the run table.
-typedef uint32_t Quad __attribute__((ext_vector_type(4)));
-constexpr int kRingBlocks = 8;
-static_assert(sizeof(RunRec) == 32, "a run record is two 16-byte halves");
+// Keys of the chain's 32-bit reductions: (cost relative to the level, in ps) << 6 | lane, made from the cost in units of
+// 2^-10 ps with the lane over its low bits.  The conversion saturates: a cost 2^26 ps or more away has a key from
+// kFarKey on (no near candidate); one that would have to lie on the other side of the level comes out below 64.
+constexpr uint32_t kFarKey = 0xFFFFFFC0u;
+constexpr double kKeyUnit = 1.0 / 1024.0;
+constexpr double kSingleBias = (double)(1ull << 31);   // single slices: the window reaches 2^25 ps to either side of the level
+constexpr int kRepairMax = 8;              // slots added or dropped one by one before the general path takes over
 
-template <int kWide>
-struct RecordRing {
-    Quad lo[kRingBlocks][kWide];
-    Quad hi[kRingBlocks][kWide];
-    uint32_t filled;
-    uint32_t taken;
+// v_cvt_u32_f64: truncates; values below zero, minus infinity and not-a-number give 0, above 2^32 - 1 saturate.
+__device__ __forceinline__ uint32_t saturating_u32(double x)
+{
+    uint32_t r;
+    asm("v_cvt_u32_f64_e32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+// What the next byte of a rail with A bytes queued would cost, relative to the level, in units of 2^-16 ps, exactly (A c1 is,
+// by the plan's precondition); infinity for a rail that is far above the level or takes no slices, not-a-number for
+// one far below it (every key made from it then comes out below 64, which sends the run or slice to the integers).
+__device__ __forceinline__ double relative_cost(const Rail& rail, bool live, uint64_t A, double level)
+{
+    const uint64_t P = A * (uint64_t)rail.c1;
+    const int64_t ps = (int64_t)(rail.c0 + (P >> 16) - (uint64_t)level);
+    double x = (double)ps * kUnit + (double)(uint32_t)(P & 65535u);
+    if (ps < -(1ll << kFarBits)) x = __builtin_nan("");
+    if (!live || ps >= (1ll << kFarBits)) x = __builtin_inf();
+    return x;
+}
+
+// First guess of a run's split for one rail: the slots at or below the level.  Slot j is iff X + (j + 1) lc1 < 65536,
+// so the count is trunc((65535.5 - X) / lc1); half a unit keeps the quotient off the whole numbers by more than it can be
+// rounded.  A wrong count would show: its last slot above the level, or its first free one not, gives a key below 64.
+struct SplitGuess {
+    double p, p_next;                      // where the last slot taken and the first free one end, relative to the level
+    uint32_t kk;                           // slots taken
+    __device__ __forceinline__ SplitGuess(double X, double lc1, double inv, double kf0)
+    {
+        kk = saturating_u32(fma(-X, inv, kf0));
+        kk = kk < kLevelRunMax ? kk : kLevelRunMax;
+        p = fma((double)kk, lc1, X);
+        p_next = p + lc1;
+    }
+    // cheapest free slot: floor(p_next / 65536) >= 1; dearest taken slot: 1 - floor(p / 65536) >= 1
+    // (ties: the free slot of the lowest rail is next, the taken slot of the highest rail is last)
+    __device__ __forceinline__ uint32_t up_key(uint32_t who) const { return (saturating_u32(p_next * kKeyUnit) & ~63u) | who; }
+    __device__ __forceinline__ uint32_t down_key(uint32_t who, double unit, double bias) const
+    {
+        const uint32_t key = (saturating_u32(fma(p, -unit, bias)) & ~63u) | who;
+        return kk != 0 ? key : ~0u;
+    }
 };
 
-// First instruction of both roles, before the workgroup's barrier.
+struct SplitResult {
+    double X;
+    uint32_t kk;
+};
+
+// A run whose guess does not hold, by the general path.  Out of line, like everything the chain's loop seldom needs.
 template <int kWide>
-__device__ __forceinline__ void ring_reset(RecordRing<kWide>& ring)
+__device__ __attribute__((noinline)) SplitResult split_odd_run(uint32_t m, bool serves, double T, uint32_t cnt, Rail rail, bool live, uint64_t A_less_T,
+                                                               int lane, const Quad* rec)
 {
-    if (threadIdx.x == 0) { ring.filled = 0; ring.taken = 0; }
+    const Quad q2 = rec[2], q3 = rec[3];
+    const double level = join_f64(q2.x, q2.y);
+    const uint32_t kk = bind_run_general<kWide>((uint64_t)T, cnt, rail, live, A_less_T, lane, q2.z, m, serves, level, join_f64(q3.x, q3.y));
+    return SplitResult{relative_cost(rail, live, A_less_T + (uint64_t)T + (uint64_t)kk * q2.z, level), kk};
 }
 
+// The rail of one slice that leaves `end` bytes queued on the rail, from the whole costs.
 template <int kWide>
-__device__ __forceinline__ void feed_records(const BatchDev& b, const RunRec* __restrict__ recs, RecordRing<kWide>& ring, int lane)
+__device__ __attribute__((noinline)) uint32_t odd_single(Rail rail, uint64_t end, bool live, int lane)
 {
-    if (lane >= kWide) return;
-    const uint64_t n_runs = b.plan->n_runs;
-    const Quad* src = reinterpret_cast<const Quad*>(recs);
-    for (uint64_t j = 0; j * kWide < n_runs; ++j) {
-        while (__hip_atomic_load(&ring.taken, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) + (uint32_t)kRingBlocks <= (uint32_t)j)
-            __builtin_amdgcn_s_sleep(4);
-        const uint64_t r = j * kWide + lane < n_runs ? j * kWide + lane : n_runs;      // the table ends with a spare record
-        const Quad lo = src[2 * r], hi = src[2 * r + 1];
-        ring.lo[j % kRingBlocks][lane] = lo;
-        ring.hi[j % kRingBlocks][lane] = hi;
-        __hip_atomic_store(&ring.filled, (uint32_t)j + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
+    return (uint32_t)argmin_cost(rail.c0 + ((end * (uint64_t)rail.c1) >> 16), live, lane, kWide);
 }
 
-template <int kWide, bool kFar>
-__device__ __forceinline__ void bind_chain(const BatchDev& b, const RailParams& rp, int mode, RecordRing<kWide>& ring)
+// kWide = 16, 32 or 64: lanes that can hold a rail; with 16 every reduction stays inside one DPP row.
+// Runs in lanes 0 .. kWide-1 of the first wavefront of a workgroup; the other lanes leave at once.
+//
+// The loop is a chain of dependent instructions on one wavefront that leaves the device idle, so what bounds a plan
+// of many transfers is how many instructions it issues per transfer (4-5 cycles each, 8 when the next depends on
+// it, 16 for a cross-lane step, 25 and more for a branch taken).  Hence: all state as doubles relative to the level, so that a
+// slot's cost is one fma and the comparison with the level needs no shift; the checks of the estimate folded into the
+// keys that are reduced anyway; the first repair step without a branch; a lane knows that it won a reduction by its own key;
+// what depends on the slice length only is kept from run to run; two 16-byte record reads ahead of their use, by all lanes at
+// one address; one 16-byte row store per transfer; and everything unusual behind one test of the record's flags.
+// About 110 instructions and 270 ns per transfer of a run and a tail on MI355X with 16 rails, from 190 and 510 ns when the state
+// was kept in 64-bit integers and every single slice had a record and a row of its own: 24,576 transfers 12.62 -> 6.46 ms,
+// 4,096 transfers 2.34 -> 1.15 ms, 2,048 transfers on 9 rails 1.18 -> 0.52 ms.
+template <int kWide>
+__device__ __forceinline__ void bind_chain(const BatchDev& b, const RailParams& rp, int mode, RecordRing& ring)
 {
     const int lane = threadIdx.x;
     if (lane >= kWide) return;
     constexpr int R = kWide;                                  // reduction width
-    const int n_rails = (int)rp.n_rails;
-    const bool live = lane < n_rails && ((rp.admitted >> lane) & 1);
-    const uint64_t live_mask = __ballot(live);
+    const bool live = lane < (int)rp.n_rails && ((rp.admitted >> lane) & 1);
     Rail rail;
     rail.c0 = rp.c0[lane];
     rail.c1 = live ? (uint32_t)rp.c1[lane] : 1u;
     rail.inv_c1 = 1.0 / (double)rail.c1;
-    const double G = live ? 65536.0 * rail.inv_c1 : 0.0;      // bytes the rail absorbs per picosecond
-    const double g = (double)rail.c0 * G;                     // its fixed latency expressed in bytes
-    uint64_t T = 0;
+    const double c1_f = (double)rail.c1;
+    double T = 0.0;                                           // bytes bound so far, a whole number
     uint32_t cnt = 0;                                         // a batch holds fewer than 2^32 - 1 slices
     uint64_t n_before = 0;
     if (mode & kBindAfterRotation) {          // the rotation pass went first: its bytes are queued and staged ahead
-        T = b.plan->Tr[lane];
+        T = (double)b.plan->Tr[lane];
         cnt = (uint32_t)b.plan->cr[lane];
         n_before = b.plan->n_retry;
     }
     const uint64_t A_less_T = rp.A[lane];                     // A = A_less_T + T at any time
-    uint64_t P = (A_less_T + T) * (uint64_t)rail.c1;          // exact: (max A + pending bytes) * max c1 < 2^63
-    // xmax(v) - A, the bytes the rail may still take up to cost level v, is estimated as v * G + Bd
-    double Bd = (1.0 - (double)rail.c0) * G - (double)(A_less_T + T);
-    const uint64_t n_runs = b.plan->n_runs;
+    const uint32_t lane_up = (uint32_t)lane, lane_down = 63u - (uint32_t)lane;
+
+    double X = 0.0;                                           // see relative_cost
+    // what depends on the slice length of the current run only
+    double l_f = 0.0, lc1 = 0.0, inv = 0.0, kf0 = 0.0;
+    uint32_t at = 0;                                          // record in hand
+    // constants that have to stay in registers (as literals they would cost two moves at every use)
+    double down_bias = 131071.0 * kKeyUnit, single_bias = kSingleBias, key_unit = kKeyUnit;
+    asm("" : "+v"(down_bias), "+v"(single_bias), "+s"(key_unit));
+
+    // Split a run of m slices: returns the slots this rail takes and moves X.
+    auto split_run = [&](uint32_t m, bool serves) -> uint32_t {
+        SplitGuess g(X, lc1, inv, kf0);
+        // three reductions side by side: slots taken, cheapest free slot, dearest taken slot
+        uint32_t my_up = g.up_key(lane_up), my_down = g.down_key(lane_down, key_unit, down_bias);
+        const uint32_t sum = wave_reduce32(g.kk, R, Add32{});
+        uint32_t up = wave_reduce32(my_up, R, Min32{});
+        uint32_t down = wave_reduce32(my_down, R, Min32{});
+        int miss = (int)(m - sum);
+        const uint32_t nearest = up < down ? up : down;
+        uint32_t dearest = 0;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64((uint32_t)(miss + 1) > 2u) != 0, 0)) {
+            // all but the last slot to add or drop (with 16 rails one run in four needs this, with 9 one in eight)
+            int left = __builtin_amdgcn_readfirstlane(miss);
+            if (left > 1 && left <= kRepairMax) {
+                do {
+                    dearest = up > dearest ? up : dearest;
+                    if (my_up == up) { ++g.kk; g.p = g.p_next; g.p_next += lc1; my_up = g.up_key(lane_up); }
+                    up = wave_reduce32(my_up, R, Min32{});
+                } while (--left > 1);
+            } else if (left < -1 && left >= -kRepairMax) {
+                do {
+                    dearest = down > dearest ? down : dearest;
+                    if (my_down == down) { --g.kk; g.p_next = g.p; g.p -= lc1; my_down = g.down_key(lane_down, key_unit, down_bias); }
+                    down = wave_reduce32(my_down, R, Min32{});
+                } while (++left < -1);
+            }
+            miss = left;
+        }
+        const uint32_t used = miss == 1 ? up : down;
+        const bool odd = ((uint32_t)(miss + 1) > 2u) | (nearest < 64u) | ((used > dearest ? used : dearest) >= kFarKey);
+        // the last slot: add it (miss = 1), drop it (miss = -1) or nothing
+        const bool add = (my_up == up) & (miss == 1), drop = (my_down == down) & (miss == -1);
+        double X_after = add ? g.p_next : drop ? g.p - lc1 : g.p;
+        uint32_t kk = g.kk + (add ? 1u : 0u) - (drop ? 1u : 0u);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0 || !serves, 0)) {
+            const SplitResult r = split_odd_run<kWide>(m, serves, T, cnt, rail, live, A_less_T, lane,
+                                                       &ring.rec[at % kRingRecords][0]);
+            X_after = r.X;
+            kk = r.kk;
+        }
+        X = X_after;
+        return kk;
+    };
+
+    // One slice of t bytes: plain argmin.  Returns a word whose low six bits name the rail.
+    auto bind_single = [&](double t, bool serves) -> uint32_t {
+        const double p = fma(t, c1_f, X);
+        uint32_t mine = (saturating_u32(fma(p, key_unit, single_bias)) & ~63u) | lane_up;
+        uint32_t best = wave_reduce32(mine, R, Min32{});
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(best - 64u >= kFarKey - 64u) != 0 || !serves, 0)) {
+            // outside the window: compare whole costs
+            best = odd_single<kWide>(rail, A_less_T + (uint64_t)T + (uint64_t)t, live, lane);
+            mine = lane_up;
+        }
+        const bool won = mine == best;
+        X = won ? p : X;
+        const double T_more = T + t;
+        T = won ? T_more : T;
+        cnt += won ? 1u : 0u;
+        return best;
+    };
+
+    // The records' cells: the rail's bytes before the run, its slots, and the rail of the single slice behind it.
+    RunCell* const my_cell = b.run_cell + lane;
     const uint32_t stride = b.run_stride;
-    uint64_t* row_T = b.run_T + lane;
-    uint32_t* row_K = b.run_K + lane;
-
-    bool all_proven = false;                                  // every admitted rail has received a slot
-    // cost level of the last run that went down the lean path: single slices that follow are compared
-    // relative to it with 32-bit keys
-    uint64_t ref_level = kNoLevel;
-    const uint32_t lane_rev = 63u - (uint32_t)lane;
-
-    // One slice of l bytes: plain argmin.  Near a known level the costs are compared as 32-bit keys
-    // (cost - level + 2^24) << 6 | lane; a rail far above the window gets a far key, a rail below it key 0, and a
-    // winning key below 64 or a far one sends the slice to the 64-bit compare, as does an unknown level.
-    // Returns 1 in the winning lane.
-    auto bind_single = [&](uint32_t l) -> uint32_t {
-        const uint64_t p_one = P + (uint64_t)l * rail.c1;
-        const uint64_t cost = rail.c0 + (p_one >> 16);
-        int win = 0;
-        bool keyed = ref_level != kNoLevel;
-        if (__builtin_expect(keyed, 1)) {
-            const uint64_t rel = cost - ref_level + (kRelSpan >> 1);
-            uint32_t key;
-            if constexpr (kFar) {
-                const uint32_t near_key = rel < kRelSpan ? (((uint32_t)rel << 6) | (uint32_t)lane) : kFarKey | (uint32_t)lane;
-                key = live ? ((int64_t)rel < 0 ? 0u : near_key) : kNoKey;
-            } else {
-                key = live ? (rel < kRelSpan ? (((uint32_t)rel << 6) | (uint32_t)lane) : 0u) : kNoKey;
-            }
-            const uint32_t best = wave_min_key<R>(key);
-            win = (int)(best & 63u);
-            keyed = best - 64u < kFarKey - 64u;
-        }
-        if (__builtin_expect(!keyed, 0)) win = argmin_cost(cost, live, lane, R);
-        const bool mine = lane == win;
-        if (mine) {
-            P = p_one;
-            T += l;
-            cnt += 1u;
-            Bd -= (double)l;
-        }
-        return mine ? 1u : 0u;
-    };
-
-    // A run of m >= 2 slices of l bytes with estimated end level vi: slots per rail.
-    auto bind_run = [&](uint32_t l, uint32_t m, uint64_t vi, double level_f, double inv_l) -> uint32_t {
-        const uint64_t lc1 = (uint64_t)l * rail.c1;           // cost numerator of one slice on this rail
-        if (__builtin_expect(vi != kNoLevel, 1)) {          // a record carries a level only for kTol < m < kLeanRunMax
-            // Lean path.  Slots at or below the level, per rail: slot j is iff j + 1 < kf, so the count is
-            // ceil(kf) - 1, taken as trunc(kf - 1e-6) (an exactly integer kf, common when all lengths are
-            // multiples of a power of two, must not count, hence the small bias against rounding noise).  The
-            // estimate is confirmed by the integer cost of the slot below (last one taken), which must not exceed
-            // the level, and of the slot above (first one free), which must; a count beyond the run's length
-            // fails the same test.  A rail whose first slot lies far above the level (a long queue) takes no
-            // slot and stays out of the repair through its far key.
-            const double kf = fma(fma(level_f, G, Bd), inv_l, -1.0e-6);
-            uint32_t kk;                                                          // trunc(kf); below zero gives 0, above 2^32 - 1 saturates
-            asm("v_cvt_u32_f64_e32 %0, %1" : "=v"(kk) : "v"(kf));
-            // kk * lc1 from a 32 x 32 -> 64 product and one 32-bit product for the high half (sums are modulo 2^64,
-            // as the exact value fits by the plan's precondition whenever kk is a count that the test below accepts)
-            uint64_t p_prev = P + (uint64_t)kk * (uint32_t)lc1;                  // slot kk-1 ends here
-            p_prev += (uint64_t)((uint32_t)(lc1 >> 32) * kk) << 32;
-            uint64_t p_next = p_prev + lc1;                                       // slot kk ends here
-            // costs relative to the level, signed: the first free slot must lie above it (up >= 1), the last taken
-            // slot not above it (below <= 0)
-            const int64_t cv = (int64_t)(rail.c0 - vi);
-            int64_t up = (int64_t)(p_next >> 16) + cv;
-            int64_t below = (int64_t)(p_prev >> 16) + cv;
-            // kFar: a rail may lie far on the harmless side of the level (far keys); otherwise every rail must
-            // lie within the window, which saves the two selects per run where all rails stay close to the level
-            const bool off = kFar ? live & ((kk > m) | ((kk < m) & (up < 1)) | ((kk > 0) & (below > 0)))
-                                  : live & ((kk > m) | ((kk < m) & ((uint64_t)(up - 1) >= kRelSpan - 1)) |
-                                            ((kk > 0) & ((uint64_t)(below + (int64_t)(kRelSpan - 1)) >= kRelSpan)));
-            auto up_key = [&]() -> uint32_t {
-                return up < (int64_t)kRelSpan ? (((uint32_t)up << 6) | (uint32_t)lane) : kFarKey | (uint32_t)lane;
-            };
-            auto down_key = [&]() -> uint32_t {
-                return below > -(int64_t)kRelSpan ? (((0u - (uint32_t)below) << 6) | lane_rev) : kFarKey | lane_rev;
-            };
-            {   // a lane that is off adds kOffMark to the slot sum, which then misses m by more than any repair covers
-                // three reductions side by side: slots taken, cheapest free slot, dearest taken slot
-                // (ties: the free slot of the lowest rail is next, the taken slot of the highest rail is last)
-                uint32_t key_up = (live & (kk < m)) ? (kFar ? up_key() : (((uint32_t)up << 6) | (uint32_t)lane)) : kNoKey;
-                uint32_t key_down = (live & (kk > 0)) ? (kFar ? down_key() : (((0u - (uint32_t)below) << 6) | lane_rev)) : kNoKey;
-                const uint32_t sum_r = wave_reduce32(off ? kOffMark : kk, R, Add32{});
-                uint32_t up_r = wave_reduce32(key_up, R, Min32{});
-                uint32_t down_r = wave_reduce32(key_down, R, Min32{});
-                int miss = (int)m - (int)(uint32_t)__builtin_amdgcn_readfirstlane((int)sum_r);
-                if (__builtin_expect(miss >= -kTol && miss <= kTol, 1)) {
-                    // repair one slot at a time: add the cheapest free slot / drop the dearest taken slot; the
-                    // first step's winners are already known, further steps redo one reduction each
-                    // (true: done; false: no near candidate, start over in the general path)
-                    auto repair = [&]() -> bool {
-                        if (miss > 0) {
-                            for (int need = miss;;) {
-                                const uint32_t best = (uint32_t)__builtin_amdgcn_readfirstlane((int)up_r);
-                                if (best >= kFarKey) return false;
-                                if (lane == (int)(best & 63u)) {
-                                    ++kk;
-                                    p_prev = p_next;
-                                    p_next += lc1;
-                                    up = (int64_t)(p_next >> 16) + cv;
-                                    key_up = kk < m ? up_key() : kNoKey;
-                                }
-                                if (--need == 0) return true;
-                                up_r = wave_reduce32(key_up, R, Min32{});
-                            }
-                        }
-                        for (int drop = -miss;;) {
-                            const uint32_t best = (uint32_t)__builtin_amdgcn_readfirstlane((int)down_r);
-                            if (best >= kFarKey) return false;
-                            if (lane == 63 - (int)(best & 63u)) {
-                                --kk;
-                                p_next = p_prev;
-                                p_prev -= lc1;
-                                below = (int64_t)(p_prev >> 16) + cv;
-                                key_down = kk > 0 ? down_key() : kNoKey;
-                            }
-                            if (--drop == 0) return true;
-                            down_r = wave_reduce32(key_down, R, Min32{});
-                        }
-                    };
-                    const bool exact = miss == 0 || repair();
-                    if (__builtin_expect(exact, 1)) {
-                        P = p_prev;
-                        T += (uint64_t)kk * l;
-                        cnt += kk;
-                        Bd = fma(-(double)kk, (double)l, Bd);
-                        ref_level = vi;
-                        return kk;
-                    }
-                }
-            }
-        }
-        // General path (any state, any level), kept out of line so that the loop stays short.
-        const uint64_t res = bind_run_general<kWide>(ChainVars{P, T, Bd, ref_level, cnt, all_proven ? 1u : 0u, 0u}, rail, G, g, live,
-                                                     live_mask, A_less_T, lane, l, m, vi, level_f, inv_l);
-        const uint32_t k = (uint32_t)res;
-        all_proven = (res >> 32) != 0;
-        T += (uint64_t)k * l;
-        cnt += k;
-        Bd = fma(-(double)k, (double)l, Bd);
-        P = (A_less_T + T) * (uint64_t)rail.c1;
-        ref_level = kNoLevel;
-        return k;
-    };
-
-    auto put_row = [&](uint64_t T_before, uint32_t k) {
-        *row_T = T_before;
-        *row_K = k;
-        row_T += stride;
-        row_K += stride;
-    };
-
-    auto pair64 = [](uint32_t lo, uint32_t hi, int t) -> uint64_t {
-        return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, t) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)lo, t);
-    };
-
-    // Block j of kWide records, one per lane, from the ring the feeder wavefront keeps filled.
-    auto take_block = [&](uint64_t j, Quad& lo, Quad& hi) {
-        while (__hip_atomic_load(&ring.filled, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= (uint32_t)j)
+    uint32_t block_end = 0;                                   // the chain may read records before this one
+    auto next_block = [&]() {
+        if (lane == 0) __hip_atomic_store(&ring.taken, at, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        uint32_t filled;
+        while ((filled = (uint32_t)__builtin_amdgcn_readfirstlane(
+                    (int)__hip_atomic_load(&ring.filled, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP))) <= at)
             __builtin_amdgcn_s_sleep(1);
-        lo = ring.lo[j % kRingBlocks][lane];
-        hi = ring.hi[j % kRingBlocks][lane];
-        if (lane == 0) __hip_atomic_store(&ring.taken, (uint32_t)j + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        block_end = filled < at + kFeedBlock ? filled : at + kFeedBlock;
     };
-    Quad mine_lo = {0, 0, 0, 0}, mine_hi = {0, 0, 0, 0};
-    for (uint64_t blk = 0; blk < n_runs; blk += kWide) {
-        take_block(blk / kWide, mine_lo, mine_hi);
-        const int in_blk = (int)(n_runs - blk < (uint64_t)kWide ? n_runs - blk : (uint64_t)kWide);
-        for (int t = 0; t < in_blk; ++t) {
-            const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)mine_lo.x, t);
-            const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)mine_lo.y, t);
-            const uint64_t T_before = T;
-            if (m == 1) {
-                put_row(T_before, bind_single(l));
-                continue;
-            }
-            put_row(T_before, bind_run(l, m, pair64(mine_lo.z, mine_lo.w, t), __longlong_as_double((long long)pair64(mine_hi.x, mine_hi.y, t)),
-                                       __longlong_as_double((long long)pair64(mine_hi.z, mine_hi.w, t))));
-            // the single slice that usually follows a run (a transfer's tail) is bound in the same round
-            if (t + 1 < in_blk && (uint32_t)__builtin_amdgcn_readlane((int)mine_lo.y, t + 1) == 1u) {
-                ++t;
-                const uint32_t l_tail = (uint32_t)__builtin_amdgcn_readlane((int)mine_lo.x, t);
-                const uint64_t T_mid = T;
-                put_row(T_mid, bind_single(l_tail));
-            }
+    next_block();
+    Quad q0 = ring.rec[0][0], q1 = ring.rec[0][1];
+    auto step_on = [&]() {
+        ++at;
+        if (__builtin_expect(at == block_end, 0)) next_block();
+        q0 = ring.rec[at % kRingRecords][0];
+    };
+    for (;;) {
+        uint32_t flags = (uint32_t)__builtin_amdgcn_readfirstlane((int)q0.y);
+        while (flags == kRecShort) {                                  // a loop of its own: nothing to merge with the rest
+            const double T_before = T;
+            X += join_f64(q0.z, q0.w);                                // from the level of the record before to this one's
+            const uint32_t kk = split_run(q0.x, true);
+            T = fma((double)kk, l_f, T);
+            cnt += kk;
+            step_on();
+            const uint32_t tail_rail = bind_single(join_f64(q1.x, q1.y), true);
+            *(my_cell + (uint64_t)q1.z * stride) = RunCell{T_before, kk, tail_rail};
+            q1 = ring.rec[at % kRingRecords][1];
+            flags = (uint32_t)__builtin_amdgcn_readfirstlane((int)q0.y);
         }
+        if (flags & kRecEnd) break;
+        const Quad q2 = ring.rec[at % kRingRecords][2], q3 = ring.rec[at % kRingRecords][3];
+        const bool serves = !(flags & kRecNoLevel);
+        const double T_before = T;
+        uint32_t kk = 0, tail_rail = 0;
+        if (flags & kRecRebase) X = relative_cost(rail, live, A_less_T + (uint64_t)T, join_f64(q2.x, q2.y));
+        else X += join_f64(q0.z, q0.w);
+        if (!(flags & kRecSingle)) {
+            l_f = (double)q2.z;
+            lc1 = l_f * c1_f;                                         // whole, below 2^53 where the record serves
+            inv = join_f64(q3.x, q3.y) * rail.inv_c1;
+            kf0 = 65535.5 * inv;
+            kk = split_run(q0.x, serves);
+            T = fma((double)kk, l_f, T);
+            cnt += kk;
+        }
+        if (flags & (kRecTail | kRecSingle)) tail_rail = bind_single(join_f64(q1.x, q1.y), serves);
+        *(my_cell + (uint64_t)q1.z * stride) = RunCell{T_before, kk, tail_rail};
+        step_on();
+        q1 = ring.rec[at % kRingRecords][1];
     }
 
     // per-rail totals and staging region bases (exclusive sum of 256-byte-rounded totals)
-    const uint64_t rounded = (T + 255) & ~255ull;
+    const uint64_t bound = (uint64_t)T;
+    const uint64_t rounded = (bound + 255) & ~255ull;
     uint64_t inc = rounded;
 #pragma unroll
     for (int d = 1; d < kWide; d <<= 1) {
@@ -642,38 +681,41 @@ __device__ __forceinline__ void bind_chain(const BatchDev& b, const RailParams& 
         if (lane >= d) inc += up;
     }
     PlanState* ps = b.plan;
-    ps->T[lane] = T;
+    ps->T[lane] = bound;
     ps->cnt[lane] = cnt;
-    ps->A_after[lane] = A_less_T + T;
+    ps->A_after[lane] = A_less_T + bound;
     ps->base[lane] = inc - rounded;
     if (lane == 0) ps->n_bound = ps->n_pending + n_before;
 }
 
 // Wavefront 0 walks the chain, wavefront 1 feeds it the run records.
-template <int kWide, bool kFar>
-__global__ void __launch_bounds__(128) bind_chain_kernel(BatchDev b, RailParams rp, int mode,
-                                                         const RunRec* __restrict__ recs)
+template <int kWide>
+__device__ __forceinline__ void chain_workgroup(const BatchDev& b, const RailParams& rp, int mode, RecordRing& ring, LevelModel& lm)
 {
-    __shared__ RecordRing<kWide> ring;
-    ring_reset(ring);
-    __syncthreads();
-    if (threadIdx.x < 64) bind_chain<kWide, kFar>(b, rp, mode, ring);
-    else feed_records<kWide>(b, recs, ring, (int)threadIdx.x - 64);
+    if (threadIdx.x == 0) { ring.filled = 0; ring.taken = 0; }
+    build_level_model(lm, b, rp, mode);                              // (with barriers)
+    if (threadIdx.x < 64) bind_chain<kWide>(b, rp, mode, ring);
+    else if (threadIdx.x < 128) feed_records(b, mode, lm, ring, threadIdx.x - 64);
+}
+
+template <int kWide>
+__global__ void __launch_bounds__(128) bind_chain_kernel(BatchDev b, RailParams rp, int mode)
+{
+    __shared__ RecordRing ring;
+    __shared__ LevelModel lm;
+    chain_workgroup<kWide>(b, rp, mode, ring, lm);
 }
 
 // The chain is one wavefront; the tile tables of the copy kernels depend on the slice table only, not
 // on the binding.  On a first plan both go into one launch: workgroup 0 walks the chain, the others
 // build the tables, so the tables cost no time of their own.
-template <int kWide, bool kFar>
-__global__ void __launch_bounds__(256) bind_chain_tables_kernel(BatchDev b, RailParams rp, int mode,
-                                                                const RunRec* __restrict__ recs)
+template <int kWide>
+__global__ void __launch_bounds__(256) bind_chain_tables_kernel(BatchDev b, RailParams rp, int mode)
 {
-    __shared__ RecordRing<kWide> ring;
+    __shared__ RecordRing ring;
+    __shared__ LevelModel lm;
     if (blockIdx.x == 0) {
-        ring_reset(ring);
-        __syncthreads();
-        if (threadIdx.x < 64) bind_chain<kWide, kFar>(b, rp, mode, ring);
-        else if (threadIdx.x < 128) feed_records<kWide>(b, recs, ring, (int)threadIdx.x - 64);
+        chain_workgroup<kWide>(b, rp, mode, ring, lm);
         return;
     }
     build_tile_tables(b, blockIdx.x - 1, gridDim.x - 1);
@@ -707,28 +749,43 @@ __global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams r
             if (!head) r -= 1;
         }
         const uint32_t start = b.run_start[r];
+        const RunCell* row = b.run_cell + r * stride;
+        if (b.run_start[r + 1] - start == 1) {
+            // a single slice: its rail stands in the row of the longer run it was bound with, or in its own
+            const bool joined = r > 0 && start - b.run_start[r - 1] > 1;
+            const RunCell* own = joined ? row - stride : row;
+            const uint32_t d = own->tail & 63u;
+            uint64_t off = (uint64_t)own[d].T;
+            if (joined) {
+                const uint32_t before = b.run_start[r - 1];
+                off += (uint64_t)own[d].K * b.s_len[use_pending ? b.pending[before] : before];
+            }
+            b.s_rail[id_q] = d;
+            b.s_stage_off[id_q] = off;
+            b.s_state[id_q] = TENT_SLICE_BOUND;
+            continue;
+        }
         const uint32_t l = b.s_len[id_q];
         const double inv_l = 1.0 / (double)l;
-        const uint64_t row = r * stride;
         // slot t -> (d, k)
         uint32_t t = (uint32_t)(q - start), d = 0;
         for (; d < R; ++d) {
-            const uint32_t kd = ((rp.admitted >> d) & 1) ? b.run_K[row + d] : 0;
+            const uint32_t kd = ((rp.admitted >> d) & 1) ? row[d].K : 0;
             if (t < kd) break;
             t -= kd;
         }
         if (d >= R) continue;
         const uint32_t k = t;
-        const uint64_t T_d = b.run_T[row + d];
+        const uint64_t T_d = (uint64_t)row[d].T;
         Rail me{sh_c0[d], sh_c1[d], sh_inv[d]};
         const uint64_t f = slot_cost(me, rp.A[d] + T_d, l, k);
         uint64_t rank = k;
         for (uint32_t o = 0; o < R; ++o) {
             if (o == d || !((rp.admitted >> o) & 1)) continue;
-            const uint32_t ko = b.run_K[row + o];
+            const uint32_t ko = row[o].K;
             if (ko == 0) continue;
             Rail other{sh_c0[o], sh_c1[o], sh_inv[o]};
-            const uint64_t A_o = rp.A[o] + b.run_T[row + o];
+            const uint64_t A_o = rp.A[o] + (uint64_t)row[o].T;
             // slots of a lower rail win ties, slots of a higher rail lose them
             const uint32_t c = slots_upto(other, A_o, l, inv_l, o < d ? (int64_t)f : (int64_t)f - 1, ko);
             rank += c;
@@ -756,40 +813,16 @@ hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, h
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     hipLaunchKernelGGL(run_table_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, up);
-    // one record per run for the chain
-    hipLaunchKernelGGL(run_records_kernel, dim3((b.run_capacity + 1 + 255) / 256), dim3(256), 0, s, b, rp, mode);
-    // Which variant of the chain: when the rails' head costs lie close together at the start (idle rails, short
-    // queues) and no rail's slots are far apart, all rails stay close to the common level throughout and the
-    // variant without far keys is a few percent faster; otherwise (long queues, bytes of a rotation pass ahead,
-    // large slices on a slow rail) rails may sit far from the level.  Either variant is exact for any input.
-    bool far_keys = (mode & kBindAfterRotation) != 0;
-    {
-        uint64_t lo = ~0ull, hi = 0;
-        for (uint32_t d = 0; d < rp.n_rails; ++d) {
-            if (!((rp.admitted >> d) & 1)) continue;
-            const uint64_t h = rp.c0[d] + ((rp.A[d] * rp.c1[d]) >> 16);       // in range by the plan's precondition
-            lo = h < lo ? h : lo;
-            hi = h > hi ? h : hi;
-            // a rail whose slots are a large part of the window apart often has its next slot outside it
-            if (((b.slice_bytes * rp.c1[d]) >> 16) >= (kRelSpan >> 2)) far_keys = true;
-        }
-        if (hi >= lo && hi - lo >= (kRelSpan >> 1)) far_keys = true;
-    }
-    auto launch_chain = [&](auto wide, auto far) {
+    auto launch_chain = [&](auto wide) {
         constexpr int kW = decltype(wide)::value;
-        constexpr bool kF = decltype(far)::value;
         if (mode & kBindBuildTables)
-            hipLaunchKernelGGL((bind_chain_tables_kernel<kW, kF>), dim3(1 + tile_table_blocks(b)), dim3(256), 0, s, b, rp, mode, b.run_rec);
+            hipLaunchKernelGGL(bind_chain_tables_kernel<kW>, dim3(1 + tile_table_blocks(b)), dim3(256), 0, s, b, rp, mode);
         else
-            hipLaunchKernelGGL((bind_chain_kernel<kW, kF>), dim3(1), dim3(128), 0, s, b, rp, mode, b.run_rec);
+            hipLaunchKernelGGL(bind_chain_kernel<kW>, dim3(1), dim3(128), 0, s, b, rp, mode);
     };
-    auto launch_width = [&](auto far) {
-        if (rp.n_rails <= 16)      launch_chain(std::integral_constant<int, 16>{}, far);
-        else if (rp.n_rails <= 32) launch_chain(std::integral_constant<int, 32>{}, far);
-        else                       launch_chain(std::integral_constant<int, 64>{}, far);
-    };
-    if (far_keys) launch_width(std::true_type{});
-    else          launch_width(std::false_type{});
+    if (rp.n_rails <= 16)      launch_chain(std::integral_constant<int, 16>{});
+    else if (rp.n_rails <= 32) launch_chain(std::integral_constant<int, 32>{});
+    else                       launch_chain(std::integral_constant<int, 64>{});
     hipLaunchKernelGGL(bind_emit_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, rp, up);
     return hipGetLastError();
 }

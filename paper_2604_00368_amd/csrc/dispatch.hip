@@ -130,8 +130,7 @@ __device__ __forceinline__ void dispatch_chain(const BatchDev& b, const RailPara
             }
             if (lane < (int)stride) {
                 const uint64_t row = (uint64_t)(blk + t) * stride + lane;
-                b.run_K[row] = (uint32_t)K;
-                b.run_T[row] = T;
+                b.run_cell[row] = RunCell{(double)T, (uint32_t)K, 0u};
             }
             A += bytes;
             T += bytes;
@@ -201,7 +200,7 @@ __global__ void __launch_bounds__(256) dispatch_emit_kernel(BatchDev b, RailPara
         const uint64_t row = (uint64_t)j * stride;
         uint32_t t = (uint32_t)(q - q0), d = 0;
         for (; d < R; ++d) {
-            const uint32_t kd = b.run_K[row + d];
+            const uint32_t kd = b.run_cell[row + d].K;
             if (t < kd) break;
             t -= kd;
         }
@@ -211,13 +210,13 @@ __global__ void __launch_bounds__(256) dispatch_emit_kernel(BatchDev b, RailPara
         if (mode == 2) {
             const uint64_t req_len = b.src_pre[b.src_ptr[j + 1]] - b.src_pre[b.src_ptr[j]];
             const uint64_t L = req_len < S ? req_len : S;
-            uint64_t s_d = rp.c0[d] + (((rp.A[d] + b.run_T[row + d] + L) * rp.c1[d]) >> 16);
+            uint64_t s_d = rp.c0[d] + (((rp.A[d] + (uint64_t)b.run_cell[row + d].T + L) * rp.c1[d]) >> 16);
             if (s_d == 0) s_d = 1;
             const uint64_t key = (uint64_t)(k + 1) * s_d;
             for (uint32_t o = 0; o < R; ++o) {
-                const uint32_t ko = b.run_K[row + o];
+                const uint32_t ko = b.run_cell[row + o].K;
                 if (o == d || ko == 0) continue;
-                uint64_t s_o = rp.c0[o] + (((rp.A[o] + b.run_T[row + o] + L) * rp.c1[o]) >> 16);
+                uint64_t s_o = rp.c0[o] + (((rp.A[o] + (uint64_t)b.run_cell[row + o].T + L) * rp.c1[o]) >> 16);
                 if (s_o == 0) s_o = 1;
                 // slots of a lower rail win ties, slots of a higher rail lose them
                 const uint64_t before = (o < d ? key : key - 1) / s_o;
@@ -226,7 +225,7 @@ __global__ void __launch_bounds__(256) dispatch_emit_kernel(BatchDev b, RailPara
         }
         const uint32_t id = b.pending[q0 + rank];
         b.s_rail[id] = d;
-        b.s_stage_off[id] = b.run_T[row + d] + (uint64_t)k * S;
+        b.s_stage_off[id] = (uint64_t)b.run_cell[row + d].T + (uint64_t)k * S;
         b.s_state[id] = TENT_SLICE_BOUND;
     }
 }

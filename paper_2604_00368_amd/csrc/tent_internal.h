@@ -87,13 +87,13 @@ struct PlanState {
     uint64_t n_act_asked;                 // one-pass copies: tiles of the BOUND slices, listed or not
 };
 
-// What the binding chain needs to know about a run of equal-length slices: 32 bytes, read as two 16-byte halves.
-struct RunRec {
-    uint32_t len;                  // slice length of the run
-    uint32_t m;                    // slices in the run
-    uint64_t level;                // estimated cost level at the end of the run, ~0 = no estimate
-    double   level_f;              // the same as a double
-    double   inv_len;              // 1.0 / len
+// What the binding chains leave for the emit kernels, per run (request) and rail, in one 16-byte store: bytes bound to
+// the rail before it (a whole number below 2^53), slots the rail takes in it, and in its low six bits the rail of the
+// single slice that was bound together with the run.
+struct RunCell {
+    double   T;
+    uint32_t K;
+    uint32_t tail;
 };
 
 // What a copy workgroup needs to know about its slice, in one 16-byte scalar load.
@@ -181,11 +181,9 @@ struct BatchDev {
 
     // Run-parallel binding: maximal runs of equal-length pending slices (at most two per transfer)
     uint32_t* run_start;           // [run_capacity + 1] first pending position of every run
-    uint64_t* run_T;               // [run_capacity * run_stride] bytes bound per rail before the run
-    uint32_t* run_K;               // [run_capacity * run_stride] slots each rail takes in the run
+    RunCell*  run_cell;            // [run_capacity * run_stride]
     uint32_t  run_capacity;        // 2 * n_desc
     uint32_t  run_stride;          // entries per row: the context's rail limit rounded up to 16, 32 or 64
-    RunRec*   run_rec;             // [run_capacity + 1] one record per run (the last one is a spare the chain's look-ahead may read)
     uint64_t* len_pre;             // [n_slices + 1] bytes of the pending slices before every pending position
 
     uint32_t* pending;             // [n_slices] ascending ids of slices not DONE and never failed (re-planning)

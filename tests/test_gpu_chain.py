@@ -1,0 +1,99 @@
+"""The binding chain where its short path gives way: rails far from the cost level, slots and runs that lift the level
+by more than the relative state spans, slices outside the key window, more records than the ring holds, runs of a few
+slices.  Rails, staging offsets and totals against the oracle, bit for bit."""
+import numpy as np
+import pytest
+
+from paper_2604_00368_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+PS = 10 ** 12
+
+
+@pytest.fixture(scope="module")
+def H():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_harness
+    return gpu_harness
+
+
+def transfers(lens, S, rails):
+    """Contiguous transfers of the given byte lengths, destinations in the same order."""
+    lens = np.asarray(lens, dtype=np.uint64)
+    D = lens.shape[0]
+    ext = np.zeros(D, dtype=W.EXTENT_DTYPE)
+    ext["len"], ext["off"] = lens, np.concatenate([[0], np.cumsum(lens)[:-1]])
+    ptr = np.arange(D + 1, dtype=np.uint32)
+    dst = ext.copy()
+    dst["seg"] = W.DST_SEG
+    total = int(lens.sum())
+    return W.Workload("transfers", 0, S, [total, total], ptr, ext, ptr.copy(), dst, rails, "u8")
+
+
+def check_binding(H, oracle, w):
+    s = oracle.split(w.src_ptr, w.src_ext, w.slice_bytes)
+    b = oracle.bind(s.len, w.rails)
+    assert b.status == 0
+    with H.Engine(w) as eng:
+        eng.declare()
+        st, info = eng.plan()
+        assert st == 0
+        H.assert_plan_equal(eng.table(), s, b, info)
+        st, info = eng.plan()                                  # the same again over a used run table
+        H.assert_plan_equal(eng.table(), s, b, info)
+
+
+def mixed_lengths(rng, n, S, most):
+    """Whole multiples, tails of every length, transfers shorter than a slice, equal neighbours."""
+    lens = rng.integers(1, most * S, size=n)
+    lens[rng.random(n) < 0.15] = S * int(rng.integers(1, most))
+    lens[rng.random(n) < 0.1] = int(rng.integers(1, S))
+    return lens
+
+
+KINDS = {
+    # queues 0 .. 0.25 s apart: rails are infinitely far (2^36 ps) at first and join while the plan runs
+    "queues_that_are_reached": lambda g, R: W.make_rails(g.integers(16, 40, size=R), queued=g.integers(0, 1 << 22, size=R)),
+    "queues_never_reached": lambda g, R: W.make_rails(g.integers(20000, 90000, size=R),
+                                                      queued=np.where(np.arange(R) % 3 == 1, 1 << 36, 0)),
+    # one slice of 512 KiB costs 2^34 ps and more on some rails: no level serves
+    "slots_beyond_a_step": lambda g, R: W.make_rails(np.where(np.arange(R) % 2 == 0, 16, 90)),
+    # tails and single slices far outside the window of the 32-bit keys
+    "wide_spread": lambda g, R: W.make_rails(np.where(np.arange(R) % 2 == 0, 400000, 20), lat_ns=g.integers(0, 1 << 20, size=R)),
+    "one_fast_rail": lambda g, R: W.make_rails(np.where(np.arange(R) == R - 1, 4000000, 1000)),
+    "identical": lambda g, R: W.make_rails([50000] * R),
+    "degraded_and_excluded": lambda g, R: W.make_rails(g.integers(1000, 90000, size=R), queued=g.integers(0, 1 << 16, size=R),
+                                                       health=np.where(np.arange(R) % 4 == 0, 0, np.arange(R) % 3)),
+    "free_of_cost": lambda g, R: W.make_rails([4000000] * R, lat_ns=0, beta1_q8=1, penalty_q8=256),
+}
+
+
+@pytest.mark.parametrize("R", [1, 2, 9, 16, 17, 40])
+@pytest.mark.parametrize("kind", sorted(KINDS))
+def test_chain_against_oracle(H, oracle, kind, R):
+    g = np.random.Generator(np.random.PCG64([R, len(kind)]))
+    S, n = {"slots_beyond_a_step": (1 << 19, 60), "queues_that_are_reached": (4096, 700)}.get(kind, (192, 700))
+    check_binding(H, oracle, transfers(mixed_lengths(g, n, S, 12), S, KINDS[kind](g, R)))
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 127, 128, 129, 300, 3000])
+def test_record_ring_and_feeder_blocks(H, oracle, n):
+    # two runs per transfer, 64 runs to a feeder block, 256 records to the ring
+    g = np.random.Generator(np.random.PCG64(n))
+    rails = W.make_rails([25000, 50000] * 8, queued=g.integers(0, 5000, size=16))
+    check_binding(H, oracle, transfers(g.integers(40, 90, size=n) * 100, 1600, rails))
+
+
+@pytest.mark.parametrize("case", ["singles_only", "whole_slices_only", "pairs", "alternating_slice_of_one_byte", "one_long_run"])
+def test_run_shapes(H, oracle, case):
+    g = np.random.Generator(np.random.PCG64(17))
+    S, n = 500, 400
+    lens = {"singles_only": g.integers(1, S, size=n), "whole_slices_only": S * g.integers(1, 9, size=n),
+            "pairs": np.full(n, 2 * S), "alternating_slice_of_one_byte": np.where(np.arange(n) % 2 == 0, 1, 3 * S + 1),
+            "one_long_run": np.array([S * 60000 + 7])}[case]
+    for rails in (W.make_rails([50000] * 8 + [400000]), W.make_rails([12000, 31000, 77000], queued=[0, 40000, 9])):
+        check_binding(H, oracle, transfers(lens, S, rails))
