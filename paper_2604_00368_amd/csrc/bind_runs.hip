@@ -84,36 +84,38 @@ __device__ __forceinline__ uint32_t slots_upto(const Rail& r, uint64_t A, uint32
 // ---- step 1: run table ------------------------------------------------------------------------
 struct RunHead {
     const uint32_t* s_len;
-    const uint32_t* pending;      // nullptr: position = slice index
+    const uint32_t* pending;
     const uint64_t* n_pending;    // device-resident count of positions
     __device__ uint64_t operator()(uint64_t q) const
     {
         if (q >= *n_pending) return 0;
         if (q == 0) return 1;
-        const uint32_t a = pending ? pending[q] : (uint32_t)q;
-        const uint32_t p = pending ? pending[q - 1] : (uint32_t)(q - 1);
-        return s_len[a] != s_len[p];
+        return s_len[pending[q]] != s_len[pending[q - 1]];
     }
 };
 
 struct PendingLen {
     const uint32_t* s_len;
-    const uint32_t* pending;      // nullptr: position = slice index
+    const uint32_t* pending;
     const uint64_t* n_pending;
     __device__ uint64_t operator()(uint64_t q) const
     {
         if (q >= *n_pending) return 0;
-        return s_len[pending ? pending[q] : (uint32_t)q];
+        return s_len[pending[q]];
     }
 };
 
-__global__ void __launch_bounds__(256) run_table_kernel(BatchDev b, int use_pending)
+__global__ void __launch_bounds__(256) run_table_kernel(BatchDev b)
 {
     const uint64_t n = b.plan->n_pending;
-    RunHead head{b.s_len, use_pending ? b.pending : nullptr, &b.plan->n_pending};
+    RunHead head{b.s_len, b.pending, &b.plan->n_pending};
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += stride)
-        if (head(q) && b.scan_tmp[q] < b.run_capacity) b.run_start[b.scan_tmp[q]] = (uint32_t)q;
+    for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += stride) {
+        const bool starts = head(q) != 0;
+        const uint64_t run = b.scan_tmp[q] - (starts ? 0 : 1);
+        b.s_run[q] = (uint32_t)run;
+        if (starts && run < b.run_capacity) b.run_start[run] = (uint32_t)q;
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         // a transfer contributes at most two runs, so the capacity of 2 * n_desc always suffices
         uint64_t n_runs = b.scan_tmp[b.n_slices];
@@ -122,8 +124,6 @@ __global__ void __launch_bounds__(256) run_table_kernel(BatchDev b, int use_pend
         b.run_start[n_runs] = (uint32_t)n;
     }
 }
-
-__global__ void set_pending_all_kernel(BatchDev b) { b.plan->n_pending = b.n_slices; }
 
 // ---- step 2: chain over runs ------------------------------------------------------------------
 // Same value as slots_upto, reached from a floating-point estimate that is then checked against
@@ -273,7 +273,7 @@ __device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const 
         const uint32_t before = r > 0 ? b.run_start[r - 1] : start;
         const uint32_t len = b.s_len[pending ? b.pending[start] : start];
         const uint32_t len_after = after > end ? b.s_len[pending ? b.pending[end] : end] : 0;
-        const double bytes = (double)b.len_pre[start];
+        const double bytes = (double)(pending ? b.len_pre[start] : b.s_pos[start]);
         const uint32_t m = end - start;
         const bool single = m == 1;
         const bool joined = single && start - before > 1;            // bound together with the run before it
@@ -741,13 +741,8 @@ __global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams r
     const uint32_t stride = b.run_stride;
     const uint64_t gstride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gstride) {
-        // run of this position: number of heads at or before q, minus one
         const uint32_t id_q = use_pending ? b.pending[q] : (uint32_t)q;
-        uint64_t r = b.scan_tmp[q];
-        {
-            const bool head = q == 0 || b.s_len[id_q] != b.s_len[use_pending ? b.pending[q - 1] : (uint32_t)(q - 1)];
-            if (!head) r -= 1;
-        }
+        const uint64_t r = b.s_run[q];
         const uint32_t start = b.run_start[r];
         const RunCell* row = b.run_cell + r * stride;
         if (b.run_start[r + 1] - start == 1) {
@@ -804,15 +799,16 @@ hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, h
 {
     const bool use_pending = (mode & kBindUsePending) != 0;
     const int up = use_pending ? 1 : 0;
-    if (!use_pending) hipLaunchKernelGGL(set_pending_all_kernel, dim3(1), dim3(1), 0, s, b);
-    // run ids (a scan of the run heads) and the bytes bound before every pending position, in the same launches
-    RunHead head{b.s_len, use_pending ? b.pending : nullptr, &b.plan->n_pending};
-    PendingLen plen{b.s_len, use_pending ? b.pending : nullptr, &b.plan->n_pending};
-    hipError_t e = exclusive_scan2(head, plen, b.n_slices, b.n_slices, b.scan_tmp, b.len_pre, b.scan_partials, b.scan_partials2, s);
-    if (e != hipSuccess) return e;
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(run_table_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, up);
+    // A first plan has its run table from the slice table's expansion.  A re-plan finds run ids (a scan of the run heads) and
+    // the bytes bound before every pending position in the same launches.
+    if (use_pending) {
+        hipError_t e = run_scans(s, scan_job(RunHead{b.s_len, b.pending, &b.plan->n_pending}, b.n_slices, b.scan_tmp, b.scan_partials),
+                                 scan_job(PendingLen{b.s_len, b.pending, &b.plan->n_pending}, b.n_slices, b.len_pre, b.scan_partials2));
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(run_table_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);
+    }
     auto launch_chain = [&](auto wide) {
         constexpr int kW = decltype(wide)::value;
         if (mode & kBindBuildTables)

@@ -235,6 +235,16 @@ struct NotDone {
     __device__ uint64_t operator()(uint64_t i) const { return state[i] != TENT_SLICE_DONE; }
 };
 
+__global__ void __launch_bounds__(256) all_pending_kernel(BatchDev b)
+{
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < b.n_slices; i += stride) {
+        b.pending[i] = (uint32_t)i;
+        b.scan_tmp[i] = i;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) b.scan_tmp[b.n_slices] = b.n_slices;
+}
+
 __global__ void __launch_bounds__(256) pending_list_kernel(BatchDev b)
 {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -247,15 +257,20 @@ __global__ void __launch_bounds__(256) pending_list_kernel(BatchDev b)
 
 }  // namespace
 
-hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, bool build_tables,
+hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, bool first_plan,
                            hipStream_t s)
 {
-    hipError_t e = exclusive_scan(NotDone{b.s_state}, b.n_slices, b.scan_tmp, b.scan_partials, s);
-    if (e != hipSuccess) return e;
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(pending_list_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);
-    if (build_tables) {
+    if (first_plan) {
+        // nothing is DONE yet: every slice is its own pending position
+        hipLaunchKernelGGL(all_pending_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);
+    } else {
+        hipError_t e = exclusive_scan(NotDone{b.s_state}, b.n_slices, b.scan_tmp, b.scan_partials, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(pending_list_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);
+    }
+    if (first_plan) {
         const dim3 grid(1 + tile_table_blocks(b)), block(256);
         if (rp.n_rails <= 16)      hipLaunchKernelGGL(dispatch_chain_tables_kernel<16>, grid, block, 0, s, b, rp, dp);
         else if (rp.n_rails <= 32) hipLaunchKernelGGL(dispatch_chain_tables_kernel<32>, grid, block, 0, s, b, rp, dp);

@@ -1,12 +1,16 @@
 // Device-wide exclusive prefix scan over 64-bit integers for gfx950.
 //
-// Three launches: (1) every workgroup reduces its tile, (2) one workgroup scans the
-// per-tile results, (3) every workgroup scans its tile again and combines with its tile's prefix.
-// Inside a workgroup each lane owns kScanItems consecutive elements; lane totals are
-// combined with a 64-wide wavefront scan and the wavefront totals are carried through LDS.
+// Two launches: (1) every workgroup reduces its tile, (2) every workgroup combines the results of the tiles
+// before its own and scans its tile behind them.  One launch when everything fits one tile, three (the
+// tile results scanned by one workgroup in between) from kSelfSpine tiles on, where reading them all in every
+// workgroup would cost more than the launch.  Inside a workgroup each lane owns kScanItems consecutive elements; lane
+// totals are combined with a 64-wide wavefront scan and the wavefront totals are carried through LDS.
 // The operator is any associative, commutative integer operation with identity 0 (sum by default,
 // maximum for "furthest end seen so far").  The result does not depend on scheduling (a fixed
 // tree of integer operations), and no workgroup ever waits on another one.
+//
+// What bounds a scan here is the launches (4.6 us each on MI355X even when they do next to nothing), so scans that do not
+// depend on each other are jobs of one call and share theirs, one row of workgroups per job.
 #pragma once
 
 #include "tent_internal.h"
@@ -53,152 +57,136 @@ __device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t* b
     return lane == 0 ? carry : op(carry, before);
 }
 
-template <class F, class Op>
-__global__ void __launch_bounds__(kScanBlock) scan_reduce_kernel(F f, Op op, uint64_t n, uint64_t* partials)
+// Where a scan's results go: out(i, f(0) op ... op f(i - 1)) is called for every i in [0, n].
+struct StoreTo {
+    uint64_t* out;
+    __device__ __forceinline__ void operator()(uint64_t i, uint64_t v) const { out[i] = v; }
+};
+
+// One scan of n > 0 values f(0) .. f(n - 1); partials needs scan_partials_capacity(n) entries.
+template <class F, class Op, class Out>
+struct ScanJob {
+    F f;
+    Op op;
+    Out out;
+    uint64_t n;
+    uint64_t* partials;
+};
+template <class F, class Op = ScanSum>
+ScanJob<F, Op, StoreTo> scan_job(F f, uint64_t n, uint64_t* out, uint64_t* partials, Op op = Op{})
+{
+    return {f, op, StoreTo{out}, n, partials};
+}
+
+constexpr uint64_t kSelfSpine = 2048;
+
+inline uint64_t scan_tiles(uint64_t n) { return (n + kScanTile - 1) / kScanTile; }
+
+// (everything below has internal linkage: the same instantiation may exist in several translation units, each
+// with its own code object)
+template <class J>
+static __device__ __forceinline__ void scan_reduce_job(const J& job)
 {
     const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
+    if ((uint64_t)blockIdx.x * kScanTile >= job.n) return;
     uint64_t sum = 0;
 #pragma unroll
     for (int k = 0; k < (int)kScanItems; ++k)
-        if (base + k < n) sum = op(sum, f(base + k));
+        if (base + k < job.n) sum = job.op(sum, job.f(base + k));
     uint64_t total;
-    block_exclusive_scan(sum, &total, op);
-    if (threadIdx.x == 0) partials[blockIdx.x] = total;
+    block_exclusive_scan(sum, &total, job.op);
+    if (threadIdx.x == 0) job.partials[blockIdx.x] = total;
 }
 
-// One workgroup: partials[0..nb) -> exclusive prefix in place, partials[nb] = grand total.
-// (internal linkage: the same instantiation exists in several translation units, each with its own code object)
-template <class Op>
-static __global__ void __launch_bounds__(kScanBlock) scan_spine_kernel(Op op, uint64_t* partials, uint64_t nb)
+// One workgroup: partials[0..nb) -> exclusive prefix in place.
+template <class J>
+static __device__ __forceinline__ void scan_spine_job(const J& job)
 {
+    const uint64_t nb = (job.n + kScanTile - 1) / kScanTile;
     uint64_t carry = 0;
     for (uint64_t lo = 0; lo < nb; lo += kScanBlock) {
-        uint64_t i = lo + threadIdx.x;
-        uint64_t v = i < nb ? partials[i] : 0;
+        const uint64_t i = lo + threadIdx.x;
+        const uint64_t v = i < nb ? job.partials[i] : 0;
         uint64_t total;
-        uint64_t ex = block_exclusive_scan(v, &total, op);
-        if (i < nb) partials[i] = op(carry, ex);
-        carry = op(carry, total);
+        const uint64_t ex = block_exclusive_scan(v, &total, job.op);
+        if (i < nb) job.partials[i] = job.op(carry, ex);
+        carry = job.op(carry, total);
     }
-    if (threadIdx.x == 0) partials[nb] = carry;
 }
 
-template <class F, class Op>
-__global__ void __launch_bounds__(kScanBlock) scan_down_kernel(F f, Op op, uint64_t n, const uint64_t* partials,
-                                                              uint64_t* out)
+template <class J>
+static __device__ __forceinline__ void scan_down_job(const J& job, bool spined)
 {
     const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
+    if ((uint64_t)blockIdx.x * kScanTile >= job.n) return;
+    uint64_t before = 0;                                     // what the tiles before this one hold
+    if (spined) {
+        before = job.partials[blockIdx.x];
+    } else if (blockIdx.x != 0) {
+        uint64_t mine = 0;
+        for (uint64_t t = threadIdx.x; t < blockIdx.x; t += kScanBlock) mine = job.op(mine, job.partials[t]);
+        block_exclusive_scan(mine, &before, job.op);
+    }
     uint64_t v[kScanItems];
     uint64_t sum = 0;
 #pragma unroll
     for (int k = 0; k < (int)kScanItems; ++k) {
-        v[k] = base + k < n ? f(base + k) : 0;
-        sum = op(sum, v[k]);
+        v[k] = base + k < job.n ? job.f(base + k) : 0;
+        sum = job.op(sum, v[k]);
     }
     uint64_t total;
-    uint64_t run = op(partials[blockIdx.x], block_exclusive_scan(sum, &total, op));
+    uint64_t run = job.op(before, block_exclusive_scan(sum, &total, job.op));
 #pragma unroll
     for (int k = 0; k < (int)kScanItems; ++k) {
-        if (base + k < n) out[base + k] = run;
-        run = op(run, v[k]);
+        if (base + k <= job.n) job.out(base + k, run);       // entry n: the grand total, by the lane that reaches it
+        run = job.op(run, v[k]);
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanBlock - 1) out[n] = run;   // grand total
+    if (base + kScanItems == job.n) job.out(job.n, run);
 }
 
-// out[i] = op over f(0..i-1) for i in [0, n] (out has n + 1 entries); partials needs
-// scan_partials_capacity(n) entries.
+// workgroup row y takes job y
+template <class... J>
+static __global__ void __launch_bounds__(kScanBlock) scan_reduce_kernel(J... jobs)
+{
+    uint32_t y = 0;
+    ((blockIdx.y == y++ ? scan_reduce_job(jobs) : void()), ...);
+}
+template <class... J>
+static __global__ void __launch_bounds__(kScanBlock) scan_spine_kernel(J... jobs)
+{
+    uint32_t y = 0;
+    ((blockIdx.y == y++ ? scan_spine_job(jobs) : void()), ...);
+}
+template <class... J>
+static __global__ void __launch_bounds__(kScanBlock) scan_down_kernel(bool spined, J... jobs)
+{
+    uint32_t y = 0;
+    ((blockIdx.y == y++ ? scan_down_job(jobs, spined) : void()), ...);
+}
+
+template <class... J>
+hipError_t run_scans(hipStream_t s, J... jobs)
+{
+    uint64_t n = 0;
+    for (uint64_t each : {jobs.n...}) {
+        if (each == 0) return hipErrorInvalidValue;
+        n = each > n ? each : n;
+    }
+    const uint64_t nb = scan_tiles(n);
+    if (nb > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    const dim3 grid((uint32_t)nb, (uint32_t)sizeof...(J)), block(kScanBlock);
+    const bool spined = nb > kSelfSpine;
+    if (nb > 1) hipLaunchKernelGGL((scan_reduce_kernel<J...>), grid, block, 0, s, jobs...);
+    if (spined) hipLaunchKernelGGL((scan_spine_kernel<J...>), dim3(1, grid.y), block, 0, s, jobs...);
+    hipLaunchKernelGGL((scan_down_kernel<J...>), grid, block, 0, s, spined, jobs...);
+    return hipGetLastError();
+}
+
+// out[i] = op over f(0..i-1) for i in [0, n] (out has n + 1 entries).
 template <class F, class Op = ScanSum>
 hipError_t exclusive_scan(F f, uint64_t n, uint64_t* out, uint64_t* partials, hipStream_t s, Op op = Op{})
 {
-    if (n == 0) return hipErrorInvalidValue;
-    const uint64_t nb = (n + kScanTile - 1) / kScanTile;
-    if (nb > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((scan_reduce_kernel<F, Op>), dim3((uint32_t)nb), dim3(kScanBlock), 0, s, f, op, n, partials);
-    hipLaunchKernelGGL((scan_spine_kernel<Op>), dim3(1), dim3(kScanBlock), 0, s, op, partials, nb);
-    hipLaunchKernelGGL((scan_down_kernel<F, Op>), dim3((uint32_t)nb), dim3(kScanBlock), 0, s, f, op, n, partials, out);
-    return hipGetLastError();
-}
-
-// Two independent sum scans in the same three launches (a launch of a small kernel costs more than its
-// work): out1[i] = sum f1(0..i-1) for i in [0, n1], out2 likewise over n2; partials1 and partials2 each
-// need scan_partials_capacity(max(n1, n2)) entries.
-template <class F1, class F2>
-__global__ void __launch_bounds__(kScanBlock) scan_reduce2_kernel(F1 f1, F2 f2, uint64_t n1, uint64_t n2,
-                                                                 uint64_t* partials1, uint64_t* partials2)
-{
-    const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
-    uint64_t sum1 = 0, sum2 = 0;
-#pragma unroll
-    for (int k = 0; k < (int)kScanItems; ++k) {
-        if (base + k < n1) sum1 += f1(base + k);
-        if (base + k < n2) sum2 += f2(base + k);
-    }
-    uint64_t total1, total2;
-    block_exclusive_scan(sum1, &total1, ScanSum{});
-    block_exclusive_scan(sum2, &total2, ScanSum{});
-    if (threadIdx.x == 0) { partials1[blockIdx.x] = total1; partials2[blockIdx.x] = total2; }
-}
-
-// (a template for the same reason as scan_spine_kernel: internal linkage without an unused-function warning)
-template <class Op>
-static __global__ void __launch_bounds__(kScanBlock) scan_spine2_kernel(Op, uint64_t* partials1, uint64_t* partials2, uint64_t nb)
-{
-    uint64_t carry1 = 0, carry2 = 0;
-    for (uint64_t lo = 0; lo < nb; lo += kScanBlock) {
-        const uint64_t i = lo + threadIdx.x;
-        uint64_t total1, total2;
-        const uint64_t ex1 = block_exclusive_scan(i < nb ? partials1[i] : 0, &total1, ScanSum{});
-        const uint64_t ex2 = block_exclusive_scan(i < nb ? partials2[i] : 0, &total2, ScanSum{});
-        if (i < nb) { partials1[i] = carry1 + ex1; partials2[i] = carry2 + ex2; }
-        carry1 += total1;
-        carry2 += total2;
-    }
-    if (threadIdx.x == 0) { partials1[nb] = carry1; partials2[nb] = carry2; }
-}
-
-template <class F1, class F2>
-__global__ void __launch_bounds__(kScanBlock) scan_down2_kernel(F1 f1, F2 f2, uint64_t n1, uint64_t n2,
-                                                               const uint64_t* partials1, const uint64_t* partials2,
-                                                               uint64_t* out1, uint64_t* out2)
-{
-    const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
-    uint64_t v1[kScanItems], v2[kScanItems];
-    uint64_t sum1 = 0, sum2 = 0;
-#pragma unroll
-    for (int k = 0; k < (int)kScanItems; ++k) {
-        v1[k] = base + k < n1 ? f1(base + k) : 0;
-        v2[k] = base + k < n2 ? f2(base + k) : 0;
-        sum1 += v1[k];
-        sum2 += v2[k];
-    }
-    uint64_t total1, total2;
-    uint64_t run1 = partials1[blockIdx.x] + block_exclusive_scan(sum1, &total1, ScanSum{});
-    uint64_t run2 = partials2[blockIdx.x] + block_exclusive_scan(sum2, &total2, ScanSum{});
-    // entry n of either output is its grand total: it is written by the lane that reaches index n
-#pragma unroll
-    for (int k = 0; k < (int)kScanItems; ++k) {
-        if (base + k <= n1) out1[base + k] = run1;
-        if (base + k <= n2) out2[base + k] = run2;
-        run1 += v1[k];
-        run2 += v2[k];
-    }
-    if (base + kScanItems == n1) out1[n1] = run1;
-    if (base + kScanItems == n2) out2[n2] = run2;
-}
-
-template <class F1, class F2>
-hipError_t exclusive_scan2(F1 f1, F2 f2, uint64_t n1, uint64_t n2, uint64_t* out1, uint64_t* out2, uint64_t* partials1,
-                           uint64_t* partials2, hipStream_t s)
-{
-    if (n1 == 0 || n2 == 0) return hipErrorInvalidValue;
-    const uint64_t n = n1 > n2 ? n1 : n2;
-    const uint64_t nb = (n + kScanTile - 1) / kScanTile;
-    if (nb > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((scan_reduce2_kernel<F1, F2>), dim3((uint32_t)nb), dim3(kScanBlock), 0, s, f1, f2, n1, n2, partials1, partials2);
-    hipLaunchKernelGGL((scan_spine2_kernel<ScanSum>), dim3(1), dim3(kScanBlock), 0, s, ScanSum{}, partials1, partials2, nb);
-    hipLaunchKernelGGL((scan_down2_kernel<F1, F2>), dim3((uint32_t)nb), dim3(kScanBlock), 0, s, f1, f2, n1, n2, partials1, partials2,
-                       out1, out2);
-    return hipGetLastError();
+    return run_scans(s, scan_job(f, n, out, partials, op));
 }
 
 }  // namespace tent

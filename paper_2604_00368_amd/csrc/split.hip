@@ -10,40 +10,73 @@ namespace tent {
 
 uint64_t scan_partials_capacity(uint64_t n) { return (n + kScanTile - 1) / kScanTile + 2; }
 
-// ---- S1: exclusive prefix of extent lengths over the whole batch -----------------------------
+// ---- S1: exclusive prefixes of extent lengths over the whole batch ----------------------------
 struct ExtentLen {
     const tent_extent* ext;
     __device__ uint64_t operator()(uint64_t e) const { return ext[e].len; }
 };
+// destination extents in ascending address order (for the tile tables that go by destination address)
+struct OrderedLen {
+    const tent_extent* ext;
+    const uint32_t* order;
+    __device__ uint64_t operator()(uint64_t r) const { return ext[order[r]].len; }
+};
 
-hipError_t launch_extent_scan(const tent_extent* ext, uint64_t n_ext, uint64_t* pre, uint64_t* partials,
-                              hipStream_t s)
-{
-    return exclusive_scan(ExtentLen{ext}, n_ext, pre, partials, s);
-}
-
-// both sides' prefixes in the same three launches
+// all prefixes the batch needs, in the same launches
 hipError_t launch_extent_scans(const BatchDev& b, hipStream_t s)
 {
-    return exclusive_scan2(ExtentLen{b.src_ext}, ExtentLen{b.dst_ext}, b.n_src_ext, b.n_dst_ext, b.src_pre, b.dst_pre,
-                           b.scan_partials, b.scan_partials2, s);
+    const auto src = scan_job(ExtentLen{b.src_ext}, b.n_src_ext, b.src_pre, b.scan_partials);
+    const auto dst = scan_job(ExtentLen{b.dst_ext}, b.n_dst_ext, b.dst_pre, b.scan_partials2);
+    if (!b.ord_pre) return run_scans(s, src, dst);
+    return run_scans(s, src, dst, scan_job(OrderedLen{b.dst_ext, b.dst_order}, b.n_dst_ext, b.ord_pre, b.scan_partials3));
 }
 
-// ---- S2: slices per transfer, exclusive scan -> first slice index of every transfer ---------
-struct SliceCount {
+// ---- S2: slices and runs per transfer -----------------------------------------------------------
+// A transfer of len bytes has ceil(len / S) slices, all of S bytes but the last.  Maximal runs of equal-length
+// slices (bind_runs.hip) therefore start in at most two places per transfer: at its first slice, unless that is as long as the
+// slice before it, and at its last one, if that is short and not also the first.  One scan over the transfers yields the
+// first slice of every transfer (low half of the scanned word) and the runs that start before it (high half).
+struct TransferShape {
+    uint64_t slices, last;         // slices; length of the last one
+    bool new_run, short_tail;      // runs that start at the first slice, at the last one
+    __device__ TransferShape(const uint32_t* ptr, const uint64_t* pre, uint64_t S, uint64_t j)
+    {
+        const uint64_t at = pre[ptr[j]], len = pre[ptr[j + 1]] - at;
+        slices = (len + S - 1) / S;
+        last = len - (slices - 1) * S;
+        short_tail = slices > 1 && last != S;
+        new_run = true;
+        if (j > 0) {
+            const uint64_t len_before = at - pre[ptr[j - 1]];
+            const uint64_t last_before = len_before - ((len_before + S - 1) / S - 1) * S;
+            new_run = last_before != (len < S ? len : S);
+        }
+    }
+};
+struct TransferCounts {
     const uint32_t* ptr;
     const uint64_t* pre;
     uint64_t S;
     __device__ uint64_t operator()(uint64_t j) const
     {
-        uint64_t len = pre[ptr[j + 1]] - pre[ptr[j]];
-        return (len + S - 1) / S;
+        const TransferShape t(ptr, pre, S, j);
+        return ((uint64_t)((t.new_run ? 1u : 0u) + (t.short_tail ? 1u : 0u)) << 32) | t.slices;
+    }
+};
+struct StoreCounts {
+    uint64_t* first;
+    uint32_t* runs;
+    __device__ void operator()(uint64_t j, uint64_t v) const
+    {
+        first[j] = v & 0xFFFFFFFFu;
+        runs[j] = (uint32_t)(v >> 32);
     }
 };
 
 hipError_t launch_slice_scan(const BatchDev& b, hipStream_t s)
 {
-    return exclusive_scan(SliceCount{b.src_ptr, b.src_pre, b.slice_bytes}, b.n_desc, b.first, b.scan_partials, s);
+    return run_scans(s, ScanJob<TransferCounts, ScanSum, StoreCounts>{TransferCounts{b.src_ptr, b.src_pre, b.slice_bytes}, ScanSum{},
+                                                                      StoreCounts{b.first, b.runs_before}, b.n_desc, b.scan_partials});
 }
 
 // ---- S3: slice table expansion ---------------------------------------------------------------
@@ -68,6 +101,18 @@ __global__ void __launch_bounds__(256) expand_kernel(BatchDev b)
         b.s_rail[i] = 0xFFFFFFFFu;
         b.s_stage_off[i] = 0;
         b.s_state[i] = TENT_SLICE_PENDING;
+        // the run table: every run is entered by the slice it starts at
+        const TransferShape t(b.src_ptr, b.src_pre, b.slice_bytes, j);
+        const uint32_t run = b.runs_before[j] + (t.new_run ? 1u : 0u) - 1u;      // of the transfer's first slice
+        const bool tail = t.short_tail && rest <= b.slice_bytes;
+        b.s_run[i] = run + (tail ? 1u : 0u);
+        if ((off == 0 && t.new_run) || tail) b.run_start[run + (tail ? 1u : 0u)] = (uint32_t)i;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const uint32_t n_runs = b.runs_before[b.n_desc];
+        b.run_start[n_runs] = (uint32_t)n;
+        b.plan->n_runs = n_runs;
+        b.plan->n_pending = n;
     }
 }
 
@@ -80,26 +125,11 @@ hipError_t launch_expand(const BatchDev& b, hipStream_t s)
 }
 
 // ---- S3b: tile tables ------------------------------------------------------------------------
-// The builders are in tile_tables.h.  The destination-ordered table needs the exclusive prefix of
-// the destination extent lengths in ascending address order first.
-struct OrderedLen {
-    const tent_extent* ext;
-    const uint32_t* order;
-    __device__ uint64_t operator()(uint64_t r) const { return ext[order[r]].len; }
-};
-
+// The builders are in tile_tables.h.
 __global__ void __launch_bounds__(256) tile_tables_kernel(BatchDev b) { build_tile_tables(b, blockIdx.x, gridDim.x); }
-
-hipError_t launch_tile_tables_prepare(const BatchDev& b, hipStream_t s)
-{
-    if (b.n_sc_tiles == 0 || !b.ord_pre) return hipSuccess;      // no tile goes by destination address
-    return exclusive_scan(OrderedLen{b.dst_ext, b.dst_order}, b.n_dst_ext, b.ord_pre, b.scan_partials, s);
-}
 
 hipError_t launch_tile_tables(const BatchDev& b, hipStream_t s)
 {
-    hipError_t e = launch_tile_tables_prepare(b, s);
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(tile_tables_kernel, dim3(tile_table_blocks(b)), dim3(256), 0, s, b);
     return hipGetLastError();
 }
@@ -235,34 +265,53 @@ __global__ void __launch_bounds__(256) stage_tiles_kernel(BatchDev b, uint8_t* a
 }
 
 // The same when few slices move: the tiles of the BOUND slices are listed with their three addresses, in any
-// order (the copy's result does not depend on it), every slice taking its place in the list with one atomic add.
-// A slice that does not fit the list, or the host's bound on it that sizes the copy, stays BOUND and is not listed;
-// the slices that do fit occupy the list without gaps, because the first that does not moves the counter past the bound.
+// order (the copy's result does not depend on it).  A workgroup looks at 64 slices, places those that are BOUND one behind
+// the other and takes room for all of them with one atomic add (one per slice measured 32 us over 20,000 slices, 17,000 of them
+// BOUND; one per workgroup: 9 us); groups of lanes then write the entries.  A workgroup whose tiles do not fit the list, or the
+// host's bound that sizes the copy, leaves its slices BOUND and lists nothing; the others occupy the list without
+// gaps, because the first that does not fit moves the counter past the bound.
+constexpr uint32_t kListSlices = 64;
 __global__ void __launch_bounds__(256) list_tiles_kernel(BatchDev b, uint8_t* arena, uint32_t group_shift, uint32_t tile_shift,
                                                          uint64_t max_tiles)
 {
-    const uint64_t at = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t i = at >> group_shift;
-    const uint32_t group = 1u << group_shift;
-    const uint32_t t0 = (uint32_t)at & (group - 1);
-    const bool bound = i < b.n_slices && b.s_state[i] == TENT_SLICE_BOUND;
-    const uint32_t n_t = bound ? b.s_len[i] >> tile_shift : 0;
-    uint64_t from = 0;
-    if (bound && t0 == 0) {
-        from = atomicAdd((unsigned long long*)&b.plan->n_act_asked, (unsigned long long)n_t);
-        if (from + n_t <= max_tiles) atomicAdd((unsigned long long*)&b.plan->n_act, (unsigned long long)n_t);
+    __shared__ uint64_t sh_at[kListSlices], sh_lin[kListSlices], sh_q0[kListSlices];
+    __shared__ uint32_t sh_n[kListSlices];
+    const uint64_t first = (uint64_t)blockIdx.x * kListSlices;
+    if (threadIdx.x < kListSlices) {
+        const uint64_t i = first + threadIdx.x;
+        const bool bound = i < b.n_slices && b.s_state[i] == TENT_SLICE_BOUND;
+        uint32_t n_t = 0;
+        if (bound) {
+            n_t = b.s_len[i] >> tile_shift;
+            sh_lin[threadIdx.x] = (uint64_t)arena + b.plan->base[b.s_rail[i]] + b.s_stage_off[i];
+            sh_q0[threadIdx.x] = b.s_pos[i] >> tile_shift;
+        }
+        const uint64_t up_to = wave_inclusive_scan((uint64_t)n_t);
+        const uint64_t all = __shfl((unsigned long long)up_to, 63, 64);
+        uint64_t from = 0;
+        if (threadIdx.x == 0 && all != 0) {
+            from = atomicAdd((unsigned long long*)&b.plan->n_act_asked, (unsigned long long)all);
+            if (from + all <= max_tiles) atomicAdd((unsigned long long*)&b.plan->n_act, (unsigned long long)all);
+        }
+        from = __shfl((unsigned long long)from, 0, 64);
+        const bool fits = from + all <= max_tiles;
+        sh_at[threadIdx.x] = from + up_to - n_t;
+        sh_n[threadIdx.x] = fits ? n_t : 0;
+        if (bound && fits) b.s_state[i] = TENT_SLICE_DONE;
     }
-    from = __shfl((unsigned long long)from, (int)((threadIdx.x & 63u) & ~(group - 1)), 64);
-    if (!bound || from + n_t > max_tiles) return;
-    const uint64_t lin = (uint64_t)arena + b.plan->base[b.s_rail[i]] + b.s_stage_off[i];
-    const uint64_t q0 = b.s_pos[i] >> tile_shift;
-    for (uint32_t t = t0; t < n_t; t += group) {
-        const uint64_t p = b.tile_pos ? b.tile_pos[q0 + t] : q0 + t;
-        b.act_src[from + t] = b.op_src[p];
-        b.act_lin[from + t] = lin + ((uint64_t)t << tile_shift);
-        b.act_dst[from + t] = b.op_dst[p];
+    __syncthreads();
+    const uint32_t group = 1u << group_shift, groups = 256u >> group_shift;
+    const uint32_t t0 = threadIdx.x & (group - 1);
+    for (uint32_t k = threadIdx.x >> group_shift; k < kListSlices; k += groups) {
+        const uint32_t n_t = sh_n[k];
+        for (uint32_t t = t0; t < n_t; t += group) {
+            const uint64_t q = sh_q0[k] + t, at = sh_at[k] + t;
+            const uint64_t p = b.tile_pos ? b.tile_pos[q] : q;
+            b.act_src[at] = b.op_src[p];
+            b.act_lin[at] = sh_lin[k] + ((uint64_t)t << tile_shift);
+            b.act_dst[at] = b.op_dst[p];
+        }
     }
-    if (t0 == 0) b.s_state[i] = TENT_SLICE_DONE;
 }
 
 __global__ void clear_list_kernel(BatchDev b)
@@ -288,7 +337,8 @@ hipError_t launch_stage_and_mark(const BatchDev& b, uint8_t* arena, bool compact
     if (compact) {
         if (max_tiles > b.act_capacity) max_tiles = b.act_capacity;
         hipLaunchKernelGGL(clear_list_kernel, dim3(1), dim3(1), 0, s, b);
-        hipLaunchKernelGGL(list_tiles_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, arena, group_shift, tile_shift, max_tiles);
+        hipLaunchKernelGGL(list_tiles_kernel, dim3((uint32_t)((b.n_slices + kListSlices - 1) / kListSlices)), dim3(256), 0, s, b, arena,
+                           group_shift, tile_shift, max_tiles);
     } else {
         hipLaunchKernelGGL(stage_tiles_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, arena, group_shift, tile_shift, parts);
         if (parts > 1) return launch_mark_done(b, false, s);

@@ -721,6 +721,8 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     }
     d.run_capacity = 2u * n_desc;
     d.run_stride = ctx->max_rails <= 16 ? 16u : ctx->max_rails <= 32 ? 32u : 64u;   // a row per run, one entry per lane of the chain
+    cv.want(&d.runs_before, (uint64_t)n_desc + 1);
+    cv.want(&d.s_run, n_slices);
     cv.want(&d.run_start, (uint64_t)d.run_capacity + 1);
     cv.want(&d.run_cell, (uint64_t)d.run_capacity * d.run_stride);
     cv.want(&d.len_pre, n_slices + 1);
@@ -774,6 +776,7 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     cv.want(&d.scan_tmp, scan_n + 1);
     cv.want(&d.scan_partials, scan_partials_capacity(scan_n));
     cv.want(&d.scan_partials2, scan_partials_capacity(scan_n));
+    cv.want(&d.scan_partials3, scan_partials_capacity(scan_n));
     cv.want(&d.plan, 1);
     if (cv.overflow) return TENT_ERR_NOMEM;
 
@@ -1041,7 +1044,6 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
             StageTimer t(ctx, TENT_T_EXPAND, s);
             HIP_TRY(launch_expand(d, s));
             if (serial) HIP_TRY(launch_tile_tables(d, s));
-            else        HIP_TRY(launch_tile_tables_prepare(d, s));
         }
     } else {
         StageTimer t(ctx, TENT_T_COMPACT, s);
@@ -1155,7 +1157,6 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
         {
             StageTimer t(ctx, TENT_T_EXPAND, s);
             HIP_TRY(launch_expand(d, s));
-            HIP_TRY(launch_tile_tables_prepare(d, s));      // the tables themselves: beside the chain, in its launch
         }
     }
     {

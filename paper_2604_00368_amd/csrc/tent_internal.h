@@ -180,6 +180,8 @@ struct BatchDev {
     uint32_t* sc_x;
 
     // Run-parallel binding: maximal runs of equal-length pending slices (at most two per transfer)
+    uint32_t* runs_before;         // [n_desc+1] runs that start before each descriptor's first slice (first plan)
+    uint32_t* s_run;               // [n_slices] run of every pending position
     uint32_t* run_start;           // [run_capacity + 1] first pending position of every run
     RunCell*  run_cell;            // [run_capacity * run_stride]
     uint32_t  run_capacity;        // 2 * n_desc
@@ -192,7 +194,8 @@ struct BatchDev {
     uint32_t* rot_cnt;             // same shape: slices per chunk and rail
     uint64_t* scan_tmp;            // [max(n_ext, n_slices, n_desc)+1] scan workspace
     uint64_t* scan_partials;       // per-block partial sums of the scans
-    uint64_t* scan_partials2;      // the same for the second of two scans that share their launches
+    uint64_t* scan_partials2;      // the same for the second and
+    uint64_t* scan_partials3;      // the third of the scans that share their launches
     PlanState* plan;               // one result block
     const uint64_t* seg_base;      // context-wide table of segment base addresses
 };
@@ -209,8 +212,6 @@ enum : int { kBindUsePending = 1, kBindAfterRotation = 2, kBindBuildTables = 4 }
 
 // ---- launch wrappers (each enqueues on `s` and returns the launch status) -------------------
 hipError_t launch_extent_scans(const BatchDev& b, hipStream_t s);
-hipError_t launch_extent_scan(const tent_extent* ext, uint64_t n_ext, uint64_t* pre, uint64_t* partials,
-                              hipStream_t s);
 hipError_t launch_slice_scan(const BatchDev& b, hipStream_t s);
 hipError_t launch_expand(const BatchDev& b, hipStream_t s);
 hipError_t launch_compact(const BatchDev& b, hipStream_t s);
@@ -223,10 +224,9 @@ hipError_t launch_bounded_prepare(const BatchDev& b, uint64_t payload, uint64_t 
 hipError_t launch_bounded_copy(const BatchDev& b, bool gather, uint32_t chunk, uint64_t payload, uint64_t chunk_bytes,
                                uint64_t slot_bytes, uint32_t slots, uint8_t* arena, hipStream_t s);
 hipError_t launch_mark_done_bounded(const BatchDev& b, hipStream_t s);
-hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, bool build_tables,
+hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, bool first_plan,
                            hipStream_t s);
 hipError_t launch_tile_tables(const BatchDev& b, hipStream_t s);
-hipError_t launch_tile_tables_prepare(const BatchDev& b, hipStream_t s);   // what the builders need when they run inside the chain launch
 hipError_t launch_finalize(const BatchDev& b, uint8_t* arena, bool compact, uint64_t max_tiles, hipStream_t s);
 hipError_t launch_copy(const BatchDev& b, bool gather, hipStream_t s);
 hipError_t launch_stage_and_mark(const BatchDev& b, uint8_t* arena, bool compact, uint64_t max_tiles, hipStream_t s);
