@@ -724,7 +724,7 @@ __global__ void __launch_bounds__(256) bind_chain_tables_kernel(BatchDev b, Rail
 // ---- step 3: emit -----------------------------------------------------------------------------
 // One lane per position q of the pending sequence; inside its run the lane enumerates slot
 // t = q - run_start as (rail d, index k) in rail-major order and computes the slot's rank.
-__global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams rp, int use_pending)
+__global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams rp, int use_pending, PlanState* told)
 {
     __shared__ uint64_t sh_c0[TENT_MAX_RAILS];
     __shared__ uint32_t sh_c1[TENT_MAX_RAILS];
@@ -737,6 +737,7 @@ __global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams r
         sh_inv[threadIdx.x] = 1.0 / (double)(c1 ? c1 : 1u);
     }
     __syncthreads();
+    if (told && blockIdx.x == 0) tell_totals(*b.plan, told);
     const uint64_t n = b.plan->n_pending;
     const uint32_t stride = b.run_stride;
     const uint64_t gstride = (uint64_t)gridDim.x * blockDim.x;
@@ -795,7 +796,7 @@ __global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams r
 
 }  // namespace
 
-hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, hipStream_t s)
+hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, PlanState* told, hipStream_t s)
 {
     const bool use_pending = (mode & kBindUsePending) != 0;
     const int up = use_pending ? 1 : 0;
@@ -819,7 +820,7 @@ hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, h
     if (rp.n_rails <= 16)      launch_chain(std::integral_constant<int, 16>{});
     else if (rp.n_rails <= 32) launch_chain(std::integral_constant<int, 32>{});
     else                       launch_chain(std::integral_constant<int, 64>{});
-    hipLaunchKernelGGL(bind_emit_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, rp, up);
+    hipLaunchKernelGGL(bind_emit_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, rp, up, told);
     return hipGetLastError();
 }
 

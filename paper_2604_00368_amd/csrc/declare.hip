@@ -7,8 +7,12 @@
 // furthest end of everything before it, a source extent overlaps a destination iff it starts before
 // the furthest end of the destinations before it.  The scans are the engine's own (scan.h).
 //
-// Nothing here allocates, copies to the host or waits: the caller hands in a workspace and reads
-// the verdict from device memory when the stream has got that far.
+// Only the address bits in which the extents differ are sorted: KV pages of 32 KiB in a pool of 20 GiB differ in 20 of 64.
+// Declarations of up to kSmallOrder extents do all of it in one workgroup (a bitonic sort in LDS), because there the dozen
+// launches cost more than the work: 626 extents on either side 115 -> 25 us from the first kernel to the last.
+//
+// Nothing here allocates, copies to the host or waits: the caller hands in a workspace and a word of host memory
+// for the verdict, and reads it when the stream has got that far.
 #include <cstring>
 
 #include <rocprim/rocprim.hpp>
@@ -19,20 +23,31 @@ namespace tent {
 
 namespace {
 
-// value = index into [destinations | sources]: v < n_dst is destination extent v
-__global__ void __launch_bounds__(256) declare_keys_kernel(const tent_extent* dst_ext, uint64_t n_dst,
-                                                           const tent_extent* src_ext, uint64_t n_src,
-                                                           const uint64_t* seg_base, uint64_t* keys, uint32_t* vals,
-                                                           uint32_t* overlap)
+// What must start at zero in a batch's tables: retry counts, request modes, the result block.
+__device__ __forceinline__ void clear_tables(const BatchDev& b, uint64_t at, uint64_t stride)
 {
-    const uint64_t n = n_dst + n_src;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-        const tent_extent x = v < n_dst ? dst_ext[v] : src_ext[v - n_dst];
-        keys[v] = seg_base[x.seg] + x.off;
+    for (uint64_t i = at; i < b.n_slices; i += stride) b.s_retry[i] = 0;
+    for (uint64_t i = at; i < b.n_desc; i += stride) b.req_mode[i] = 0;
+    uint64_t* plan = reinterpret_cast<uint64_t*>(b.plan);
+    static_assert(sizeof(PlanState) % 8 == 0, "the result block is cleared in words of 8 bytes");
+    for (uint64_t i = at; i < sizeof(PlanState) / 8; i += stride) plan[i] = 0;
+}
+
+__global__ void __launch_bounds__(256) declare_clear_kernel(BatchDev b)
+{
+    clear_tables(b, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, (uint64_t)gridDim.x * blockDim.x);
+}
+
+// value = index into [destinations | sources]: v < n_dst is destination extent v
+__global__ void __launch_bounds__(256) declare_keys_kernel(BatchDev b, uint64_t n, uint64_t* keys, uint32_t* vals)
+{
+    const uint64_t at = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
+    clear_tables(b, at, stride);
+    for (uint64_t v = at; v < n; v += stride) {
+        const tent_extent x = v < b.n_dst_ext ? b.dst_ext[v] : b.src_ext[v - b.n_dst_ext];
+        keys[v] = b.seg_base[x.seg] + x.off;
         vals[v] = (uint32_t)v;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *overlap = 0;
 }
 
 // End of the extent at sorted position p (all extents / destinations only).
@@ -59,29 +74,112 @@ struct IsDst {
     __device__ uint64_t operator()(uint64_t p) const { return vals[p] < n_dst; }
 };
 
-__global__ void __launch_bounds__(256) declare_check_kernel(uint64_t n_dst, uint64_t n, const uint64_t* keys,
-                                                            const uint32_t* vals, const uint64_t* far_any,
-                                                            const uint64_t* far_dst, uint32_t* overlap)
+// The overlap check, and the destinations in sorted order (a stable compaction of the sorted values).  `told` is host
+// memory; every thread that writes it writes the same.
+__global__ void __launch_bounds__(256) declare_verdict_kernel(uint64_t n_dst, uint64_t n, const uint64_t* keys, const uint32_t* vals,
+                                                              const uint64_t* far_any, const uint64_t* far_dst,
+                                                              const uint64_t* pos, uint32_t* order, uint32_t* rank, uint32_t* told)
 {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     bool bad = false;
     for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride) {
-        const bool is_dst = vals[p] < n_dst;
-        bad |= keys[p] < (is_dst ? far_any[p] : far_dst[p]);
+        const uint32_t v = vals[p];
+        const bool is_dst = v < n_dst;
+        if (far_any) bad |= keys[p] < (is_dst ? far_any[p] : far_dst[p]);
+        if (is_dst) {
+            order[pos[p]] = v;
+            rank[v] = (uint32_t)pos[p];                      // the inverse: position of every extent in address order
+        }
     }
-    if (bad) atomicOr(overlap, 1u);
+    if (bad) *told = 1;
 }
 
-// destinations in sorted order: stable compaction of the sorted values
-__global__ void __launch_bounds__(256) declare_order_kernel(uint64_t n_dst, uint64_t n, const uint32_t* vals,
-                                                            const uint64_t* pos, uint32_t* order, uint32_t* rank)
+// ---- all of it in one workgroup ------------------------------------------------------------------
+constexpr uint32_t kSmallOrder = 4096, kSmallThreads = 1024, kSmallItems = kSmallOrder / kSmallThreads;
+constexpr uint32_t kSmallBits = 13;              // a sorted word is (differing address bits) << kSmallBits | value
+
+// Exclusive scan of one value per thread over the workgroup.
+template <class Op>
+__device__ __forceinline__ uint64_t small_scan(uint64_t v, uint64_t* wave_out, Op op)
 {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride)
-        if (vals[p] < n_dst) {
-            order[pos[p]] = vals[p];
-            if (rank) rank[vals[p]] = (uint32_t)pos[p];    // the inverse: position of every extent in address order
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t inc = wave_inclusive_scan(v, op);
+    __syncthreads();
+    if (lane == 63) wave_out[wave] = inc;
+    __syncthreads();
+    uint64_t before = 0;
+    for (uint32_t w = 0; w < wave; ++w) before = op(before, wave_out[w]);
+    const uint64_t below = __shfl_up((unsigned long long)inc, 1, 64);
+    return lane == 0 ? before : op(before, below);
+}
+
+__global__ void __launch_bounds__(kSmallThreads) declare_small_kernel(BatchDev b, uint32_t n, uint32_t n_pow2, int check, KeyBits bits,
+                                                                      uint32_t* order, uint32_t* rank, uint32_t* told)
+{
+    __shared__ uint64_t word[kSmallOrder];
+    __shared__ uint64_t wave_out[kSmallThreads / 64];
+    const uint32_t t = threadIdx.x;
+    clear_tables(b, t, kSmallThreads);
+    const uint32_t n_dst = (uint32_t)b.n_dst_ext;
+    const uint64_t mask = (1ull << (bits.end - bits.begin)) - 1;
+    for (uint32_t v = t; v < n_pow2; v += kSmallThreads) {
+        uint64_t w = ~0ull;                                  // behind every extent
+        if (v < n) {
+            const tent_extent x = v < n_dst ? b.dst_ext[v] : b.src_ext[v - n_dst];
+            w = (((b.seg_base[x.seg] + x.off) >> bits.begin & mask) << kSmallBits) | v;
         }
+        word[v] = w;
+    }
+    __syncthreads();
+    for (uint32_t k = 2; k <= n_pow2; k <<= 1)
+        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+            for (uint32_t p = t; p < n_pow2 / 2; p += kSmallThreads) {
+                const uint32_t lo = ((p & ~(j - 1)) << 1) | (p & (j - 1)), hi = lo | j;
+                const uint64_t x = word[lo], y = word[hi];
+                if ((x > y) == ((lo & k) == 0)) { word[lo] = y; word[hi] = x; }
+            }
+            __syncthreads();
+        }
+    // kSmallItems consecutive sorted extents per thread
+    uint64_t begin[kSmallItems], end_any[kSmallItems], end_dst[kSmallItems];
+    uint32_t value[kSmallItems];
+    uint64_t far_any = 0, far_dst = 0, dsts = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kSmallItems; ++i) {
+        const uint32_t p = t * kSmallItems + i;
+        value[i] = 0xFFFFFFFFu;
+        begin[i] = end_any[i] = end_dst[i] = 0;
+        if (p < n) {
+            const uint32_t v = (uint32_t)word[p] & ((1u << kSmallBits) - 1);
+            const bool is_dst = v < n_dst;
+            const tent_extent x = is_dst ? b.dst_ext[v] : b.src_ext[v - n_dst];
+            value[i] = v;
+            begin[i] = b.seg_base[x.seg] + x.off;
+            end_any[i] = begin[i] + x.len;
+            end_dst[i] = is_dst ? end_any[i] : 0;
+            dsts += is_dst ? 1 : 0;
+        }
+        far_any = end_any[i] > far_any ? end_any[i] : far_any;
+        far_dst = end_dst[i] > far_dst ? end_dst[i] : far_dst;
+    }
+    far_any = small_scan(far_any, wave_out, ScanMax{});
+    far_dst = small_scan(far_dst, wave_out, ScanMax{});
+    uint64_t pos = small_scan(dsts, wave_out, ScanSum{});
+    bool bad = false;
+#pragma unroll
+    for (uint32_t i = 0; i < kSmallItems; ++i) {
+        if (value[i] == 0xFFFFFFFFu) continue;
+        const bool is_dst = value[i] < n_dst;
+        bad |= begin[i] < (is_dst ? far_any : far_dst);
+        if (is_dst) {
+            order[pos] = value[i];
+            rank[value[i]] = (uint32_t)pos;
+            ++pos;
+        }
+        far_any = end_any[i] > far_any ? end_any[i] : far_any;
+        far_dst = end_dst[i] > far_dst ? end_dst[i] : far_dst;
+    }
+    if (bad && check) *told = 1;
 }
 
 uint32_t grid_for(uint64_t n)
@@ -95,17 +193,17 @@ size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Carves the workspace: two key arrays, two value arrays, three scan outputs, scan partials, the
 // sort's own temporary storage.
 struct OrderWorkspace {
-    uint64_t *keys_in, *keys, *far_any, *far_dst, *pos, *partials;
+    uint64_t *keys_in, *keys, *far_any, *far_dst, *pos, *partials, *partials2, *partials3;
     uint32_t *vals_in, *vals;
     void* sort_tmp;
     size_t sort_bytes, total;
 };
 
-hipError_t layout(uint64_t n, uint8_t* base, OrderWorkspace* w)
+hipError_t layout(uint64_t n, KeyBits bits, uint8_t* base, OrderWorkspace* w)
 {
     size_t sort_bytes = 0;
     hipError_t e = rocprim::radix_sort_pairs(nullptr, sort_bytes, (uint64_t*)nullptr, (uint64_t*)nullptr,
-                                             (uint32_t*)nullptr, (uint32_t*)nullptr, n, 0, 64, nullptr);
+                                             (uint32_t*)nullptr, (uint32_t*)nullptr, n, bits.begin, bits.end, nullptr);
     if (e != hipSuccess) return e;
     const size_t n8 = up256((size_t)(n + 1) * 8), n4 = up256((size_t)n * 4);
     size_t at = 0;
@@ -116,6 +214,8 @@ hipError_t layout(uint64_t n, uint8_t* base, OrderWorkspace* w)
     w->far_dst = (uint64_t*)take(n8);
     w->pos = (uint64_t*)take(n8);
     w->partials = (uint64_t*)take(scan_partials_capacity(n) * 8);
+    w->partials2 = (uint64_t*)take(scan_partials_capacity(n) * 8);
+    w->partials3 = (uint64_t*)take(scan_partials_capacity(n) * 8);
     w->vals_in = (uint32_t*)take(n4);
     w->vals = (uint32_t*)take(n4);
     w->sort_tmp = take(sort_bytes);
@@ -126,45 +226,58 @@ hipError_t layout(uint64_t n, uint8_t* base, OrderWorkspace* w)
 
 }  // namespace
 
-// Bytes of workspace device_order_destinations needs for n_dst destination and n_src source extents.
-hipError_t order_workspace_bytes(uint64_t n_dst, uint64_t n_src, bool check, uint64_t* bytes_out)
+static bool is_small(uint64_t n, KeyBits bits) { return n <= kSmallOrder && bits.end - bits.begin + kSmallBits < 64; }
+
+// Bytes of workspace launch_declare needs for n_dst destination and n_src source extents.
+hipError_t order_workspace_bytes(uint64_t n_dst, uint64_t n_src, bool check, KeyBits bits, uint64_t* bytes_out)
 {
+    const uint64_t n = n_dst + (check ? n_src : 0);
+    *bytes_out = 0;
+    if (is_small(n, bits)) return hipSuccess;
     OrderWorkspace w;
-    hipError_t e = layout(n_dst + (check ? n_src : 0), nullptr, &w);
+    hipError_t e = layout(n, bits, nullptr, &w);
     *bytes_out = w.total;
     return e;
 }
 
-// Fills order_out[n_dst] with destination extent indices in ascending address, rank_out[n_dst] (if
-// not null) with the inverse (position of every extent in that order) and, when `check` is set,
-// *overlap_dev (device) with 1 if a destination extent overlaps another destination or any source
-// extent, else 0.  Only enqueues on `s`; `workspace` (device, order_workspace_bytes() bytes, 256-byte
-// aligned) is in use until the stream has passed this work.
-hipError_t device_order_destinations(const tent_extent* dst_ext, uint64_t n_dst, const tent_extent* src_ext,
-                                     uint64_t n_src, const uint64_t* seg_base, bool check, uint32_t* order_out,
-                                     uint32_t* rank_out, uint32_t* overlap_dev, void* workspace, hipStream_t s)
+// The device work of a declaration whose descriptors lie in the batch's tables.  Clears what must start at zero; with
+// `order` fills order_out[n_dst] with destination extent indices in ascending address and rank_out[n_dst] with the
+// inverse (position of every extent in that order); with `check` sets *overlap_told (host memory, 0 before) if a
+// destination extent overlaps another destination or any source extent.  Only enqueues on `s`; `workspace`
+// (device, order_workspace_bytes() bytes, 256-byte aligned) is in use until the stream has passed this work.
+hipError_t launch_declare(const BatchDev& b, bool order, bool check, KeyBits bits, uint32_t* order_out, uint32_t* rank_out,
+                          uint32_t* overlap_told, void* workspace, hipStream_t s)
 {
-    const uint64_t n = n_dst + (check ? n_src : 0);
+    const uint64_t n = b.n_dst_ext + (check ? b.n_src_ext : 0);
+    if (!order) {
+        hipLaunchKernelGGL(declare_clear_kernel, dim3(grid_for(b.n_slices)), dim3(256), 0, s, b);
+        return hipGetLastError();
+    }
+    if (is_small(n, bits)) {
+        uint32_t n_pow2 = 2;
+        while (n_pow2 < n) n_pow2 <<= 1;
+        hipLaunchKernelGGL(declare_small_kernel, dim3(1), dim3(kSmallThreads), 0, s, b, (uint32_t)n, n_pow2, check ? 1 : 0, bits,
+                           order_out, rank_out, overlap_told);
+        return hipGetLastError();
+    }
     OrderWorkspace w;
-    hipError_t e = layout(n, static_cast<uint8_t*>(workspace), &w);
+    hipError_t e = layout(n, bits, static_cast<uint8_t*>(workspace), &w);
     if (e != hipSuccess) return e;
     const uint32_t g = grid_for(n);
-    hipLaunchKernelGGL(declare_keys_kernel, dim3(g), dim3(256), 0, s, dst_ext, n_dst, src_ext, check ? n_src : 0,
-                       seg_base, w.keys_in, w.vals_in, overlap_dev);
+    hipLaunchKernelGGL(declare_keys_kernel, dim3(g), dim3(256), 0, s, b, n, w.keys_in, w.vals_in);
     size_t bytes = w.sort_bytes;
-    e = rocprim::radix_sort_pairs(w.sort_tmp, bytes, w.keys_in, w.keys, w.vals_in, w.vals, n, 0, 64, s);
+    e = rocprim::radix_sort_pairs(w.sort_tmp, bytes, w.keys_in, w.keys, w.vals_in, w.vals, n, bits.begin, bits.end, s);
     if (e != hipSuccess) return e;
+    const auto pos = scan_job(IsDst{w.vals, b.n_dst_ext}, n, w.pos, w.partials3);
     if (check) {
-        e = exclusive_scan(EndAny{dst_ext, src_ext, n_dst, w.keys, w.vals}, n, w.far_any, w.partials, s, ScanMax{});
-        if (e != hipSuccess) return e;
-        e = exclusive_scan(EndDst{dst_ext, n_dst, w.keys, w.vals}, n, w.far_dst, w.partials, s, ScanMax{});
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(declare_check_kernel, dim3(g), dim3(256), 0, s, n_dst, n, w.keys, w.vals, w.far_any,
-                           w.far_dst, overlap_dev);
+        e = run_scans(s, scan_job(EndAny{b.dst_ext, b.src_ext, b.n_dst_ext, w.keys, w.vals}, n, w.far_any, w.partials, ScanMax{}),
+                      scan_job(EndDst{b.dst_ext, b.n_dst_ext, w.keys, w.vals}, n, w.far_dst, w.partials2, ScanMax{}), pos);
+    } else {
+        e = run_scans(s, pos);
     }
-    e = exclusive_scan(IsDst{w.vals, n_dst}, n, w.pos, w.partials, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(declare_order_kernel, dim3(g), dim3(256), 0, s, n_dst, n, w.vals, w.pos, order_out, rank_out);
+    hipLaunchKernelGGL(declare_verdict_kernel, dim3(g), dim3(256), 0, s, b.n_dst_ext, n, w.keys, w.vals, check ? w.far_any : nullptr,
+                       w.far_dst, w.pos, order_out, rank_out, overlap_told);
     return hipGetLastError();
 }
 

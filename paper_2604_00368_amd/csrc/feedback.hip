@@ -7,7 +7,7 @@
 // The window is the set of BOUND slices.  Per-rail maxima are integer, so the reduction order does
 // not matter: every workgroup keeps 64 maxima in LDS (atomic max), then merges them into the
 // batch's result block with one global atomic max per rail.
-#include "tent_internal.h"
+#include "finish.h"
 
 namespace tent {
 
@@ -37,12 +37,7 @@ hipError_t launch_sim_latency(const BatchDev& b, const LatencyParams& lp, hipStr
     return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(64) probe_clear_kernel(BatchDev b)
-{
-    b.plan->peak[threadIdx.x] = 0;
-}
-
-__global__ void __launch_bounds__(256) probe_peak_kernel(BatchDev b, ProbeParams pp)
+__global__ void __launch_bounds__(256) probe_kernel(BatchDev b, ProbeParams pp, PlanState* told)
 {
     __shared__ unsigned long long peak[TENT_MAX_RAILS];
     if (threadIdx.x < TENT_MAX_RAILS) peak[threadIdx.x] = 0;
@@ -59,16 +54,14 @@ __global__ void __launch_bounds__(256) probe_peak_kernel(BatchDev b, ProbeParams
         atomicMax(&peak[d], (unsigned long long)sample + 1);  // stored +1 so that 0 means "no sample"
     }
     __syncthreads();
+    unsigned long long added = 0;
     if (threadIdx.x < TENT_MAX_RAILS && peak[threadIdx.x])
-        atomicMax((unsigned long long*)&b.plan->peak[threadIdx.x], peak[threadIdx.x]);
-}
-
-// Cap by the hardware bandwidth and fold the probe into the estimate.
-__global__ void __launch_bounds__(64) probe_update_kernel(BatchDev b, ProbeParams pp)
-{
+        added = atomicMax((unsigned long long*)&b.plan->peak[threadIdx.x], peak[threadIdx.x]);
+    if (!finishes_last(b.plan, kTicketProbe, added) || threadIdx.x >= TENT_MAX_RAILS) return;
+    // cap by the hardware bandwidth and fold the probe into the estimate
     const uint32_t d = threadIdx.x;
     uint32_t probe = 0, next = pp.bw_MBps[d];
-    const uint64_t pk = b.plan->peak[d];
+    const uint64_t pk = take_counter(&b.plan->peak[d]);
     if (d < pp.n_rails && pk) {
         const tent_probe_params cal = pp.cal[d];
         const uint64_t best = pk - 1;
@@ -76,17 +69,15 @@ __global__ void __launch_bounds__(64) probe_update_kernel(BatchDev b, ProbeParam
         const uint64_t mixed = ((uint64_t)cal.ewma_q8 * probe + (uint64_t)(256 - cal.ewma_q8) * next) >> 8;
         next = (uint32_t)(mixed ? mixed : 1);
     }
-    b.plan->probe[d] = probe;
-    b.plan->bw_next[d] = next;
+    told->probe[d] = probe;
+    told->bw_next[d] = next;
 }
 
-hipError_t launch_probe(const BatchDev& b, const ProbeParams& pp, hipStream_t s)
+hipError_t launch_probe(const BatchDev& b, const ProbeParams& pp, PlanState* told, hipStream_t s)
 {
-    hipLaunchKernelGGL(probe_clear_kernel, dim3(1), dim3(64), 0, s, b);
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(probe_peak_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, pp);
-    hipLaunchKernelGGL(probe_update_kernel, dim3(1), dim3(64), 0, s, b, pp);
+    hipLaunchKernelGGL(probe_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, pp, told);
     return hipGetLastError();
 }
 

@@ -8,7 +8,7 @@
 // bytes of the earlier retried slices on the same rail -- one prefix sum per rail over the retry
 // list.  Three launches: per-chunk byte and slice counts per rail, an exclusive scan of those
 // over the chunks (one lane per rail), and the in-order walk of every chunk by one wavefront.
-#include "tent_internal.h"
+#include "finish.h"
 
 namespace tent {
 namespace {
@@ -55,12 +55,22 @@ __global__ void __launch_bounds__(64) rotate_spine_kernel(BatchDev b)
     const uint64_t n = b.plan->n_retry;
     const uint64_t chunks = (n + kRotChunk - 1) / kRotChunk;
     uint64_t run = 0, slices = 0;
-    for (uint64_t c = 0; c < chunks; ++c) {
-        const uint64_t at = c * TENT_MAX_RAILS + threadIdx.x;
-        const uint64_t t = b.rot_bytes[at];
-        b.rot_bytes[at] = run;
-        run += t;
-        slices += b.rot_cnt[at];
+    constexpr int kAhead = 8;                                    // loads in flight per lane
+    for (uint64_t c0 = 0; c0 < chunks; c0 += kAhead) {
+        uint64_t bytes[kAhead];
+        uint32_t count[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const uint64_t at = (c0 + k) * TENT_MAX_RAILS + threadIdx.x;
+            bytes[k] = c0 + k < chunks ? b.rot_bytes[at] : 0;
+            count[k] = c0 + k < chunks ? b.rot_cnt[at] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            if (c0 + k < chunks) b.rot_bytes[(c0 + k) * TENT_MAX_RAILS + threadIdx.x] = run;
+            run += bytes[k];
+            slices += count[k];
+        }
     }
     b.plan->Tr[threadIdx.x] = run;
     b.plan->cr[threadIdx.x] = slices;
@@ -113,7 +123,7 @@ __global__ void __launch_bounds__(64) rotate_emit_kernel(BatchDev b, RotateParam
 }
 
 // Rail simulator: every BOUND slice on a failed rail returns to the pending set with one more retry.
-__global__ void __launch_bounds__(256) fail_kernel(BatchDev b, FailParams fp)
+__global__ void __launch_bounds__(256) fail_kernel(BatchDev b, FailParams fp, PlanState* told)
 {
     __shared__ uint32_t cnt[TENT_MAX_RAILS];
     if (threadIdx.x < TENT_MAX_RAILS) cnt[threadIdx.x] = 0;
@@ -129,11 +139,13 @@ __global__ void __launch_bounds__(256) fail_kernel(BatchDev b, FailParams fp)
         atomicAdd(&cnt[d], 1u);
     }
     __syncthreads();
+    unsigned long long added = 0;
     if (threadIdx.x < TENT_MAX_RAILS && cnt[threadIdx.x])
-        atomicAdd((unsigned long long*)&b.plan->fail_cnt[threadIdx.x], (unsigned long long)cnt[threadIdx.x]);
+        added = atomicAdd((unsigned long long*)&b.plan->fail_cnt[threadIdx.x], (unsigned long long)cnt[threadIdx.x]);
+    if (!finishes_last(b.plan, kTicketFail, added) || threadIdx.x >= TENT_MAX_RAILS) return;
+    const unsigned long long total = take_counter(&b.plan->fail_cnt[threadIdx.x]);
+    if (told) told->fail_cnt[threadIdx.x] = total;
 }
-
-__global__ void __launch_bounds__(64) fail_clear_kernel(BatchDev b) { b.plan->fail_cnt[threadIdx.x] = 0; }
 
 }  // namespace
 
@@ -148,12 +160,11 @@ hipError_t launch_rotate(const BatchDev& b, const RotateParams& rot, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_fail(const BatchDev& b, const FailParams& fp, hipStream_t s)
+hipError_t launch_fail(const BatchDev& b, const FailParams& fp, PlanState* told, hipStream_t s)
 {
-    hipLaunchKernelGGL(fail_clear_kernel, dim3(1), dim3(64), 0, s, b);
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(fail_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, fp);
+    hipLaunchKernelGGL(fail_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, fp, told);
     return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 // batch is re-planned.  Follows the paper's slice decomposition (Section 4.2): a
 // transfer of len bytes becomes ceil(len / S) slices; slice k covers [k*S, min((k+1)*S, len))
 // and keeps that absolute offset so it can be written straight to its destination.
+#include "finish.h"
 #include "scan.h"
 #include "tile_tables.h"
 
@@ -265,12 +266,12 @@ __global__ void __launch_bounds__(256) stage_tiles_kernel(BatchDev b, uint8_t* a
 }
 
 // The same when few slices move: the tiles of the BOUND slices are listed with their three addresses, in any
-// order (the copy's result does not depend on it).  A workgroup looks at 64 slices, places those that are BOUND one behind
-// the other and takes room for all of them with one atomic add (one per slice measured 32 us over 20,000 slices, 17,000 of them
-// BOUND; one per workgroup: 9 us); groups of lanes then write the entries.  A workgroup whose tiles do not fit the list, or the
+// order (the copy's result does not depend on it).  A workgroup looks at 16 slices, places those that are BOUND one behind
+// the other and takes room for all of them with one atomic add (over 20,000 slices of which 1,200 move: an add per slice
+// 32 us; 64 slices to a workgroup 22 us, because BOUND slices lie together and few workgroups then have all the work); groups of lanes then write the entries.  A workgroup whose tiles do not fit the list, or the
 // host's bound that sizes the copy, leaves its slices BOUND and lists nothing; the others occupy the list without
 // gaps, because the first that does not fit moves the counter past the bound.
-constexpr uint32_t kListSlices = 64;
+constexpr uint32_t kListSlices = 16;
 __global__ void __launch_bounds__(256) list_tiles_kernel(BatchDev b, uint8_t* arena, uint32_t group_shift, uint32_t tile_shift,
                                                          uint64_t max_tiles)
 {
@@ -287,7 +288,7 @@ __global__ void __launch_bounds__(256) list_tiles_kernel(BatchDev b, uint8_t* ar
             sh_q0[threadIdx.x] = b.s_pos[i] >> tile_shift;
         }
         const uint64_t up_to = wave_inclusive_scan((uint64_t)n_t);
-        const uint64_t all = __shfl((unsigned long long)up_to, 63, 64);
+        const uint64_t all = __shfl((unsigned long long)up_to, kListSlices - 1, 64);
         uint64_t from = 0;
         if (threadIdx.x == 0 && all != 0) {
             from = atomicAdd((unsigned long long*)&b.plan->n_act_asked, (unsigned long long)all);
@@ -423,7 +424,7 @@ hipError_t launch_reset(const BatchDev& b, hipStream_t s)
 // ahead of the plan, the slices staged before it, and the slice itself; otherwise it returns to
 // the pending set.  The count of completed slices is an integer sum, so its value does not
 // depend on the order of the atomic adds.
-__global__ void __launch_bounds__(256) retire_kernel(BatchDev b, BudgetParams bp)
+__global__ void __launch_bounds__(256) retire_kernel(BatchDev b, BudgetParams bp, PlanState* told)
 {
     __shared__ unsigned long long block_done;
     if (threadIdx.x == 0) block_done = 0;
@@ -439,21 +440,22 @@ __global__ void __launch_bounds__(256) retire_kernel(BatchDev b, BudgetParams bp
     }
     if (mine) atomicAdd(&block_done, mine);
     __syncthreads();
-    if (threadIdx.x == 0 && block_done) atomicAdd((unsigned long long*)&b.plan->n_done, block_done);
+    unsigned long long added = 0;
+    if (threadIdx.x == 0 && block_done) added = atomicAdd((unsigned long long*)&b.plan->n_done, block_done);
+    if (!finishes_last(b.plan, kTicketRetire, added) || threadIdx.x != 0) return;
+    const unsigned long long total = take_counter(&b.plan->n_done);
+    if (told) told->n_done = total;
 }
 
-__global__ void zero_counter_kernel(uint64_t* p) { *p = 0; }
-
-hipError_t launch_retire(const BatchDev& b, const BudgetParams& bp, hipStream_t s)
+hipError_t launch_retire(const BatchDev& b, const BudgetParams& bp, PlanState* told, hipStream_t s)
 {
-    hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, s, &b.plan->n_done);
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(retire_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, bp);
+    hipLaunchKernelGGL(retire_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, bp, told);
     return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) count_remaining_kernel(BatchDev b)
+__global__ void __launch_bounds__(256) count_remaining_kernel(BatchDev b, PlanState* told)
 {
     __shared__ unsigned long long block_cnt;
     if (threadIdx.x == 0) block_cnt = 0;
@@ -464,15 +466,17 @@ __global__ void __launch_bounds__(256) count_remaining_kernel(BatchDev b)
         mine += b.s_state[i] != TENT_SLICE_DONE;
     if (mine) atomicAdd(&block_cnt, mine);
     __syncthreads();
-    if (threadIdx.x == 0 && block_cnt) atomicAdd((unsigned long long*)&b.plan->n_remaining, block_cnt);
+    unsigned long long added = 0;
+    if (threadIdx.x == 0 && block_cnt) added = atomicAdd((unsigned long long*)&b.plan->n_remaining, block_cnt);
+    if (!finishes_last(b.plan, kTicketRemaining, added) || threadIdx.x != 0) return;
+    told->n_remaining = take_counter(&b.plan->n_remaining);
 }
 
-hipError_t launch_count_remaining(const BatchDev& b, hipStream_t s)
+hipError_t launch_count_remaining(const BatchDev& b, PlanState* told, hipStream_t s)
 {
-    hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, s, &b.plan->n_remaining);
-    uint64_t blocks = (b.n_slices + 255) / 256;
-    if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(count_remaining_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);
+    uint64_t blocks = (b.n_slices + 1023) / 1024;
+    if (blocks > 256) blocks = 256;
+    hipLaunchKernelGGL(count_remaining_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, told);
     return hipGetLastError();
 }
 

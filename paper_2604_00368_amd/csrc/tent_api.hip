@@ -52,7 +52,6 @@ struct Batch {
     // context's own stream and ends at decl_event; `verdict` (pinned host memory) then holds the
     // overlap check's result.
     bool decl_pending = false;
-    uint32_t* overlap_dev = nullptr;
     // Device memory of the tables: an allocation of the batch's own, or the library's static workspace.
     void* block = nullptr;
     uint64_t block_bytes = 0;
@@ -86,7 +85,7 @@ struct tent_ctx {
     uint32_t seg_capacity = 0;
     std::vector<Batch> batches;
     Batch static_batch;                     // the one batch whose tables live in the static workspace
-    PlanState* host_plan = nullptr;         // pinned read-back buffer
+    PlanState* host_plan = nullptr;         // pinned result block, written by the kernels of calls that report something
     hipStream_t aux_stream = nullptr;       // second stream of the pipelined bounded execute (default priority)
     std::vector<hipEvent_t> sync_events;    // ordering events of the pipelined bounded execute, reused
     // tent_declare: its device work runs on a stream of the library's own, so that it neither waits for
@@ -165,7 +164,7 @@ struct StreamNote {
     Batch& b;
     hipStream_t s;
     StreamNote(Batch& batch, hipStream_t stream) : b(batch), s(stream) {}
-    ~StreamNote() { note_stream(b, s); }
+    ~StreamNote() { if (b.alive) note_stream(b, s); }
 };
 
 // Host-side wait for everything that was enqueued for the batch.
@@ -385,6 +384,7 @@ bool pointers_ok(uint32_t n_desc, const uint32_t* p)
 struct WalkResult {
     int rc = TENT_OK;
     uint64_t total = 0, slices = 0, bits = 0, most = 0;
+    uint64_t src_apart = 0, dst_apart = 0;      // address bits in which an extent differs from the first destination extent
 };
 
 void validate_range(const tent_ctx* ctx, uint32_t j0, uint32_t j1, const uint32_t* sp, const tent_extent* se,
@@ -393,6 +393,7 @@ void validate_range(const tent_ctx* ctx, uint32_t j0, uint32_t j1, const uint32_
     const uint64_t S = ctx->cfg.slice_bytes;
     const size_t n_seg = ctx->segments.size();
     const Segment* seg = ctx->segments.data();
+    const uint64_t origin = de[0].seg < n_seg ? (uint64_t)seg[de[0].seg].base + de[0].off : 0;
     WalkResult r;
     for (uint32_t j = j0; j < j1; ++j) {
         uint64_t ls = 0, ld = 0;
@@ -402,6 +403,7 @@ void validate_range(const tent_ctx* ctx, uint32_t j0, uint32_t j1, const uint32_
             const uint64_t seg_len = seg[x.seg].len;
             if (x.off > seg_len || x.len > seg_len - x.off) { r.rc = TENT_ERR_INVALID; *out = r; return; }
             if (se_out) se_out[e] = x;
+            r.src_apart |= ((uint64_t)seg[x.seg].base + x.off) ^ origin;
             ls += x.len;
             r.bits |= x.len;
         }
@@ -411,6 +413,7 @@ void validate_range(const tent_ctx* ctx, uint32_t j0, uint32_t j1, const uint32_
             const uint64_t seg_len = seg[x.seg].len;
             if (x.off > seg_len || x.len > seg_len - x.off) { r.rc = TENT_ERR_INVALID; *out = r; return; }
             if (de_out) de_out[e] = x;
+            r.dst_apart |= ((uint64_t)seg[x.seg].base + x.off) ^ origin;
             ld += x.len;
             r.bits |= x.len;
         }
@@ -423,12 +426,12 @@ void validate_range(const tent_ctx* ctx, uint32_t j0, uint32_t j1, const uint32_
     *out = r;
 }
 
-// The whole batch; also returns the payload and the number of slices the device splitter will produce.
+// The whole batch, with the payload and the number of slices the device splitter will produce.
 // Large batches are walked by a few threads, each over a range of transfers with about the same number of
 // extents: the walk streams some tens of megabytes and is the longest part of a declaration.
 int validate(const tent_ctx* ctx, uint32_t n_desc, const uint32_t* sp, const tent_extent* se,
              const uint32_t* dp, const tent_extent* de, tent_extent* se_out, tent_extent* de_out,
-             uint64_t* payload, uint64_t* n_slices, uint64_t* len_bits, uint64_t* max_req_slices, bool may_spawn)
+             WalkResult* all, bool may_spawn)
 {
     constexpr uint32_t kMaxWalkers = 4;
     constexpr uint64_t kExtentsPerWalker = 1ull << 16;
@@ -470,18 +473,15 @@ int validate(const tent_ctx* ctx, uint32_t n_desc, const uint32_t* sp, const ten
     } else {
         validate_range(ctx, 0, n_desc, sp, se, dp, de, se_out, de_out, &part[0]);
     }
-    uint64_t total = 0, slices = 0, bits = 0, most = 0;
     for (uint32_t k = 0; k < used; ++k) {
         if (part[k].rc != TENT_OK) return part[k].rc;
-        total += part[k].total;
-        slices += part[k].slices;
-        bits |= part[k].bits;
-        most = std::max(most, part[k].most);
+        all->total += part[k].total;
+        all->slices += part[k].slices;
+        all->bits |= part[k].bits;
+        all->most = std::max(all->most, part[k].most);
+        all->src_apart |= part[k].src_apart;
+        all->dst_apart |= part[k].dst_apart;
     }
-    *payload = total;
-    *n_slices = slices;
-    *len_bits = bits;
-    *max_req_slices = most;
     return TENT_OK;
 }
 
@@ -561,6 +561,17 @@ int finish_declare(tent_ctx* ctx, Batch& b)
     return TENT_OK;
 }
 
+// The same for a plan that enqueues first and asks afterwards: the declaration's device work, the host's launches and the plan
+// then follow each other without a host wait in between (20-40 us for a small batch).  A batch whose destinations overlap
+// is planned like any other -- its tables are sound, only no byte may move -- and released here.
+int finish_declare_behind(tent_ctx* ctx, Batch& b, hipStream_t s)
+{
+    if (!b.decl_pending) return TENT_OK;
+    HIP_TRY(hipEventSynchronize(b.decl_event));
+    if (*b.verdict != 0) HIP_TRY(hipStreamSynchronize(s));
+    return finish_declare(ctx, b);
+}
+
 // Telemetry -> integer coefficients (Eq. 1 with the topology penalty folded in).
 int convert_rails(const tent_rail_state* rails, uint32_t n_rails, uint64_t pending_bytes, RailParams* rp)
 {
@@ -628,10 +639,11 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     uint8_t* st = acquire_stage(ctx, stage_need, !use_static, &which);
     if (!st && !use_static) return TENT_ERR_NOMEM;
 
-    uint64_t payload = 0, n_slices = 0, len_bits = 0, max_req_slices = 0;
+    WalkResult walk;
     int rc = validate(ctx, n_desc, src_ptr, src_ext, dst_ptr, dst_ext, st ? (tent_extent*)(st + o_se) : nullptr,
-                      st ? (tent_extent*)(st + o_de) : nullptr, &payload, &n_slices, &len_bits, &max_req_slices, !use_static);
+                      st ? (tent_extent*)(st + o_de) : nullptr, &walk, !use_static);
     if (rc != TENT_OK) return rc;
+    const uint64_t payload = walk.total, n_slices = walk.slices, len_bits = walk.bits, max_req_slices = walk.most;
     if (n_slices >= 0xFFFFFFFEull) return TENT_ERR_RANGE;
 
     Batch* slot_b = nullptr;
@@ -685,17 +697,12 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
         d.n_sc_tiles = (bits & (d.tile_bytes - 1)) == 0 ? payload / d.tile_bytes : 0;
     }
 
-    uint32_t *sp = nullptr, *dp = nullptr;
-    tent_extent *se = nullptr, *de = nullptr;
+    uint8_t* upload = nullptr;                            // pointers, extents and the device view, laid out as in the pinned buffer
     const uint64_t scan_n = std::max<uint64_t>(std::max(ns, nd), std::max<uint64_t>(n_slices, n_desc));
-    BatchDev* self_dev = nullptr;
     uint32_t* order_dev = nullptr;
     uint32_t* rank_dev = nullptr;
     Carver cv;
-    cv.want(&sp, (uint64_t)n_desc + 1);
-    cv.want(&dp, (uint64_t)n_desc + 1);
-    cv.want(&se, ns);
-    cv.want(&de, nd);
+    cv.want(&upload, stage_need);
     cv.want(&d.src_pre, ns + 1);
     cv.want(&d.dst_pre, nd + 1);
     cv.want(&d.first, (uint64_t)n_desc + 1);
@@ -713,8 +720,6 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     cv.want(&d.s_retry, n_slices);
     cv.want(&d.priority, (uint64_t)n_desc);
     cv.want(&d.req_mode, (uint64_t)n_desc);
-    cv.want(&self_dev, 1);
-    cv.want(&b.overlap_dev, 1);
     if (d.n_sc_tiles == 0) {                              // per-slice tile tables only for untiled geometry
         cv.want(&d.src_tile, n_tiles);
         cv.want(&d.dst_tile, n_tiles);
@@ -783,7 +788,10 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     // destination extents in address order (for the scatter) and the overlap check run on the device
     const bool order = check || d.n_sc_tiles != 0;
     uint64_t ws_need = 0;
-    if (order && order_workspace_bytes(nd, ns, check, &ws_need) != hipSuccess) { (void)hipGetLastError(); return TENT_ERR_HIP; }
+    KeyBits key_bits{0, 1};
+    if (const uint64_t apart = walk.dst_apart | (check ? walk.src_apart : 0))
+        key_bits = KeyBits{(uint32_t)__builtin_ctzll(apart), 64u - (uint32_t)__builtin_clzll(apart)};
+    if (order && order_workspace_bytes(nd, ns, check, key_bits, &ws_need) != hipSuccess) { (void)hipGetLastError(); return TENT_ERR_HIP; }
     const uint64_t table_bytes = cv.total();
     void* workspace = nullptr;
     if (use_static) {
@@ -821,10 +829,13 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
         workspace = ctx->order_ws;
     }
     cv.place(b.block);
-    d.src_ptr = sp; d.dst_ptr = dp; d.src_ext = se; d.dst_ext = de;
+    d.src_ptr = reinterpret_cast<uint32_t*>(upload + o_sp);
+    d.dst_ptr = reinterpret_cast<uint32_t*>(upload + o_dp);
+    d.src_ext = reinterpret_cast<tent_extent*>(upload + o_se);
+    d.dst_ext = reinterpret_cast<tent_extent*>(upload + o_de);
     d.dst_order = order_dev;
     d.dst_rank = rank_dev;
-    d.self = self_dev;
+    d.self = reinterpret_cast<BatchDev*>(upload + o_self);
 
     // Everything from here on is enqueued on the context's own stream; nothing waits for the device
     // unless the host arrays could not go through the pinned buffer.
@@ -834,29 +845,18 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
         std::memcpy(st + o_sp, src_ptr, ptr_bytes);
         std::memcpy(st + o_dp, dst_ptr, ptr_bytes);
         std::memcpy(st + o_self, &d, sizeof(BatchDev));
-        ok = hipMemcpyAsync(sp, st + o_sp, ptr_bytes, hipMemcpyHostToDevice, ds) == hipSuccess &&
-             hipMemcpyAsync(dp, st + o_dp, ptr_bytes, hipMemcpyHostToDevice, ds) == hipSuccess &&
-             hipMemcpyAsync(se, st + o_se, ns * sizeof(tent_extent), hipMemcpyHostToDevice, ds) == hipSuccess &&
-             hipMemcpyAsync(de, st + o_de, nd * sizeof(tent_extent), hipMemcpyHostToDevice, ds) == hipSuccess &&
-             hipMemcpyAsync(self_dev, st + o_self, sizeof(BatchDev), hipMemcpyHostToDevice, ds) == hipSuccess &&
+        ok = hipMemcpyAsync(upload, st, stage_need, hipMemcpyHostToDevice, ds) == hipSuccess &&
              hipEventRecord(ctx->stage_event[which], ds) == hipSuccess;
         if (ok) ctx->stage_busy[which] = true;
     } else {
         // the pinned buffer is too small and may not grow: the arrays go through it piece by piece
-        ok = upload_in_pieces(ctx, sp, src_ptr, ptr_bytes) && upload_in_pieces(ctx, dp, dst_ptr, ptr_bytes) &&
-             upload_in_pieces(ctx, se, src_ext, ns * sizeof(tent_extent)) &&
-             upload_in_pieces(ctx, de, dst_ext, nd * sizeof(tent_extent)) &&
-             upload_in_pieces(ctx, self_dev, &d, sizeof(BatchDev));
+        ok = upload_in_pieces(ctx, upload + o_sp, src_ptr, ptr_bytes) && upload_in_pieces(ctx, upload + o_dp, dst_ptr, ptr_bytes) &&
+             upload_in_pieces(ctx, upload + o_se, src_ext, ns * sizeof(tent_extent)) &&
+             upload_in_pieces(ctx, upload + o_de, dst_ext, nd * sizeof(tent_extent)) &&
+             upload_in_pieces(ctx, upload + o_self, &d, sizeof(BatchDev));
     }
-    ok = ok && hipMemsetAsync(d.s_retry, 0, std::max<uint64_t>(n_slices, 1), ds) == hipSuccess &&
-         hipMemsetAsync(d.req_mode, 0, n_desc, ds) == hipSuccess &&
-         hipMemsetAsync(d.plan, 0, sizeof(PlanState), ds) == hipSuccess &&
-         hipMemsetAsync(b.overlap_dev, 0, sizeof(uint32_t), ds) == hipSuccess;
-    if (ok && order)
-        ok = device_order_destinations(de, nd, se, ns, ctx->seg_base_dev, check, order_dev, rank_dev, b.overlap_dev,
-                                       workspace, ds) == hipSuccess;
     *b.verdict = 0;
-    ok = ok && hipMemcpyAsync(b.verdict, b.overlap_dev, sizeof(uint32_t), hipMemcpyDeviceToHost, ds) == hipSuccess &&
+    ok = ok && launch_declare(d, order, check, key_bits, order_dev, rank_dev, b.verdict, workspace, ds) == hipSuccess &&
          hipEventRecord(b.decl_event, ds) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -999,14 +999,17 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
     if (rc != TENT_OK) return rc;
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
-    rc = finish_declare(ctx, *b);
-    if (rc != TENT_OK) return rc;
-    if (rp.admitted == 0) return TENT_DEFER;
-    if (!(ctx->cfg.flags & TENT_FLAG_BOUNDED_STAGING) && b->payload + 256ull * n_rails > ctx->cfg.staging_bytes)
-        return TENT_ERR_RANGE;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    const bool too_small = !(ctx->cfg.flags & TENT_FLAG_BOUNDED_STAGING) && b->payload + 256ull * n_rails > ctx->cfg.staging_bytes;
+    if (rp.admitted == 0 || too_small || capturing(s)) {
+        rc = finish_declare(ctx, *b);
+        if (rc != TENT_OK) return rc;
+        if (rp.admitted == 0) return TENT_DEFER;
+        if (too_small) return TENT_ERR_RANGE;
+    }
     const BatchDev& d = b->dev;
     StreamNote note(*b, s);
+    if (b->decl_pending) HIP_TRY(hipStreamWaitEvent(s, b->decl_event, 0));
     HIP_TRY(order_after_execute_bookkeeping(*b, s));
 
     // Retry rotation (Section 4.3, "Link-Level Resilience"): candidates are the HEALTHY rails, else the
@@ -1058,16 +1061,18 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
     {
         StageTimer t(ctx, TENT_T_BIND, s);
         if (serial) HIP_TRY(launch_bind_serial(d, rp, mode, s));
-        else        HIP_TRY(launch_bind_runs(d, rp, mode | (replan ? 0 : kBindBuildTables), s));
+        else        HIP_TRY(launch_bind_runs(d, rp, mode | (replan ? 0 : kBindBuildTables), info ? ctx->host_plan : nullptr, s));
     }
     b->planned = true;
     b->bound_hint = b->dev.n_slices;
     b->tile_hint = ~0ull;
     b->last_rails = rp;
     for (uint32_t r = 0; r < n_rails; ++r) b->last_lat_ns[r] = rails[r].lat_ns;
+    rc = finish_declare_behind(ctx, *b, s);
+    if (rc != TENT_OK) return rc;
 
     if (info) {
-        HIP_TRY(hipMemcpyAsync(ctx->host_plan, d.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
+        if (serial) HIP_TRY(hipMemcpyAsync(ctx->host_plan, d.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         const PlanState& ps = *ctx->host_plan;
         std::memset(info, 0, sizeof(*info));
@@ -1161,7 +1166,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     }
     {
         StageTimer t(ctx, TENT_T_BIND, s);
-        HIP_TRY(launch_dispatch(d, rp, dp, first_plan, s));
+        HIP_TRY(launch_dispatch(d, rp, dp, first_plan, info ? ctx->host_plan : nullptr, s));
     }
     b->planned = true;
     b->bound_hint = b->dev.n_slices;
@@ -1170,7 +1175,6 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     for (uint32_t r = 0; r < n_rails; ++r) b->last_lat_ns[r] = rails[r].lat_ns;
 
     if (info) {
-        HIP_TRY(hipMemcpyAsync(ctx->host_plan, d.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         const PlanState& ps = *ctx->host_plan;
         std::memset(info, 0, sizeof(*info));
@@ -1221,7 +1225,7 @@ int tent_sim_advance(tent_ctx* ctx, tent_batch_t batch, const uint64_t* budget_b
         bp.budget[d] = budget_bytes[d];
     }
     StreamNote note(*b, s);
-    HIP_TRY(launch_retire(b->dev, bp, s));
+    HIP_TRY(launch_retire(b->dev, bp, n_done ? ctx->host_plan : nullptr, s));
     // What stays BOUND on rail d fits in budget_d - queued_d bytes, which bounds the tiles the next execute
     // copies without asking the device (slices of a tiled batch are whole tiles).
     uint64_t tiles = 0;
@@ -1229,7 +1233,6 @@ int tent_sim_advance(tent_ctx* ctx, tent_batch_t batch, const uint64_t* budget_b
         if (bp.budget[d] > bp.queued[d]) tiles += (bp.budget[d] - bp.queued[d]) / (b->dev.tile_bytes ? b->dev.tile_bytes : 1u);
     b->tile_hint = tiles;
     if (!n_done) return TENT_OK;
-    HIP_TRY(hipMemcpyAsync(ctx->host_plan, b->dev.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     b->bound_hint = ctx->host_plan->n_done;
     *n_done = ctx->host_plan->n_done;
@@ -1256,13 +1259,12 @@ int tent_sim_fail(tent_ctx* ctx, tent_batch_t batch, const uint8_t* rail_failed,
     hipStream_t s = static_cast<hipStream_t>(stream);
     StreamNote note(*b, s);
     if (any) {
-        HIP_TRY(launch_fail(b->dev, fp, s));
+        HIP_TRY(launch_fail(b->dev, fp, failed_per_rail ? ctx->host_plan : nullptr, s));
         b->has_retry = true;
     }
     if (failed_per_rail) {
         for (uint32_t d = 0; d < n_rails; ++d) failed_per_rail[d] = 0;
         if (any) {
-            HIP_TRY(hipMemcpyAsync(ctx->host_plan, b->dev.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
             HIP_TRY(hipStreamSynchronize(s));
             for (uint32_t d = 0; d < n_rails; ++d) failed_per_rail[d] = ctx->host_plan->fail_cnt[d];
         }
@@ -1329,9 +1331,8 @@ int tent_update_bandwidth(tent_ctx* ctx, tent_batch_t batch, const tent_probe_pa
     hipStream_t s = static_cast<hipStream_t>(stream);
     {
         StageTimer t(ctx, TENT_T_FEEDBACK, s);
-        HIP_TRY(launch_probe(b->dev, pp, s));
+        HIP_TRY(launch_probe(b->dev, pp, ctx->host_plan, s));
     }
-    HIP_TRY(hipMemcpyAsync(ctx->host_plan, b->dev.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     for (uint32_t d = 0; d < n_rails; ++d) {
         rails[d].bw_MBps = ctx->host_plan->bw_next[d];
@@ -1517,8 +1518,7 @@ int tent_poll(tent_ctx* ctx, tent_batch_t batch, uint64_t* remaining, void* stre
     // slices are marked DONE ahead of their copies: completion is only reported once the last
     // execute's copies have ended, whichever stream the caller polls on
     if (b->done_recorded && s != b->exec_stream) HIP_TRY(hipStreamWaitEvent(s, b->done_event, 0));
-    HIP_TRY(launch_count_remaining(b->dev, s));
-    HIP_TRY(hipMemcpyAsync(ctx->host_plan, b->dev.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
+    HIP_TRY(launch_count_remaining(b->dev, ctx->host_plan, s));
     HIP_TRY(hipStreamSynchronize(s));
     *remaining = ctx->host_plan->n_remaining;
     return TENT_OK;

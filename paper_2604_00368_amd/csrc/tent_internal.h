@@ -85,6 +85,7 @@ struct PlanState {
     uint64_t n_act;                       // tent_execute with few BOUND slices: entries of the list of tiles that move
     uint64_t compact_overflow;            // nonzero: more tiles move than the launch was sized for (nothing is marked DONE)
     uint64_t n_act_asked;                 // one-pass copies: tiles of the BOUND slices, listed or not
+    uint32_t ticket[4];                   // workgroups that have finished, per kind of counting kernel (finish.h); 0 between launches
 };
 
 // What the binding chains leave for the emit kernels, per run (request) and rail, in one 16-byte store: bytes bound to
@@ -206,7 +207,7 @@ enum : uint32_t { kOrderedLanes = 256 };             // lanes of a table-driven 
                                                      // measure the same on MI355X, 64 / 512 / 1024 are slower
 constexpr uint64_t kTileSlow = 1ull << 63;
 enum : uint32_t { kMaxChunks = 4096 };               // most chunks one bounded execute may use
-enum : uint32_t { kRotChunk = 1024 };                // retried slices one rotation workgroup handles
+enum : uint32_t { kRotChunk = 256 };                 // retried slices one rotation wavefront handles (1024: four times the rounds, 32 against 17 us a pass)
 // `mode` argument of the bind kernels
 enum : int { kBindUsePending = 1, kBindAfterRotation = 2, kBindBuildTables = 4 };
 
@@ -216,16 +217,17 @@ hipError_t launch_slice_scan(const BatchDev& b, hipStream_t s);
 hipError_t launch_expand(const BatchDev& b, hipStream_t s);
 hipError_t launch_compact(const BatchDev& b, hipStream_t s);
 hipError_t launch_bind_serial(const BatchDev& b, const RailParams& rp, int mode, hipStream_t s);
-hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, hipStream_t s);
+// `told` (host memory the device can write, or null): where the plan's totals go as well
+hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, PlanState* told, hipStream_t s);
 hipError_t launch_rotate(const BatchDev& b, const RotateParams& rot, hipStream_t s);
-hipError_t launch_fail(const BatchDev& b, const FailParams& fp, hipStream_t s);
+hipError_t launch_fail(const BatchDev& b, const FailParams& fp, PlanState* told, hipStream_t s);
 hipError_t launch_bounded_prepare(const BatchDev& b, uint64_t payload, uint64_t chunk_bytes, uint32_t n_chunks,
                                   uint64_t slot_bytes, uint32_t slots, uint8_t* arena, hipStream_t s);
 hipError_t launch_bounded_copy(const BatchDev& b, bool gather, uint32_t chunk, uint64_t payload, uint64_t chunk_bytes,
                                uint64_t slot_bytes, uint32_t slots, uint8_t* arena, hipStream_t s);
 hipError_t launch_mark_done_bounded(const BatchDev& b, hipStream_t s);
 hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, bool first_plan,
-                           hipStream_t s);
+                           PlanState* told, hipStream_t s);
 hipError_t launch_tile_tables(const BatchDev& b, hipStream_t s);
 hipError_t launch_finalize(const BatchDev& b, uint8_t* arena, bool compact, uint64_t max_tiles, hipStream_t s);
 hipError_t launch_copy(const BatchDev& b, bool gather, hipStream_t s);
@@ -234,17 +236,20 @@ hipError_t launch_copy_one_pass(const BatchDev& b, bool compact, uint64_t max_ti
 hipError_t launch_copy_ordered(const BatchDev& b, bool gather, hipStream_t s);
 hipError_t launch_copy_compact(const BatchDev& b, bool gather, uint64_t max_tiles, hipStream_t s);
 hipError_t launch_mark_done(const BatchDev& b, bool compact, hipStream_t s);
-hipError_t launch_retire(const BatchDev& b, const BudgetParams& bp, hipStream_t s);
-hipError_t launch_count_remaining(const BatchDev& b, hipStream_t s);
+hipError_t launch_retire(const BatchDev& b, const BudgetParams& bp, PlanState* told, hipStream_t s);
+hipError_t launch_count_remaining(const BatchDev& b, PlanState* told, hipStream_t s);
 hipError_t launch_reset(const BatchDev& b, hipStream_t s);
 hipError_t launch_sim_latency(const BatchDev& b, const LatencyParams& lp, hipStream_t s);
-hipError_t launch_probe(const BatchDev& b, const ProbeParams& pp, hipStream_t s);
+hipError_t launch_probe(const BatchDev& b, const ProbeParams& pp, PlanState* told, hipStream_t s);
 
 uint64_t scan_partials_capacity(uint64_t n);
 
-hipError_t order_workspace_bytes(uint64_t n_dst, uint64_t n_src, bool check, uint64_t* bytes_out);
-hipError_t device_order_destinations(const tent_extent* dst_ext, uint64_t n_dst, const tent_extent* src_ext,
-                                     uint64_t n_src, const uint64_t* seg_base, bool check, uint32_t* order_out,
-                                     uint32_t* rank_out, uint32_t* overlap_dev, void* workspace, hipStream_t s);
+// Address bits in which the extents of a declaration differ: all others are the same, so they need no sorting.
+struct KeyBits {
+    uint32_t begin, end;           // begin < end
+};
+hipError_t order_workspace_bytes(uint64_t n_dst, uint64_t n_src, bool check, KeyBits bits, uint64_t* bytes_out);
+hipError_t launch_declare(const BatchDev& b, bool order, bool check, KeyBits bits, uint32_t* order_out, uint32_t* rank_out,
+                          uint32_t* overlap_told, void* workspace, hipStream_t s);
 
 }  // namespace tent

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "tent_internal.h"
+
 namespace tent {
 
 template <int kCtrl>
@@ -98,6 +100,25 @@ __device__ __forceinline__ int argmax_cost(uint64_t cost, bool valid, int lane, 
     const uint32_t hi_max = wave_reduce32(hi, wide, Max32{});
     const uint32_t lo_max = wave_reduce32(hi == hi_max && valid ? lo : 0u, wide, Max32{});
     return (int)(__builtin_amdgcn_readfirstlane((int)lo_max) & 63);
+}
+
+// The totals a plan reports, by the first wavefront of one workgroup behind the chain's launch.
+__device__ __forceinline__ void tell_totals(const PlanState& ps, PlanState* told)
+{
+    const uint32_t d = threadIdx.x;
+    if (d >= TENT_MAX_RAILS) return;
+    told->T[d] = ps.T[d];
+    told->cnt[d] = ps.cnt[d];
+    told->A_after[d] = ps.A_after[d];
+    told->base[d] = ps.base[d];
+    if (d == 0) {
+        told->n_pending = ps.n_pending;
+        told->n_bound = ps.n_bound;
+        told->n_mice = ps.n_mice;
+        told->n_elephant = ps.n_elephant;
+        told->n_deferred = ps.n_deferred;
+        told->rr_next = ps.rr_next;
+    }
 }
 
 }  // namespace tent

@@ -1,0 +1,149 @@
+"""Declarations at the sizes where the address order changes its method (one workgroup up to 4096 extents, a device-wide sort
+above), address bits that differ in few or many places, and overlaps wherever they can hide."""
+import numpy as np
+import pytest
+
+from paper_2604_00368_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def T():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_00368_amd import binding
+    return binding
+
+
+class Pools:
+    """Source and destination pools of `n` extents of `size` bytes (destination `gap` bytes apart) in shuffled order."""
+
+    def __init__(self, T, n, size, gap=0, per_desc=3, seed=1, flags=0, dst_base=0):
+        g = np.random.Generator(np.random.PCG64([n, size, seed]))
+        self.T, self.n, self.size = T, n, size
+        pitch = size + gap
+        self.src = torch.from_numpy(g.integers(0, 256, size=n * size + 64, dtype=np.uint8)).cuda()
+        self.dst = torch.zeros(dst_base + n * pitch + 64, dtype=torch.uint8, device="cuda")
+        self.arena = torch.zeros(n * size + 1024, dtype=torch.uint8, device="cuda")
+        self.ctx = T.tent_create(4 * size, self.arena.data_ptr(), self.arena.numel(), flags)
+        T.tent_register_segment(self.ctx, self.src.data_ptr(), self.src.numel())
+        T.tent_register_segment(self.ctx, self.dst.data_ptr(), self.dst.numel())
+        self.se, self.de = np.zeros(n, dtype=W.EXTENT_DTYPE), np.zeros(n, dtype=W.EXTENT_DTYPE)
+        self.se["off"], self.se["len"] = g.permutation(n) * size, size
+        self.de["seg"], self.de["off"], self.de["len"] = W.DST_SEG, dst_base + g.permutation(n) * pitch, size
+        self.ptr = np.append(np.arange(0, n, per_desc), n).astype(np.uint32)
+        self.rails = W.make_rails([50000, 20000, 70000])
+
+    def declare(self, se=None, de=None):
+        return self.T.tent_declare(self.ctx, self.ptr, self.se if se is None else se, self.ptr, self.de if de is None else de)
+
+    def move(self, h, info=False):
+        stream = torch.cuda.current_stream()
+        self.T.tent_plan(self.ctx, h, self.rails, info, stream)
+        self.T.tent_execute(self.ctx, h, stream)
+        assert self.T.tent_poll(self.ctx, h, stream) == 0
+
+    def check(self):
+        src, dst = self.src.cpu().numpy(), self.dst.cpu().numpy()
+        want = np.zeros_like(dst)
+        for a, b in zip(self.se["off"].tolist(), self.de["off"].tolist()):
+            want[b:b + self.size] = src[a:a + self.size]
+        assert np.array_equal(dst, want)
+
+    def close(self):
+        self.T.tent_destroy(self.ctx)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 1023, 1024, 1025, 2047, 2048, 2049, 5000])
+@pytest.mark.parametrize("size,gap", [(64, 0), (61, 0), (1024, 3072)])
+def test_address_order_at_the_edges(T, n, size, gap):
+    p = Pools(T, n, size, gap)
+    h = p.declare()
+    p.move(h, info=n % 2 == 0)
+    p.check()
+    p.close()
+
+
+def test_order_without_the_check(T):
+    for n in (2048, 4096, 4097):                             # destinations only
+        p = Pools(T, n, 1024, 0, flags=T.TENT_FLAG_SKIP_OVERLAP_CHECK)
+        p.move(p.declare())
+        p.check()
+        p.close()
+
+
+@pytest.mark.parametrize("n", [2, 40, 2048, 2049, 4000])
+@pytest.mark.parametrize("where", ["first_two", "last_two", "inside_a_longer_one", "source_under_destination", "same_place"])
+def test_overlaps_are_found(T, n, where):
+    p = Pools(T, n, 64, 0)
+    se, de = p.se.copy(), p.de.copy()
+    order = np.argsort(de["off"])
+    if where == "first_two":
+        de["off"][order[1]] -= 1
+    elif where == "last_two":
+        de["off"][order[-1]] -= 63
+    elif where == "same_place":
+        de["off"][order[n // 2]] = de["off"][order[n // 2 - 1]]
+    elif where == "inside_a_longer_one":                     # a long extent covers several that do not touch each other
+        se, de = np.append(se, se[:1]), np.append(de, de[:1])
+        se["len"][-1] = de["len"][-1] = 2 * 64 if n > 1 else 64
+        se["off"][-1], de["off"][-1] = 0, 0
+    else:                                                    # a source extent lies where a destination is
+        se["seg"][0], se["off"][0] = W.DST_SEG, de["off"][order[n // 2]] + 60
+    ptr = p.ptr.copy()
+    ptr[-1] = se.shape[0]
+    for info in (False, True):
+        h = T.tent_declare(p.ctx, ptr, se, ptr, de)
+        with pytest.raises(T.TentError) as err:
+            T.tent_plan(p.ctx, h, p.rails, info, torch.cuda.current_stream())
+        assert err.value.status == T.TENT_ERR_INVALID
+        with pytest.raises(T.TentError) as err:              # the batch is gone
+            T.tent_slice_count(p.ctx, h)
+        assert err.value.status == T.TENT_ERR_INVALID
+    # the verdict comes before "no rail" and "arena too small", and the context goes on
+    h = T.tent_declare(p.ctx, ptr, se, ptr, de)
+    none = p.rails.copy()
+    none["health"] = 2
+    with pytest.raises(T.TentError) as err:
+        T.tent_plan(p.ctx, h, none, True, torch.cuda.current_stream())
+    assert err.value.status == T.TENT_ERR_INVALID
+    p.move(p.declare())
+    p.check()
+    p.close()
+
+
+def test_extents_that_touch_do_not_overlap(T):
+    p = Pools(T, 500, 33, 0)
+    p.move(p.declare())
+    p.check()
+    p.close()
+
+
+def test_counters_start_afresh_every_time(T):
+    """Calls that report counts, repeated and interleaved: every one counts from zero."""
+    p = Pools(T, 3000, 64, 0)
+    stream = torch.cuda.current_stream()
+    h = p.declare()
+    n = T.tent_slice_count(p.ctx, h)
+    for _ in range(3):
+        T.tent_reset(p.ctx, h, stream)
+        _, info = T.tent_plan(p.ctx, h, p.rails, True, stream)
+        assert info.n_slices == n and sum(info.rail_slices) == n
+        assert T.tent_poll(p.ctx, h, stream) == n
+        failed = T.tent_sim_fail(p.ctx, h, [0, 1, 0], True, stream)
+        assert failed[1] == info.rail_slices[1] and failed[0] == failed[2] == 0
+        assert T.tent_sim_advance(p.ctx, h, [1 << 40] * 3, stream) == n - failed[1]
+        T.tent_sim_latency(p.ctx, h, [50000, 20000, 70000], stream)
+        for _ in range(2):
+            rails, probe = T.tent_update_bandwidth(p.ctx, h, W.make_probe_params([100000] * 3), p.rails, stream)
+            assert probe[1] == 0 and probe[0] > 0 and rails["bw_MBps"][1] == 20000
+        T.tent_execute(p.ctx, h, stream)
+        assert T.tent_poll(p.ctx, h, stream) == failed[1]
+        T.tent_plan(p.ctx, h, p.rails, False, stream)
+        T.tent_execute(p.ctx, h, stream)
+        assert T.tent_poll(p.ctx, h, stream) == 0
+    p.check()
+    p.close()
