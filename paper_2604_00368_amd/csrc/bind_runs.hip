@@ -24,7 +24,7 @@
 #include <type_traits>
 
 #include "scan.h"
-#include "tile_tables.h"
+#include "slices.h"
 #include "wave.h"
 
 namespace tent {
@@ -718,30 +718,34 @@ __global__ void __launch_bounds__(256) bind_chain_tables_kernel(BatchDev b, Rail
         chain_workgroup<kWide>(b, rp, mode, ring, lm);
         return;
     }
-    build_tile_tables(b, blockIdx.x - 1, gridDim.x - 1);
+    build_tile_tables_in(b, blockIdx.x - 1, gridDim.x - 1);
 }
 
 // ---- step 3: emit -----------------------------------------------------------------------------
 // One lane per position q of the pending sequence; inside its run the lane enumerates slot
 // t = q - run_start as (rail d, index k) in rail-major order and computes the slot's rank.
-__global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams rp, int use_pending, PlanState* told)
+struct EmitRails {
+    uint64_t c0[TENT_MAX_RAILS];
+    double inv[TENT_MAX_RAILS];
+    uint32_t c1[TENT_MAX_RAILS];
+};
+
+// By a whole workgroup (with a barrier), thread `at` of `threads`.
+__device__ __forceinline__ void bind_emit(const BatchDev& b, const RailParams& rp, int use_pending, PlanState* told, EmitRails& er,
+                                          uint64_t at, uint64_t threads)
 {
-    __shared__ uint64_t sh_c0[TENT_MAX_RAILS];
-    __shared__ uint32_t sh_c1[TENT_MAX_RAILS];
-    __shared__ double sh_inv[TENT_MAX_RAILS];
     const uint32_t R = rp.n_rails;
     if (threadIdx.x < TENT_MAX_RAILS) {
         const uint32_t c1 = (uint32_t)rp.c1[threadIdx.x];
-        sh_c0[threadIdx.x] = rp.c0[threadIdx.x];
-        sh_c1[threadIdx.x] = c1 ? c1 : 1u;
-        sh_inv[threadIdx.x] = 1.0 / (double)(c1 ? c1 : 1u);
+        er.c0[threadIdx.x] = rp.c0[threadIdx.x];
+        er.c1[threadIdx.x] = c1 ? c1 : 1u;
+        er.inv[threadIdx.x] = 1.0 / (double)(c1 ? c1 : 1u);
     }
     __syncthreads();
     if (told && blockIdx.x == 0) tell_totals(*b.plan, told);
     const uint64_t n = b.plan->n_pending;
     const uint32_t stride = b.run_stride;
-    const uint64_t gstride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gstride) {
+    for (uint64_t q = at; q < n; q += threads) {
         const uint32_t id_q = use_pending ? b.pending[q] : (uint32_t)q;
         const uint64_t r = b.s_run[q];
         const uint32_t start = b.run_start[r];
@@ -773,14 +777,14 @@ __global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams r
         if (d >= R) continue;
         const uint32_t k = t;
         const uint64_t T_d = (uint64_t)row[d].T;
-        Rail me{sh_c0[d], sh_c1[d], sh_inv[d]};
+        Rail me{er.c0[d], er.c1[d], er.inv[d]};
         const uint64_t f = slot_cost(me, rp.A[d] + T_d, l, k);
         uint64_t rank = k;
         for (uint32_t o = 0; o < R; ++o) {
             if (o == d || !((rp.admitted >> o) & 1)) continue;
             const uint32_t ko = row[o].K;
             if (ko == 0) continue;
-            Rail other{sh_c0[o], sh_c1[o], sh_inv[o]};
+            Rail other{er.c0[o], er.c1[o], er.inv[o]};
             const uint64_t A_o = rp.A[o] + (uint64_t)row[o].T;
             // slots of a lower rail win ties, slots of a higher rail lose them
             const uint32_t c = slots_upto(other, A_o, l, inv_l, o < d ? (int64_t)f : (int64_t)f - 1, ko);
@@ -794,7 +798,131 @@ __global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams r
     }
 }
 
+__global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams rp, int use_pending, PlanState* told)
+{
+    __shared__ EmitRails er;
+    bind_emit(b, rp, use_pending, told, er, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, (uint64_t)gridDim.x * blockDim.x);
+}
+
+// ---- a small batch's first plan in one workgroup ----------------------------------------------------
+// Prefixes, slice table, run table, chain, tile tables and emit one after the other with barriers in between, the tile
+// tables beside the chain as in the large form.  What bounds a small plan is launches, not work: 64 transfers, 626 extents,
+// 182 slices took five launches and 44 us of device time in a graph and take one of 32 us.
+constexpr uint32_t kSmallThreads = 1024;
+constexpr uint32_t kSmallExtents = 2048;         // per side; two per thread
+constexpr uint32_t kSmallSlices = 2048;
+constexpr uint64_t kSmallTiles = 16384;          // 18 per thread that the chain and its feeder leave over
+
+struct SmallPlan {
+    uint64_t src_pre[kSmallExtents + 1], dst_pre[kSmallExtents + 1];
+    uint32_t first[kSmallExtents + 1], runs_before[kSmallExtents + 1];
+    uint64_t wave_out[kSmallThreads / 64];
+    union {
+        RecordRing ring;
+        EmitRails er;
+    };
+    LevelModel lm;
+};
+
+// Exclusive prefix of two values per thread (elements 2 t and 2 t + 1) over the workgroup.
+__device__ __forceinline__ uint64_t pair_prefix(uint64_t v0, uint64_t v1, uint64_t* wave_out)
+{
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t inc = wave_inclusive_scan(v0 + v1);
+    __syncthreads();
+    if (lane == 63) wave_out[wave] = inc;
+    __syncthreads();
+    uint64_t before = 0;
+    for (uint32_t w = 0; w < wave; ++w) before += wave_out[w];
+    return before + inc - (v0 + v1);
+}
+
+template <int kWide>
+__global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, RailParams rp, PlanState* told)
+{
+    __shared__ SmallPlan sh;
+    const uint32_t t = threadIdx.x, e0 = 2 * t, e1 = 2 * t + 1;
+    const uint32_t ns = (uint32_t)b.n_src_ext, nd = (uint32_t)b.n_dst_ext, D = b.n_desc, N = (uint32_t)b.n_slices;
+    {   // extent prefixes of both sides, and in address order where a table goes by it
+        const uint64_t s0 = e0 < ns ? b.src_ext[e0].len : 0, s1 = e1 < ns ? b.src_ext[e1].len : 0;
+        const uint64_t d0 = e0 < nd ? b.dst_ext[e0].len : 0, d1 = e1 < nd ? b.dst_ext[e1].len : 0;
+        uint64_t o0 = 0, o1 = 0;
+        if (b.ord_pre) {
+            o0 = e0 < nd ? b.dst_ext[b.dst_order[e0]].len : 0;
+            o1 = e1 < nd ? b.dst_ext[b.dst_order[e1]].len : 0;
+        }
+        auto put = [&](uint64_t* out, uint64_t* in_lds, uint32_t n, uint64_t at, uint64_t v0, uint64_t v1) {
+            auto one = [&](uint32_t e, uint64_t v) {
+                if (e > n) return;
+                out[e] = v;
+                if (in_lds) in_lds[e] = v;
+            };
+            one(e0, at);
+            one(e1, at + v0);
+            if (e1 + 1 == n) one(n, at + v0 + v1);                   // (entry n otherwise comes from the thread behind)
+        };
+        put(b.src_pre, sh.src_pre, ns, pair_prefix(s0, s1, sh.wave_out), s0, s1);
+        put(b.dst_pre, sh.dst_pre, nd, pair_prefix(d0, d1, sh.wave_out), d0, d1);
+        if (b.ord_pre) put(b.ord_pre, nullptr, nd, pair_prefix(o0, o1, sh.wave_out), o0, o1);
+    }
+    __syncthreads();
+    {   // first slice and runs before every transfer
+        const TransferCounts counts{b.src_ptr, sh.src_pre, b.slice_bytes};
+        const uint64_t c0 = e0 < D ? counts(e0) : 0, c1 = e1 < D ? counts(e1) : 0;
+        const uint64_t at = pair_prefix(c0, c1, sh.wave_out);
+        auto one = [&](uint32_t j, uint64_t v) {
+            if (j > D) return;
+            b.first[j] = v & 0xFFFFFFFFu;
+            b.runs_before[j] = (uint32_t)(v >> 32);
+            sh.first[j] = (uint32_t)v;
+            sh.runs_before[j] = (uint32_t)(v >> 32);
+        };
+        one(e0, at);
+        one(e1, at + c0);
+        if (e1 + 1 == D) one(D, at + c0 + c1);
+    }
+    __syncthreads();
+    for (uint32_t i = t; i < N; i += kSmallThreads) {
+        uint32_t lo = 0, hi = D;                                      // last transfer that starts at or before slice i
+        while (hi - lo > 1) {
+            const uint32_t mid = lo + ((hi - lo) >> 1);
+            if (sh.first[mid] <= i) lo = mid; else hi = mid;
+        }
+        write_slice(b, i, lo, sh.first[lo], sh.runs_before[lo], sh.src_pre, sh.dst_pre);
+    }
+    if (t == 0) {
+        const uint32_t n_runs = sh.runs_before[D];
+        b.run_start[n_runs] = N;
+        b.plan->n_runs = n_runs;
+        b.plan->n_pending = N;
+        sh.ring.filled = 0;
+        sh.ring.taken = 0;
+    }
+    __syncthreads();
+    build_level_model(sh.lm, b, rp, kBindBuildTables);
+    if (t < 64) bind_chain<kWide>(b, rp, kBindBuildTables, sh.ring);
+    else if (t < 128) feed_records(b, kBindBuildTables, sh.lm, sh.ring, t - 64);
+    else build_tile_tables(b, t - 128, kSmallThreads - 128);
+    __syncthreads();
+    bind_emit(b, rp, 0, told, sh.er, t, kSmallThreads);
+}
+
 }  // namespace
+
+bool plan_is_small(const BatchDev& b)
+{
+    return b.n_src_ext <= kSmallExtents && b.n_dst_ext <= kSmallExtents && b.n_slices <= kSmallSlices &&
+           b.n_slices * (uint64_t)b.tiles_per_slice <= kSmallTiles;
+}
+
+hipError_t launch_plan_small(const BatchDev& b, const RailParams& rp, PlanState* told, hipStream_t s)
+{
+    const dim3 grid(1), block(kSmallThreads);
+    if (rp.n_rails <= 16)      hipLaunchKernelGGL(plan_small_kernel<16>, grid, block, 0, s, b, rp, told);
+    else if (rp.n_rails <= 32) hipLaunchKernelGGL(plan_small_kernel<32>, grid, block, 0, s, b, rp, told);
+    else                       hipLaunchKernelGGL(plan_small_kernel<64>, grid, block, 0, s, b, rp, told);
+    return hipGetLastError();
+}
 
 hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, PlanState* told, hipStream_t s)
 {

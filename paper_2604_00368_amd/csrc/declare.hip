@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(256) declare_verdict_kernel(uint64_t n_dst, ui
 }
 
 // ---- all of it in one workgroup ------------------------------------------------------------------
-constexpr uint32_t kSmallOrder = 4096, kSmallThreads = 1024, kSmallItems = kSmallOrder / kSmallThreads;
+constexpr uint32_t kSmallOrder = 4096, kSmallThreads = 1024;
 constexpr uint32_t kSmallBits = 13;              // a sorted word is (differing address bits) << kSmallBits | value
 
 // Exclusive scan of one value per thread over the workgroup.
@@ -113,40 +113,73 @@ __device__ __forceinline__ uint64_t small_scan(uint64_t v, uint64_t* wave_out, O
     return lane == 0 ? before : op(before, below);
 }
 
+// Bitonic sort of kItems * kSmallThreads words, of which the first n_pow2 count; thread t holds the words t, t +
+// kSmallThreads, ...  Partners up to 32 apart are lanes of one wavefront and those kSmallThreads and more apart are the thread's own,
+// so that only one step in four needs LDS and barriers (all steps through LDS: 27 instead of 25 us for the whole kernel
+// at 1252 extents).  The sorted words end in LDS.
+template <uint32_t kItems>
+__device__ __forceinline__ void small_sort(uint64_t (&w)[kItems], uint32_t n_pow2, uint64_t* word)
+{
+    const uint32_t t = threadIdx.x;
+    for (uint32_t k = 2; k <= n_pow2; k <<= 1)
+        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+            uint64_t other[kItems];
+            if (j >= kSmallThreads) {
+#pragma unroll
+                for (uint32_t e = 0; e < kItems; ++e)
+                    other[e] = (j / kSmallThreads) == 1 ? w[(e ^ 1) % kItems] : w[(e ^ 2) % kItems];
+            } else if (j >= 64) {
+#pragma unroll
+                for (uint32_t e = 0; e < kItems; ++e) word[e * kSmallThreads + t] = w[e];
+                __syncthreads();
+#pragma unroll
+                for (uint32_t e = 0; e < kItems; ++e) other[e] = word[e * kSmallThreads + (t ^ j)];
+                __syncthreads();
+            } else {
+#pragma unroll
+                for (uint32_t e = 0; e < kItems; ++e) other[e] = __shfl_xor((unsigned long long)w[e], (int)j, 64);
+            }
+#pragma unroll
+            for (uint32_t e = 0; e < kItems; ++e) {
+                const uint32_t p = e * kSmallThreads + t;
+                const bool take_least = ((p & j) == 0) == ((p & k) == 0);
+                const uint64_t least = w[e] < other[e] ? w[e] : other[e], most = w[e] < other[e] ? other[e] : w[e];
+                w[e] = take_least ? least : most;
+            }
+        }
+#pragma unroll
+    for (uint32_t e = 0; e < kItems; ++e) word[e * kSmallThreads + t] = w[e];
+    __syncthreads();
+}
+
+template <uint32_t kItems>
 __global__ void __launch_bounds__(kSmallThreads) declare_small_kernel(BatchDev b, uint32_t n, uint32_t n_pow2, int check, KeyBits bits,
                                                                       uint32_t* order, uint32_t* rank, uint32_t* told)
 {
-    __shared__ uint64_t word[kSmallOrder];
+    __shared__ uint64_t word[kItems * kSmallThreads];
     __shared__ uint64_t wave_out[kSmallThreads / 64];
     const uint32_t t = threadIdx.x;
     clear_tables(b, t, kSmallThreads);
     const uint32_t n_dst = (uint32_t)b.n_dst_ext;
     const uint64_t mask = (1ull << (bits.end - bits.begin)) - 1;
-    for (uint32_t v = t; v < n_pow2; v += kSmallThreads) {
-        uint64_t w = ~0ull;                                  // behind every extent
+    uint64_t w[kItems];
+#pragma unroll
+    for (uint32_t e = 0; e < kItems; ++e) {
+        const uint32_t v = e * kSmallThreads + t;
+        w[e] = ~0ull;                                        // behind every extent
         if (v < n) {
             const tent_extent x = v < n_dst ? b.dst_ext[v] : b.src_ext[v - n_dst];
-            w = (((b.seg_base[x.seg] + x.off) >> bits.begin & mask) << kSmallBits) | v;
+            w[e] = (((b.seg_base[x.seg] + x.off) >> bits.begin & mask) << kSmallBits) | v;
         }
-        word[v] = w;
     }
-    __syncthreads();
-    for (uint32_t k = 2; k <= n_pow2; k <<= 1)
-        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-            for (uint32_t p = t; p < n_pow2 / 2; p += kSmallThreads) {
-                const uint32_t lo = ((p & ~(j - 1)) << 1) | (p & (j - 1)), hi = lo | j;
-                const uint64_t x = word[lo], y = word[hi];
-                if ((x > y) == ((lo & k) == 0)) { word[lo] = y; word[hi] = x; }
-            }
-            __syncthreads();
-        }
-    // kSmallItems consecutive sorted extents per thread
-    uint64_t begin[kSmallItems], end_any[kSmallItems], end_dst[kSmallItems];
-    uint32_t value[kSmallItems];
+    small_sort<kItems>(w, n_pow2, word);
+    // kItems consecutive sorted extents per thread
+    uint64_t begin[kItems], end_any[kItems], end_dst[kItems];
+    uint32_t value[kItems];
     uint64_t far_any = 0, far_dst = 0, dsts = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < kSmallItems; ++i) {
-        const uint32_t p = t * kSmallItems + i;
+    for (uint32_t i = 0; i < kItems; ++i) {
+        const uint32_t p = t * kItems + i;
         value[i] = 0xFFFFFFFFu;
         begin[i] = end_any[i] = end_dst[i] = 0;
         if (p < n) {
@@ -167,7 +200,7 @@ __global__ void __launch_bounds__(kSmallThreads) declare_small_kernel(BatchDev b
     uint64_t pos = small_scan(dsts, wave_out, ScanSum{});
     bool bad = false;
 #pragma unroll
-    for (uint32_t i = 0; i < kSmallItems; ++i) {
+    for (uint32_t i = 0; i < kItems; ++i) {
         if (value[i] == 0xFFFFFFFFu) continue;
         const bool is_dst = value[i] < n_dst;
         bad |= begin[i] < (is_dst ? far_any : far_dst);
@@ -256,8 +289,14 @@ hipError_t launch_declare(const BatchDev& b, bool order, bool check, KeyBits bit
     if (is_small(n, bits)) {
         uint32_t n_pow2 = 2;
         while (n_pow2 < n) n_pow2 <<= 1;
-        hipLaunchKernelGGL(declare_small_kernel, dim3(1), dim3(kSmallThreads), 0, s, b, (uint32_t)n, n_pow2, check ? 1 : 0, bits,
-                           order_out, rank_out, overlap_told);
+        const dim3 one(1), block(kSmallThreads);
+        const int test = check ? 1 : 0;
+        if (n <= kSmallThreads)
+            hipLaunchKernelGGL(declare_small_kernel<1>, one, block, 0, s, b, (uint32_t)n, n_pow2, test, bits, order_out, rank_out, overlap_told);
+        else if (n <= 2 * kSmallThreads)
+            hipLaunchKernelGGL(declare_small_kernel<2>, one, block, 0, s, b, (uint32_t)n, n_pow2, test, bits, order_out, rank_out, overlap_told);
+        else
+            hipLaunchKernelGGL(declare_small_kernel<4>, one, block, 0, s, b, (uint32_t)n, n_pow2, test, bits, order_out, rank_out, overlap_told);
         return hipGetLastError();
     }
     OrderWorkspace w;

@@ -177,7 +177,7 @@ __global__ void __launch_bounds__(256) dispatch_chain_tables_kernel(BatchDev b, 
         if (threadIdx.x < 64) dispatch_chain<kWide>(b, rp, dp);
         return;
     }
-    build_tile_tables(b, blockIdx.x - 1, gridDim.x - 1);
+    build_tile_tables_in(b, blockIdx.x - 1, gridDim.x - 1);
 }
 
 // ---- emit: one lane per pending position ---------------------------------------------------------

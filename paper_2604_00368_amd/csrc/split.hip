@@ -5,7 +5,7 @@
 // and keeps that absolute offset so it can be written straight to its destination.
 #include "finish.h"
 #include "scan.h"
-#include "tile_tables.h"
+#include "slices.h"
 
 namespace tent {
 
@@ -33,37 +33,8 @@ hipError_t launch_extent_scans(const BatchDev& b, hipStream_t s)
 }
 
 // ---- S2: slices and runs per transfer -----------------------------------------------------------
-// A transfer of len bytes has ceil(len / S) slices, all of S bytes but the last.  Maximal runs of equal-length
-// slices (bind_runs.hip) therefore start in at most two places per transfer: at its first slice, unless that is as long as the
-// slice before it, and at its last one, if that is short and not also the first.  One scan over the transfers yields the
-// first slice of every transfer (low half of the scanned word) and the runs that start before it (high half).
-struct TransferShape {
-    uint64_t slices, last;         // slices; length of the last one
-    bool new_run, short_tail;      // runs that start at the first slice, at the last one
-    __device__ TransferShape(const uint32_t* ptr, const uint64_t* pre, uint64_t S, uint64_t j)
-    {
-        const uint64_t at = pre[ptr[j]], len = pre[ptr[j + 1]] - at;
-        slices = (len + S - 1) / S;
-        last = len - (slices - 1) * S;
-        short_tail = slices > 1 && last != S;
-        new_run = true;
-        if (j > 0) {
-            const uint64_t len_before = at - pre[ptr[j - 1]];
-            const uint64_t last_before = len_before - ((len_before + S - 1) / S - 1) * S;
-            new_run = last_before != (len < S ? len : S);
-        }
-    }
-};
-struct TransferCounts {
-    const uint32_t* ptr;
-    const uint64_t* pre;
-    uint64_t S;
-    __device__ uint64_t operator()(uint64_t j) const
-    {
-        const TransferShape t(ptr, pre, S, j);
-        return ((uint64_t)((t.new_run ? 1u : 0u) + (t.short_tail ? 1u : 0u)) << 32) | t.slices;
-    }
-};
+// (TransferShape in slices.h.)  One scan over the transfers yields the first slice of every transfer (low half of the
+// scanned word) and the runs that start before it (high half).
 struct StoreCounts {
     uint64_t* first;
     uint32_t* runs;
@@ -88,26 +59,7 @@ __global__ void __launch_bounds__(256) expand_kernel(BatchDev b)
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         // owning transfer: transfers without slices cannot occur (every transfer has len > 0)
         const uint32_t j = (uint32_t)last_not_above(b.first, 0, b.n_desc, i);
-        const uint32_t slo = b.src_ptr[j], shi = b.src_ptr[j + 1];
-        const uint32_t dlo = b.dst_ptr[j], dhi = b.dst_ptr[j + 1];
-        const uint64_t len_j = b.src_pre[shi] - b.src_pre[slo];
-        const uint64_t off = (i - b.first[j]) * b.slice_bytes;
-        const uint64_t rest = len_j - off;
-        b.s_desc[i] = j;
-        b.s_off[i] = off;
-        b.s_pos[i] = b.src_pre[slo] + off;
-        b.s_len[i] = (uint32_t)(rest < b.slice_bytes ? rest : b.slice_bytes);
-        b.s_src_e0[i] = (uint32_t)last_not_above(b.src_pre, slo, shi, b.src_pre[slo] + off);
-        b.s_dst_e0[i] = (uint32_t)last_not_above(b.dst_pre, dlo, dhi, b.dst_pre[dlo] + off);
-        b.s_rail[i] = 0xFFFFFFFFu;
-        b.s_stage_off[i] = 0;
-        b.s_state[i] = TENT_SLICE_PENDING;
-        // the run table: every run is entered by the slice it starts at
-        const TransferShape t(b.src_ptr, b.src_pre, b.slice_bytes, j);
-        const uint32_t run = b.runs_before[j] + (t.new_run ? 1u : 0u) - 1u;      // of the transfer's first slice
-        const bool tail = t.short_tail && rest <= b.slice_bytes;
-        b.s_run[i] = run + (tail ? 1u : 0u);
-        if ((off == 0 && t.new_run) || tail) b.run_start[run + (tail ? 1u : 0u)] = (uint32_t)i;
+        write_slice(b, i, j, b.first[j], b.runs_before[j], b.src_pre, b.dst_pre);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         const uint32_t n_runs = b.runs_before[b.n_desc];
@@ -127,7 +79,7 @@ hipError_t launch_expand(const BatchDev& b, hipStream_t s)
 
 // ---- S3b: tile tables ------------------------------------------------------------------------
 // The builders are in tile_tables.h.
-__global__ void __launch_bounds__(256) tile_tables_kernel(BatchDev b) { build_tile_tables(b, blockIdx.x, gridDim.x); }
+__global__ void __launch_bounds__(256) tile_tables_kernel(BatchDev b) { build_tile_tables_in(b, blockIdx.x, gridDim.x); }
 
 hipError_t launch_tile_tables(const BatchDev& b, hipStream_t s)
 {

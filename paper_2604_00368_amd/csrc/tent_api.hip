@@ -1032,7 +1032,12 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
     bool serial = (ctx->cfg.flags & TENT_FLAG_SERIAL_BINDING) != 0;
     for (uint32_t r = 0; r < n_rails; ++r)
         if (((rp.admitted >> r) & 1) && rp.c1[r] == 0) serial = true;
-    if (!replan) {
+    const bool small = !replan && !serial && plan_is_small(d);
+    if (small) {
+        // one launch does it all and counts as binding (so does a caller that asks for the time of every stage see it)
+        StageTimer t(ctx, TENT_T_BIND, s);
+        HIP_TRY(launch_plan_small(d, rp, info ? ctx->host_plan : nullptr, s));
+    } else if (!replan) {
         {
             StageTimer t(ctx, TENT_T_EXTENT_SCAN, s);
             HIP_TRY(launch_extent_scans(d, s));
@@ -1058,7 +1063,7 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
         HIP_TRY(launch_rotate(d, rot, s));
         mode |= kBindAfterRotation;
     }
-    {
+    if (!small) {
         StageTimer t(ctx, TENT_T_BIND, s);
         if (serial) HIP_TRY(launch_bind_serial(d, rp, mode, s));
         else        HIP_TRY(launch_bind_runs(d, rp, mode | (replan ? 0 : kBindBuildTables), info ? ctx->host_plan : nullptr, s));

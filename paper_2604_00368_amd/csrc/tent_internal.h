@@ -219,6 +219,9 @@ hipError_t launch_compact(const BatchDev& b, hipStream_t s);
 hipError_t launch_bind_serial(const BatchDev& b, const RailParams& rp, int mode, hipStream_t s);
 // `told` (host memory the device can write, or null): where the plan's totals go as well
 hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, PlanState* told, hipStream_t s);
+// A first plan in one workgroup, for batches small enough.
+bool plan_is_small(const BatchDev& b);
+hipError_t launch_plan_small(const BatchDev& b, const RailParams& rp, PlanState* told, hipStream_t s);
 hipError_t launch_rotate(const BatchDev& b, const RotateParams& rot, hipStream_t s);
 hipError_t launch_fail(const BatchDev& b, const FailParams& fp, PlanState* told, hipStream_t s);
 hipError_t launch_bounded_prepare(const BatchDev& b, uint64_t payload, uint64_t chunk_bytes, uint32_t n_chunks,

@@ -1,8 +1,8 @@
 // Tile tables of the copy kernels (slice decomposition of Section 4.2 carried down to tiles of
 // 1-4 KiB): for every tile the device address of its bytes on the paged side, so that the copy
 // kernels reach their bytes with one table load.  The builders are device functions over a
-// virtual grid (block `vb` of `nb`, any block size), because they run in two places: as kernels of
-// their own, and in the spare workgroups of the launch whose first workgroup walks the binding
+// range of threads (thread `at` of `stride`), because they run in several places: as kernels of
+// their own, in the workgroup that plans a small batch alone, and in the spare workgroups of the launch whose first workgroup walks the binding
 // chain -- the chain is one wavefront and leaves the rest of the device idle, and the tables
 // depend on the slice table only, not on the binding.
 #pragma once
@@ -23,11 +23,10 @@ __device__ __forceinline__ uint64_t last_not_above(const uint64_t* a, uint64_t l
 
 // Geometry whose tiles may cross extent boundaries.  One thread per (slice, tile): locate the extent
 // that holds the tile's first byte on either side; tiles that cross a boundary are flagged.
-__device__ __forceinline__ void slice_tile_tables(const BatchDev& b, uint64_t vb, uint64_t nb)
+__device__ __forceinline__ void slice_tile_tables(const BatchDev& b, uint64_t at, uint64_t stride)
 {
     const uint64_t n = b.n_slices * (uint64_t)b.tiles_per_slice;
-    const uint64_t stride = nb * blockDim.x;
-    for (uint64_t q = vb * blockDim.x + threadIdx.x; q < n; q += stride) {
+    for (uint64_t q = at; q < n; q += stride) {
         const uint64_t i = q / b.tiles_per_slice;
         const uint64_t x = (q - i * b.tiles_per_slice) * b.tile_bytes;      // byte offset inside the slice
         const uint32_t len = b.s_len[i];
@@ -65,13 +64,12 @@ __device__ __forceinline__ void slice_tile_tables(const BatchDev& b, uint64_t vb
 // the slice table already holds the first source and destination extent of the slice, so each side
 // costs a search over the few extents of one slice; the tile's place in the destination order
 // follows from the rank of its extent in that order and the prefix of the extent lengths.
-__device__ __forceinline__ void ordered_tile_tables(const BatchDev& b, uint64_t vb, uint64_t nb)
+__device__ __forceinline__ void ordered_tile_tables(const BatchDev& b, uint64_t at, uint64_t stride)
 {
     const uint32_t tps = b.tiles_per_slice;
     const uint32_t tile = b.tile_bytes;
     const uint64_t n = b.n_slices * (uint64_t)tps;
-    const uint64_t stride = nb * blockDim.x;
-    for (uint64_t idx = vb * blockDim.x + threadIdx.x; idx < n; idx += stride) {
+    for (uint64_t idx = at; idx < n; idx += stride) {
         const uint64_t i = idx / tps;
         const uint64_t x = (idx - i * tps) * tile;                 // byte offset inside the slice
         if (x >= b.s_len[i]) continue;
@@ -111,14 +109,20 @@ __device__ __forceinline__ void ordered_tile_tables(const BatchDev& b, uint64_t 
     }
 }
 
-// All tile tables of a batch, whichever its geometry.
-__device__ __forceinline__ void build_tile_tables(const BatchDev& b, uint64_t vb, uint64_t nb)
+// All tile tables of a batch, whichever its geometry: thread `at` of `stride`.
+__device__ __forceinline__ void build_tile_tables(const BatchDev& b, uint64_t at, uint64_t stride)
 {
     if (b.n_sc_tiles == 0) {
-        slice_tile_tables(b, vb, nb);
+        slice_tile_tables(b, at, stride);
     } else {
-        ordered_tile_tables(b, vb, nb);
+        ordered_tile_tables(b, at, stride);
     }
+}
+
+// ... by the workgroups of a launch, workgroup vb of nb.
+__device__ __forceinline__ void build_tile_tables_in(const BatchDev& b, uint64_t vb, uint64_t nb)
+{
+    build_tile_tables(b, vb * blockDim.x + threadIdx.x, nb * blockDim.x);
 }
 
 // Workgroups of 256 lanes that the table builders are launched with.

@@ -97,3 +97,17 @@ def test_run_shapes(H, oracle, case):
             "one_long_run": np.array([S * 60000 + 7])}[case]
     for rails in (W.make_rails([50000] * 8 + [400000]), W.make_rails([12000, 31000, 77000], queued=[0, 40000, 9])):
         check_binding(H, oracle, transfers(lens, S, rails))
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 2046, 2047, 2048, 2049])
+@pytest.mark.parametrize("what", ["transfers", "slices", "tiles"])
+def test_plan_in_one_workgroup_and_beyond(H, oracle, n, what):
+    # one workgroup plans up to 2048 extents a side, 2048 slices and 16384 tiles
+    g = np.random.Generator(np.random.PCG64([n, len(what)]))
+    rails = W.make_rails([25000, 50000, 40000, 10000], queued=g.integers(0, 5000, size=4))
+    if what == "transfers":
+        check_binding(H, oracle, transfers(g.integers(1, 900, size=n), 1 << 20, rails))      # a slice each
+    elif what == "slices":
+        check_binding(H, oracle, transfers([700 * (n // 2) + 1] * (2 if n > 1 else 1), 700, rails))
+    else:
+        check_binding(H, oracle, transfers([8 * 1024 * n - 1024 * (n > 2)], 8 * 1024, rails))
