@@ -94,8 +94,10 @@ __global__ void __launch_bounds__(256) declare_verdict_kernel(uint64_t n_dst, ui
     if (bad) *told = 1;
 }
 
+constexpr uint32_t kSmallOrder = 4096;           // extents one workgroup puts in order
+
 // ---- all of it in one workgroup ------------------------------------------------------------------
-constexpr uint32_t kSmallOrder = 4096, kSmallThreads = 1024;
+constexpr uint32_t kSmallThreads = 1024;
 constexpr uint32_t kSmallBits = 13;              // a sorted word is (differing address bits) << kSmallBits | value
 
 // Exclusive scan of one value per thread over the workgroup.

@@ -48,6 +48,8 @@ struct Batch {
     hipStream_t exec_stream = nullptr;
     bool prep_recorded = false;
     bool done_recorded = false;
+    hipEvent_t done_at = nullptr;            // the event that ends the last execute: its stream's mark, or done_event
+    bool may_replan = false;                 // slices may be left over by the next execute: the simulator or a dispatch ran since the plan
     // The declaration's device work (descriptor upload, address sort, overlap check) runs on the
     // context's own stream and ends at decl_event; `verdict` (pinned host memory) then holds the
     // overlap check's result.
@@ -142,9 +144,9 @@ bool capturing(hipStream_t s)
 
 // Remember that work of the batch was just enqueued on `s` (nothing is recorded into a stream that is
 // being captured into a graph: such work is only known to be over when the device is idle).
-void note_stream(Batch& b, hipStream_t s)
+StreamMark* note_stream(Batch& b, hipStream_t s)
 {
-    if (capturing(s)) { b.marks_lost = true; return; }
+    if (capturing(s)) { b.marks_lost = true; return nullptr; }
     StreamMark* slot = nullptr;
     for (StreamMark& m : b.marks) {
         if (m.used && m.stream == s) { slot = &m; break; }
@@ -153,18 +155,20 @@ void note_stream(Batch& b, hipStream_t s)
     if (!slot || !slot->event || hipEventRecord(slot->event, s) != hipSuccess) {
         (void)hipGetLastError();
         b.marks_lost = true;
-        return;
+        return nullptr;
     }
     slot->stream = s;
     slot->used = true;
+    return slot;
 }
 
 // Records the batch's stream use when an entry point returns, whichever way it returns.
 struct StreamNote {
     Batch& b;
     hipStream_t s;
+    bool noted = false;          // an event recorded by the call itself covers its work
     StreamNote(Batch& batch, hipStream_t stream) : b(batch), s(stream) {}
-    ~StreamNote() { if (b.alive) note_stream(b, s); }
+    ~StreamNote() { if (b.alive && !noted) (void)note_stream(b, s); }
 };
 
 // Host-side wait for everything that was enqueued for the batch.
@@ -179,12 +183,15 @@ void wait_batch_idle(Batch& b)
 
 bool init_slot(Batch& b)
 {
-    bool ok = hipEventCreateWithFlags(&b.prep_event, hipEventDisableTiming) == hipSuccess &&
-              hipEventCreateWithFlags(&b.done_event, hipEventDisableTiming) == hipSuccess &&
+    // Events that order device work, or tell the host only that work is over, need no release to the whole system: each of those
+    // is a bubble of 6 us behind the launch it is recorded after.  The declaration's event releases a verdict in host memory.
+    constexpr unsigned kOrderOnly = hipEventDisableTiming | hipEventDisableSystemFence;
+    bool ok = hipEventCreateWithFlags(&b.prep_event, kOrderOnly) == hipSuccess &&
+              hipEventCreateWithFlags(&b.done_event, kOrderOnly) == hipSuccess &&
               hipEventCreateWithFlags(&b.decl_event, hipEventDisableTiming) == hipSuccess &&
               hipHostMalloc((void**)&b.verdict, 64, hipHostMallocDefault) == hipSuccess;
     for (StreamMark& m : b.marks)
-        ok = ok && hipEventCreateWithFlags(&m.event, hipEventDisableTiming) == hipSuccess;
+        ok = ok && hipEventCreateWithFlags(&m.event, kOrderOnly) == hipSuccess;
     if (!ok) (void)hipGetLastError();
     return ok;
 }
@@ -516,8 +523,11 @@ struct StageTimer {
 // only has to come after the execute's bookkeeping.
 hipError_t order_after_execute_bookkeeping(const Batch& b, hipStream_t s)
 {
-    if (!b.prep_recorded || s == b.exec_stream) return hipSuccess;
-    return hipStreamWaitEvent(s, b.prep_event, 0);
+    if (s == b.exec_stream) return hipSuccess;
+    if (b.prep_recorded) return hipStreamWaitEvent(s, b.prep_event, 0);
+    // an execute that left nothing over records its end only (every event is a bubble on the stream)
+    if (b.done_recorded && !capturing(s)) return hipStreamWaitEvent(s, b.done_at, 0);
+    return hipSuccess;
 }
 
 // Marks the end of an execute's bookkeeping on its stream.  Nothing is recorded into a stream that is
@@ -526,7 +536,7 @@ hipError_t record_execute_bookkeeping(Batch& b, hipStream_t s)
 {
     b.prep_recorded = false;
     b.done_recorded = false;
-    if (capturing(s)) return hipSuccess;
+    if (!b.may_replan || capturing(s)) return hipSuccess;
     hipError_t e = hipEventRecord(b.prep_event, s);
     if (e != hipSuccess) return e;
     b.exec_stream = s;
@@ -535,12 +545,19 @@ hipError_t record_execute_bookkeeping(Batch& b, hipStream_t s)
 }
 
 // Marks the end of an execute's copies on its stream: what batch-level completion waits for.
-hipError_t record_execute_done(Batch& b, hipStream_t s)
+// It is the stream's mark as well (a later call on the same stream moves it on, which only makes it later).
+hipError_t record_execute_done(Batch& b, hipStream_t s, StreamNote& note)
 {
     b.done_recorded = false;
     if (capturing(s)) return hipSuccess;
-    hipError_t e = hipEventRecord(b.done_event, s);
-    if (e != hipSuccess) return e;
+    if (const StreamMark* mark = note_stream(b, s)) {
+        note.noted = true;
+        b.done_at = mark->event;
+    } else {
+        hipError_t e = hipEventRecord(b.done_event, s);
+        if (e != hipSuccess) return e;
+        b.done_at = b.done_event;
+    }
     b.exec_stream = s;
     b.done_recorded = true;
     return hipSuccess;
@@ -1069,6 +1086,7 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
         else        HIP_TRY(launch_bind_runs(d, rp, mode | (replan ? 0 : kBindBuildTables), info ? ctx->host_plan : nullptr, s));
     }
     b->planned = true;
+    b->may_replan = false;                                    // every pending slice is BOUND now
     b->bound_hint = b->dev.n_slices;
     b->tile_hint = ~0ull;
     b->last_rails = rp;
@@ -1174,6 +1192,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
         HIP_TRY(launch_dispatch(d, rp, dp, first_plan, info ? ctx->host_plan : nullptr, s));
     }
     b->planned = true;
+    b->may_replan = true;                                     // deferred transfers stay pending
     b->bound_hint = b->dev.n_slices;
     b->tile_hint = ~0ull;
     b->last_rails = rp;
@@ -1230,6 +1249,7 @@ int tent_sim_advance(tent_ctx* ctx, tent_batch_t batch, const uint64_t* budget_b
         bp.budget[d] = budget_bytes[d];
     }
     StreamNote note(*b, s);
+    b->may_replan = true;
     HIP_TRY(launch_retire(b->dev, bp, n_done ? ctx->host_plan : nullptr, s));
     // What stays BOUND on rail d fits in budget_d - queued_d bytes, which bounds the tiles the next execute
     // copies without asking the device (slices of a tiled batch are whole tiles).
@@ -1264,6 +1284,7 @@ int tent_sim_fail(tent_ctx* ctx, tent_batch_t batch, const uint8_t* rail_failed,
     hipStream_t s = static_cast<hipStream_t>(stream);
     StreamNote note(*b, s);
     if (any) {
+        b->may_replan = true;
         HIP_TRY(launch_fail(b->dev, fp, failed_per_rail ? ctx->host_plan : nullptr, s));
         b->has_retry = true;
     }
@@ -1396,7 +1417,7 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
             StageTimer t(ctx, TENT_T_GATHER, s);
             e = launch_copy_one_pass(b->dev, compact, max_tiles, s);
             if (e != hipSuccess) return e;
-            return record_execute_done(*b, s);
+            return record_execute_done(*b, s, note);
         }
         {
             StageTimer t(ctx, TENT_T_GATHER, s);
@@ -1410,7 +1431,7 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
                 : b->dev.n_sc_tiles ? launch_copy_ordered(b->dev, false, s) : launch_copy(b->dev, false, s);
         }
         if (e != hipSuccess) return e;
-        return record_execute_done(*b, s);
+        return record_execute_done(*b, s, note);
     };
     b->has_done = true;
     b->bound_hint = 0;
@@ -1506,7 +1527,7 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     b->prep_recorded = false;                                 // the bounded execute offers no overlap with a re-plan
     b->has_done = true;
     b->bound_hint = 0;
-    HIP_TRY(record_execute_done(*b, s));
+    HIP_TRY(record_execute_done(*b, s, note));
     return TENT_OK;
 }
 
@@ -1522,7 +1543,7 @@ int tent_poll(tent_ctx* ctx, tent_batch_t batch, uint64_t* remaining, void* stre
     hipStream_t s = static_cast<hipStream_t>(stream);
     // slices are marked DONE ahead of their copies: completion is only reported once the last
     // execute's copies have ended, whichever stream the caller polls on
-    if (b->done_recorded && s != b->exec_stream) HIP_TRY(hipStreamWaitEvent(s, b->done_event, 0));
+    if (b->done_recorded && s != b->exec_stream) HIP_TRY(hipStreamWaitEvent(s, b->done_at, 0));
     HIP_TRY(launch_count_remaining(b->dev, ctx->host_plan, s));
     HIP_TRY(hipStreamSynchronize(s));
     *remaining = ctx->host_plan->n_remaining;
@@ -1540,7 +1561,7 @@ int tent_reset(tent_ctx* ctx, tent_batch_t batch, void* stream)
     if (b->planned) {
         StreamNote note(*b, s);
         // the reset must not overtake the copies of an execute that runs on another stream
-        if (b->done_recorded && s != b->exec_stream && !capturing(s)) HIP_TRY(hipStreamWaitEvent(s, b->done_event, 0));
+        if (b->done_recorded && s != b->exec_stream && !capturing(s)) HIP_TRY(hipStreamWaitEvent(s, b->done_at, 0));
         HIP_TRY(launch_reset(b->dev, s));
     }
     b->planned = false;
