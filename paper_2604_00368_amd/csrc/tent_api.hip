@@ -43,10 +43,10 @@ struct Batch {
     uint64_t max_req_slices = 0; // most slices any one transfer has
     RailParams last_rails{};     // telemetry of the last plan (for the rail simulator)
     uint32_t last_lat_ns[TENT_MAX_RAILS] = {};
-    // The last execute's bookkeeping (staging addresses, tile lists, DONE marks) ends at prep_event on
-    // exec_stream; its copies, which follow, read none of what a re-plan writes, and end at done_event.
+    // The last execute's bookkeeping (staging addresses, tile lists, DONE marks) ends on exec_stream; its
+    // copies, which follow, read none of what a re-plan writes, and end at done_at.
     hipStream_t exec_stream = nullptr;
-    bool prep_recorded = false;
+    hipEvent_t replan_at = nullptr;          // what a re-plan on another stream waits for: prep_event, done_at, or nothing
     bool done_recorded = false;
     hipEvent_t done_at = nullptr;            // the event that ends the last execute: its stream's mark, or done_event
     bool may_replan = false;                 // slices may be left over by the next execute: the simulator or a dispatch ran since the plan
@@ -183,15 +183,14 @@ void wait_batch_idle(Batch& b)
 
 bool init_slot(Batch& b)
 {
-    // Events that order device work, or tell the host only that work is over, need no release to the whole system: each of those
-    // is a bubble of 6 us behind the launch it is recorded after.  The declaration's event releases a verdict in host memory.
-    constexpr unsigned kOrderOnly = hipEventDisableTiming | hipEventDisableSystemFence;
-    bool ok = hipEventCreateWithFlags(&b.prep_event, kOrderOnly) == hipSuccess &&
-              hipEventCreateWithFlags(&b.done_event, kOrderOnly) == hipSuccess &&
+    // Every one keeps its release to the whole system: the host waits for the marks before it frees or reuses what
+    // the work wrote, and an event without that release (1.2 us cheaper) promises such a wait nothing.
+    bool ok = hipEventCreateWithFlags(&b.prep_event, hipEventDisableTiming) == hipSuccess &&
+              hipEventCreateWithFlags(&b.done_event, hipEventDisableTiming) == hipSuccess &&
               hipEventCreateWithFlags(&b.decl_event, hipEventDisableTiming) == hipSuccess &&
               hipHostMalloc((void**)&b.verdict, 64, hipHostMallocDefault) == hipSuccess;
     for (StreamMark& m : b.marks)
-        ok = ok && hipEventCreateWithFlags(&m.event, kOrderOnly) == hipSuccess;
+        ok = ok && hipEventCreateWithFlags(&m.event, hipEventDisableTiming) == hipSuccess;
     if (!ok) (void)hipGetLastError();
     return ok;
 }
@@ -247,7 +246,8 @@ void free_batch(tent_ctx* ctx, Batch& b)
     b.block_bytes = 0;
     b.alive = false;
     b.decl_pending = false;
-    b.prep_recorded = b.done_recorded = false;
+    b.replan_at = nullptr;
+    b.done_recorded = false;
     b.marks_lost = false;
     for (StreamMark& m : b.marks) { m.used = false; m.stream = nullptr; }
     b.dev = BatchDev{};
@@ -520,27 +520,25 @@ struct StageTimer {
 };
 
 // A re-plan enqueued on another stream than the last execute's may overlap that execute's copies: it
-// only has to come after the execute's bookkeeping.
+// only has to come after the execute's bookkeeping.  An execute that could leave nothing over records no
+// event for that (each is a bubble of 6 us on the stream): a plan on another stream waits for its end.
 hipError_t order_after_execute_bookkeeping(const Batch& b, hipStream_t s)
 {
-    if (s == b.exec_stream) return hipSuccess;
-    if (b.prep_recorded) return hipStreamWaitEvent(s, b.prep_event, 0);
-    // an execute that left nothing over records its end only (every event is a bubble on the stream)
-    if (b.done_recorded && !capturing(s)) return hipStreamWaitEvent(s, b.done_at, 0);
-    return hipSuccess;
+    if (!b.replan_at || s == b.exec_stream) return hipSuccess;
+    return hipStreamWaitEvent(s, b.replan_at, 0);
 }
 
 // Marks the end of an execute's bookkeeping on its stream.  Nothing is recorded into a stream that is
 // being captured into a graph; a graph holds its launches in stream order anyway.
 hipError_t record_execute_bookkeeping(Batch& b, hipStream_t s)
 {
-    b.prep_recorded = false;
+    b.replan_at = nullptr;
     b.done_recorded = false;
     if (!b.may_replan || capturing(s)) return hipSuccess;
     hipError_t e = hipEventRecord(b.prep_event, s);
     if (e != hipSuccess) return e;
     b.exec_stream = s;
-    b.prep_recorded = true;
+    b.replan_at = b.prep_event;
     return hipSuccess;
 }
 
@@ -1400,7 +1398,7 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
     // The copies below are driven by the tables that the bookkeeping writes and read no slice state, so the slices
     // are marked DONE ahead of them: in stream order nothing changes, and the next re-plan, if it
     // is enqueued on another stream, can run beside the copies.  tent_poll, on whatever stream, waits
-    // for the end of the copies (done_event), so a slice is never reported complete while its bytes move.
+    // for the end of the copies (done_at), so a slice is never reported complete while its bytes move.
     uint8_t* arena = static_cast<uint8_t*>(ctx->cfg.staging_arena);
     if (b->dev.one_pass) {
         HIP_TRY(launch_stage_and_mark(b->dev, arena, compact, max_tiles, s));
@@ -1410,6 +1408,11 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
     }
     // From here on a failure would leave slices marked DONE whose bytes were never moved: the batch
     // is then flagged, and every call but tent_reset and tent_release refuses it.
+    auto record_end = [&]() -> hipError_t {
+        hipError_t e = record_execute_done(*b, s, note);
+        if (e == hipSuccess && b->done_recorded && !b->replan_at) b->replan_at = b->done_at;
+        return e;
+    };
     auto copies = [&]() -> hipError_t {
         hipError_t e = record_execute_bookkeeping(*b, s);
         if (e != hipSuccess) return e;
@@ -1417,7 +1420,7 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
             StageTimer t(ctx, TENT_T_GATHER, s);
             e = launch_copy_one_pass(b->dev, compact, max_tiles, s);
             if (e != hipSuccess) return e;
-            return record_execute_done(*b, s, note);
+            return record_end();
         }
         {
             StageTimer t(ctx, TENT_T_GATHER, s);
@@ -1431,7 +1434,7 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
                 : b->dev.n_sc_tiles ? launch_copy_ordered(b->dev, false, s) : launch_copy(b->dev, false, s);
         }
         if (e != hipSuccess) return e;
-        return record_execute_done(*b, s, note);
+        return record_end();
     };
     b->has_done = true;
     b->bound_hint = 0;
@@ -1524,7 +1527,7 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
         if (n_chunks >= 2) HIP_TRY(hipStreamWaitEvent(s, ctx->sync_events[2 * (n_chunks - 2) + 1], 0));
     }
     HIP_TRY(launch_mark_done_bounded(d, s));
-    b->prep_recorded = false;                                 // the bounded execute offers no overlap with a re-plan
+    b->replan_at = nullptr;                                   // the bounded execute offers no overlap with a re-plan
     b->has_done = true;
     b->bound_hint = 0;
     HIP_TRY(record_execute_done(*b, s, note));

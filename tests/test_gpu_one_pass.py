@@ -121,3 +121,37 @@ def test_arena_inside_a_segment(H, oracle):
     assert np.array_equal(dst.cpu().numpy(), want)
     assert np.array_equal(whole[at:at + w.staging_bytes].cpu().numpy(), staging)
     T.tent_destroy(ctx)
+
+
+@pytest.mark.parametrize("partial", [False, True])
+def test_a_replan_on_another_stream_than_the_execute(H, partial):
+    """After an execute that leaves slices over and after one that cannot, a plan on another stream comes after the
+    bookkeeping: it finds exactly what is left, and the batch ends as on one stream."""
+    from paper_2604_00368_amd import binding as T
+    w = LAYOUTS["tiles_4KiB"]()
+    src, dst0 = W.fill_numpy(w, 0), W.fill_numpy(w, 1)
+    R = w.rails.shape[0]
+    results = []
+    for two_streams in (False, True):
+        with H.Engine(w, src, dst0) as eng:
+            eng.declare()
+            torch.cuda.synchronize(eng.dev)
+            side = torch.cuda.Stream(eng.dev) if two_streams else None
+            s = side.cuda_stream if two_streams else eng.stream
+            st, info = T.tent_plan(eng.ctx, eng.batch, w.rails, stream=s)
+            assert st == 0
+            if partial:
+                share = np.array(list(info.rail_bytes)[:R], dtype=np.uint64) // np.uint64(2)
+                T.tent_sim_advance(eng.ctx, eng.batch, w.rails["queued_bytes"] + share, s)
+            T.tent_execute(eng.ctx, eng.batch, s)
+            st, info = eng.plan()                                # on the engine's stream
+            left = (st, info.n_slices)
+            if two_streams:
+                side.synchronize()
+            eng.execute()
+            assert T.tent_poll(eng.ctx, eng.batch, eng.stream) == 0
+            results.append((left, eng.dst.cpu().numpy(), eng.table()))
+    assert (results[0][0][1] > 0) == partial
+    assert results[0][0] == results[1][0]
+    assert np.array_equal(results[0][1], results[1][1])
+    assert np.array_equal(results[0][2], results[1][2])
