@@ -40,10 +40,13 @@ ALL_LEGS = ("configs", "declare", "concurrent", "feedback", "recovery", "replann
 # plain-copy calibration dispatch of the same run; summaries under profiles/).  The figures belong
 # to one version of the copy kernels and of the kernels that build their tables: when one of those
 # sources changes they are reported as null until the counters are taken again.
-PMC_SOURCES = ("copy.hip", "copy_generic.h", "split.hip", "tile_tables.h")
+PMC_SOURCES = ("copy.hip", "copy_generic.h", "split.hip", "tile_tables.h", "slices.h")
 PMC_TRAFFIC = {
-    "copy_sources_sha256": "40cb27ddb00ff4ebb63f4a50cccb998e176129192c040f14719fefbf480c15aa",
+    "copy_sources_sha256": "3b82e6e112b8c0fa411835995dde2e9fa6ff64f9b8949cd724c5184d1445dd9c",
     # bytes read + bytes written per launch (profiles/copy_kernels_hbm_traffic.txt)
+    "kv_migration": 64530284058,
+    "rl_params": 45733204631,
+    "many_small_x6": 49626857174,
 }
 
 
