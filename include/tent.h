@@ -59,7 +59,7 @@ typedef enum {
 } tent_status;
 
 enum { TENT_MAX_RAILS = 64 };
-enum { TENT_STATIC_WORKSPACE_BYTES = 64 << 20 };   /* static device array behind tent_declare_static, per GPU */
+enum { TENT_STATIC_WORKSPACE_BYTES = 64 << 20 };   /* limit of tent_declare_static, per GPU */
 
 /* tent_config.flags */
 enum {
@@ -218,10 +218,10 @@ int tent_declare(tent_ctx *ctx, uint32_t n_desc,
  * serving loops, harnesses that ban allocation, set-up phases of graph-driven pipelines).  Same
  * arguments, same checks and the same batch as tent_declare, but the batch's device tables and the
  * workspace of the address sort are carved from a static device array of the library
- * (TENT_STATIC_WORKSPACE_BYTES = 64 MiB per GPU, held by every GPU the library runs on until the
- * process ends) and the call allocates nothing, neither on the device nor on the host; host arrays
+ * (room for batches that count TENT_STATIC_WORKSPACE_BYTES = 64 MiB and 20 MiB more for how their tables are laid
+ * out, per GPU, held by every GPU the library runs on until the process ends) and the call allocates nothing, neither on the device nor on the host; host arrays
  * larger than the context's pinned buffer are uploaded through it piece by piece, each piece waited for.
- * TENT_ERR_RANGE when tables plus workspace exceed the static array (about 75 bytes per extent,
+ * TENT_ERR_RANGE for a batch that counts more than TENT_STATIC_WORKSPACE_BYTES (about 75 bytes per extent,
  * 70 bytes per slice and 60 bytes per 4 KiB tile of payload: batches up to about 2 GiB of payload in
  * 32 KiB pages fit).
  * One static batch exists per GPU: the array keeps the last call's contents, and every call clears

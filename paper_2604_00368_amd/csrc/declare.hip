@@ -275,6 +275,18 @@ hipError_t order_workspace_bytes(uint64_t n_dst, uint64_t n_src, bool check, Key
     return e;
 }
 
+// What the address order counts against the limit of tent_declare_static: the workspace of a sort over all address
+// bits with one array of scan partials, whatever order_workspace_bytes() comes to.
+hipError_t order_measure(uint64_t n_dst, uint64_t n_src, bool check, uint64_t* bytes_out)
+{
+    const uint64_t n = n_dst + (check ? n_src : 0);
+    OrderWorkspace w;
+    hipError_t e = layout(n, KeyBits{0, 64}, nullptr, &w);
+    if (e != hipSuccess) return e;
+    *bytes_out = w.total - 2 * up256(scan_partials_capacity(n) * 8);
+    return hipSuccess;
+}
+
 // The device work of a declaration whose descriptors lie in the batch's tables.  Clears what must start at zero; with
 // `order` fills order_out[n_dst] with destination extent indices in ascending address and rank_out[n_dst] with the
 // inverse (position of every extent in that order); with `check` sets *overlap_told (host memory, 0 before) if a

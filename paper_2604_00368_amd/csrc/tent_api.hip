@@ -16,7 +16,11 @@ using namespace tent;
 // here.  One copy per GPU, held until the process ends.  In host code the array's name is only a
 // stand-in: its address on a GPU is looked up once, with that GPU current, and host code uses the
 // looked-up pointer and nothing else.
-static __device__ __align__(256) unsigned char scratch[TENT_STATIC_WORKSPACE_BYTES];
+//
+// The array is 5/16 larger than the limit that a batch is held to (static_measure): the tables of a batch at the
+// limit take at most 1.28 times what it is counted with (64 rails: 2,078 against 1,626 bytes per transfer).
+constexpr uint64_t kStaticArea = (uint64_t)TENT_STATIC_WORKSPACE_BYTES + TENT_STATIC_WORKSPACE_BYTES / 16 * 5;
+static __device__ __align__(256) unsigned char scratch[kStaticArea];
 
 namespace {
 
@@ -112,7 +116,6 @@ constexpr size_t kSpareBlocks = 4;                // released table allocations 
 constexpr uint64_t kStageInitial = 1ull << 20;    // pinned bytes per staging buffer at tent_create
 constexpr uint32_t kStaticSlot = 0xFFFFFFFFu;     // slot field of a handle whose tables live in the static workspace
 
-constexpr uint64_t kStaticBytes = TENT_STATIC_WORKSPACE_BYTES;
 struct StaticArea {
     void* ptr = nullptr;         // device address of `scratch` on this GPU
     uint64_t generation = 0;     // goes up with every tent_declare_static on this GPU: older static batches are dead
@@ -304,6 +307,39 @@ struct Carver {
         }
     }
 };
+
+// What a batch counts against the limit of tent_declare_static: by kind of entry, not by what its tables happen to take,
+// so that the batches which are accepted and refused stay the same when the layout changes.
+uint64_t static_measure(const BatchDev& d, bool bounded, uint64_t order_bytes)
+{
+    uint64_t t = order_bytes;
+    const auto add = [&t](uint64_t count, uint64_t size) { t += (std::max<uint64_t>(count, 1) * size + 255) & ~255ull; };
+    const uint64_t D = d.n_desc, ns = d.n_src_ext, nd = d.n_dst_ext, N = d.n_slices, q = d.n_sc_tiles;
+    const uint64_t scan_n = std::max(std::max(ns, nd), std::max(N, D)), runs = 2 * D;
+    const uint64_t rot = (N + 1023) / 1024 * TENT_MAX_RAILS;
+    add(D + 1, 4); add(D + 1, 4); add(ns, 16); add(nd, 16);              // descriptors
+    add(ns + 1, 8); add(nd + 1, 8); add(D + 1, 8);                       // prefixes
+    for (int k = 0; k < 5; ++k) add(N, 4);                               // slices: transfer, length, extents, rail;
+    for (int k = 0; k < 3; ++k) add(N, 8);                               //   offset, staging offset, latency;
+    add(N, 1); add(N, 1); add(N, 16);                                    //   state, retries, copy record
+    add(D, 1); add(D, 1); add(1, 528); add(1, 4);                        // priority, mode, the batch itself, verdict
+    if (q == 0) { add(N * d.tiles_per_slice, 8); add(N * d.tiles_per_slice, 8); }
+    add(runs + 1, 4); add(runs * d.run_stride, 8); add(runs * d.run_stride, 4); add(runs + 1, 32);
+    add(N + 1, 8); add(nd, 4); add(nd, 4);
+    if (q) {
+        add(nd + 1, 8);
+        for (int k = 0; k < 4; ++k) { add(q, 8); add(q, 4); }            // tiles, by either order
+        if (bounded) add(q, 8);
+        add(N + 1, 8); add(scan_partials_capacity(N), 8);
+        for (int k = 0; k < 3; ++k) add(q / 2 + 1, 8);                   // tiles of a partial execute
+    }
+    if (bounded)
+        for (int k = 0; k < 3; ++k) add((uint64_t)kMaxChunks * TENT_MAX_RAILS, 8);
+    add(N, 4); add(N, 4); add(rot, 8); add(rot, 4);                      // pending and retried slices
+    add(scan_n + 1, 8); add(scan_partials_capacity(scan_n), 8); add(scan_partials_capacity(scan_n), 8);
+    add(1, 4712);                                                        // the result block
+    return t;
+}
 
 // Device memory for a batch's tables: a spare allocation of a released batch when one is large enough
 // (and not absurdly larger), else a new one.
@@ -810,8 +846,10 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     const uint64_t table_bytes = cv.total();
     void* workspace = nullptr;
     if (use_static) {
-        // both the tables and the sort's workspace must fit the static workspace
-        if (table_bytes + ws_need > kStaticBytes) return TENT_ERR_RANGE;
+        uint64_t order_bytes = 0;
+        if (order && order_measure(nd, ns, check, &order_bytes) != hipSuccess) { (void)hipGetLastError(); return TENT_ERR_HIP; }
+        if (static_measure(d, bounded, order_bytes) > TENT_STATIC_WORKSPACE_BYTES) return TENT_ERR_RANGE;
+        if (table_bytes + ws_need > kStaticArea) return TENT_ERR_RANGE;   // (not reached by a batch within the limit)
         uint8_t* area = nullptr;
         {
             std::lock_guard<std::mutex> lk(g_static_mutex);

@@ -252,6 +252,7 @@ struct KeyBits {
     uint32_t begin, end;           // begin < end
 };
 hipError_t order_workspace_bytes(uint64_t n_dst, uint64_t n_src, bool check, KeyBits bits, uint64_t* bytes_out);
+hipError_t order_measure(uint64_t n_dst, uint64_t n_src, bool check, uint64_t* bytes_out);
 hipError_t launch_declare(const BatchDev& b, bool order, bool check, KeyBits bits, uint32_t* order_out, uint32_t* rank_out,
                           uint32_t* overlap_told, void* workspace, hipStream_t s);
 

@@ -147,3 +147,55 @@ def test_counters_start_afresh_every_time(T):
         assert T.tent_poll(p.ctx, h, stream) == 0
     p.check()
     p.close()
+
+
+@pytest.mark.parametrize("max_rails", [16, 64])
+def test_static_limit_counts_entries_not_layout(T, max_rails):
+    """The largest batch that the 64 MiB limit accepts is declared, planned and moved; one transfer more than fits is
+    refused.  Geometry without a tile size and without the address order, whose tables take most per counted byte."""
+    n, S, length = 0, 4096, 1001
+    stride = max_rails
+
+    def counted(n):
+        def up(count, size):
+            return (max(count, 1) * size + 255) // 256 * 256
+        part = (n + 2047) // 2048 + 2
+        rot = (n + 1023) // 1024 * 64
+        return sum(up(c, s) for c, s in (
+            [(n + 1, 4)] * 2 + [(n, 16)] * 2 + [(n + 1, 8)] * 3 + [(n, 4)] * 5 + [(n, 8)] * 3 + [(n, 1)] * 4 + [(n, 16)]
+            + [(1, 528), (1, 4)] + [(4 * n, 8)] * 2 + [(2 * n + 1, 4), (2 * n * stride, 8), (2 * n * stride, 4), (2 * n + 1, 32)]
+            + [(n + 1, 8)] + [(n, 4)] * 4 + [(rot, 8), (rot, 4), (n + 1, 8), (part, 8), (part, 8), (1, 4712)]))
+
+    n = max(k for k in range(1 << 10, 1 << 17) if counted(k) <= T.TENT_STATIC_WORKSPACE_BYTES)
+    rails = W.tiny().rails
+    pool = (n + 1) * 1024
+    src = torch.randint(0, 256, (pool,), dtype=torch.uint8, device="cuda:0")
+    dst = torch.zeros_like(src)
+    arena = torch.empty((n + 1) * length + 256 * 64, dtype=torch.uint8, device="cuda:0")
+    ctx = T.tent_create(S, arena.data_ptr(), arena.numel(), T.TENT_FLAG_SKIP_OVERLAP_CHECK, max_rails)
+    try:
+        T.tent_register_segment(ctx, src.data_ptr(), pool)
+        T.tent_register_segment(ctx, dst.data_ptr(), pool)
+
+        def batch(n):
+            ptr = np.arange(n + 1, dtype=np.uint32)
+            se = np.zeros(n, dtype=W.tiny().src_ext.dtype)
+            se["off"], se["len"], se["seg"] = np.arange(n, dtype=np.uint64) * 1024, length, W.SRC_SEG
+            de = se.copy()
+            de["seg"] = W.DST_SEG
+            return ptr, se, ptr, de
+
+        stream = torch.cuda.current_stream()
+        h = T.tent_declare_static(ctx, *batch(n))
+        st, _ = T.tent_plan(ctx, h, rails, True, stream)
+        assert st == 0
+        T.tent_execute(ctx, h, stream)
+        assert T.tent_poll(ctx, h, stream) == 0
+        rows = torch.arange(pool, device="cuda:0") % 1024 < length
+        rows[n * 1024:] = False
+        assert torch.equal(dst, torch.where(rows, src, torch.zeros_like(src)))
+        with pytest.raises(T.TentError) as ei:
+            T.tent_declare_static(ctx, *batch(n + 1))
+        assert ei.value.status == T.TENT_ERR_RANGE
+    finally:
+        T.tent_destroy(ctx)
