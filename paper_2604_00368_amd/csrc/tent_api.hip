@@ -1121,14 +1121,15 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
         if (serial) HIP_TRY(launch_bind_serial(d, rp, mode, s));
         else        HIP_TRY(launch_bind_runs(d, rp, mode | (replan ? 0 : kBindBuildTables), info ? ctx->host_plan : nullptr, s));
     }
+    // Only a batch whose verdict has been read counts as planned: an execute relies on there being no overlap.
+    rc = finish_declare_behind(ctx, *b, s);
+    if (rc != TENT_OK) return rc;
     b->planned = true;
     b->may_replan = false;                                    // every pending slice is BOUND now
     b->bound_hint = b->dev.n_slices;
     b->tile_hint = ~0ull;
     b->last_rails = rp;
     for (uint32_t r = 0; r < n_rails; ++r) b->last_lat_ns[r] = rails[r].lat_ns;
-    rc = finish_declare_behind(ctx, *b, s);
-    if (rc != TENT_OK) return rc;
 
     if (info) {
         if (serial) HIP_TRY(hipMemcpyAsync(ctx->host_plan, d.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));

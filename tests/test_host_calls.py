@@ -1,0 +1,104 @@
+"""What the library's host side enqueues and answers, without a device: a child process loads a stand-in for the HIP runtime
+(fake_hip.c: launches do nothing, every launch, event and wait is logged) and runs one scenario of this file."""
+import ctypes as C
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+MiB = 1 << 20
+LAUNCH, RECORD, WAIT = 1, 2, 3
+STREAM_A, STREAM_B = 0xA0, 0xB0                      # never dereferenced
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    from paper_2604_00368_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2604_00368_amd import build
+        build.build()
+    lib = tmp_path_factory.mktemp("fake_hip") / "libamdhip64.so.7"
+    subprocess.check_call(["gcc", "-std=gnu11", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-shared", "-fPIC",
+                           "-Wl,-soname,libamdhip64.so.7", "-o", str(lib), os.path.join(HERE, "fake_hip.c")])
+    return lib
+
+
+def run(fake, scenario, *args):
+    env = dict(os.environ)
+    env["LD_LIBRARY_PATH"] = os.pathsep.join(p for p in (str(fake.parent), env.get("LD_LIBRARY_PATH")) if p)
+    code = f"import sys; sys.path[:0] = [{ROOT!r}, {HERE!r}]; import test_host_calls as t; t.{scenario}(*{args!r})"
+    r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+class Host:
+    """In the child process: the library over the stand-in, one context with a source and a destination segment."""
+
+    def __init__(self, slice_bytes=65536, flags=0, max_rails=0, pool=1 << 40):
+        from paper_2604_00368_amd import binding as T
+        from paper_2604_00368_amd import workloads as W
+        self.T, self.W = T, W
+        T.lib()
+        self.hip = C.CDLL("libamdhip64.so.7")
+        self.hip.fake_kernel_name.restype = C.c_char_p
+        self.hip.fake_kernel_name.argtypes = [C.c_void_p]
+        self.hip.fake_capture.argtypes = [C.c_void_p]
+        self.ctx = T.tent_create(slice_bytes, 1 << 52, 1 << 60, flags, max_rails)
+        T.tent_register_segment(self.ctx, 1 << 44, pool)
+        T.tent_register_segment(self.ctx, 1 << 46, pool)
+
+    def extents(self, n, length, step=None):
+        """n transfers of one extent each."""
+        ext = np.zeros(n, dtype=self.W.EXTENT_DTYPE)
+        ext["off"], ext["len"] = np.arange(n, dtype=np.uint64) * np.uint64(step or length), length
+        dst = ext.copy()
+        dst["seg"] = self.W.DST_SEG
+        ptr = np.arange(n + 1, dtype=np.uint32)
+        return ptr, ext, ptr, dst
+
+    def log(self):
+        """(kind, stream, kernel name or event) of everything since the last call."""
+        out = []
+        for i in range(self.hip.fake_log_size()):
+            stream, what = C.c_void_p(), C.c_void_p()
+            kind = self.hip.fake_log_at(i, C.byref(stream), C.byref(what))
+            out.append((kind, stream.value, self.hip.fake_kernel_name(what).decode() if kind == LAUNCH else what.value))
+        self.hip.fake_log_clear()
+        return out
+
+
+def status_of(T, f, *args):
+    try:
+        f(*args)
+    except T.TentError as e:
+        return e.status
+    return T.TENT_OK
+
+
+def unverified_batch(bounded):
+    h = Host(flags=8 if bounded else 0)
+    T = h.T
+    b = T.tent_declare(h.ctx, *h.extents(8, 65536))
+    rails = h.W.make_rails([50000, 25000])
+    h.hip.fake_fail_host_waits(1)
+    assert status_of(T, T.tent_plan, h.ctx, b, rails, False, STREAM_A) == T.TENT_ERR_HIP
+    h.log()
+    move = (T.tent_execute_bounded, h.ctx, b, MiB, STREAM_A) if bounded else (T.tent_execute, h.ctx, b, STREAM_A)
+    assert status_of(T, *move) == T.TENT_ERR_STATE
+    assert not [x for x in h.log() if x[0] == LAUNCH]
+    # the next plan gets the verdict, and the batch moves
+    assert T.tent_plan(h.ctx, b, rails, False, STREAM_A)[0] == T.TENT_OK
+    assert status_of(T, *move) == T.TENT_OK
+    assert [x for x in h.log() if x[0] == LAUNCH]
+    T.tent_destroy(h.ctx)
+
+
+@pytest.mark.parametrize("bounded", [False, True])
+def test_nothing_moves_before_the_overlap_verdict(fake, bounded):
+    """A plan that cannot read the verdict of the overlap check (the host's wait fails) leaves the batch unplanned: bytes of
+    extents that may overlap are not moved in one pass."""
+    run(fake, "unverified_batch", bounded)
