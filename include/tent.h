@@ -26,8 +26,10 @@
  *     DONE -- and may then run beside its copies, which read none of what a re-plan writes.
  *     That is what overlaps the re-planning of the unfinished slices with the data movement of
  *     the finished ones.  An execute that can leave nothing over (no tent_sim_advance, tent_sim_fail
- *     or tent_plan_dispatch since the last tent_plan) is waited for as a whole.  The next tent_execute must still come after that plan (the
- *     host-side wait of tent_sim_advance with n_done != NULL, or an event).
+ *     or tent_plan_dispatch since the last tent_plan) is waited for as a whole, and so is a
+ *     tent_execute_bounded.  No such wait is recorded into a graph.  The next tent_execute must
+ *     still come after that plan (the host-side wait of tent_sim_advance with n_done != NULL, or
+ *     an event).
  *   - HIP graphs: tent_reset, tent_plan with info = NULL and tent_execute allocate nothing, copy
  *     nothing from or to the host and enqueue kernels only (no memset nodes), so a caller may
  *     record them on a capturing stream and replay the graph.  The host-side bookkeeping of a

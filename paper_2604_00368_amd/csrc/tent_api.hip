@@ -557,10 +557,11 @@ struct StageTimer {
 
 // A re-plan enqueued on another stream than the last execute's may overlap that execute's copies: it
 // only has to come after the execute's bookkeeping.  An execute that could leave nothing over records no
-// event for that (each is a bubble of 6 us on the stream): a plan on another stream waits for its end.
+// event for that (each is a bubble of 6 us on the stream): a plan on another stream waits for its end, as it does for a
+// bounded execute's.  What is being captured into a graph runs when its caller replays it: no wait is recorded there.
 hipError_t order_after_execute_bookkeeping(const Batch& b, hipStream_t s)
 {
-    if (!b.replan_at || s == b.exec_stream) return hipSuccess;
+    if (!b.replan_at || s == b.exec_stream || capturing(s)) return hipSuccess;
     return hipStreamWaitEvent(s, b.replan_at, 0);
 }
 
@@ -1566,10 +1567,12 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
         if (n_chunks >= 2) HIP_TRY(hipStreamWaitEvent(s, ctx->sync_events[2 * (n_chunks - 2) + 1], 0));
     }
     HIP_TRY(launch_mark_done_bounded(d, s));
-    b->replan_at = nullptr;                                   // the bounded execute offers no overlap with a re-plan
+    b->replan_at = nullptr;
     b->has_done = true;
     b->bound_hint = 0;
     HIP_TRY(record_execute_done(*b, s, note));
+    // the range copies read what a re-plan rewrites, and the DONE marks come last: a re-plan on another stream waits for it all
+    if (b->done_recorded) b->replan_at = b->done_at;
     return TENT_OK;
 }
 

@@ -102,3 +102,41 @@ def test_nothing_moves_before_the_overlap_verdict(fake, bounded):
     """A plan that cannot read the verdict of the overlap check (the host's wait fails) leaves the batch unplanned: bytes of
     extents that may overlap are not moved in one pass."""
     run(fake, "unverified_batch", bounded)
+
+
+def plan_beside_bounded(flags, slots, dispatch):
+    h = Host(flags=8 | flags)
+    T = h.T
+    b = T.tent_declare(h.ctx, *h.extents(48, 65536))
+    rails = h.W.make_rails([50000, 25000])
+
+    def plan(stream):
+        if dispatch:
+            T.tent_plan_dispatch(h.ctx, b, rails, h.W.make_dispatch_params(1 << 18), None, False, stream)
+        else:
+            T.tent_plan(h.ctx, b, rails, False, stream)
+
+    plan(STREAM_A)
+    T.tent_execute_bounded(h.ctx, b, MiB, STREAM_A, slots=slots)
+    before = h.log()
+    last = max(i for i, x in enumerate(before) if x[0] == LAUNCH and x[1] == STREAM_A)
+    ends = {x[2] for x in before[last:] if x[0] == RECORD and x[1] == STREAM_A}
+    plan(STREAM_B)
+    after = h.log()
+    first = min(i for i, x in enumerate(after) if x[0] == LAUNCH and x[1] == STREAM_B)
+    assert ends & {x[2] for x in after[:first] if x[0] == WAIT and x[1] == STREAM_B}
+    # on the execute's own stream there is nothing to wait for, and nothing is waited for inside a capture
+    T.tent_execute_bounded(h.ctx, b, MiB, STREAM_A, slots=slots)
+    h.log()
+    plan(STREAM_A)
+    h.hip.fake_capture(STREAM_B)
+    plan(STREAM_B)
+    assert not [x for x in h.log() if x[0] == WAIT]
+    T.tent_destroy(h.ctx)
+
+
+@pytest.mark.parametrize("dispatch", [False, True])
+@pytest.mark.parametrize("flags,slots", [(0, 1), (0, 2), (1, 1), (1, 2)])
+def test_a_plan_on_another_stream_waits_for_a_bounded_execute(fake, flags, slots, dispatch):
+    """Its range copies read the rails and staging offsets that a re-plan rewrites, and its slices are marked DONE at its end."""
+    run(fake, "plan_beside_bounded", flags, slots, dispatch)
