@@ -10,6 +10,9 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 MiB = 1 << 20
+# without a flag the chunks move in one pass (source -> slot and destination), with TENT_FLAG_SKIP_OVERLAP_CHECK in two:
+# gather on the caller's stream, scatter on it or, with two slots, on the library's own
+passes = pytest.mark.parametrize("flags", [0, 1], ids=["one_pass", "two_passes"])
 
 
 @pytest.fixture(scope="module")
@@ -20,10 +23,11 @@ def H():
     return gpu_harness
 
 
+@passes
 @pytest.mark.parametrize("slots", [1, 2])
 @pytest.mark.parametrize("name,chunk", [("tiny", 1 * MiB), ("tiny", 3 * MiB), ("kv_migration", 2 * MiB),
                                         ("rl_params", 1 * MiB), ("many_small", 1 * MiB)])
-def test_bounded_execute_bit_exact(H, oracle, name, chunk, slots):
+def test_bounded_execute_bit_exact(H, oracle, name, chunk, slots, flags):
     from paper_2604_00368_amd import binding as T
     w = W.small_variant(name)
     R = w.rails.shape[0]
@@ -35,7 +39,7 @@ def test_bounded_execute_bit_exact(H, oracle, name, chunk, slots):
     b = oracle.bind(s.len, w.rails)
     dst_want, staging_want = dst0.copy(), np.zeros(cap, dtype=np.uint8)
     assert oracle.execute_bounded(w, s, b, [src, dst_want], staging_want, chunk, slots=slots, slot_bytes=slot) == 0
-    with H.Engine(w, src, dst0, flags=T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=cap) as eng:
+    with H.Engine(w, src, dst0, flags=flags | T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=cap) as eng:
         eng.declare()
         st, info = eng.plan()
         assert st == 0
@@ -49,8 +53,9 @@ def test_bounded_execute_bit_exact(H, oracle, name, chunk, slots):
         assert np.array_equal(eng.src.cpu().numpy(), src)
 
 
+@passes
 @pytest.mark.parametrize("slots", [1, 2])
-def test_bounded_execute_over_replanning_epochs(H, oracle, slots):
+def test_bounded_execute_over_replanning_epochs(H, oracle, slots, flags):
     # every epoch only the slices that stayed bound move (a FIFO prefix per rail), through a 1 MiB buffer
     from paper_2604_00368_amd import binding as T
     w = W.replanning(n_req=6, layers=4, ctx_lo=400, ctx_hi=2000, queued_hi=1 << 20)
@@ -62,7 +67,7 @@ def test_bounded_execute_over_replanning_epochs(H, oracle, slots):
     s = oracle.split(w.src_ptr, w.src_ext, w.slice_bytes)
     dst_want, staging_want = dst0.copy(), np.zeros(cap, dtype=np.uint8)
     pending = np.arange(s.n, dtype=np.uint32)
-    with H.Engine(w, src, dst0, flags=T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=cap) as eng:
+    with H.Engine(w, src, dst0, flags=flags | T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=cap) as eng:
         eng.declare()
         for e, ep in enumerate(list(w.epochs) + [w.drain]):
             if pending.shape[0] == 0:
@@ -128,12 +133,13 @@ def test_bounded_argument_errors(H, oracle):
         assert T.tent_poll(eng.ctx, h, eng.stream) == 0
 
 
+@passes
 @pytest.mark.parametrize("slots", [1, 2])
 @pytest.mark.parametrize("seed,kw", [(3, {}), (4, dict(n_desc=9, max_len=1_500_000, slice_bytes=65536 + 3)),
                                      (5, dict(n_desc=40, max_len=90_000, slice_bytes=1, max_ext=7)),
                                      (6, dict(n_desc=6, max_len=3_000_000, slice_bytes=1 << 20, max_ext=1 << 18)),
                                      (7, dict(n_desc=30, max_len=300_000, slice_bytes=5000, align=8))])
-def test_bounded_execute_ragged_geometry_bit_exact(H, oracle, seed, kw, slots):
+def test_bounded_execute_ragged_geometry_bit_exact(H, oracle, seed, kw, slots, flags):
     # lengths that are no multiple of any tile size (1-byte slices, 1-byte extents, source and destination cut
     # differently): the chunks are moved byte-exactly in ranges of 1 KiB; arena and destination against the oracle
     from paper_2604_00368_amd import binding as T
@@ -149,7 +155,7 @@ def test_bounded_execute_ragged_geometry_bit_exact(H, oracle, seed, kw, slots):
     dst_want, staging_want = dst0.copy(), np.zeros(cap, dtype=np.uint8)
     assert oracle.execute_bounded(w, s, b, [src, dst_want], staging_want, chunk, slots=slots, slot_bytes=slot) == 0
     print("ragged bounded", seed, "payload", w.payload, "slices", s.n, "chunks", -(-w.payload // chunk), flush=True)
-    with H.Engine(w, src, dst0, flags=T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=cap, arena_skew=seed % 3) as eng:
+    with H.Engine(w, src, dst0, flags=flags | T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=cap, arena_skew=seed % 3) as eng:
         eng.declare()
         st, info = eng.plan()
         assert st == 0
@@ -162,7 +168,8 @@ def test_bounded_execute_ragged_geometry_bit_exact(H, oracle, seed, kw, slots):
         assert np.array_equal(eng.src.cpu().numpy(), src)
 
 
-def test_bounded_execute_ragged_partial_sets(H, oracle):
+@passes
+def test_bounded_execute_ragged_partial_sets(H, oracle, flags):
     # re-planning epochs on ragged geometry: only the slices that stayed bound move, the rest is re-planned
     from paper_2604_00368_amd import binding as T
     w = W.ragged(11, n_desc=16, max_len=600_000, slice_bytes=30_000 + 1)
@@ -175,7 +182,7 @@ def test_bounded_execute_ragged_partial_sets(H, oracle):
     dst_want, staging_want = dst0.copy(), np.zeros(slot, dtype=np.uint8)
     pending = np.arange(s.n, dtype=np.uint32)
     rng = np.random.Generator(np.random.PCG64(77))
-    with H.Engine(w, src, dst0, flags=T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=slot) as eng:
+    with H.Engine(w, src, dst0, flags=flags | T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=slot) as eng:
         eng.declare()
         for epoch in range(12):
             if pending.shape[0] == 0:
@@ -201,7 +208,8 @@ def test_bounded_execute_ragged_partial_sets(H, oracle):
         assert pending.shape[0] == 0
 
 
-def test_bounded_execute_after_dispatch_with_odd_addresses(H, oracle):
+@passes
+def test_bounded_execute_after_dispatch_with_odd_addresses(H, oracle, flags):
     # the bounded execute moves whatever is BOUND, whoever planned it: request-level dispatch with deferred
     # transfers, pages and arena at odd addresses, 1 KiB tiles
     from paper_2604_00368_amd import binding as T
@@ -215,7 +223,7 @@ def test_bounded_execute_after_dispatch_with_odd_addresses(H, oracle):
     prio = W.make_priorities(8, w.n_desc)
     dst_want, staging_want = dst0.copy(), np.zeros(cap, dtype=np.uint8)
     done = np.zeros(s.n, dtype=np.uint8)
-    with H.Engine(w, src, dst0, flags=T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=cap, arena_skew=7) as eng:
+    with H.Engine(w, src, dst0, flags=flags | T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=cap, arena_skew=7) as eng:
         eng.declare()
         for window in range(3):
             dp = W.make_dispatch_params(4 * w.slice_bytes, window=window)

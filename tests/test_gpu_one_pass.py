@@ -155,3 +155,59 @@ def test_a_replan_on_another_stream_than_the_execute(H, partial):
     assert results[0][0] == results[1][0]
     assert np.array_equal(results[0][1], results[1][1])
     assert np.array_equal(results[0][2], results[1][2])
+
+
+@pytest.mark.parametrize("two_passes", [False, True])
+def test_a_list_too_short_for_what_is_bound(H, two_passes):
+    """A partial execute recorded into a graph and replayed when far more is BOUND than its tile list holds: in one pass the
+    workgroups that fit move theirs, in two passes nothing counts as moved.  A slice is DONE only if its bytes have arrived,
+    the rest stays BOUND, and a later plan and execute complete the batch."""
+    from helpers import expected_destination
+    from paper_2604_00368_amd import binding as T
+    w = W.kv_migration(n_req=12, layers=2, ctx_lo=200, ctx_hi=400, page_tokens=16, slice_bytes=256 * KiB)
+    src, dst0 = W.fill_numpy(w, 0), W.fill_numpy(w, 1)
+    dst_want = expected_destination(w, src, dst0)
+    R = w.rails.shape[0]
+    with H.Engine(w, src, dst0, flags=T.TENT_FLAG_SKIP_OVERLAP_CHECK if two_passes else 0) as eng:
+        eng.declare()
+        _, info = eng.plan()
+        quarter = np.array(list(info.rail_bytes)[:R], dtype=np.uint64) // np.uint64(4)
+        stayed = T.tent_sim_advance(eng.ctx, eng.batch, w.rails["queued_bytes"] + quarter, eng.stream)
+        assert 0 < stayed < info.n_slices
+        side = torch.cuda.Stream(eng.dev)
+        side.wait_stream(torch.cuda.current_stream(eng.dev))
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(side):
+            with torch.cuda.graph(graph, stream=side):
+                T.tent_execute(eng.ctx, eng.batch, torch.cuda.current_stream(eng.dev))
+        torch.cuda.synchronize(eng.dev)
+        _, info = eng.plan()                                       # nothing has moved: every slice is BOUND now
+        assert info.n_slices == info.n_pending_before == eng.table().shape[0]
+        graph.replay()
+        torch.cuda.synchronize(eng.dev)
+        tab, dst = eng.table(), eng.dst.cpu().numpy()
+        done = tab["state"] == T.TENT_SLICE_DONE
+        assert (tab["state"][~done] == T.TENT_SLICE_BOUND).all()
+        assert T.tent_poll(eng.ctx, eng.batch, eng.stream) == int((~done).sum())
+        moved = int(tab["len"][done].astype(np.uint64).sum())
+        if two_passes:
+            assert moved == 0
+        else:
+            assert 0 < moved <= int(quarter.sum())
+        print("listed", int(done.sum()), "of", done.shape[0], "slices", flush=True)
+        # the bytes of every DONE slice are where they belong
+        first = np.zeros(w.n_desc + 1, dtype=np.int64)             # payload position of every transfer
+        for j in range(w.n_desc):
+            first[j + 1] = first[j] + int(w.src_ext["len"][w.src_ptr[j]:w.src_ptr[j + 1]].sum())
+        def payload(pool, ext, keep):
+            return np.concatenate([pool[int(e["off"]):int(e["off"]) + int(e["len"])] for e in ext])[keep]
+        keep = np.zeros(int(first[-1]), dtype=bool)
+        for row in tab[done]:
+            at = int(first[row["desc"]]) + int(row["off"])
+            keep[at:at + int(row["len"])] = True
+        assert np.array_equal(payload(dst, w.dst_ext, keep), payload(src, w.src_ext, keep))
+        st, info = eng.plan()
+        assert st == 0 and info.n_slices == int((~done).sum())
+        eng.execute()
+        assert T.tent_poll(eng.ctx, eng.batch, eng.stream) == 0
+        assert np.array_equal(eng.dst.cpu().numpy(), dst_want)

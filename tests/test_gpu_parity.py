@@ -228,6 +228,7 @@ def test_replanning_epochs_plan_beside_copies(H, oracle):
     from paper_2604_00368_amd import binding as T
     run_epochs_plan_beside_copies(H, oracle, W.small_variant("replanning"))
     run_epochs_plan_beside_copies(H, oracle, W.small_variant("replanning"), flags=T.TENT_FLAG_SERIAL_BINDING)
+    run_epochs_plan_beside_copies(H, oracle, W.small_variant("replanning"), flags=T.TENT_FLAG_SKIP_OVERLAP_CHECK)   # two passes
 
 
 def test_replanning_epochs_enqueued_without_a_host_wait(H, oracle):
@@ -266,6 +267,7 @@ def test_replanning_epochs_enqueued_without_a_host_wait(H, oracle):
 def test_partial_executes_random_tiled_geometry(H, oracle, seed):
     # lengths in multiples of 1-4 KiB, source and destination cut differently, a few epochs with random budgets:
     # partial executes go over the list of the BOUND slices' tiles, on one stream and with plans on a second
+    from paper_2604_00368_amd import binding as T
     rng = np.random.Generator(np.random.PCG64(9000 + seed))
     align = int(rng.choice([1024, 2048, 4096]))
     w = W.ragged(7000 + seed, n_desc=int(rng.integers(3, 60)), max_len=int(rng.integers(20, 400)) * 1024,
@@ -282,6 +284,7 @@ def test_partial_executes_random_tiled_geometry(H, oracle, seed):
     w.drain = W.Epoch(epochs[-1].rails.copy(), np.full(R, np.iinfo(np.uint64).max, dtype=np.uint64))
     run_epochs_and_compare(H, oracle, w)
     run_epochs_plan_beside_copies(H, oracle, w)
+    run_epochs_plan_beside_copies(H, oracle, w, flags=T.TENT_FLAG_SKIP_OVERLAP_CHECK)
 
 
 def test_replanning_many_small_shape(H, oracle):
