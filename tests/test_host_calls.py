@@ -140,3 +140,42 @@ def plan_beside_bounded(flags, slots, dispatch):
 def test_a_plan_on_another_stream_waits_for_a_bounded_execute(fake, flags, slots, dispatch):
     """Its range copies read the rails and staging offsets that a re-plan rewrites, and its slices are marked DONE at its end."""
     run(fake, "plan_beside_bounded", flags, slots, dispatch)
+
+
+def extents_in_turn():
+    h = Host(slice_bytes=4096, flags=1)
+    T, W = h.T, h.W
+    sizes = [1 << 40, 1 << 40, 5000, 4096]              # two more segments, short ones
+    for k, n in enumerate(sizes[2:]):
+        assert T.tent_register_segment(h.ctx, (1 << 47) + (k << 20), n) == 2 + k
+    rng = np.random.Generator(np.random.PCG64(3))
+    for side in (0, 1):
+        for _ in range(200):
+            n = int(rng.integers(1, 9))
+            ext = np.zeros(n, dtype=W.EXTENT_DTYPE)
+            ext["seg"] = rng.integers(0, 4, size=n)
+            ext["len"] = rng.integers(1, 4097, size=n)
+            ext["off"] = [int(rng.integers(0, sizes[s] - l + 1)) for s, l in zip(ext["seg"].tolist(), ext["len"].tolist())]
+            other = ext.copy()
+            ptr = np.array([0, n], dtype=np.uint32)
+            at, kind = int(rng.integers(0, n)), int(rng.integers(0, 6))
+            size = sizes[int(ext["seg"][at])]
+            if kind == 1:
+                ext["seg"][at] = 4
+            elif kind == 2:
+                ext["seg"][at], ext["off"][at] = 0xFFFFFFFF, 0
+            elif kind == 3:
+                ext["off"][at] = size - int(ext["len"][at]) + 1
+            elif kind == 4:
+                ext["off"][at] = 0xFFFFFFFFFFFFFFFF
+            elif kind == 5:
+                ext["len"][at] = other["len"][at] = 0
+            lists = (ptr, ext, ptr, other) if side == 0 else (ptr, other, ptr, ext)
+            st = status_of(T, T.tent_declare, h.ctx, *lists)
+            assert st == (T.TENT_ERR_INVALID if kind else T.TENT_OK), (side, kind, ext, other)
+    T.tent_destroy(h.ctx)
+
+
+def test_extents_whose_segments_take_turns(fake):
+    """Every extent is held to its own segment, whichever segment the one before it lay in."""
+    run(fake, "extents_in_turn")
