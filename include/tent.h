@@ -258,8 +258,8 @@ int tent_declare_static(tent_ctx *ctx, uint32_t n_desc,
  * Returns TENT_DEFER (and binds nothing) when every rail is excluded;
  * TENT_ERR_INVALID for a health value above 2 (and for a batch that failed its overlap check, see
  * tent_declare); TENT_ERR_RANGE when n_rails exceeds the context's max_rails, bw_MBps = 0,
- * c1_d >= 2^32, (max A_d + the batch's payload) * max c1_d >= 2^63, or the arena is smaller than the
- * batch's payload + 256*n_rails; TENT_ERR_STATE for a batch whose last tent_execute failed half way
+ * c1_d >= 2^32, (max A_d + the batch's payload) * max c1_d >= 2^63, the payload is 2^53 bytes or
+ * more, or the arena is smaller than the batch's payload + 256*n_rails; TENT_ERR_STATE for a batch whose last tent_execute failed half way
  * (see there).
  */
 int tent_plan(tent_ctx *ctx, tent_batch_t batch, const tent_rail_state *rails, uint32_t n_rails,

@@ -670,6 +670,9 @@ int convert_rails(const tent_rail_state* rails, uint32_t n_rails, uint64_t pendi
     // (max A + pending bytes) * max c1 must stay below 2^63 so that no cost wraps
     const unsigned __int128 worst = ((unsigned __int128)max_A + pending_bytes) * max_c1;
     if (worst >= ((unsigned __int128)1 << 63)) return TENT_ERR_RANGE;
+    // the binding chains count the bytes they bind to a rail in doubles (RunCell::T): whole numbers below 2^53 are exact.  No
+    // device has room for the tables of such a batch
+    if (pending_bytes >= (1ull << 53)) return TENT_ERR_RANGE;
     return TENT_OK;
 }
 

@@ -179,3 +179,27 @@ def extents_in_turn():
 def test_extents_whose_segments_take_turns(fake):
     """Every extent is held to its own segment, whichever segment the one before it lay in."""
     run(fake, "extents_in_turn")
+
+
+def payload_at(limit_log2, over):
+    h = Host(slice_bytes=1 << 31, flags=1)
+    T, W = h.T, h.W
+    big = (1 << 32) - 1
+    n = (1 << limit_log2) // big
+    ext = np.zeros(n + 1, dtype=W.EXTENT_DTYPE)
+    ext["len"] = big
+    ext["len"][n] = (1 << limit_log2) - n * big - (0 if over else 1)
+    assert int(ext["len"].astype(np.uint64).sum()) == (1 << limit_log2) - (0 if over else 1)
+    dst = ext.copy()
+    dst["seg"] = W.DST_SEG
+    ptr = np.array([0, n + 1], dtype=np.uint32)
+    b = T.tent_declare(h.ctx, ptr, ext, ptr, dst)
+    rails = W.make_rails([4000000000, 2000000000])
+    assert status_of(T, T.tent_plan, h.ctx, b, rails, False, STREAM_A) == (T.TENT_ERR_RANGE if over else T.TENT_OK)
+    T.tent_destroy(h.ctx)
+
+
+@pytest.mark.parametrize("over", [False, True])
+def test_bytes_bound_to_a_rail_stay_below_2_to_53(fake, over):
+    """The binding chains count a rail's bytes in doubles, which hold whole numbers below 2^53 exactly."""
+    run(fake, "payload_at", 53, over)
