@@ -308,23 +308,26 @@ struct Carver {
     }
 };
 
-// What a batch counts against the limit of tent_declare_static: by kind of entry, not by what its tables happen to take,
-// so that the batches which are accepted and refused stay the same when the layout changes.
+// What a batch counts against the limit of tent_declare_static.  The entries and their sizes are the limit's definition, so
+// that the batches which are accepted and refused stay the same whatever the tables look like: several of them are no size of
+// a table or structure of today's (a run counts 12 bytes per rail and a record, its cells take 16 bytes per rail; retried
+// slices count in chunks of 1024).  That the tables of an accepted batch fit the array is checked by the caller.
 uint64_t static_measure(const BatchDev& d, bool bounded, uint64_t order_bytes)
 {
+    constexpr uint64_t kView = 528, kResult = 4712, kRunRecord = 32, kRotation = 1024;
     uint64_t t = order_bytes;
     const auto add = [&t](uint64_t count, uint64_t size) { t += (std::max<uint64_t>(count, 1) * size + 255) & ~255ull; };
     const uint64_t D = d.n_desc, ns = d.n_src_ext, nd = d.n_dst_ext, N = d.n_slices, q = d.n_sc_tiles;
     const uint64_t scan_n = std::max(std::max(ns, nd), std::max(N, D)), runs = 2 * D;
-    const uint64_t rot = (N + 1023) / 1024 * TENT_MAX_RAILS;
+    const uint64_t rot = (N + kRotation - 1) / kRotation * TENT_MAX_RAILS;
     add(D + 1, 4); add(D + 1, 4); add(ns, 16); add(nd, 16);              // descriptors
     add(ns + 1, 8); add(nd + 1, 8); add(D + 1, 8);                       // prefixes
     for (int k = 0; k < 5; ++k) add(N, 4);                               // slices: transfer, length, extents, rail;
     for (int k = 0; k < 3; ++k) add(N, 8);                               //   offset, staging offset, latency;
     add(N, 1); add(N, 1); add(N, 16);                                    //   state, retries, copy record
-    add(D, 1); add(D, 1); add(1, 528); add(1, 4);                        // priority, mode, the batch itself, verdict
+    add(D, 1); add(D, 1); add(1, kView); add(1, 4);                      // priority, mode, the batch itself, verdict
     if (q == 0) { add(N * d.tiles_per_slice, 8); add(N * d.tiles_per_slice, 8); }
-    add(runs + 1, 4); add(runs * d.run_stride, 8); add(runs * d.run_stride, 4); add(runs + 1, 32);
+    add(runs + 1, 4); add(runs * d.run_stride, 8); add(runs * d.run_stride, 4); add(runs + 1, kRunRecord);
     add(N + 1, 8); add(nd, 4); add(nd, 4);
     if (q) {
         add(nd + 1, 8);
@@ -337,7 +340,7 @@ uint64_t static_measure(const BatchDev& d, bool bounded, uint64_t order_bytes)
         for (int k = 0; k < 3; ++k) add((uint64_t)kMaxChunks * TENT_MAX_RAILS, 8);
     add(N, 4); add(N, 4); add(rot, 8); add(rot, 4);                      // pending and retried slices
     add(scan_n + 1, 8); add(scan_partials_capacity(scan_n), 8); add(scan_partials_capacity(scan_n), 8);
-    add(1, 4712);                                                        // the result block
+    add(1, kResult);                                                     // the result block
     return t;
 }
 

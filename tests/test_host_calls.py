@@ -203,3 +203,48 @@ def payload_at(limit_log2, over):
 def test_bytes_bound_to_a_rail_stay_below_2_to_53(fake, over):
     """The binding chains count a rail's bytes in doubles, which hold whole numbers below 2^53 exactly."""
     run(fake, "payload_at", 53, over)
+
+
+# The largest batches tent_declare_static accepts, in units of each kind: flags 0, no overlap check, bounded staging, both;
+# with 16 rails and with 64 each.  Found by bisection over a library whose limit was the space its tables took.
+STATIC_LIMITS = {
+    ("bytes", 4096): [83791, 34360, 98560, 36608, 75935, 31137, 89323, 33178],
+    ("slices", 4096): [431520, 431520, 432191, 432191, 371935, 371904, 372479, 372479],
+    ("pages", 262144): [97516, 95911, 106832, 104904, 80848, 79632, 87864, 86424],
+    ("pieces", 300): [240640, 151327, 422559, 207501, 218080, 137135, 382928, 188048],
+}
+
+
+def static_batch(W, kind, n):
+    if kind == "bytes":                                  # transfers of 1001 bytes
+        lens, ptr = [1001] * n, np.arange(n + 1)
+    elif kind == "slices":                               # one transfer, whole slices
+        lens = [MiB] * (n // 256) + ([n % 256 * 4096] if n % 256 else [])
+        ptr = np.array([0, len(lens)])
+    elif kind == "pages":                                # requests of 100 pages
+        lens, ptr = [32768] * n, np.unique(np.append(np.arange(0, n, 100), n))
+    else:                                                # transfers of seven extents
+        lens, ptr = [77] * n, np.unique(np.append(np.arange(0, n, 7), n))
+    src = np.zeros(len(lens), dtype=W.EXTENT_DTYPE)
+    src["len"], src["off"] = lens, np.cumsum([0] + lens[:-1])
+    dst = src.copy()
+    dst["seg"] = W.DST_SEG
+    ptr = ptr.astype(np.uint32)
+    return ptr, src, ptr, dst
+
+
+def static_limit(kind, slice_bytes):
+    most = iter(STATIC_LIMITS[kind, slice_bytes])
+    for flags in (0, 1, 8, 9):
+        for max_rails in (16, 64):
+            n = next(most)
+            h = Host(slice_bytes, flags, max_rails)
+            for k in (n, n + 1):
+                st = status_of(h.T, h.T.tent_declare_static, h.ctx, *static_batch(h.W, kind, k))
+                assert st == (h.T.TENT_OK if k == n else h.T.TENT_ERR_RANGE), (kind, flags, max_rails, k)
+            h.T.tent_destroy(h.ctx)
+
+
+@pytest.mark.parametrize("kind,slice_bytes", sorted(STATIC_LIMITS))
+def test_static_limit_stays_where_it_was(fake, kind, slice_bytes):
+    run(fake, "static_limit", kind, slice_bytes)
