@@ -220,12 +220,16 @@ int tent_declare(tent_ctx *ctx, uint32_t n_desc,
  * serving loops, harnesses that ban allocation, set-up phases of graph-driven pipelines).  Same
  * arguments, same checks and the same batch as tent_declare, but the batch's device tables and the
  * workspace of the address sort are carved from a static device array of the library
- * (room for batches that count TENT_STATIC_WORKSPACE_BYTES = 64 MiB and 20 MiB more for how their tables are laid
- * out, per GPU, held by every GPU the library runs on until the process ends) and the call allocates nothing, neither on the device nor on the host; host arrays
- * larger than the context's pinned buffer are uploaded through it piece by piece, each piece waited for.
- * TENT_ERR_RANGE for a batch that counts more than TENT_STATIC_WORKSPACE_BYTES (about 75 bytes per extent,
- * 70 bytes per slice and 60 bytes per 4 KiB tile of payload: batches up to about 2 GiB of payload in
- * 32 KiB pages fit).
+ * (room for batches that count TENT_STATIC_WORKSPACE_BYTES = 64 MiB and 20 MiB more for how their
+ * tables are laid out, per GPU, held by every GPU the library runs on until the process ends) and
+ * the call allocates nothing, neither on the device nor on the host; host arrays larger than the
+ * context's pinned buffer are uploaded through it piece by piece, each piece waited for.
+ * TENT_ERR_RANGE for a batch that counts more than TENT_STATIC_WORKSPACE_BYTES: about 90 bytes per
+ * extent (32 with TENT_FLAG_SKIP_OVERLAP_CHECK), 95 bytes per slice, 60 bytes per tile of payload
+ * (4 KiB for pages and slices in multiples of it) and, per transfer, 90 bytes and 24 bytes for every
+ * rail the context allows (max_rails rounded up to 16, 32 or 64: 474, 858 or 1,626 bytes in all).
+ * About 2.9 GiB of payload in 32 KiB pages fit, or 83,000 (16 rails) to 34,000 (64) transfers of
+ * one extent shorter than a slice; bounded staging takes 6 MiB for its chunks.
  * One static batch exists per GPU: the array keeps the last call's contents, and every call clears
  * what must start at zero.  A new call from the same context waits for and replaces that context's
  * previous static batch; a call from another context on the same GPU invalidates the other context's
@@ -456,6 +460,10 @@ int tent_get_plan(tent_ctx *ctx, tent_batch_t batch, tent_slice *host_out, uint6
  * pair of HIP events on the caller's stream.  This call waits for the recorded events and
  * returns, per stage, the summed milliseconds and the number of bracketed intervals since
  * the previous call (0 for stages that did not run), then starts a new accounting period.
+ * Where one launch does the work of several stages its time stands under one of them: the first
+ * plan of a small batch (at most 2048 extents a side, 2048 slices and 16384 tiles, not bound
+ * serially) is a single launch under TENT_T_BIND and leaves EXTENT_SCAN, SLICE_SCAN and EXPAND at
+ * 0; one-pass copies stand under TENT_T_GATHER and leave SCATTER at 0.
  * `ms_out` and `launches_out` are host memory with TENT_T_COUNT entries each. */
 int tent_get_timings(tent_ctx *ctx, float *ms_out, uint32_t *launches_out);
 

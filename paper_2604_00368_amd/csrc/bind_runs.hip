@@ -8,7 +8,8 @@
 // are nondecreasing in k, so picking the cheapest rail m times is a merge of R sorted sequences: the
 // run takes the m smallest triples (f_d(k), d, k) in lexicographic order, and the slice at position
 // p of the run gets the triple of rank p.  Three steps follow from that:
-//   1. run table     maximal runs of equal-length pending slices (flag heads, exclusive scan);
+//   1. run table     maximal runs of equal-length pending slices: on a first plan written with the slice table, on a
+//                    re-plan from the pending list (flag heads, exclusive scan);
 //   2. chain         one wavefront, lane = rail, walks the runs in order and finds, per run, how many
 //                    slots k_d each rail takes.  A second wavefront, the feeder, goes ahead of it and hands it one record
 //                    per run with everything that does not depend on the rails' state, among it the cost level at
@@ -81,7 +82,7 @@ __device__ __forceinline__ uint32_t slots_upto(const Rail& r, uint64_t A, uint32
     return (uint32_t)(k < m ? k : m);
 }
 
-// ---- step 1: run table ------------------------------------------------------------------------
+// ---- step 1: run table of a re-plan ------------------------------------------------------------
 struct RunHead {
     const uint32_t* s_len;
     const uint32_t* pending;
@@ -125,7 +126,7 @@ __global__ void __launch_bounds__(256) run_table_kernel(BatchDev b)
     }
 }
 
-// ---- step 2: chain over runs ------------------------------------------------------------------
+// ---- step 2: chain over runs: exact slot counts -----------------------------------------------
 // Same value as slots_upto, reached from a floating-point estimate that is then checked against
 // the integer cost of the neighbouring slots; falls back to the closed form when the estimate
 // cannot be trusted to be within a few slots.
@@ -329,7 +330,7 @@ __device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const 
     __hip_atomic_store(&ring.filled, written + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// ---- step 2: chain over runs ------------------------------------------------------------------
+// ---- the chain ---------------------------------------------------------------------------------
 // A run of m slices of l bytes from any state and with any (or no) level estimate: the level is searched
 // with exact slot counts (bracket, interpolation, bisection) and the split repaired slot by slot.  Kept
 // out of line: the chain's loop calls it only where its short path does not apply.  Returns the lane's slot count.
@@ -493,8 +494,8 @@ struct SplitResult {
 
 // A run whose guess does not hold, by the general path.  Out of line, like everything the chain's loop seldom needs.
 template <int kWide>
-__device__ __attribute__((noinline)) SplitResult split_odd_run(uint32_t m, bool serves, double T, uint32_t cnt, Rail rail, bool live, uint64_t A_less_T,
-                                                               int lane, const Quad* rec)
+__device__ __attribute__((noinline)) SplitResult split_odd_run(uint32_t m, bool serves, double T, uint32_t cnt, Rail rail,
+                                                               bool live, uint64_t A_less_T, int lane, const Quad* rec)
 {
     const Quad q2 = rec[2], q3 = rec[3];
     const double level = join_f64(q2.x, q2.y);
@@ -514,11 +515,12 @@ __device__ __attribute__((noinline)) uint32_t odd_single(Rail rail, uint64_t end
 //
 // The loop is a chain of dependent instructions on one wavefront that leaves the device idle, so what bounds a plan
 // of many transfers is how many instructions it issues per transfer (4-5 cycles each, 8 when the next depends on
-// it, 16 for a cross-lane step, 25 and more for a branch taken).  Hence: all state as doubles relative to the level, so that a
-// slot's cost is one fma and the comparison with the level needs no shift; the checks of the estimate folded into the
-// keys that are reduced anyway; the first repair step without a branch; a lane knows that it won a reduction by its own key;
-// what depends on the slice length only is kept from run to run; two 16-byte record reads ahead of their use, by all lanes at
-// one address; one 16-byte row store per transfer; and everything unusual behind one test of the record's flags.
+// it, 16 for a cross-lane step, 25 and more for a branch taken).  Hence: all state as doubles relative to the level, so
+// that a slot's cost is one fma and the comparison with the level needs no shift; the checks of the estimate folded into
+// the keys that are reduced anyway; the first repair step without a branch; a lane knows that it won a reduction by its own
+// key; what depends on the slice length only is kept from run to run; two 16-byte record reads ahead of their use, by all
+// lanes at one address; one 16-byte row store per transfer; and everything unusual behind one test of the record's flags.
+// Bytes bound (T) are whole numbers below 2^53, which convert_rails sees to, so a double holds them exactly.
 // About 110 instructions and 270 ns per transfer of a run and a tail on MI355X with 16 rails, from 190 and 510 ns when the state
 // was kept in 64-bit integers and every single slice had a record and a row of its own: 24,576 transfers 12.62 -> 6.46 ms,
 // 4,096 transfers 2.34 -> 1.15 ms, 2,048 transfers on 9 rails 1.18 -> 0.52 ms.

@@ -1,13 +1,14 @@
 // Bounded, pipelined staging (Section 4.1 of the paper: the payload is partitioned into chunks that
 // pass through an intermediate buffer of fixed size).  The payload -- the transfers' bytes laid end to
 // end in declaration order -- is cut into chunks of chunk_bytes; chunks pass through the staging
-// arena one after the other (gather of the chunk, then scatter of the chunk).  Inside the arena every
-// rail keeps one contiguous region per chunk (chunk c lives in slot c mod slots of the arena, so that
-// with two slots a chunk can be gathered while its predecessor is still being scattered): the chunk's bytes on rail d form an interval
+// arena one after the other, in one launch each where the batch allows one-pass copies (see copy.hip), else as gather
+// of the chunk, then scatter of the chunk.  Inside the arena every rail keeps one contiguous region per chunk (chunk
+// c lives in slot c mod slots of the arena, so that with two slots and two passes a chunk can be gathered while its
+// predecessor is still being scattered): the chunk's bytes on rail d form an interval
 // [lo_d, hi_d) of the rail's staging offsets, they sit at region_base_d + (offset - lo_d), and the
 // region bases are the exclusive sum of the interval lengths rounded up to 256 bytes.
 //
-// Both copies walk the chunk's tiles in declaration order (a chunk is a contiguous range of that
+// All copies walk the chunk's tiles in declaration order (a chunk is a contiguous range of that
 // enumeration), so a chunk's launch touches only its own table entries.
 //
 // Geometry whose lengths are no multiple of the tile size has no such enumeration.  There the same

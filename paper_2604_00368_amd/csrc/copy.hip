@@ -1,11 +1,14 @@
-// Gather / scatter of slice bytes between paged extents and per-rail staging regions.
+// Slice bytes between paged extents and per-rail staging regions.
 //
-// Gather: slice bytes are read from the transfer's source extents (the paged side) and written
-// contiguously at the slice's staging address (the staging hop of Section 4.1 of the paper).
-// Scatter: the same bytes are read back from staging and written to the destination extents at
-// the slice's absolute offset inside the transfer (direct-to-offset writes, Section 4.4), so the
-// result does not depend on the order in which slices are moved.
+// Every slice's bytes are read from the transfer's source extents and written contiguously at the slice's staging
+// address (the staging hop of Section 4.1 of the paper) and to the destination extents at the slice's absolute offset
+// inside the transfer (direct-to-offset writes, Section 4.4), so the result does not depend on the order in which slices
+// are moved.  Two forms of that:
+//   one pass    (second half of this file) where no destination byte is a source byte of the batch and the arena
+//               lies outside the segments: every source byte is read once and stored to both places;
+//   two passes  for every other batch: gather (source -> staging), then scatter (staging -> destination), a launch each.
 //
+// Two passes:
 // Work decomposition: one 256-lane workgroup per 4 KiB block of a slice, one 16-byte vector per
 // lane, and the workgroup ends after its store.  Consecutive workgroups touch consecutive staging
 // addresses, so the set of DRAM pages open at any time stays small; on MI355X this one-shot shape

@@ -12,8 +12,9 @@ enum : int { kTicketRetire = 0, kTicketRemaining = 1, kTicketFail = 2, kTicketPr
 
 // True in every thread of the workgroup that finishes last (and has then seen what all others added).  `added` is what this
 // thread's own atomic add or maximum returned (0 if it made none): once the old value is back the addition has
-// happened where every workgroup's atomics happen, which is all the order the counters need -- a device-wide fence would write
-// the caches back and cost 6 us more.
+// happened where every workgroup's atomics happen, which is all the order the counters need -- a device-wide fence would
+// write the caches back and cost 6 us more.  It orders nothing else: what other workgroups have written with plain stores
+// must not be read behind it, and the counters only with atomics (take_counter).
 __device__ __forceinline__ bool finishes_last(PlanState* plan, int kind, unsigned long long added)
 {
     __shared__ uint32_t is_last;

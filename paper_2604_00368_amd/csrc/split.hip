@@ -220,9 +220,11 @@ __global__ void __launch_bounds__(256) stage_tiles_kernel(BatchDev b, uint8_t* a
 // The same when few slices move: the tiles of the BOUND slices are listed with their three addresses, in any
 // order (the copy's result does not depend on it).  A workgroup looks at 16 slices, places those that are BOUND one behind
 // the other and takes room for all of them with one atomic add (over 20,000 slices of which 1,200 move: an add per slice
-// 32 us; 64 slices to a workgroup 22 us, because BOUND slices lie together and few workgroups then have all the work); groups of lanes then write the entries.  A workgroup whose tiles do not fit the list, or the
-// host's bound that sizes the copy, leaves its slices BOUND and lists nothing; the others occupy the list without
-// gaps, because the first that does not fit moves the counter past the bound.
+// 32 us; 64 slices to a workgroup 22 us, because BOUND slices lie together and few workgroups then have all the work);
+// groups of lanes then write the entries.  A workgroup whose tiles do not fit the list, or the host's bound that sizes the
+// copy, leaves its slices BOUND and lists nothing; the others occupy the list without gaps, because the first that does
+// not fit moves the counter past the bound.  (The list of the two-pass copies marks nothing DONE in that case.  It takes an
+// execute that was recorded into a graph and is replayed over more BOUND slices than it was recorded for.)
 constexpr uint32_t kListSlices = 16;
 __global__ void __launch_bounds__(256) list_tiles_kernel(BatchDev b, uint8_t* arena, uint32_t group_shift, uint32_t tile_shift,
                                                          uint64_t max_tiles)

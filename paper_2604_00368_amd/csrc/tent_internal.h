@@ -83,9 +83,9 @@ struct PlanState {
     uint64_t rr_next;                     // round-robin counter after the call
     uint64_t bounded_overflow;            // tent_execute_bounded: chunks whose regions do not fit the arena
     uint64_t n_act;                       // tent_execute with few BOUND slices: entries of the list of tiles that move
-    uint64_t compact_overflow;            // nonzero: more tiles move than the launch was sized for (nothing is marked DONE)
+    uint64_t compact_overflow;            // two passes: more tiles move than the launch was sized for (nothing is marked DONE)
     uint64_t n_act_asked;                 // one-pass copies: tiles of the BOUND slices, listed or not
-    uint32_t ticket[4];                   // workgroups that have finished, per kind of counting kernel (finish.h); 0 between launches
+    uint32_t ticket[4];                   // finished workgroups per kind of counting kernel (finish.h); 0 between launches
 };
 
 // What the binding chains leave for the emit kernels, per run (request) and rail, in one 16-byte store: bytes bound to
@@ -156,20 +156,22 @@ struct BatchDev {
     uint64_t* ga_lin;              // [n_sc_tiles] gather: staging address, 0 = not to be moved
     uint32_t* ga_slice;            // [n_sc_tiles] slice that holds the tile
     uint32_t* ga_x;                // [n_sc_tiles] byte offset of the tile inside that slice
-    uint64_t* ga_dst;              // [n_sc_tiles] destination address of the tile in declaration order (bounded staging only)
-    uint64_t* ch_lo;               // [kMaxChunks * TENT_MAX_RAILS] bounded staging (any geometry): first staging offset per chunk and rail
+    uint64_t* ga_dst;              // [n_sc_tiles] destination address of the tile in declaration order (bounded staging)
+    uint64_t* ch_lo;               // [kMaxChunks * TENT_MAX_RAILS] bounded staging: first staging offset per chunk and rail
     uint64_t* ch_hi;               // same shape: end of the interval
     uint64_t* ch_base;             // same shape: region base inside the arena
-    uint64_t* tile_scan;           // [n_slices+1] scan workspace of the per-execute tile list: tiles of the BOUND slices before slice i
+    uint64_t* tile_scan;           // [n_slices+1] two-pass tile list: tiles of the BOUND slices before slice i
     uint64_t* tile_partials;       // its per-block partial sums
-    uint64_t* act_src;             // [act_capacity] per listed tile (BOUND slices in ascending index, tiles in order): source address,
+    // Tiles of a partial execute (two passes: BOUND slices in ascending index; one pass: groups of 16 slices in any order)
+    uint64_t* act_src;             // [act_capacity] source address,
     uint64_t* act_lin;             //                staging address,
     uint64_t* act_dst;             //                destination address
     uint64_t  act_capacity;
     // One-pass copies (the batch's destinations overlap neither each other nor its sources, and the staging
-    // arena lies outside its segments, so a byte may reach its destination while others are still unread): source,
-    // staging and destination address of every tile, in ascending destination address, or in declaration order
-    // (tile_pos = nullptr) in a context with bounded staging.  They replace the four ga_ and sc_ tables below and above.
+    // arena lies outside every registered segment, so a byte may reach its destination while others are still unread):
+    // source, staging and destination address of every tile, in ascending destination address, or in declaration order
+    // (tile_pos = nullptr) in a context with bounded staging.  Such a batch has none of the ga_ and sc_ tables, but for
+    // ga_slice and ga_x in a context with bounded staging.
     uint32_t  one_pass;            // 1: the batch's copies read every source byte once and write staging and destination
     uint64_t* op_src;              // [n_sc_tiles]
     uint64_t* op_dst;              // [n_sc_tiles]
@@ -207,7 +209,8 @@ enum : uint32_t { kOrderedLanes = 256 };             // lanes of a table-driven 
                                                      // measure the same on MI355X, 64 / 512 / 1024 are slower
 constexpr uint64_t kTileSlow = 1ull << 63;
 enum : uint32_t { kMaxChunks = 4096 };               // most chunks one bounded execute may use
-enum : uint32_t { kRotChunk = 256 };                 // retried slices one rotation wavefront handles (1024: four times the rounds, 32 against 17 us a pass)
+enum : uint32_t { kRotChunk = 256 };                 // retried slices one rotation wavefront handles (1024: four times
+                                                     // the rounds, 32 against 17 us a pass)
 // `mode` argument of the bind kernels
 enum : int { kBindUsePending = 1, kBindAfterRotation = 2, kBindBuildTables = 4 };
 

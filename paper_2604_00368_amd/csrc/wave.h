@@ -39,7 +39,6 @@ __device__ __forceinline__ uint64_t wave_reduce64(uint64_t v, int wide, Op op)
     return v;
 }
 struct OpMin { __device__ uint64_t operator()(uint64_t a, uint64_t b) const { return a < b ? a : b; } };
-struct OpMax { __device__ uint64_t operator()(uint64_t a, uint64_t b) const { return a > b ? a : b; } };
 struct OpAdd { __device__ uint64_t operator()(uint64_t a, uint64_t b) const { return a + b; } };
 struct OpAddF {
     __device__ uint64_t operator()(uint64_t a, uint64_t b) const

@@ -10,8 +10,6 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-PS = 10 ** 12
-
 
 @pytest.fixture(scope="module")
 def H():
