@@ -461,8 +461,8 @@ int tent_get_plan(tent_ctx *ctx, tent_batch_t batch, tent_slice *host_out, uint6
  * returns, per stage, the summed milliseconds and the number of bracketed intervals since
  * the previous call (0 for stages that did not run), then starts a new accounting period.
  * Where one launch does the work of several stages its time stands under one of them: the first
- * plan of a small batch (at most 2048 extents a side, 2048 slices and 16384 tiles, not bound
- * serially) is a single launch under TENT_T_BIND and leaves EXTENT_SCAN, SLICE_SCAN and EXPAND at
+ * plan of a small batch (at most 2048 extents a side, 2048 slices, and 16384 tiles if every slice
+ * were a whole one; not bound serially) is a single launch under TENT_T_BIND and leaves EXTENT_SCAN, SLICE_SCAN and EXPAND at
  * 0; one-pass copies stand under TENT_T_GATHER and leave SCATTER at 0.
  * `ms_out` and `launches_out` are host memory with TENT_T_COUNT entries each. */
 int tent_get_timings(tent_ctx *ctx, float *ms_out, uint32_t *launches_out);

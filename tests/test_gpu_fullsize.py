@@ -258,7 +258,8 @@ def test_full_size_dispatch(H, oracle, name):
     torch.cuda.empty_cache()
 
 
-def test_full_size_bounded_staging(H, oracle):
+@pytest.mark.parametrize("slots", [1, 2], ids=["one_pass", "two_passes_on_two_streams"])
+def test_full_size_bounded_staging(H, oracle, slots):
     # config 2 through an arena of one sixteenth of the payload: plan in full against the oracle, every
     # destination byte by the plain definition, sampled transfers against the oracle's bounded execute
     from paper_2604_00368_amd import binding as T
@@ -266,16 +267,17 @@ def test_full_size_bounded_staging(H, oracle):
     w = full_config("kv_migration")
     R = w.rails.shape[0]
     chunk = 1280 << 20
-    cap = chunk + 256 * R
+    cap = slots * (chunk + 256 * R)
     s = oracle.split(w.src_ptr, w.src_ext, w.slice_bytes)
     b = oracle.bind(s.len, w.rails)
-    eng = H.Engine(w, flags=T.TENT_FLAG_PROFILE | T.TENT_FLAG_BOUNDED_STAGING, arena_bytes=cap)
+    skip = T.TENT_FLAG_SKIP_OVERLAP_CHECK if slots == 2 else 0
+    eng = H.Engine(w, flags=T.TENT_FLAG_PROFILE | T.TENT_FLAG_BOUNDED_STAGING | skip, arena_bytes=cap)
     try:
         eng.declare()
         st, _ = eng.plan(want_info=False)
         assert st == 0
-        T.tent_execute_bounded(eng.ctx, eng.batch, chunk, eng.stream)
-        torch.cuda.synchronize()
+        T.tent_execute_bounded(eng.ctx, eng.batch, chunk, eng.stream, slots=slots)
+        eng.stream.synchronize()
         H.assert_plan_equal(eng.table(), s, b)
         assert T.tent_poll(eng.ctx, eng.batch, eng.stream) == 0
         device_definition_check(w, eng.src, eng.dst)

@@ -97,29 +97,37 @@ def test_destinations_that_reuse_source_bytes_keep_two_passes(H, size):
     T.tent_destroy(ctx)
 
 
-def test_arena_inside_a_segment(H, oracle):
-    """The arena may be part of a registered range; the result is the same."""
+@pytest.mark.parametrize("chunk", [0, 1 << 20])
+def test_arena_inside_a_segment(H, oracle, chunk):
+    """The arena may be part of a registered range; the result is the same, in one piece and in chunks."""
     from paper_2604_00368_amd import binding as T
     w = W.small_variant("many_small")
     src_h, dst_h = W.fill_numpy(w, 0), W.fill_numpy(w, 1)
-    whole = torch.zeros(src_h.size + w.staging_bytes + 512, dtype=torch.uint8, device="cuda:0")
+    n_arena = chunk + 256 * w.rails.shape[0] if chunk else w.staging_bytes
+    whole = torch.zeros(src_h.size + n_arena + 512, dtype=torch.uint8, device="cuda:0")
     at = -(-src_h.size // 256) * 256
     whole[:src_h.size] = torch.from_numpy(src_h).to(whole.device)
     dst = torch.from_numpy(dst_h).to(whole.device)
-    ctx = T.tent_create(w.slice_bytes, whole.data_ptr() + at, w.staging_bytes)
+    ctx = T.tent_create(w.slice_bytes, whole.data_ptr() + at, n_arena, T.TENT_FLAG_BOUNDED_STAGING if chunk else 0)
     T.tent_register_segment(ctx, whole.data_ptr(), whole.numel())
     T.tent_register_segment(ctx, dst.data_ptr(), dst.numel())
     stream = torch.cuda.current_stream()
     h = T.tent_declare(ctx, w.src_ptr, w.src_ext, w.dst_ptr, w.dst_ext)
     T.tent_plan(ctx, h, w.rails, False, stream)
-    T.tent_execute(ctx, h, stream)
+    if chunk:
+        T.tent_execute_bounded(ctx, h, chunk, stream)
+    else:
+        T.tent_execute(ctx, h, stream)
     torch.cuda.synchronize()
     s = oracle.split(w.src_ptr, w.src_ext, w.slice_bytes)
     b = oracle.bind(s.len, w.rails)
-    want, staging = dst_h.copy(), np.zeros(w.staging_bytes, dtype=np.uint8)
-    oracle.execute(w, s, b, [src_h, want], staging)
+    want, staging = dst_h.copy(), np.zeros(n_arena, dtype=np.uint8)
+    if chunk:
+        assert chunk < w.payload and oracle.execute_bounded(w, s, b, [src_h, want], staging, chunk) == 0
+    else:
+        oracle.execute(w, s, b, [src_h, want], staging)
     assert np.array_equal(dst.cpu().numpy(), want)
-    assert np.array_equal(whole[at:at + w.staging_bytes].cpu().numpy(), staging)
+    assert np.array_equal(whole[at:at + n_arena].cpu().numpy(), staging)
     T.tent_destroy(ctx)
 
 

@@ -205,6 +205,24 @@ def test_bytes_bound_to_a_rail_stay_below_2_to_53(fake, over):
     run(fake, "payload_at", 53, over)
 
 
+def timed_stages():
+    h = Host(slice_bytes=4096, flags=2)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    one = lambda *names: {k: int(k in names) for k in T.TENT_T_NAMES}
+    for n, plan in ((2048, ("bind",)), (2049, ("extent_scan", "slice_scan", "expand", "bind"))):
+        b = T.tent_declare(h.ctx, *h.extents(n, 4096))
+        T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+        assert {k: v[1] for k, v in T.tent_get_timings(h.ctx).items()} == one(*plan)
+        T.tent_execute(h.ctx, b, STREAM_A)
+        assert {k: v[1] for k, v in T.tent_get_timings(h.ctx).items()} == one("gather")
+    T.tent_destroy(h.ctx)
+
+
+def test_stages_that_one_launch_stands_for(fake):
+    """A small batch's first plan is one interval under "bind", one-pass copies are one under "gather"."""
+    run(fake, "timed_stages")
+
+
 # The largest batches tent_declare_static accepts, in units of each kind: flags 0, no overlap check, bounded staging, both;
 # with 16 rails and with 64 each.  Found by bisection over a library whose limit was the space its tables took.
 STATIC_LIMITS = {
