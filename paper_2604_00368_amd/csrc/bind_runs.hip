@@ -18,7 +18,9 @@
 //                    cheapest free slot / drop the dearest taken slot) until exactly m slots are taken; where
 //                    the level does not serve, count_d(v) = #{k : f_d(k) <= v} (closed form, two integer
 //                    divisions) is evaluated at bracketed levels instead.  The level only steers the guess; the
-//                    counts and repairs are exact.  Runs of one slice (tails) are a plain argmin.
+//                    counts and repairs are exact.  Runs of one slice (tails) are a plain argmin.  With up to 16
+//                    rails all slots a guess lacks are added at once, by rank, and a third wavefront, the drainer, turns
+//                    what the chain finds into the rows of the run table (bind_chain16).
 //   3. emit          one lane per slot (d, k): its rank in the run is
 //                    k + sum_{d' < d} count_d'(f) + sum_{d' > d} count_d'(f - 1),  f = f_d(k),
 //                    which gives the slice it belongs to; staging offset = T_d at run start + k l.
@@ -161,61 +163,84 @@ __device__ __forceinline__ uint32_t slots_upto_fast(const Rail& r, uint64_t A, u
 // before a run are known in advance (a prefix sum of the pending lengths), so the level after every run is too.
 struct LevelModel {
     // admitted rails in ascending order of their head cost h_d = c0_d + A_d c1_d / 65536 (what the rail's next byte
-    // would cost): h[j] the j-th smallest, G[j] and hG[j] the sums of G_d and of h_d G_d over the first j + 1
-    double h[TENT_MAX_RAILS], G[TENT_MAX_RAILS], hG[TENT_MAX_RAILS];
+    // would cost): h[j] the j-th smallest, G[j] and hG[j] the sums of G_d and of h_d G_d over the first j + 1, inv_G[j] = 1 / G[j]
+    double h[TENT_MAX_RAILS], G[TENT_MAX_RAILS], hG[TENT_MAX_RAILS], inv_G[TENT_MAX_RAILS];
     uint32_t live;
-    double max_c1;
+    double max_c1, min_c1;
+    double short_by;               // slots by which the first guess of a run's split is meant to fall short
 };
 
-// By a whole workgroup (at least 64 threads), with barriers.
+__device__ __forceinline__ double from_lane(double x, int at) { return __shfl(x, at, 64); }
+__device__ __forceinline__ double uniform_from(double x, int at)       // `at` the same in all lanes
+{
+    return __longlong_as_double((long long)read_lane64((uint64_t)__double_as_longlong(x), at));
+}
+
+// By a whole workgroup (at least 64 threads), with barriers; the first wavefront does the work, lane = rail.
+template <int kWide>
 __device__ __forceinline__ void build_level_model(LevelModel& lm, const BatchDev& b, const RailParams& rp, int mode)
 {
     const uint32_t t = threadIdx.x;
-    if (t < TENT_MAX_RAILS) {
-        auto head = [&](uint32_t d, double* G) -> double {
-            const double c1 = (double)(uint32_t)rp.c1[d];                       // c1 >= 1 on this path
-            const uint64_t A = rp.A[d] + ((mode & kBindAfterRotation) ? b.plan->Tr[d] : 0);
-            *G = 65536.0 / c1;
-            return (double)rp.c0[d] + (double)A * c1 * (1.0 / 65536.0);
-        };
-        const bool live = t < rp.n_rails && ((rp.admitted >> t) & 1);
-        double G = 0.0;
-        const double h = live ? head(t, &G) : 0.0;
-        uint32_t rank = 0, n_live = 0;
-        double max_c1 = 0.0;
+    if (t < 64) {
+        const uint64_t live_mask = rp.n_rails < 64 ? rp.admitted & ((1ull << rp.n_rails) - 1) : rp.admitted;
+        const bool live = (live_mask >> t) & 1;
+        const uint32_t n_live = (uint32_t)__popcll(live_mask);
+        const double c1 = live ? (double)(uint32_t)rp.c1[t] : 1.0;                 // c1 >= 1 on this path
+        const double G = 65536.0 / c1;
+        const uint64_t A = rp.A[t] + ((mode & kBindAfterRotation) ? b.plan->Tr[t] : 0);
+        const double h = (double)rp.c0[t] + (double)A * c1 * (1.0 / 65536.0);
+        uint32_t rank = 0;
+        double max_c1 = 0.0, min_c1 = 4294967296.0, sum_G = 0.0;
         for (uint32_t d = 0; d < rp.n_rails; ++d) {
-            if (!((rp.admitted >> d) & 1)) continue;
-            ++n_live;
-            double Gd;
-            const double hd = head(d, &Gd);
-            const double c1 = (double)(uint32_t)rp.c1[d];
-            max_c1 = c1 > max_c1 ? c1 : max_c1;
+            if (!((live_mask >> d) & 1)) continue;
+            const double hd = uniform_from(h, (int)d), c1_d = uniform_from(c1, (int)d);
+            max_c1 = c1_d > max_c1 ? c1_d : max_c1;
+            min_c1 = c1_d < min_c1 ? c1_d : min_c1;
+            sum_G += uniform_from(G, (int)d);
             rank += (hd < h || (hd == h && d < t)) ? 1u : 0u;
         }
         if (live) { lm.h[rank] = h; lm.G[rank] = G; lm.hG[rank] = h * G; }
-        if (t == 0) { lm.live = n_live; lm.max_c1 = max_c1; }
-    }
-    __syncthreads();
-    if (t == 0) {
-        for (uint32_t j = 1; j < lm.live; ++j) { lm.G[j] += lm.G[j - 1]; lm.hG[j] += lm.hG[j - 1]; }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        double g = t < n_live ? lm.G[t] : 0.0, hg = t < n_live ? lm.hG[t] : 0.0;
+        for (int step = 1; step < (int)n_live; step <<= 1) {
+            const double g_up = __shfl_up(g, step, 64), hg_up = __shfl_up(hg, step, 64);
+            if ((int)t >= step) { g += g_up; hg += hg_up; }
+        }
+        if (t < n_live) { lm.G[t] = g; lm.hG[t] = hg; lm.inv_G[t] = 1.0 / g; }
+        if (t == 0) {
+            lm.live = n_live;
+            lm.max_c1 = max_c1;
+            lm.min_c1 = min_c1;
+            // What rounding takes off the slot counts is a sum of n_live fractions, n_live / 2 with a deviation of
+            // sqrt(n_live / 12).  Three deviations leave next to no guess too high; half the slots that all rails take while the
+            // fastest takes one, if that is less, so that seldom a rail is short of two.  Of 6,000 runs of 8 - 72 slices on 16 rails
+            // in two speeds none is too high or short of two, on 8 rails of 12.5 - 100 GB/s 0.2 %, on 8 equal rails and one of eight
+            // times their speed 12 %.
+            const double spread = sqrt(0.75 * (double)n_live), room = 0.5 * sum_G * min_c1 * (1.0 / 65536.0);
+            lm.short_by = kWide > 16 ? 0.0 : spread < room ? spread : room;
+        }
     }
     __syncthreads();
 }
 
-// Half a slice per participating rail comes on top of the bytes: the slot counts are rounded down.
+// Half a slice per participating rail comes on top of the bytes, because the slot counts are rounded down, less what the
+// guess is meant to fall short by.  Nearly always all rails take part.
 __device__ __forceinline__ double level_at(const LevelModel& lm, double bytes, double half_slice)
 {
-    double v = -1.0;
-    for (uint32_t j = 0; j < lm.live; ++j) {
-        v = (bytes + half_slice * (double)(j + 1) + lm.hG[j]) / lm.G[j];
-        if (j + 1 == lm.live || v <= lm.h[j + 1]) break;
-    }
+    const uint32_t last = lm.live - 1;
+    bytes -= 2.0 * half_slice * lm.short_by;
+    double v = (bytes + half_slice * (double)lm.live + lm.hG[last]) * lm.inv_G[last];
+    if (!(v > lm.h[last]))
+        for (uint32_t j = 0; j < last; ++j) {
+            v = (bytes + half_slice * (double)(j + 1) + lm.hG[j]) * lm.inv_G[j];
+            if (v <= lm.h[j + 1]) break;
+        }
     return v;
 }
 
-// A record is four 16-byte quads, read by every lane of the chain at one address; the short path reads the first two:
-//   {slices m, flags, X shift}  {length of the single slice behind the run, run index}  {level, slice length l, that length}  {1 / l}
-// A run of one slice that does not stand behind a longer run has m = 0 and is the single slice itself.
+// What a record holds: the slices m of the run (0: a single slice that does not stand behind a longer run, with no run
+// before it), the shift from the level of the record before to this one's, the level, the slice length l and 1 / l, the length
+// of the single slice behind the run, the run's index, and flags:
 typedef uint32_t Quad __attribute__((ext_vector_type(4)));
 constexpr uint32_t kRecTail = 1u;          // a single slice follows the run and is bound with it
 constexpr uint32_t kRecSingle = 2u;        // there is no run, only a single slice
@@ -224,8 +249,12 @@ constexpr uint32_t kRecRebase = 8u;        // the chain takes its relative state
 constexpr uint32_t kRecSame = 16u;         // the run's slices are as long as those of the run before
 constexpr uint32_t kRecEnd = 32u;          // behind the last run
 constexpr uint32_t kRecShort = kRecTail | kRecSame;   // what nearly every record of a long batch is: the short path
+// up to 16 rails: how the chain may take the record, and how many from it on it may take in the same way
+constexpr uint32_t kTakeOdd = 0u, kTakeSame = 1u, kTakeRun = 2u, kTakeSingle = 3u;
+constexpr uint32_t kRecTake = 6, kRecCount = 8;        // first bits of the two
 constexpr uint32_t kFeedBlock = 64;        // runs the feeder looks at a time, one per lane
-constexpr uint32_t kRingRecords = 256;
+constexpr uint32_t kRingRecords = 256;     // ring of more than 16 rails, in records
+constexpr uint32_t kRingBlocks = 3;        // ring of up to 16 rails, in blocks of kFeedBlock records
 
 // The chain keeps costs relative to the level in units of 2^-16 ps, as doubles that hold whole numbers below 2^53
 // exactly.  A rail 2^kFarBits ps or more above the level counts as infinitely far until the state is rebased, which
@@ -236,55 +265,135 @@ constexpr double kMaxLevel = 4.0e15;       // ps; levels are whole numbers, exac
 constexpr uint32_t kLevelRunMax = 1u << 25;   // slices: slot counts of up to 64 rails are summed in 32 bits
 constexpr double kUnit = 65536.0;
 
-struct RecordRing {
+// The same for up to 16 rails, whose chain keeps them in units of 2^-4 ps (whole multiples of 2^-12) above a floor that lies kBias
+// below the level, so that a 32-bit key (whole ps << 4 | rail) is one conversion away: keys cover 134 us on either side of the
+// level.  The short path takes runs whose slice costs at most kMaxStep on the slowest and the fastest rail together, which is what
+// keeps every key it looks at inside that window, and whose level and record before lie less than kMaxShift apart.
+constexpr double kBias = 2147483648.0;         // 2^31; a slot costs no more than the level iff it ends below kBias + 16
+constexpr double kFineUnit = 4096.0;           // units of 2^-16 ps in one of these
+constexpr double kGuessAt = kBias + 16.0 - 1.0 / 8192.0;   // half a unit below that bound
+constexpr double kDownFrom = 2.0 * kBias + 32.0 - 1.0 / kFineUnit;   // less where a taken slot ends: kBias + (1 - floor(ps)) * 16 and a rest
+constexpr double kMaxStep = 2147483584.0;      // 2^31 - 64
+constexpr double kMaxShift = 68719476736.0;    // 2^36
+constexpr double kMaxSlots = 67108864.0;       // 2^26: slots a level may lie above a rail's head; 16 rails' sums stay below 2^32
+constexpr uint32_t kFarKey16 = 0xFFFFFFF0u;
+constexpr uint32_t kLastBlock = 0x80000000u, kSteepBlock = 0x40000000u;
+constexpr uint32_t kStepped = ~0u;         // StepRing::Record::single of a record that stepped
+constexpr uint32_t kWalkLast = 24;         // records of the last block the chain takes between two reports to the drainer
+constexpr uint32_t kBitsOfSlots = 28;      // of a word in found
+
+struct RecordRing {                        // more than 16 rails
+    // {m, flags, shift} {length of the single slice as a double, run} {level, l, that length} {1 / l}
     Quad rec[kRingRecords][4];
     uint32_t filled;                       // records written
     uint32_t taken;                        // records read
+};
+
+// Up to 16 rails: records in blocks that start at multiples of kFeedBlock, and what the chain finds for each of them.
+struct StepRing {
+    struct Record {
+        Quad step;                         // {shift, length of the single slice less the run's l as a signed word, m}
+        Quad run;                          // {1 / l, l, near_key (see bind_chain16)}
+        Quad level;                        // {level, length of the single slice or 0, index of the run}
+        uint32_t flags;
+        uint32_t single;                   // key of the single slice (low four bits: its rail); kStepped: stands in found
+        uint32_t pad[2];
+    };
+    Record rec[kRingBlocks * kFeedBlock + 1];          // (the chain reads one record ahead)
+    // per rail the slots of the run; a record that steps has fewer than 2^28, and the single slice's rail in the bits above
+    uint32_t found[kRingBlocks * kFeedBlock][16];
+    uint32_t count[kRingBlocks];           // records in the block; kLastBlock marks the last one
+    uint32_t filled;                       // blocks written by the feeder
+    uint32_t walked;                       // records the chain is through with, as block * kFeedBlock + record
+    uint32_t drained;                      // blocks whose rows have been written
 };
 
 __device__ __forceinline__ double join_f64(uint32_t lo, uint32_t hi) { return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo)); }
 __device__ __forceinline__ uint32_t low_f64(double x) { return (uint32_t)(uint64_t)__double_as_longlong(x); }
 __device__ __forceinline__ uint32_t high_f64(double x) { return (uint32_t)((uint64_t)__double_as_longlong(x) >> 32); }
 
+// v_cvt_u32_f64: truncates; values below zero, minus infinity and not-a-number give 0, above 2^32 - 1 saturate.
+__device__ __forceinline__ uint32_t saturating_u32(double x)
+{
+    uint32_t r;
+    asm("v_cvt_u32_f64_e32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+// The same with the low four bits replaced by the rail.
+__device__ __forceinline__ uint32_t tagged_key(double x, uint32_t who)
+{
+    uint32_t r;
+    asm("v_cvt_u32_f64_e32 %0, %1\n\tv_and_or_b32 %0, %0, -16, %2" : "=&v"(r) : "v"(x), "v"(who));
+    return r;
+}
+
 // Run records reach the chain through a ring in LDS.  A load that the chain issued itself would have to be
-// awaited through the counter its row stores also use, that is, at once and at full memory latency, which is
-// long while another batch's copies saturate the memory.  The feeder stays at most kRingRecords ahead, the chain
-// waits only for a record that is not there yet.  Neither wait depends on the waiting wavefront itself, and both
-// loops end with the run table (the chain at the record behind it).
-__device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const LevelModel& lm, RecordRing& ring, uint32_t lane)
+// awaited at full memory latency, which is long while another batch's copies saturate the memory.  The feeder goes ahead of
+// the chain, as far as the ring allows.  None of the waits depends on the waiting wavefront itself: the feeder waits for room,
+// which the chain (more than 16 rails) or the drainer (up to 16) makes for records that are written, the chain for records
+// that are not, the drainer for the chain; and all loops end with the run table.
+template <int kWide, class Ring>
+__device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const LevelModel& lm, Ring& ring, uint32_t lane)
 {
     const uint32_t n_runs = (uint32_t)b.plan->n_runs;
     const bool pending = (mode & kBindUsePending) != 0;
     const double step = (double)(1ull << kStepBits);
-    uint32_t written = 0;
+    uint32_t written = 0, block = 0;
     // of the last record written: its level, whether it served, and the slice length of the last run of several slices
     double last_level = 0.0;
     bool last_served = false;
     uint32_t last_len = 0;
+    double last_run_level = 0.0;           // and the level of that run
     auto wait_for_room = [&](uint32_t count) {
-        while (written + count - __hip_atomic_load(&ring.taken, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) > kRingRecords)
-            __builtin_amdgcn_s_sleep(4);
+        if constexpr (kWide > 16) {
+            while (written + count - __hip_atomic_load(&ring.taken, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) > kRingRecords)
+                __builtin_amdgcn_s_sleep(4);
+        } else {
+            while (block - __hip_atomic_load(&ring.drained, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= kRingBlocks)
+                __builtin_amdgcn_s_sleep(2);
+        }
     };
-    auto from_lane = [](double x, int at) -> double { return __shfl(x, at, 64); };
+    // what the run table says about the lane's run: read a block ahead, two levels of loads
+    struct Run { uint32_t before, start, end, after, len, len_after; uint64_t bytes; };
+    auto places = [&](uint32_t at, Run& v) {
+        const uint32_t r = at + lane < n_runs ? at + lane : n_runs - 1;
+        v.start = b.run_start[r];
+        v.end = b.run_start[r + 1];
+        v.after = r + 1 < n_runs ? b.run_start[r + 2] : v.end;
+        v.before = r > 0 ? b.run_start[r - 1] : v.start;
+    };
+    auto lengths = [&](Run& v) {
+        v.len = b.s_len[pending ? b.pending[v.start] : v.start];
+        v.len_after = v.after > v.end ? b.s_len[pending ? b.pending[v.end] : v.end] : 0;
+        v.bytes = pending ? b.len_pre[v.start] : b.s_pos[v.start];
+    };
+    Run now, next;
+    if (n_runs > 0) {
+        places(0, now);
+        lengths(now);
+        places(kFeedBlock, next);
+    }
     for (uint32_t at = 0; at < n_runs; at += kFeedBlock) {
         const bool here = at + lane < n_runs;
         const uint32_t r = here ? at + lane : n_runs - 1;
-        const uint32_t start = b.run_start[r], end = b.run_start[r + 1];
-        const uint32_t after = r + 1 < n_runs ? b.run_start[r + 2] : end;
-        const uint32_t before = r > 0 ? b.run_start[r - 1] : start;
-        const uint32_t len = b.s_len[pending ? b.pending[start] : start];
-        const uint32_t len_after = after > end ? b.s_len[pending ? b.pending[end] : end] : 0;
-        const double bytes = (double)(pending ? b.len_pre[start] : b.s_pos[start]);
-        const uint32_t m = end - start;
+        const Run run = now;
+        if (at + kFeedBlock < n_runs) {
+            now = next;
+            lengths(now);
+            places(at + 2 * kFeedBlock, next);
+        }
+        const uint32_t m = run.end - run.start;
         const bool single = m == 1;
-        const bool joined = single && start - before > 1;            // bound together with the run before it
-        const bool has_tail = !single && after - end == 1;
-        const uint32_t tail = single ? len : has_tail ? len_after : 0;
-        const double l_f = (double)len;
+        const bool joined = single && run.start - run.before > 1;    // bound together with the run before it
+        const bool has_tail = !single && run.after - run.end == 1;
+        const uint32_t tail = single ? run.len : has_tail ? run.len_after : 0;
+        const double l_f = (double)run.len;
+        const double bytes = (double)run.bytes;
         const double v = level_at(lm, bytes + (double)m * l_f, 0.5 * l_f), v_before = level_at(lm, bytes, 0.0);
         const bool valid = v >= 0.0 && v < kMaxLevel;
         const bool serves = valid && v - v_before < step && m < kLevelRunMax && l_f * lm.max_c1 < step * kUnit;
-        const double level = valid ? __builtin_floor(v) : 0.0;
+        double level = valid ? __builtin_floor(v) : 0.0;
         // the records written before this one: the lane below among those that are written, or the last block's last
         const uint64_t written_mask = __ballot(here && !joined), run_mask = __ballot(here && !single);
         const uint64_t served_mask = __ballot(serves);
@@ -292,42 +401,108 @@ __device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const 
         const uint64_t prev_mask = written_mask & below, prev_run_mask = run_mask & below;
         const int prev = prev_mask ? 63 - __clzll((long long)prev_mask) : -1;
         const int prev_run = prev_run_mask ? 63 - __clzll((long long)prev_run_mask) : -1;
-        const double level_there = from_lane(level, prev < 0 ? 0 : prev);
-        const uint32_t len_there = __shfl(len, prev_run < 0 ? 0 : prev_run, 64);
-        const double prev_level = prev < 0 ? last_level : level_there;
+        const uint32_t len_there = __shfl(run.len, prev_run < 0 ? 0 : prev_run, 64);
         const bool prev_served = prev < 0 ? last_served : ((served_mask >> (prev < 0 ? 0 : prev)) & 1) != 0;
         const uint32_t prev_len = prev_run < 0 ? last_len : len_there;
+        // Up to 16 rails a single slice can go as a run of no slices behind the last run: at that run's level, below which no slot
+        // is free any more, as long as the slice's cost is not too far above it.  That costs twice what walk_singles takes for a
+        // slice, but a change from runs to single slices and back costs as much as two slices, so it is for up to three in a row.
+        bool no_run = false;
+        if constexpr (kWide == 16) {
+            const uint64_t runs_behind = run_mask & ~below;
+            const uint64_t between = written_mask & (prev_run < 0 ? ~0ull : ~((2ull << prev_run) - 1)) &
+                                     (runs_behind ? (1ull << (__ffsll((long long)runs_behind) - 1)) - 1 : ~0ull);
+            const double level_run = from_lane(level, prev_run < 0 ? 0 : prev_run);
+            const double at_run = prev_run < 0 ? last_run_level : level_run;
+            no_run = single && __popcll(between) <= 3 && serves && prev_served && prev_len != 0 && (v - at_run) * (kUnit / kFineUnit) <= 0.5 * kMaxStep &&
+                     (double)tail * lm.max_c1 <= 0.25 * kMaxStep * kFineUnit &&
+                     (double)prev_len * (lm.max_c1 + lm.min_c1) <= kMaxStep * kFineUnit;
+            if (run_mask) last_run_level = from_lane(level, 63 - __clzll((long long)run_mask));
+            level = no_run ? at_run : level;
+        }
+        const double level_there = from_lane(level, prev < 0 ? 0 : prev);
+        const double prev_level = prev < 0 ? last_level : level_there;
         // a block over which the level rises far is rebased record by record, any other at its start
         const double v_first = from_lane(v_before, 0), v_last = from_lane(v, 63);
         uint32_t flags = (single ? kRecSingle : 0u) | (has_tail ? kRecTail : 0u) | (serves ? 0u : kRecNoLevel);
-        if (prev < 0 || !prev_served || !(v_last - v_first < step)) flags |= kRecRebase;
-        if (!single && prev_len == len) flags |= kRecSame;
-        const double shift = (prev_level - level) * kUnit;
-        wait_for_room(kFeedBlock);
-        if (here && !joined) {
-            Quad* out = ring.rec[(written + (uint32_t)__popcll(prev_mask)) % kRingRecords];
-            const double tail_f = (double)tail, inv = 1.0 / l_f;
-            out[0] = Quad{single ? 0u : m, flags, low_f64(shift), high_f64(shift)};
-            out[1] = Quad{low_f64(tail_f), high_f64(tail_f), r, 0u};
-            out[2] = Quad{low_f64(level), high_f64(level), len, tail};
-            out[3] = Quad{low_f64(inv), high_f64(inv), 0u, 0u};
+        if (!single && prev_len == run.len) flags |= kRecSame;
+        const uint32_t place = (uint32_t)__popcll(prev_mask);
+        const double inv = 1.0 / l_f;
+        if constexpr (kWide > 16) {
+            if (prev < 0 || !prev_served || !(v_last - v_first < step)) flags |= kRecRebase;
+            const double shift = (prev_level - level) * kUnit, tail_f = (double)tail;
+            wait_for_room(kFeedBlock);
+            if (here && !joined) {
+                Quad* out = ring.rec[(written + place) % kRingRecords];
+                out[0] = Quad{single ? 0u : m, flags, low_f64(shift), high_f64(shift)};
+                out[1] = Quad{low_f64(tail_f), high_f64(tail_f), r, 0u};
+                out[2] = Quad{low_f64(level), high_f64(level), run.len, tail};
+                out[3] = Quad{low_f64(inv), high_f64(inv), 0u, 0u};
+            }
+            written += (uint32_t)__popcll(written_mask);
+            __hip_atomic_store(&ring.filled, written, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else {
+            const double shift = (prev_level - level) * (kUnit / kFineUnit);
+            const double longest = (double)(tail > run.len ? tail : run.len);
+            const double rise = shift < 0.0 ? -shift : shift;
+            // (a rail that lies far above the level makes the chain rebase at the start of a block, or for every record of one over
+            // which the level rises far)
+            if (!prev_served || !(rise < step * (kUnit / kFineUnit))) flags |= kRecRebase;
+            const bool follows = serves && prev_served && !(flags & kRecRebase);
+            const bool run_fits = longest * (lm.max_c1 + lm.min_c1) <= kMaxStep * kFineUnit && rise < kMaxShift;
+            const bool same_fits = rise * kFineUnit < l_f * lm.min_c1 * kMaxSlots;
+            uint32_t take = !follows ? kTakeOdd : no_run ? kTakeSame : single ? kTakeSingle : !run_fits ? kTakeOdd
+                                : flags == kRecShort && same_fits ? kTakeSame : kTakeRun;
+            // a stretch of few records goes with the runs around it: a change of the way costs as much as a record
+            const uint64_t others = written_mask & ~__ballot(take == kTakeSame);
+            const uint64_t other_before = others & below, other_behind = others & ~below;
+            const uint64_t stretch = written_mask & (other_before ? ~((2ull << (63 - __clzll((long long)other_before))) - 1) : ~0ull) &
+                                     (other_behind ? (1ull << (__ffsll((long long)other_behind) - 1)) - 1 : ~0ull);
+            if (take == kTakeSame && __popcll(stretch) < 4) take = kTakeRun;
+            // how many records from here on may be taken the same way
+            const uint64_t same = __ballot(take == kTakeSame), runs = __ballot(take == kTakeRun), singles = __ballot(take == kTakeSingle);
+            const uint64_t alike = take == kTakeSame ? same : take == kTakeRun ? runs : take == kTakeSingle ? singles : 0;
+            const uint64_t stops = written_mask & ~alike & ~below;
+            const uint64_t until = stops ? (1ull << (__ffsll((long long)stops) - 1)) - 1 : ~0ull;
+            flags |= (take << kRecTake) | ((uint32_t)__popcll(written_mask & ~below & until) << kRecCount);
+            wait_for_room(0);
+            const uint32_t slot = block % kRingBlocks;
+            if (here && !joined) {
+                StepRing::Record& out = ring.rec[slot * kFeedBlock + place];
+                // (a single slice that goes as a run of none has the last run's slice length)
+                const uint32_t l_step = no_run ? prev_len : take == kTakeSingle ? 0u : run.len, l_run = no_run ? prev_len : run.len;
+                const double inv_l = no_run ? 1.0 / (double)prev_len : inv;
+                const uint32_t near_key = saturating_u32(fma((double)l_run * lm.min_c1, 1.0 / kFineUnit, kBias + 16.0)) & ~15u;
+                out.step = Quad{low_f64(shift), high_f64(shift), tail - l_step, single ? 0u : m};
+                out.run = Quad{low_f64(inv_l), high_f64(inv_l), l_run, near_key};
+                out.level = Quad{low_f64(level), high_f64(level), tail, r};
+                out.flags = flags;
+                out.single = kStepped;
+            }
+            ring.count[slot] = (uint32_t)__popcll(written_mask) | (at + kFeedBlock < n_runs ? 0u : kLastBlock) |
+                               (v_last - v_first < step ? 0u : kSteepBlock);
+            ++block;
+            __hip_atomic_store(&ring.filled, block, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        written += (uint32_t)__popcll(written_mask);
         if (written_mask) {
             const int last = 63 - __clzll((long long)written_mask);
             last_level = from_lane(level, last);
             last_served = ((served_mask >> last) & 1) != 0;
         }
-        if (run_mask) last_len = __shfl(len, 63 - __clzll((long long)run_mask), 64);
-        __hip_atomic_store(&ring.filled, written, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (run_mask) last_len = __shfl(run.len, 63 - __clzll((long long)run_mask), 64);
     }
-    wait_for_room(1);
-    if (lane == 0) {
-        Quad* out = ring.rec[written % kRingRecords];
-        out[0] = Quad{0u, kRecEnd, 0u, 0u};
-        out[1] = out[2] = out[3] = Quad{0u, 0u, 0u, 0u};
+    if constexpr (kWide > 16) {
+        wait_for_room(1);
+        if (lane == 0) {
+            Quad* out = ring.rec[written % kRingRecords];
+            out[0] = Quad{0u, kRecEnd, 0u, 0u};
+            out[1] = out[2] = out[3] = Quad{0u, 0u, 0u, 0u};
+        }
+        __hip_atomic_store(&ring.filled, written + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else if (n_runs == 0) {
+        ring.count[0] = kLastBlock;
+        __hip_atomic_store(&ring.filled, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    __hip_atomic_store(&ring.filled, written + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // ---- the chain ---------------------------------------------------------------------------------
@@ -443,14 +618,6 @@ constexpr double kKeyUnit = 1.0 / 1024.0;
 constexpr double kSingleBias = (double)(1ull << 31);   // single slices: the window reaches 2^25 ps to either side of the level
 constexpr int kRepairMax = 8;              // slots added or dropped one by one before the general path takes over
 
-// v_cvt_u32_f64: truncates; values below zero, minus infinity and not-a-number give 0, above 2^32 - 1 saturate.
-__device__ __forceinline__ uint32_t saturating_u32(double x)
-{
-    uint32_t r;
-    asm("v_cvt_u32_f64_e32 %0, %1" : "=v"(r) : "v"(x));
-    return r;
-}
-
 // What the next byte of a rail with A bytes queued would cost, relative to the level, in units of 2^-16 ps, exactly (A c1 is,
 // by the plan's precondition); infinity for a rail that is far above the level or takes no slices, not-a-number for
 // one far below it (every key made from it then comes out below 64, which sends the run or slice to the integers).
@@ -510,7 +677,28 @@ __device__ __attribute__((noinline)) uint32_t odd_single(Rail rail, uint64_t end
     return (uint32_t)argmin_cost(rail.c0 + ((end * (uint64_t)rail.c1) >> 16), live, lane, kWide);
 }
 
-// kWide = 16, 32 or 64: lanes that can hold a rail; with 16 every reduction stays inside one DPP row.
+// Per-rail totals and staging region bases (exclusive sum of 256-byte-rounded totals), lane = rail.
+template <int kWide>
+__device__ __forceinline__ void write_totals(const BatchDev& b, int lane, uint64_t queued, uint64_t bound, uint32_t cnt,
+                                             uint64_t n_bound)
+{
+    const uint64_t rounded = (bound + 255) & ~255ull;
+    uint64_t inc = rounded;
+#pragma unroll
+    for (int d = 1; d < kWide; d <<= 1) {
+        uint64_t up = (uint64_t)__shfl_up((unsigned long long)inc, d, 64);
+        if (lane >= d) inc += up;
+    }
+    PlanState* ps = b.plan;
+    ps->T[lane] = bound;
+    ps->cnt[lane] = cnt;
+    ps->A_after[lane] = queued + bound;
+    ps->base[lane] = inc - rounded;
+    if (lane == 0) ps->n_bound = n_bound;
+}
+
+// More than 16 rails (kWide = 32 or 64: lanes that can hold a rail; up to 16 go through bind_chain16 below, whose ranks and
+// replicated state need the rails in one row of 16 lanes).
 // Runs in lanes 0 .. kWide-1 of the first wavefront of a workgroup; the other lanes leave at once.
 //
 // The loop is a chain of dependent instructions on one wavefront that leaves the device idle, so what bounds a plan
@@ -521,9 +709,8 @@ __device__ __attribute__((noinline)) uint32_t odd_single(Rail rail, uint64_t end
 // key; what depends on the slice length only is kept from run to run; two 16-byte record reads ahead of their use, by all
 // lanes at one address; one 16-byte row store per transfer; and everything unusual behind one test of the record's flags.
 // Bytes bound (T) are whole numbers below 2^53, which convert_rails sees to, so a double holds them exactly.
-// About 110 instructions and 270 ns per transfer of a run and a tail on MI355X with 16 rails, from 190 and 510 ns when the state
-// was kept in 64-bit integers and every single slice had a record and a row of its own: 24,576 transfers 12.62 -> 6.46 ms,
-// 4,096 transfers 2.34 -> 1.15 ms, 2,048 transfers on 9 rails 1.18 -> 0.52 ms.
+// About 110 instructions and 270 ns per transfer of a run and a tail on MI355X (measured with 16 rails when those came this way),
+// from 190 and 510 ns when the state was kept in 64-bit integers and every single slice had a record and a row of its own.
 template <int kWide>
 __device__ __forceinline__ void bind_chain(const BatchDev& b, const RailParams& rp, int mode, RecordRing& ring)
 {
@@ -673,37 +860,518 @@ __device__ __forceinline__ void bind_chain(const BatchDev& b, const RailParams& 
         q1 = ring.rec[at % kRingRecords][1];
     }
 
-    // per-rail totals and staging region bases (exclusive sum of 256-byte-rounded totals)
-    const uint64_t bound = (uint64_t)T;
-    const uint64_t rounded = (bound + 255) & ~255ull;
-    uint64_t inc = rounded;
-#pragma unroll
-    for (int d = 1; d < kWide; d <<= 1) {
-        uint64_t up = (uint64_t)__shfl_up((unsigned long long)inc, d, 64);
-        if (lane >= d) inc += up;
+    write_totals<kWide>(b, lane, A_less_T, (uint64_t)T, cnt, b.plan->n_pending + n_before);
+}
+
+// ---- the chain of up to 16 rails -------------------------------------------------------------------
+// All-reduce over rows of 16 lanes.
+template <class Op>
+__device__ __forceinline__ uint32_t row_reduce32(uint32_t v, Op op) { return wave_reduce32(v, 16, op); }
+
+// The cross-lane part of a step, for a wavefront whose four rows of 16 lanes hold the same state.  From the guess u of the slots
+// (below zero: none): kk, the whole slots; p_next = Y0 + kk lc1, where the slot behind them ends, and key, its key; sum, kk
+// over the rails; returns how many rails have a smaller key (keys are distinct and less than 2^31 apart).
+// Row r compares with the lanes 4 r .. 4 r + 3 further on; a byte of each difference's sign is gathered, and one matrix
+// instruction adds up (-1) (-1) over the bytes of all four rows.  One block of assembler, so that the wait states between a
+// register's write and its use by a cross-lane (DPP) instruction -- two instructions -- are filled by hand: kk is used four
+// instructions behind its conversion, key and turned two behind their last write, sum's steps two and more apart.
+typedef int Int4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ Int4 rank_next_slots(double u, double lc1, double Y0, uint32_t who, uint32_t& kk, uint32_t& key,
+                                                double& p_next, uint32_t& sum)
+{
+    uint32_t turned, d0, d1, d2, d3, half;
+    double kf;
+    asm("v_cvt_u32_f64_e32 %[kk], %[u]\n\t"
+        "v_cvt_f64_u32_e32 %[kf], %[kk]\n\t"
+        "v_fma_f64 %[pn], %[kf], %[lc1], %[Y0]\n\t"
+        "v_cvt_u32_f64_e32 %[key], %[pn]\n\t"
+        "v_and_or_b32 %[key], %[key], -16, %[who]\n\t"
+        "v_add_u32_dpp %[half], %[kk], %[kk] quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_mov_b32_e32 %[tu], %[key]\n\t"
+        "v_mov_b32_dpp %[tu], %[key] row_ror:4 row_mask:0x2 bank_mask:0xf\n\t"
+        "v_mov_b32_dpp %[tu], %[key] row_ror:8 row_mask:0x4 bank_mask:0xf\n\t"
+        "v_mov_b32_dpp %[tu], %[key] row_ror:12 row_mask:0x8 bank_mask:0xf\n\t"
+        "v_add_u32_dpp %[half], %[half], %[half] quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_sub_u32_e32 %[d0], %[tu], %[key]\n\t"
+        "v_sub_u32_dpp %[d1], %[tu], %[key] row_ror:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_sub_u32_dpp %[d2], %[tu], %[key] row_ror:2 row_mask:0xf bank_mask:0xf\n\t"
+        "v_sub_u32_dpp %[d3], %[tu], %[key] row_ror:3 row_mask:0xf bank_mask:0xf"
+        : [kk] "=&v"(kk), [key] "=&v"(key), [half] "=&v"(half), [tu] "=&v"(turned), [d0] "=&v"(d0), [d1] "=&v"(d1),
+          [d2] "=&v"(d2), [d3] "=&v"(d3), [kf] "=&v"(kf), [pn] "=&v"(p_next)
+        : [u] "v"(u), [lc1] "v"(lc1), [Y0] "v"(Y0), [who] "v"(who));
+    // bytes: 0xFF where a difference is negative, else 0 (selectors 11 and 9: the sign of either operand, 12: zero)
+    const uint64_t signs = (uint64_t)__builtin_amdgcn_perm(d0, d1, 0x0C0C0B09u) |
+                           ((uint64_t)__builtin_amdgcn_perm(d2, d3, 0x0C0C0B09u) << 32);
+    const Int4 none = {0, 0, 0, 0};
+    const Int4 rank = __builtin_amdgcn_mfma_i32_16x16x32_i8(-1l, (long)signs, none, 0, 0, 0);
+    half += dpp32<0x141>(half);
+    sum = half + dpp32<0x140>(half);
+    return rank;                           // four times the same
+}
+
+// The loop is a chain of dependent instructions on one wavefront that leaves the device idle.  A lone wavefront issues an
+// instruction every 4-5 cycles whatever its kind, a wait state of a cross-lane step costs as much, a branch on a fresh comparison 25
+// more.  So what bounds a plan of many transfers is the number of instructions between one transfer's state and the
+// next one's, and the short path (walk) is made of as few as possible, without a branch but the one that checks it:
+//   - the guess is taken at a level that is meant to be a little too low (LevelModel::short_by), so that slots are only ever
+//     added; all of them at once, to the rails whose next slots are the cheapest, by rank instead of one by one;
+//   - all four rows of the wavefront hold the rails' state, and each compares a quarter of the pairs (rank_next_slots);
+//   - the guess is exact by its arithmetic (below), so it needs no check; that no rail lacks two slots is seen from the keys;
+//   - whatever the chain finds is left in LDS, and a third wavefront, the drainer, derives the bytes bound from it and writes the
+//     rows, so that the state here is one number per rail.
+// State: X, the cost of the rail's next byte, in units of 2^-4 ps above kBias below the level, a whole multiple of 2^-12 and held
+// exactly (infinity: the rail takes no slices or lies far above the level; the bytes queued are then in A_far).
+//   Guess: slot j ends at X + (j + 1) lc1 and costs no more than the level iff that is below kBias + 16, so kk = trunc(Q),
+//   Q = (N - X) / lc1 with N half a unit (2^-13) below that.  Q is at least 2^-13 / lc1 off the whole numbers; its computed
+//   value is off by less than (|N - X| 2^-51 + 2^-22) / lc1, which is less while |N - X| < 2^37: kMaxShift and the test of
+//   `tight` see to that.  (Below zero both give 0.)
+//   Taken: the run takes the guessed slots and the m - sum cheapest of the rails' next ones, if no rail takes two of those:
+//   its second one costs more than the level by at least the smallest lc1, so keys below near_key are all in order.
+//   Single slice: after the split every rail's next slot ends above the level and some rail's last one below near_key, so by
+//   kMaxStep no key lies below the window, the least one lies inside it, and it is the cheapest.
+// MI355X: about 65 instructions and 310 clocks (125 ns) per transfer of a run and a tail, from 110 and 640 with one-by-one
+// repairs and the bytes bound kept here: reset, plan and execute of 24,576 transfers on 16 rails 15.5 -> 11.6 ms, of 4,096 2.68
+// -> 2.04 ms, of 2,048 shorter by partial pages 1.44 -> 1.06 ms.  What is not a stretch of equal slice lengths goes through
+// walk_runs (about 600 clocks a record) and walk_singles (290), and only the first record, one behind a rebase, and a guess
+// off by more than a few slots through odd_record (1,100); a change of the way costs about 250, a plan of 50 runs takes what
+// it took.
+struct ChainState {
+    double X, lc1, inv, kf0;
+    uint32_t near_key;
+};
+
+// A run or single slice the short path does not take.  Out of line, like everything the loop seldom needs.
+struct OddSplit {
+    uint32_t kk;
+    uint64_t A;
+};
+__device__ __attribute__((noinline)) OddSplit general_split16(Rail rail, bool live, uint64_t A, int lane, uint32_t l, uint32_t m,
+                                                              bool serves, double level, double inv_l)
+{
+    // (in the first row alone: the general path counts lanes)
+    uint32_t kk = 0;
+    if (lane < 16) kk = bind_run_general<16>(0, 1u, rail, live, A, lane, l, m, serves, level, inv_l);
+    kk = (uint32_t)__shfl((int)kk, lane & 15, 64);
+    return OddSplit{kk, A + (uint64_t)kk * l};
+}
+
+// Runs in all lanes of the first wavefront of a workgroup: lane % 16 = rail.
+__device__ __forceinline__ void bind_chain16(const BatchDev& b, const RailParams& rp, int mode, StepRing& ring)
+{
+    const int lane = threadIdx.x;
+    const uint32_t who = (uint32_t)lane & 15u;
+    const bool live = who < rp.n_rails && ((rp.admitted >> who) & 1);
+    Rail rail;
+    rail.c0 = rp.c0[who];
+    rail.c1 = live ? (uint32_t)rp.c1[who] : 1u;
+    rail.inv_c1 = 1.0 / (double)rail.c1;
+    const double c1 = (double)rail.c1 * (1.0 / kFineUnit);
+    uint64_t A_far = rp.A[who];                               // bytes queued on a rail whose X is infinite
+    if (mode & kBindAfterRotation) A_far += b.plan->Tr[who];
+    ChainState st{__builtin_inf(), 0.0, 0.0, 0.0, 0u};
+    double l_f = 0.0;                                         // length of the last run's slices
+
+    // X from the bytes queued, for a level; and the bytes queued from X and the level it refers to.
+    auto set_state = [&](uint64_t A, double level) {
+        const double x = relative_cost(rail, live, A, level);            // not-a-number: far below the level
+        const bool known = x - x == 0.0;
+        st.X = known ? fma(x, 1.0 / kFineUnit, kBias) : __builtin_inf();
+        A_far = A;
+        return __builtin_amdgcn_ballot_w64(x != x) != 0;                  // such a rail: the keys cannot be used
+    };
+    auto queued = [&](double level) -> uint64_t {
+        // A c1 = X / 2^-16 ps + (level - c0) 2^16: exact in 64-bit arithmetic with wrap, and below 2^63
+        const double rel = (st.X - kBias) * kFineUnit;
+        const uint64_t P = (uint64_t)(int64_t)(st.X < 1.0e300 ? rel : 0.0) + (((uint64_t)level - rail.c0) << 16);
+        uint64_t q = (uint64_t)((double)P * rail.inv_c1);                 // off by a few units at most
+        const int64_t rest = (int64_t)(P - q * rail.c1);                  // a multiple of c1
+        q += (uint64_t)(int64_t)__builtin_rint((double)rest * rail.inv_c1);
+        return st.X < 1.0e300 ? q : A_far;
+    };
+
+    // One record by the checked way.
+    auto odd_record = [&](uint32_t at, bool rebase) {
+        const Quad s = ring.rec[at].step, r0 = ring.rec[at].level, r1 = ring.rec[at].run;
+        const uint32_t flags = (uint32_t)__builtin_amdgcn_readfirstlane((int)ring.rec[at].flags);
+        const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.w);
+        const double level = join_f64(r0.x, r0.y), shift = join_f64(s.x, s.y), inv_l = join_f64(r1.x, r1.y);
+        const uint32_t l = r1.z, tail = r0.z;
+        const bool serves = !(flags & kRecNoLevel);
+        bool usable = serves;
+        if (rebase || (flags & kRecRebase) || !serves) {
+            const uint64_t A = queued(level + shift * (kFineUnit / kUnit));   // (the level of the record before)
+            if (set_state(A, level)) usable = false;
+            if (!usable) st.X = __builtin_inf();
+        } else {
+            st.X += shift;
+        }
+        uint32_t kk = 0, best = 0;
+        if (!(flags & kRecSingle)) {
+            l_f = (double)l;
+            st.lc1 = l_f * c1;                                            // whole multiples of 2^-12, below 2^41 where the record serves
+            st.inv = inv_l * rail.inv_c1 * kFineUnit;
+            st.kf0 = kGuessAt * st.inv;
+            st.near_key = r1.w;
+            bool done = false;
+            if (usable) {
+                // guess, then one slot at a time: the cheapest free one, or the dearest taken one
+                uint32_t k = saturating_u32(fma(-st.X, st.inv, st.kf0));
+                k = k < kLevelRunMax ? k : kLevelRunMax;
+                double p_next = fma((double)k, st.lc1, st.X) + st.lc1;    // where the cheapest free slot ends; the dearest taken one: lc1 before
+                auto down_key = [&]() { return k != 0 ? tagged_key(kDownFrom + st.lc1 - p_next, 15u - who) : ~0u; };
+                uint32_t my_up = tagged_key(p_next, who), my_down = down_key();
+                const uint32_t sum = row_reduce32(k, Add32{}), level_key = (uint32_t)kBias + 16u;
+                uint32_t farthest = 0;
+                int left = __builtin_amdgcn_readfirstlane((int)(m - sum));
+                if (left >= -kRepairMax && left <= kRepairMax && __builtin_amdgcn_ballot_w64(my_up < level_key || my_down < level_key) == 0) {
+                    for (; left > 0; --left) {
+                        const uint32_t up = row_reduce32(my_up, Min32{});
+                        const double beyond = p_next + st.lc1;
+                        farthest = up > farthest ? up : farthest;
+                        k += my_up == up ? 1u : 0u;
+                        p_next = my_up == up ? beyond : p_next;
+                        my_up = tagged_key(p_next, who);
+                    }
+                    for (; left < 0; ++left) {
+                        const uint32_t down = row_reduce32(my_down, Min32{});
+                        const double before = p_next - st.lc1;
+                        farthest = down > farthest ? down : farthest;
+                        k -= my_down == down ? 1u : 0u;
+                        p_next = my_down == down ? before : p_next;
+                        my_down = down_key();
+                    }
+                    done = __builtin_amdgcn_ballot_w64(farthest >= kFarKey16) == 0;
+                }
+                if (done) { kk = k; st.X = p_next - st.lc1; }
+            }
+            if (!done) {
+                const OddSplit g = general_split16(rail, live, queued(level), lane, l, m, serves, level, inv_l);
+                kk = g.kk;
+                usable = !set_state(g.A, level) && serves;
+                if (!usable) st.X = __builtin_inf();
+            }
+        }
+        if (tail != 0) {
+            const double t = (double)tail, y = fma(t, c1, st.X);
+            uint32_t mine = (saturating_u32(y) & ~15u) | who;
+            best = row_reduce32(mine, Min32{});
+            // outside the window (or a state that does not serve): compare whole costs
+            if (!usable || __builtin_amdgcn_ballot_w64(best - 16u >= kFarKey16 - 16u) != 0) {
+                const uint64_t A = queued(level);
+                best = odd_single<16>(rail, A + tail, live, (int)who);
+                mine = who;
+                if (mine == best) A_far = A + tail;
+            }
+            st.X = mine == best ? y : st.X;
+        }
+        if (!usable) st.X = __builtin_inf();                              // (A_far holds the bytes)
+        if (lane < 16) ring.found[at][who] = kk;
+        ring.rec[at].single = best;
+        return usable;                                                    // if not, the next record rebases
+    };
+    // Whether the heads lie where a guess is exact and not too large.
+    auto is_tight = [&]() {
+        const double below = kBias - st.X;
+        return l_f != 0.0 && __builtin_amdgcn_ballot_w64(live && !(below < kMaxShift && below < st.lc1 * kMaxSlots)) == 0;
+    };
+
+    // Records [at, at + n) of runs with the last one's slice length: returns how many it took, fewer than n if one did not pass
+    // its check.  Four records share a check, and each keeps the state it leaves, for the case that a later one does not pass.
+    auto walk_same = [&](uint32_t at, uint32_t n) -> uint32_t {
+        double Y = st.X + st.lc1;                                          // where the rail's next slot would end
+        const double lc1 = st.lc1, inv = st.inv, kf0 = fma(lc1, inv, st.kf0);
+        const uint32_t near_key = st.near_key;
+        const StepRing::Record* rec = &ring.rec[at];
+        uint32_t* found = &ring.found[at][who];
+        Quad s = rec->step;
+        // One record: the state behind it, what it found, and the lanes that object to it.
+        auto one = [&](const StepRing::Record* next, double Y_in, double& Y_out, uint32_t& word) -> uint64_t {
+            const double Y0 = Y_in + join_f64(s.x, s.y), less = (double)(int)s.z;
+            const uint32_t m = s.w;
+            uint32_t kk, key, sum;
+            double pn;
+            const Int4 rank = rank_next_slots(fma(-Y0, inv, kf0), lc1, Y0, who, kk, key, pn, sum);
+            // while the ranks are summed: where the rail stands with the next slot and without, with the single slice and without
+            const double pn_more = pn + lc1, y = fma(less, c1, pn), y_more = fma(less, c1, pn_more);
+            const uint32_t mine_less = tagged_key(y, who), mine_more = tagged_key(y_more, who);
+            const uint32_t lacking = m - sum;
+            const bool takes = rank[0] < (int)lacking;
+            asm volatile("" : : "v"(rank));                                // (its registers are not reused before: that would wait)
+            const uint64_t bad = (__builtin_amdgcn_ballot_w64(takes) & __builtin_amdgcn_ballot_w64(key >= near_key)) |
+                                 __builtin_amdgcn_ballot_w64(lacking > 15u);
+            const uint32_t mine = takes ? mine_more : mine_less;
+            s = next->step;
+            double Y1 = takes ? pn_more : pn, won = (takes ? y_more : y) + lc1;
+            kk += takes ? 1u : 0u;
+            asm volatile("" : "+v"(Y1), "+v"(won), "+v"(kk));              // here, where they fill the wait states of the minimum
+            const uint32_t best = row_reduce32(mine, Min32{});
+            Y_out = mine == best ? won : Y1;
+            word = (best << kBitsOfSlots) | kk;
+            return bad | __builtin_amdgcn_ballot_w64(best >= kFarKey16);
+        };
+        uint32_t left = n;
+        for (; left >= 4; left -= 4) {
+            double Y1, Y2, Y3, Y4;
+            uint32_t w1, w2, w3, w4;
+            const uint64_t b1 = one(rec + 1, Y, Y1, w1), b2 = one(rec + 2, Y1, Y2, w2);
+            found[0] = w1;
+            found[16] = w2;
+            const uint64_t b3 = one(rec + 3, Y2, Y3, w3), b4 = one(rec + 4, Y3, Y4, w4);
+            found[32] = w3;                                                // (written again if the record does not pass)
+            found[48] = w4;
+            if (__builtin_expect((b1 | b2 | b3 | b4) != 0, 0)) {
+                if (b1 == 0) { Y = Y1; --left; if (b2 == 0) { Y = Y2; --left; if (b3 == 0) { Y = Y3; --left; } } }
+                st.X = Y - lc1;
+                return n - left;
+            }
+            Y = Y4;
+            rec += 4;
+            found += 64;
+        }
+        for (; left != 0; --left) {
+            double Y1;
+            uint32_t w1;
+            const uint64_t b1 = one(rec + 1, Y, Y1, w1);
+            found[0] = w1;
+            if (b1 != 0) break;
+            Y = Y1;
+            ++rec;
+            found += 16;
+        }
+        st.X = Y - lc1;
+        return n - left;
+    };
+
+    // Records of runs of any slice length, with a single slice behind them or not, one by one.  Where some rail lacks two slots
+    // they are added one by one, to the cheapest free one each time; where the guess took too many (rails that the last run left
+    // far above the level, in terms of this run's shorter slices, make the level too high) the dearest are dropped one by one.
+    auto walk_runs = [&](uint32_t at, uint32_t n) -> uint32_t {
+        const StepRing::Record* rec = &ring.rec[at];
+        uint32_t* found = &ring.found[at][who];
+        uint32_t left = n;
+        for (; left != 0; --left, ++rec, found += 16) {
+            const Quad s = rec->step, r = rec->run;
+            const uint32_t near_key = r.w;
+            const double X0 = st.X + join_f64(s.x, s.y), len = (double)r.z;
+            const double lc1 = len * c1, inv = join_f64(r.x, r.y) * rail.inv_c1 * kFineUnit;
+            const double Y0 = X0 + lc1, kf0 = kGuessAt * inv;
+            uint32_t kk, key, sum;
+            double pn;
+            const Int4 rank = rank_next_slots(fma(-X0, inv, kf0), lc1, Y0, who, kk, key, pn, sum);
+            const uint32_t lacking = s.w - sum;
+            // (a rail that does not take slices or lies far above the level has an infinite head)
+            const bool odd = (lacking + (uint32_t)kRepairMax > 15u + (uint32_t)kRepairMax) | !(kBias - X0 < kMaxShift) | (kk >= (uint32_t)kMaxSlots);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) break;
+            const bool takes = rank[0] < (int)lacking;
+            double X1 = takes ? pn : pn - lc1;
+            if (__builtin_amdgcn_ballot_w64((takes & (key >= near_key)) | ((int)lacking < 0)) == 0) {
+                kk += takes ? 1u : 0u;
+            } else {
+                uint32_t last = 0;
+                int more = __builtin_amdgcn_readfirstlane((int)lacking);
+                for (; more > 0; --more) {
+                    last = row_reduce32(key, Min32{});
+                    const double beyond = pn + lc1;
+                    kk += key == last ? 1u : 0u;
+                    pn = key == last ? beyond : pn;
+                    key = tagged_key(pn, who);
+                }
+                for (; more < 0; ++more) {                                 // 1 - floor(ps) of the last slot taken, 1 and up
+                    const uint32_t down = kk != 0 ? tagged_key(kDownFrom + lc1 - pn, 15u - who) : ~0u;
+                    const double before = pn - lc1;
+                    last = row_reduce32(down, Min32{});
+                    kk -= down == last ? 1u : 0u;
+                    pn = down == last ? before : pn;
+                }
+                if (__builtin_amdgcn_ballot_w64(last >= kFarKey16) != 0) break;
+                X1 = pn - lc1;
+            }
+            uint32_t word = kk;
+            if (__builtin_amdgcn_readfirstlane((int)(s.z + r.z)) != 0) {   // a single slice stands behind it
+                const double y = fma((double)(s.z + r.z), c1, X1);
+                const uint32_t mine = tagged_key(y, who), best = row_reduce32(mine, Min32{});
+                if (__builtin_amdgcn_ballot_w64(best >= kFarKey16) != 0) break;
+                X1 = mine == best ? y : X1;
+                word |= best << kBitsOfSlots;
+            }
+            *found = word;
+            st = ChainState{X1, lc1, inv, kf0, near_key};
+            l_f = len;
+        }
+        return n - left;
+    };
+
+    // Single slices, one by one: a plain argmin by keys, unless they lie outside the window.
+    auto walk_singles = [&](uint32_t at, uint32_t n) -> uint32_t {
+        const StepRing::Record* rec = &ring.rec[at];
+        uint32_t* found = &ring.found[at][who];
+        uint32_t left = n;
+        Quad s = rec->step;
+        for (; left != 0; --left) {
+            const double X0 = st.X + join_f64(s.x, s.y), y = fma((double)s.z, c1, X0);
+            const uint32_t mine = tagged_key(y, who);
+            ++rec;
+            s = rec->step;
+            const uint32_t best = row_reduce32(mine, Min32{});
+            *found = best << kBitsOfSlots;
+            found += 16;
+            const double X1 = mine == best ? y : X0;
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(best - 16u >= kFarKey16 - 16u) != 0, 0)) break;
+            st.X = X1;
+        }
+        return n - left;
+    };
+
+    bool rebase = true, tight = false;
+    for (uint32_t block = 0;; ++block) {
+        while (__hip_atomic_load(&ring.filled, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= block) __builtin_amdgcn_s_sleep(1);
+        const uint32_t slot = block % kRingBlocks, base = slot * kFeedBlock;
+        const uint32_t told = (uint32_t)__builtin_amdgcn_readfirstlane((int)ring.count[slot]);
+        const uint32_t n = told & ~(kLastBlock | kSteepBlock);
+        uint32_t flags = ring.rec[base].flags;
+        for (uint32_t i = 0; i < n;) {
+            // a rail far above the level counts as infinitely far: look again where it lies
+            if (i == 0 || (told & kSteepBlock)) rebase = rebase || __builtin_amdgcn_ballot_w64(live && !(st.X < 1.0e300)) != 0;
+            flags = (uint32_t)__builtin_amdgcn_readfirstlane((int)flags);
+            const uint32_t take = (flags >> kRecTake) & 3u;
+            uint32_t count = rebase || take == kTakeOdd ? 0u : flags >> kRecCount, went = 0;
+            if ((told & kLastBlock) && count > kWalkLast) count = kWalkLast;
+            if (count != 0) {
+                if (take == kTakeSame && (tight || is_tight())) {
+                    flags = ring.rec[base + i + count].flags;            // of the record behind, as a rule the next one to look at
+                    went = walk_same(base + i, count);
+                    tight = true;
+                    if (went < count) {
+                        flags = (kTakeRun << kRecTake) | (1u << kRecCount);   // not by ranks: with the repairs of walk_runs
+                        i += went;
+                        continue;
+                    }
+                } else if (take == kTakeSingle) {
+                    flags = ring.rec[base + i + count].flags;
+                    went = walk_singles(base + i, count);
+                    tight = false;
+                } else {
+                    count = take == kTakeSame ? 1u : count;
+                    flags = ring.rec[base + i + count].flags;
+                    went = walk_runs(base + i, count);
+                    tight = true;
+                }
+            }
+            i += went;
+            if (count == 0 || went < count) {                  // this one by the checked way
+                rebase = !odd_record(base + i, rebase);
+                tight = false;
+                ++i;
+                flags = ring.rec[base + i].flags;
+            }
+            if (told & kLastBlock)
+                __hip_atomic_store(&ring.walked, block * kFeedBlock + i, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        __hip_atomic_store(&ring.walked, (block + 1) * kFeedBlock, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (told & kLastBlock) break;
     }
-    PlanState* ps = b.plan;
-    ps->T[lane] = bound;
-    ps->cnt[lane] = cnt;
-    ps->A_after[lane] = A_less_T + bound;
-    ps->base[lane] = inc - rounded;
-    if (lane == 0) ps->n_bound = ps->n_pending + n_before;
 }
 
-// Wavefront 0 walks the chain, wavefront 1 feeds it the run records.
-template <int kWide>
-__device__ __forceinline__ void chain_workgroup(const BatchDev& b, const RailParams& rp, int mode, RecordRing& ring, LevelModel& lm)
+// The drainer: from the slots and single slices of every record the bytes bound to every rail before it, the row that the emit
+// step reads, and the plan's totals.  T, whole and below 2^53, is exact as a double.  Lane % 16 = rail; the first row writes.
+__device__ __forceinline__ void drain_steps16(const BatchDev& b, const RailParams& rp, int mode, StepRing& ring, uint32_t lane)
 {
-    if (threadIdx.x == 0) { ring.filled = 0; ring.taken = 0; }
-    build_level_model(lm, b, rp, mode);                              // (with barriers)
-    if (threadIdx.x < 64) bind_chain<kWide>(b, rp, mode, ring);
-    else if (threadIdx.x < 128) feed_records(b, mode, lm, ring, threadIdx.x - 64);
+    const uint32_t who = lane & 15u;
+    double T = 0.0;
+    uint32_t cnt = 0;
+    uint64_t n_before = 0;
+    if (mode & kBindAfterRotation) {          // the rotation pass went first: its bytes are queued and staged ahead
+        T = (double)b.plan->Tr[who];
+        cnt = (uint32_t)b.plan->cr[who];
+        n_before = b.plan->n_retry;
+    }
+    const uint64_t queued = rp.A[who], n_bound = b.plan->n_pending + n_before;
+    RunCell* const my_cell = b.run_cell + who;
+    const uint32_t stride = b.run_stride;
+    for (uint32_t block = 0;; ++block) {
+        while (__hip_atomic_load(&ring.filled, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= block) __builtin_amdgcn_s_sleep(1);
+        const uint32_t slot = block % kRingBlocks, base = slot * kFeedBlock;
+        const uint32_t told = (uint32_t)__builtin_amdgcn_readfirstlane((int)ring.count[slot]);
+        const uint32_t n = told & ~(kLastBlock | kSteepBlock);
+        for (uint32_t i = 0; i < n;) {
+            uint32_t ready;
+            while ((ready = (uint32_t)__builtin_amdgcn_readfirstlane(
+                        (int)__hip_atomic_load(&ring.walked, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP))) <= block * kFeedBlock + i)
+                __builtin_amdgcn_s_sleep(1);
+            ready -= block * kFeedBlock;
+            if (ready > n) ready = n;
+            // four records' reads at a time; the chain hands over few at a time where it changes its way often
+            for (; i < ready; i += 4) {
+                Quad r0[4];
+                uint32_t l[4], word[4], single[4];
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    const uint32_t at = base + (i + k < ready ? i + k : i);
+                    r0[k] = ring.rec[at].level;
+                    l[k] = ring.rec[at].run.z;
+                    single[k] = ring.rec[at].single;
+                    word[k] = ring.found[at][who];
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    if (i + k >= ready) break;
+                    const uint32_t tail = r0[k].z;
+                    const bool stepped = single[k] == kStepped;
+                    const uint32_t slots = stepped ? word[k] & ((1u << kBitsOfSlots) - 1) : word[k];
+                    const uint32_t rail = stepped ? word[k] >> kBitsOfSlots : single[k] & 15u;
+                    if (lane < 16) *(my_cell + (uint64_t)r0[k].w * stride) = RunCell{T, slots, rail};
+                    const bool won = rail == who && tail != 0;
+                    T = fma((double)slots, (double)l[k], T) + (won ? (double)tail : 0.0);
+                    cnt += slots + (won ? 1u : 0u);
+                }
+            }
+            i = ready;
+        }
+        __hip_atomic_store(&ring.drained, block + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (told & kLastBlock) break;
+    }
+    if (lane >= 16) return;
+    write_totals<16>(b, lane, queued, (uint64_t)T, cnt, n_bound);
 }
 
 template <int kWide>
-__global__ void __launch_bounds__(128) bind_chain_kernel(BatchDev b, RailParams rp, int mode)
+using Ring = std::conditional_t<kWide == 16, StepRing, RecordRing>;
+constexpr uint32_t kChainThreads = 192;
+
+// Clears the ring; a barrier follows before anyone uses it.
+__device__ __forceinline__ void start_ring(RecordRing& ring) { ring.filled = ring.taken = 0; }
+__device__ __forceinline__ void start_ring(StepRing& ring) { ring.filled = ring.walked = ring.drained = 0; }
+
+// Wavefront 0 walks the chain, wavefront 1 feeds it the run records, wavefront 2 drains it (up to 16 rails).
+template <int kWide>
+__device__ __forceinline__ void chain_waves(const BatchDev& b, const RailParams& rp, int mode, Ring<kWide>& ring, LevelModel& lm)
 {
-    __shared__ RecordRing ring;
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+    if (wave == 0) {
+        __builtin_amdgcn_s_setprio(3);                 // other workgroups' or wavefronts' work must not take its issue slots
+        if constexpr (kWide == 16) bind_chain16(b, rp, mode, ring);
+        else bind_chain<kWide>(b, rp, mode, ring);
+    } else if (wave == 1) {
+        __builtin_amdgcn_s_setprio(2);
+        feed_records<kWide>(b, mode, lm, ring, lane);
+    } else if (wave == 2) {
+        __builtin_amdgcn_s_setprio(2);
+        if constexpr (kWide == 16) drain_steps16(b, rp, mode, ring, lane);
+    }
+}
+
+template <int kWide>
+__device__ __forceinline__ void chain_workgroup(const BatchDev& b, const RailParams& rp, int mode, Ring<kWide>& ring, LevelModel& lm)
+{
+    if (threadIdx.x == 0) start_ring(ring);
+    build_level_model<kWide>(lm, b, rp, mode);                       // (with barriers)
+    chain_waves<kWide>(b, rp, mode, ring, lm);
+}
+
+template <int kWide>
+__global__ void __launch_bounds__(kChainThreads, 2) bind_chain_kernel(BatchDev b, RailParams rp, int mode)
+{
+    __shared__ Ring<kWide> ring;
     __shared__ LevelModel lm;
     chain_workgroup<kWide>(b, rp, mode, ring, lm);
 }
@@ -712,9 +1380,9 @@ __global__ void __launch_bounds__(128) bind_chain_kernel(BatchDev b, RailParams 
 // on the binding.  On a first plan both go into one launch: workgroup 0 walks the chain, the others
 // build the tables, so the tables cost no time of their own.
 template <int kWide>
-__global__ void __launch_bounds__(256) bind_chain_tables_kernel(BatchDev b, RailParams rp, int mode)
+__global__ void __launch_bounds__(256, 2) bind_chain_tables_kernel(BatchDev b, RailParams rp, int mode)
 {
-    __shared__ RecordRing ring;
+    __shared__ Ring<kWide> ring;
     __shared__ LevelModel lm;
     if (blockIdx.x == 0) {
         chain_workgroup<kWide>(b, rp, mode, ring, lm);
@@ -813,14 +1481,15 @@ __global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams r
 constexpr uint32_t kSmallThreads = 1024;
 constexpr uint32_t kSmallExtents = 2048;         // per side; two per thread
 constexpr uint32_t kSmallSlices = 2048;
-constexpr uint64_t kSmallTiles = 16384;          // 18 per thread that the chain and its feeder leave over
+constexpr uint64_t kSmallTiles = 16384;          // 20 per thread that the chain, its feeder and its drainer leave over
 
+template <int kWide>
 struct SmallPlan {
     uint64_t src_pre[kSmallExtents + 1], dst_pre[kSmallExtents + 1];
     uint32_t first[kSmallExtents + 1], runs_before[kSmallExtents + 1];
     uint64_t wave_out[kSmallThreads / 64];
     union {
-        RecordRing ring;
+        Ring<kWide> ring;
         EmitRails er;
     };
     LevelModel lm;
@@ -842,7 +1511,7 @@ __device__ __forceinline__ uint64_t pair_prefix(uint64_t v0, uint64_t v1, uint64
 template <int kWide>
 __global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, RailParams rp, PlanState* told)
 {
-    __shared__ SmallPlan sh;
+    __shared__ SmallPlan<kWide> sh;
     const uint32_t t = threadIdx.x, e0 = 2 * t, e1 = 2 * t + 1;
     const uint32_t ns = (uint32_t)b.n_src_ext, nd = (uint32_t)b.n_dst_ext, D = b.n_desc, N = (uint32_t)b.n_slices;
     {   // extent prefixes of both sides, and in address order where a table goes by it
@@ -897,14 +1566,13 @@ __global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, R
         b.run_start[n_runs] = N;
         b.plan->n_runs = n_runs;
         b.plan->n_pending = N;
-        sh.ring.filled = 0;
-        sh.ring.taken = 0;
+        start_ring(sh.ring);
     }
     __syncthreads();
-    build_level_model(sh.lm, b, rp, kBindBuildTables);
-    if (t < 64) bind_chain<kWide>(b, rp, kBindBuildTables, sh.ring);
-    else if (t < 128) feed_records(b, kBindBuildTables, sh.lm, sh.ring, t - 64);
-    else build_tile_tables(b, t - 128, kSmallThreads - 128);
+    build_level_model<kWide>(sh.lm, b, rp, kBindBuildTables);
+    if (t < kChainThreads) chain_waves<kWide>(b, rp, kBindBuildTables, sh.ring, sh.lm);
+    else build_tile_tables(b, t - kChainThreads, kSmallThreads - kChainThreads);
+    __builtin_amdgcn_s_setprio(0);
     __syncthreads();
     bind_emit(b, rp, 0, told, sh.er, t, kSmallThreads);
 }
@@ -945,7 +1613,7 @@ hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, P
         if (mode & kBindBuildTables)
             hipLaunchKernelGGL(bind_chain_tables_kernel<kW>, dim3(1 + tile_table_blocks(b)), dim3(256), 0, s, b, rp, mode);
         else
-            hipLaunchKernelGGL(bind_chain_kernel<kW>, dim3(1), dim3(128), 0, s, b, rp, mode);
+            hipLaunchKernelGGL(bind_chain_kernel<kW>, dim3(1), dim3(kChainThreads), 0, s, b, rp, mode);
     };
     if (rp.n_rails <= 16)      launch_chain(std::integral_constant<int, 16>{});
     else if (rp.n_rails <= 32) launch_chain(std::integral_constant<int, 32>{});

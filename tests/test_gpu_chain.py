@@ -109,3 +109,31 @@ def test_plan_in_one_workgroup_and_beyond(H, oracle, n, what):
         check_binding(H, oracle, transfers([700 * (n // 2) + 1] * (2 if n > 1 else 1), 700, rails))
     else:
         check_binding(H, oracle, transfers([8 * 1024 * n - 1024 * (n > 2)], 8 * 1024, rails))
+
+
+def stretches(g, S, n, singles, equal):
+    """Stretches of `equal` transfers of whole slices and a tail, `singles` transfers shorter than a slice, and one whose
+    slices are short (a run of its own slice length when repeated) in turn."""
+    lens = []
+    while len(lens) < n:
+        lens += (S * g.integers(1, 60, size=equal) + g.integers(1, S, size=equal)).tolist()
+        lens += g.integers(1, S, size=singles).tolist()
+        lens += [int(g.integers(1, S))] * int(g.integers(0, 6))
+    return np.array(lens[:n])
+
+
+@pytest.mark.parametrize("singles,equal", [(0, 70), (1, 3), (1, 4), (3, 5), (4, 2), (40, 9), (70, 1)])
+@pytest.mark.parametrize("kind", ["two_speeds", "one_rail_of_half", "equal_idle", "around_the_window", "five_live"])
+def test_ways_of_taking_a_record(H, oracle, kind, singles, equal):
+    # up to 16 rails the chain takes stretches of equal slices four at a time, other runs and single slices one by one, and
+    # changes the way at the ends of stretches; keys cover 134 us on either side of the level
+    g = np.random.Generator(np.random.PCG64([singles, equal, len(kind)]))
+    S = 1 << 20 if kind == "around_the_window" else 16384
+    rails = {"two_speeds": lambda: W.make_rails([25000, 50000] * 8, queued=g.integers(0, 1 << 18, size=16)),
+             "one_rail_of_half": lambda: W.make_rails([50000] * 8 + [400000], queued=g.integers(0, 1 << 18, size=9)),
+             "equal_idle": lambda: W.make_rails([65536] * 16),
+             # a slice costs 52, 84, 105, 131, 140 us: some runs fit the window and some do not
+             "around_the_window": lambda: W.make_rails([20000, 12500, 10000, 8000, 7500][:2 + (singles + equal) % 4]),
+             "five_live": lambda: W.make_rails(g.integers(10000, 400000, size=6), lat_ns=g.integers(0, 20000, size=6),
+                                               health=[0, 1, 2, 0, 0, 0])}[kind]()
+    check_binding(H, oracle, transfers(stretches(g, S, 500 if S < 1 << 20 else 60, singles, equal), S, rails))
