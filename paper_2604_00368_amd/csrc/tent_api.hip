@@ -430,7 +430,7 @@ bool pointers_ok(uint32_t n_desc, const uint32_t* p)
 struct WalkResult {
     int rc = TENT_OK;
     uint64_t total = 0, slices = 0, bits = 0, most = 0;
-    uint64_t src_apart = 0, dst_apart = 0;      // address bits in which an extent differs from the first destination extent
+    uint64_t dst_apart = 0;                     // address bits in which a destination extent differs from the first one
 };
 
 // One side's extents.  What a check needs of a segment is kept from extent to extent, because a list seldom changes its
@@ -486,7 +486,6 @@ void validate_range(const tent_ctx* ctx, uint32_t j0, uint32_t j1, const uint32_
         r.most = std::max(r.most, cnt);
     }
     r.bits = src.bits | dst.bits;
-    r.src_apart = src.apart;
     r.dst_apart = dst.apart;
     *out = r;
 }
@@ -544,7 +543,6 @@ int validate(const tent_ctx* ctx, uint32_t n_desc, const uint32_t* sp, const ten
         all->slices += part[k].slices;
         all->bits |= part[k].bits;
         all->most = std::max(all->most, part[k].most);
-        all->src_apart |= part[k].src_apart;
         all->dst_apart |= part[k].dst_apart;
     }
     return TENT_OK;
@@ -864,17 +862,18 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
 
     // destination extents in address order (for the scatter) and the overlap check run on the device
     const bool order = check || d.n_sc_tiles != 0;
-    uint64_t ws_need = 0;
+    OrderPlan order_plan{};
     KeyBits key_bits{0, 1};
-    if (const uint64_t apart = walk.dst_apart | (check ? walk.src_apart : 0))
-        key_bits = KeyBits{(uint32_t)__builtin_ctzll(apart), 64u - (uint32_t)__builtin_clzll(apart)};
-    if (order && order_workspace_bytes(nd, ns, check, key_bits, &ws_need) != hipSuccess) { (void)hipGetLastError(); return TENT_ERR_HIP; }
+    if (walk.dst_apart) key_bits = KeyBits{(uint32_t)__builtin_ctzll(walk.dst_apart), 64u - (uint32_t)__builtin_clzll(walk.dst_apart)};
+    uint64_t order_bytes = ~0ull;                         // what the order may take
+    if (order && use_static && order_measure(nd, ns, check, &order_bytes) != hipSuccess) { (void)hipGetLastError(); return TENT_ERR_HIP; }
+    if (order && plan_order(nd, ns, check, key_bits, (uint64_t)ctx->segments[dst_ext[0].seg].base + dst_ext[0].off, order_bytes,
+                            &order_plan) != hipSuccess) { (void)hipGetLastError(); return TENT_ERR_HIP; }
+    const uint64_t ws_need = order_plan.bytes;
     const uint64_t table_bytes = cv.total();
     void* workspace = nullptr;
     if (use_static) {
-        uint64_t order_bytes = 0;
-        if (order && order_measure(nd, ns, check, &order_bytes) != hipSuccess) { (void)hipGetLastError(); return TENT_ERR_HIP; }
-        if (static_measure(d, bounded, order_bytes) > TENT_STATIC_WORKSPACE_BYTES) return TENT_ERR_RANGE;
+        if (static_measure(d, bounded, order ? order_bytes : 0) > TENT_STATIC_WORKSPACE_BYTES) return TENT_ERR_RANGE;
         if (table_bytes + ws_need > kStaticArea) return TENT_ERR_RANGE;   // (not reached by a batch within the limit)
         uint8_t* area = nullptr;
         {
@@ -935,7 +934,7 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
              upload_in_pieces(ctx, upload + o_self, &d, sizeof(BatchDev));
     }
     *b.verdict = 0;
-    ok = ok && launch_declare(d, order, check, key_bits, order_dev, rank_dev, b.verdict, workspace, ds) == hipSuccess &&
+    ok = ok && launch_declare(d, order, check, order_plan, order_dev, rank_dev, b.verdict, workspace, ds) == hipSuccess &&
          hipEventRecord(b.decl_event, ds) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();

@@ -250,13 +250,35 @@ hipError_t launch_probe(const BatchDev& b, const ProbeParams& pp, PlanState* tol
 
 uint64_t scan_partials_capacity(uint64_t n);
 
-// Address bits in which the extents of a declaration differ: all others are the same, so they need no sorting.
+// Address bits in which the destinations of a declaration differ: all others are the same.
 struct KeyBits {
     uint32_t begin, end;           // begin < end
 };
-hipError_t order_workspace_bytes(uint64_t n_dst, uint64_t n_src, bool check, KeyBits bits, uint64_t* bytes_out);
+// The places those bits can name, in ascending address.
+struct AddressSlots {
+    uint64_t base;                 // address of place 0
+    uint64_t n_slots;              // power of two
+    uint32_t shift;                // log2 of the distance of two places
+    // place of a destination's first byte
+    __host__ __device__ uint64_t slot(uint64_t begin) const { return (begin - base) >> shift; }
+    // places whose address lies below `end` (any address)
+    __host__ __device__ uint64_t starts_before(uint64_t end) const
+    {
+        if (end <= base) return 0;
+        const uint64_t k = ((end - base - 1) >> shift) + 1;
+        return k < n_slots ? k : n_slots;
+    }
+};
+struct OrderPlan {
+    enum Way { kSmallSlots, kSmallSort, kSlots, kSort };
+    Way way;
+    AddressSlots map;
+    KeyBits bits;
+    uint64_t bytes;                // of workspace
+};
+hipError_t plan_order(uint64_t n_dst, uint64_t n_src, bool check, KeyBits bits, uint64_t origin, uint64_t most, OrderPlan* out);
 hipError_t order_measure(uint64_t n_dst, uint64_t n_src, bool check, uint64_t* bytes_out);
-hipError_t launch_declare(const BatchDev& b, bool order, bool check, KeyBits bits, uint32_t* order_out, uint32_t* rank_out,
+hipError_t launch_declare(const BatchDev& b, bool order, bool check, const OrderPlan& plan, uint32_t* order_out, uint32_t* rank_out,
                           uint32_t* overlap_told, void* workspace, hipStream_t s);
 
 }  // namespace tent

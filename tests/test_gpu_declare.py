@@ -187,3 +187,81 @@ def test_static_limit_counts_entries_not_layout(T, max_rails):
         assert ei.value.status == T.TENT_ERR_RANGE
     finally:
         T.tent_destroy(ctx)
+
+
+@pytest.mark.parametrize("n", [1, 3, 700, 1025, 2600, 4096, 4097, 6000])
+@pytest.mark.parametrize("n_src", ["half", "same", "double"])
+@pytest.mark.parametrize("grid", ["dense", "sparse", "any"])
+def test_every_way_to_the_order(T, n, n_src, grid):
+    # sources and destinations side by side in one pool, at multiples of 256 bytes that fill the pool or leave most of it, or at any
+    # address: places in LDS, a sort in LDS, places in device memory, a device-wide sort; then one extent is moved by a byte
+    g = np.random.Generator(np.random.PCG64([n, len(n_src), len(grid)]))
+    L = 64
+    k = {"half": 1, "same": 2, "double": 4}[n_src]               # sources: n k / 2 of 2 L / k bytes each
+    n = n + n % 2
+    ns, ls = n * k // 2, 2 * L // k
+    pitch = {"dense": 256, "sparse": 256, "any": 139}[grid]
+    room = (n + ns) * (40 if grid == "sparse" else 1)
+    at = g.choice(room, size=n + ns, replace=False).astype(np.uint64) * np.uint64(pitch)
+    if grid == "any":
+        at += g.integers(0, 10, size=n + ns).astype(np.uint64)
+    pool = torch.from_numpy(g.integers(0, 256, size=room * pitch + 256, dtype=np.uint8)).cuda()
+    before = pool.cpu().numpy()
+    arena = torch.zeros(n * L + 4096, dtype=torch.uint8, device="cuda")
+    ctx = T.tent_create(1000, arena.data_ptr(), arena.numel())
+    T.tent_register_segment(ctx, pool.data_ptr(), pool.numel())
+    se, de = np.zeros(ns, dtype=W.EXTENT_DTYPE), np.zeros(n, dtype=W.EXTENT_DTYPE)
+    se["off"], se["len"] = at[:ns], ls
+    de["off"], de["len"] = at[ns:], L
+    rails, stream = W.make_rails([50000, 20000, 70000]), torch.cuda.current_stream()
+    sp, dp = np.array([0, ns], dtype=np.uint32), np.array([0, n], dtype=np.uint32)
+
+    def overlaps(se, de):
+        starts = np.concatenate([de["off"], se["off"]])
+        order = np.lexsort((np.arange(starts.shape[0]), starts))
+        far_any = far_dst = 0
+        for v in order.tolist():
+            a = int(starts[v])
+            if a < (far_any if v < n else far_dst):
+                return True
+            end = a + (L if v < n else ls)
+            far_any = max(far_any, end)
+            far_dst = max(far_dst, end) if v < n else far_dst
+        return False
+
+    assert not overlaps(se, de)
+    h = T.tent_declare(ctx, sp, se, dp, de)
+    T.tent_plan(ctx, h, rails, False, stream)
+    T.tent_execute(ctx, h, stream)
+    assert T.tent_poll(ctx, h, stream) == 0
+    want = before.copy()
+    data = np.concatenate([before[a:a + ls] for a in se["off"].tolist()])
+    for j, a in enumerate(de["off"].tolist()):
+        want[a:a + L] = data[j * L:(j + 1) * L]
+    assert np.array_equal(pool.cpu().numpy(), want)
+    T.tent_release(ctx, h)
+    for _ in range(12):
+        s2, d2 = se.copy(), de.copy()
+        i, j = int(g.integers(0, n)), int(g.integers(0, ns))
+        what = int(g.integers(0, 6))
+        if what == 0:
+            d2["off"][i] = d2["off"][(i + 1) % n]                # two at one place
+        elif what == 1:
+            d2["off"][i] = s2["off"][j] + (ls - 1)               # the source's last byte
+        elif what == 2:
+            s2["off"][j] = d2["off"][i] + (L - 1)
+        elif what == 3:
+            s2["off"][j] = max(0, int(d2["off"][i]) - (ls - 1))
+        elif what == 4:
+            s2["off"][j] = s2["off"][(j + 1) % ns]               # two sources may share their bytes
+        else:
+            d2["off"][i] = max(0, int(d2["off"][(i + 1) % n]) - (L - 1))
+        h = T.tent_declare(ctx, sp, s2, dp, d2)
+        if overlaps(s2, d2):
+            with pytest.raises(T.TentError) as err:
+                T.tent_plan(ctx, h, rails, False, stream)
+            assert err.value.status == T.TENT_ERR_INVALID
+        else:
+            T.tent_plan(ctx, h, rails, True, stream)
+            T.tent_release(ctx, h)
+    T.tent_destroy(ctx)
