@@ -1401,7 +1401,7 @@ struct EmitRails {
 };
 
 // By a whole workgroup (with a barrier), thread `at` of `threads`.
-__device__ __forceinline__ void bind_emit(const BatchDev& b, const RailParams& rp, int use_pending, PlanState* told, EmitRails& er,
+__device__ __forceinline__ void bind_emit(const BatchDev& b, const RailParams& rp, int use_pending, Report told, EmitRails& er,
                                           uint64_t at, uint64_t threads)
 {
     const uint32_t R = rp.n_rails;
@@ -1412,7 +1412,7 @@ __device__ __forceinline__ void bind_emit(const BatchDev& b, const RailParams& r
         er.inv[threadIdx.x] = 1.0 / (double)(c1 ? c1 : 1u);
     }
     __syncthreads();
-    if (told && blockIdx.x == 0) tell_totals(*b.plan, told);
+    if (told.to && blockIdx.x == 0) tell_totals(*b.plan, told);
     const uint64_t n = b.plan->n_pending;
     const uint32_t stride = b.run_stride;
     for (uint64_t q = at; q < n; q += threads) {
@@ -1468,7 +1468,7 @@ __device__ __forceinline__ void bind_emit(const BatchDev& b, const RailParams& r
     }
 }
 
-__global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams rp, int use_pending, PlanState* told)
+__global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams rp, int use_pending, Report told)
 {
     __shared__ EmitRails er;
     bind_emit(b, rp, use_pending, told, er, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, (uint64_t)gridDim.x * blockDim.x);
@@ -1509,7 +1509,7 @@ __device__ __forceinline__ uint64_t pair_prefix(uint64_t v0, uint64_t v1, uint64
 }
 
 template <int kWide>
-__global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, RailParams rp, PlanState* told)
+__global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, RailParams rp, Report told)
 {
     __shared__ SmallPlan<kWide> sh;
     const uint32_t t = threadIdx.x, e0 = 2 * t, e1 = 2 * t + 1;
@@ -1585,7 +1585,7 @@ bool plan_is_small(const BatchDev& b)
            b.n_slices * (uint64_t)b.tiles_per_slice <= kSmallTiles;
 }
 
-hipError_t launch_plan_small(const BatchDev& b, const RailParams& rp, PlanState* told, hipStream_t s)
+hipError_t launch_plan_small(const BatchDev& b, const RailParams& rp, Report told, hipStream_t s)
 {
     const dim3 grid(1), block(kSmallThreads);
     if (rp.n_rails <= 16)      hipLaunchKernelGGL(plan_small_kernel<16>, grid, block, 0, s, b, rp, told);
@@ -1594,7 +1594,7 @@ hipError_t launch_plan_small(const BatchDev& b, const RailParams& rp, PlanState*
     return hipGetLastError();
 }
 
-hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, PlanState* told, hipStream_t s)
+hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, Report told, hipStream_t s)
 {
     const bool use_pending = (mode & kBindUsePending) != 0;
     const int up = use_pending ? 1 : 0;

@@ -184,9 +184,9 @@ __global__ void __launch_bounds__(256) dispatch_chain_tables_kernel(BatchDev b, 
 // Position q of the pending list belongs to request j; inside the request the lane takes slot
 // number t = q - (first pending position of j) in rail-major order, i.e. slot k of rail d, computes
 // the slot's rank in the merge and hands it to the request's rank-th pending slice.
-__global__ void __launch_bounds__(256) dispatch_emit_kernel(BatchDev b, RailParams rp, DispatchParams dp, PlanState* told)
+__global__ void __launch_bounds__(256) dispatch_emit_kernel(BatchDev b, RailParams rp, DispatchParams dp, Report told)
 {
-    if (told && blockIdx.x == 0) tell_totals(*b.plan, told);
+    if (told.to && blockIdx.x == 0) tell_totals(*b.plan, told);
     const uint32_t R = rp.n_rails;
     const uint32_t stride = b.run_stride;
     const uint64_t S = b.slice_bytes;
@@ -259,7 +259,7 @@ __global__ void __launch_bounds__(256) pending_list_kernel(BatchDev b)
 }  // namespace
 
 hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, bool first_plan,
-                           PlanState* told, hipStream_t s)
+                           Report told, hipStream_t s)
 {
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 4096) blocks = 4096;

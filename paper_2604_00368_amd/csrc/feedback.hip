@@ -37,7 +37,7 @@ hipError_t launch_sim_latency(const BatchDev& b, const LatencyParams& lp, hipStr
     return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) probe_kernel(BatchDev b, ProbeParams pp, PlanState* told)
+__global__ void __launch_bounds__(256) probe_kernel(BatchDev b, ProbeParams pp, Report told)
 {
     __shared__ unsigned long long peak[TENT_MAX_RAILS];
     if (threadIdx.x < TENT_MAX_RAILS) peak[threadIdx.x] = 0;
@@ -69,11 +69,12 @@ __global__ void __launch_bounds__(256) probe_kernel(BatchDev b, ProbeParams pp, 
         const uint64_t mixed = ((uint64_t)cal.ewma_q8 * probe + (uint64_t)(256 - cal.ewma_q8) * next) >> 8;
         next = (uint32_t)(mixed ? mixed : 1);
     }
-    told->probe[d] = probe;
-    told->bw_next[d] = next;
+    tell(&told.to->probe[d], probe);
+    tell(&told.to->bw_next[d], next);
+    if (d == 0) tell_done(told);
 }
 
-hipError_t launch_probe(const BatchDev& b, const ProbeParams& pp, PlanState* told, hipStream_t s)
+hipError_t launch_probe(const BatchDev& b, const ProbeParams& pp, Report told, hipStream_t s)
 {
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 1024) blocks = 1024;

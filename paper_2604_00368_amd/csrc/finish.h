@@ -4,7 +4,7 @@
 // MI355X, 10 us with the copy engine's share); no workgroup waits on another.
 #pragma once
 
-#include "tent_internal.h"
+#include "report.h"
 
 namespace tent {
 

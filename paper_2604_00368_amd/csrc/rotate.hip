@@ -123,7 +123,7 @@ __global__ void __launch_bounds__(64) rotate_emit_kernel(BatchDev b, RotateParam
 }
 
 // Rail simulator: every BOUND slice on a failed rail returns to the pending set with one more retry.
-__global__ void __launch_bounds__(256) fail_kernel(BatchDev b, FailParams fp, PlanState* told)
+__global__ void __launch_bounds__(256) fail_kernel(BatchDev b, FailParams fp, Report told)
 {
     __shared__ uint32_t cnt[TENT_MAX_RAILS];
     if (threadIdx.x < TENT_MAX_RAILS) cnt[threadIdx.x] = 0;
@@ -144,7 +144,9 @@ __global__ void __launch_bounds__(256) fail_kernel(BatchDev b, FailParams fp, Pl
         added = atomicAdd((unsigned long long*)&b.plan->fail_cnt[threadIdx.x], (unsigned long long)cnt[threadIdx.x]);
     if (!finishes_last(b.plan, kTicketFail, added) || threadIdx.x >= TENT_MAX_RAILS) return;
     const unsigned long long total = take_counter(&b.plan->fail_cnt[threadIdx.x]);
-    if (told) told->fail_cnt[threadIdx.x] = total;
+    if (!told.to) return;
+    tell(&told.to->fail_cnt[threadIdx.x], (uint64_t)total);
+    if (threadIdx.x == 0) tell_done(told);
 }
 
 }  // namespace
@@ -160,7 +162,7 @@ hipError_t launch_rotate(const BatchDev& b, const RotateParams& rot, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_fail(const BatchDev& b, const FailParams& fp, PlanState* told, hipStream_t s)
+hipError_t launch_fail(const BatchDev& b, const FailParams& fp, Report told, hipStream_t s)
 {
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 1024) blocks = 1024;

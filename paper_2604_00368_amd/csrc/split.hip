@@ -378,7 +378,7 @@ hipError_t launch_reset(const BatchDev& b, hipStream_t s)
 // ahead of the plan, the slices staged before it, and the slice itself; otherwise it returns to
 // the pending set.  The count of completed slices is an integer sum, so its value does not
 // depend on the order of the atomic adds.
-__global__ void __launch_bounds__(256) retire_kernel(BatchDev b, BudgetParams bp, PlanState* told)
+__global__ void __launch_bounds__(256) retire_kernel(BatchDev b, BudgetParams bp, Report told)
 {
     __shared__ unsigned long long block_done;
     if (threadIdx.x == 0) block_done = 0;
@@ -398,10 +398,12 @@ __global__ void __launch_bounds__(256) retire_kernel(BatchDev b, BudgetParams bp
     if (threadIdx.x == 0 && block_done) added = atomicAdd((unsigned long long*)&b.plan->n_done, block_done);
     if (!finishes_last(b.plan, kTicketRetire, added) || threadIdx.x != 0) return;
     const unsigned long long total = take_counter(&b.plan->n_done);
-    if (told) told->n_done = total;
+    if (!told.to) return;
+    tell(&told.to->n_done, (uint64_t)total);
+    tell_done(told);
 }
 
-hipError_t launch_retire(const BatchDev& b, const BudgetParams& bp, PlanState* told, hipStream_t s)
+hipError_t launch_retire(const BatchDev& b, const BudgetParams& bp, Report told, hipStream_t s)
 {
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 1024) blocks = 1024;
@@ -409,7 +411,7 @@ hipError_t launch_retire(const BatchDev& b, const BudgetParams& bp, PlanState* t
     return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) count_remaining_kernel(BatchDev b, PlanState* told)
+__global__ void __launch_bounds__(256) count_remaining_kernel(BatchDev b, Report told)
 {
     __shared__ unsigned long long block_cnt;
     if (threadIdx.x == 0) block_cnt = 0;
@@ -423,10 +425,11 @@ __global__ void __launch_bounds__(256) count_remaining_kernel(BatchDev b, PlanSt
     unsigned long long added = 0;
     if (threadIdx.x == 0 && block_cnt) added = atomicAdd((unsigned long long*)&b.plan->n_remaining, block_cnt);
     if (!finishes_last(b.plan, kTicketRemaining, added) || threadIdx.x != 0) return;
-    told->n_remaining = take_counter(&b.plan->n_remaining);
+    tell(&told.to->n_remaining, (uint64_t)take_counter(&b.plan->n_remaining));
+    tell_done(told);
 }
 
-hipError_t launch_count_remaining(const BatchDev& b, PlanState* told, hipStream_t s)
+hipError_t launch_count_remaining(const BatchDev& b, Report told, hipStream_t s)
 {
     uint64_t blocks = (b.n_slices + 1023) / 1024;
     if (blocks > 256) blocks = 256;

@@ -1,6 +1,7 @@
 // Host runtime behind the C ABI: argument validation, device tables, rail-state conversion and
 // kernel sequencing.  Every step of the hot path itself runs in the HIP kernels of this library.
 #include <algorithm>
+#include <chrono>
 #include <cstring>
 #include <mutex>
 #include <thread>
@@ -92,6 +93,7 @@ struct tent_ctx {
     std::vector<Batch> batches;
     Batch static_batch;                     // the one batch whose tables live in the static workspace
     PlanState* host_plan = nullptr;         // pinned result block, written by the kernels of calls that report something
+    uint64_t reports = 0;                   // such calls so far: the number a kernel writes behind its figures
     hipStream_t aux_stream = nullptr;       // second stream of the pipelined bounded execute (default priority)
     std::vector<hipEvent_t> sync_events;    // ordering events of the pipelined bounded execute, reused
     // tent_declare: its device work runs on a stream of the library's own, so that it neither waits for
@@ -143,6 +145,30 @@ bool capturing(hipStream_t s)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); return false; }
     return cap != hipStreamCaptureStatusNone;
+}
+
+// Where the kernels of the next call that reports something put it; nowhere without `wanted`.
+Report next_report(tent_ctx* ctx, bool wanted)
+{
+    return wanted ? Report{ctx->host_plan, ++ctx->reports} : Report{nullptr, 0};
+}
+
+// Waits until the figures of `told` are there: everything enqueued on `s` before the kernel that tells them has ended then, and
+// that kernel is past its last look at what it counts (a plan's goes on to write the slices' rails).  After kReportSpin, under
+// capture (where it is refused) and behind an error this is a wait for the stream: a call of more than a millisecond does not
+// notice the 4 us.
+constexpr std::chrono::microseconds kReportSpin{1000};
+hipError_t await_report(const Report& told, hipStream_t s)
+{
+    if (capturing(s)) return hipStreamSynchronize(s);
+    const auto until = std::chrono::steady_clock::now() + kReportSpin;
+    do {
+        for (int k = 0; k < 64; ++k) {
+            if (__atomic_load_n(&told.to->call, __ATOMIC_ACQUIRE) == told.call) return hipSuccess;
+            __builtin_ia32_pause();
+        }
+    } while (std::chrono::steady_clock::now() < until);
+    return hipStreamSynchronize(s);
 }
 
 // Remember that work of the batch was just enqueued on `s` (nothing is recorded into a stream that is
@@ -982,9 +1008,10 @@ int tent_create(tent_ctx** out, const tent_config* cfg)
     bool ok = true;
     try { ctx->spare.reserve(kSpareBlocks); ctx->batches.reserve(16); } catch (const std::bad_alloc&) { ok = false; }
     ok = ok && hipMalloc((void**)&ctx->seg_base_dev, sizeof(uint64_t) * ctx->seg_capacity) == hipSuccess &&
-         hipHostMalloc((void**)&ctx->host_plan, sizeof(PlanState), hipHostMallocDefault) == hipSuccess &&
+         hipHostMalloc((void**)&ctx->host_plan, sizeof(PlanState), hipHostMallocCoherent) == hipSuccess &&
          hipStreamCreateWithFlags(&ctx->decl_stream, hipStreamNonBlocking) == hipSuccess &&
          init_slot(ctx->static_batch);
+    if (ok) ctx->host_plan->call = 0;
     for (int k = 0; k < 2 && ok; ++k) {
         ok = hipHostMalloc((void**)&ctx->stage[k], kStageInitial, hipHostMallocDefault) == hipSuccess &&
              hipEventCreateWithFlags(&ctx->stage_event[k], hipEventDisableTiming) == hipSuccess;
@@ -1111,10 +1138,11 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
     for (uint32_t r = 0; r < n_rails; ++r)
         if (((rp.admitted >> r) & 1) && rp.c1[r] == 0) serial = true;
     const bool small = !replan && !serial && plan_is_small(d);
+    const Report told = next_report(ctx, info && !serial);
     if (small) {
         // one launch does it all and counts as binding (so does a caller that asks for the time of every stage see it)
         StageTimer t(ctx, TENT_T_BIND, s);
-        HIP_TRY(launch_plan_small(d, rp, info ? ctx->host_plan : nullptr, s));
+        HIP_TRY(launch_plan_small(d, rp, told, s));
     } else if (!replan) {
         {
             StageTimer t(ctx, TENT_T_EXTENT_SCAN, s);
@@ -1144,7 +1172,7 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
     if (!small) {
         StageTimer t(ctx, TENT_T_BIND, s);
         if (serial) HIP_TRY(launch_bind_serial(d, rp, mode, s));
-        else        HIP_TRY(launch_bind_runs(d, rp, mode | (replan ? 0 : kBindBuildTables), info ? ctx->host_plan : nullptr, s));
+        else        HIP_TRY(launch_bind_runs(d, rp, mode | (replan ? 0 : kBindBuildTables), told, s));
     }
     // Only a batch whose verdict has been read counts as planned: an execute relies on there being no overlap.
     rc = finish_declare_behind(ctx, *b, s);
@@ -1157,8 +1185,12 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
     for (uint32_t r = 0; r < n_rails; ++r) b->last_lat_ns[r] = rails[r].lat_ns;
 
     if (info) {
-        if (serial) HIP_TRY(hipMemcpyAsync(ctx->host_plan, d.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        if (serial) {
+            HIP_TRY(hipMemcpyAsync(ctx->host_plan, d.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
+            HIP_TRY(hipStreamSynchronize(s));
+        } else {
+            HIP_TRY(await_report(told, s));
+        }
         const PlanState& ps = *ctx->host_plan;
         std::memset(info, 0, sizeof(*info));
         b->bound_hint = ps.n_bound;
@@ -1235,6 +1267,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     dp.all_high = priority ? 0u : 1u;
     if (priority) HIP_TRY(hipMemcpyAsync(d.priority, priority, d.n_desc, hipMemcpyHostToDevice, s));
     const bool first_plan = !b->planned;
+    const Report told = next_report(ctx, info != nullptr);
     if (first_plan) {
         {
             StageTimer t(ctx, TENT_T_EXTENT_SCAN, s);
@@ -1251,7 +1284,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     }
     {
         StageTimer t(ctx, TENT_T_BIND, s);
-        HIP_TRY(launch_dispatch(d, rp, dp, first_plan, info ? ctx->host_plan : nullptr, s));
+        HIP_TRY(launch_dispatch(d, rp, dp, first_plan, told, s));
     }
     b->planned = true;
     b->may_replan = true;                                     // deferred transfers stay pending
@@ -1261,7 +1294,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     for (uint32_t r = 0; r < n_rails; ++r) b->last_lat_ns[r] = rails[r].lat_ns;
 
     if (info) {
-        HIP_TRY(hipStreamSynchronize(s));
+        HIP_TRY(await_report(told, s));
         const PlanState& ps = *ctx->host_plan;
         std::memset(info, 0, sizeof(*info));
         b->bound_hint = ps.n_bound;
@@ -1312,7 +1345,8 @@ int tent_sim_advance(tent_ctx* ctx, tent_batch_t batch, const uint64_t* budget_b
     }
     StreamNote note(*b, s);
     b->may_replan = true;
-    HIP_TRY(launch_retire(b->dev, bp, n_done ? ctx->host_plan : nullptr, s));
+    const Report told = next_report(ctx, n_done != nullptr);
+    HIP_TRY(launch_retire(b->dev, bp, told, s));
     // What stays BOUND on rail d fits in budget_d - queued_d bytes, which bounds the tiles the next execute
     // copies without asking the device (slices of a tiled batch are whole tiles).
     uint64_t tiles = 0;
@@ -1320,7 +1354,7 @@ int tent_sim_advance(tent_ctx* ctx, tent_batch_t batch, const uint64_t* budget_b
         if (bp.budget[d] > bp.queued[d]) tiles += (bp.budget[d] - bp.queued[d]) / (b->dev.tile_bytes ? b->dev.tile_bytes : 1u);
     b->tile_hint = tiles;
     if (!n_done) return TENT_OK;
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(await_report(told, s));
     b->bound_hint = ctx->host_plan->n_done;
     *n_done = ctx->host_plan->n_done;
     return TENT_OK;
@@ -1345,15 +1379,16 @@ int tent_sim_fail(tent_ctx* ctx, tent_batch_t batch, const uint8_t* rail_failed,
     if (!g.ok) return TENT_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
     StreamNote note(*b, s);
+    const Report told = next_report(ctx, any && failed_per_rail);
     if (any) {
         b->may_replan = true;
-        HIP_TRY(launch_fail(b->dev, fp, failed_per_rail ? ctx->host_plan : nullptr, s));
+        HIP_TRY(launch_fail(b->dev, fp, told, s));
         b->has_retry = true;
     }
     if (failed_per_rail) {
         for (uint32_t d = 0; d < n_rails; ++d) failed_per_rail[d] = 0;
         if (any) {
-            HIP_TRY(hipStreamSynchronize(s));
+            HIP_TRY(await_report(told, s));
             for (uint32_t d = 0; d < n_rails; ++d) failed_per_rail[d] = ctx->host_plan->fail_cnt[d];
         }
     }
@@ -1417,11 +1452,12 @@ int tent_update_bandwidth(tent_ctx* ctx, tent_batch_t batch, const tent_probe_pa
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    const Report told = next_report(ctx, true);
     {
         StageTimer t(ctx, TENT_T_FEEDBACK, s);
-        HIP_TRY(launch_probe(b->dev, pp, ctx->host_plan, s));
+        HIP_TRY(launch_probe(b->dev, pp, told, s));
     }
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(await_report(told, s));
     for (uint32_t d = 0; d < n_rails; ++d) {
         rails[d].bw_MBps = ctx->host_plan->bw_next[d];
         if (probe_MBps_out) probe_MBps_out[d] = ctx->host_plan->probe[d];
@@ -1613,8 +1649,9 @@ int tent_poll(tent_ctx* ctx, tent_batch_t batch, uint64_t* remaining, void* stre
     // slices are marked DONE ahead of their copies: completion is only reported once the last
     // execute's copies have ended, whichever stream the caller polls on
     if (b->done_recorded && s != b->exec_stream) HIP_TRY(hipStreamWaitEvent(s, b->done_at, 0));
-    HIP_TRY(launch_count_remaining(b->dev, ctx->host_plan, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    const Report told = next_report(ctx, true);
+    HIP_TRY(launch_count_remaining(b->dev, told, s));
+    HIP_TRY(await_report(told, s));
     *remaining = ctx->host_plan->n_remaining;
     return TENT_OK;
 }

@@ -86,6 +86,13 @@ struct PlanState {
     uint64_t compact_overflow;            // two passes: more tiles move than the launch was sized for (nothing is marked DONE)
     uint64_t n_act_asked;                 // one-pass copies: tiles of the BOUND slices, listed or not
     uint32_t ticket[4];                   // finished workgroups per kind of counting kernel (finish.h); 0 between launches
+    uint64_t call;                        // in host memory: the call whose figures these are, written behind them (report.h)
+};
+
+// Where the kernels of a call that reports something put it: a result block in host memory (or null) and the call's number.
+struct Report {
+    PlanState* to;
+    uint64_t   call;
 };
 
 // What the binding chains leave for the emit kernels, per run (request) and rail, in one 16-byte store: bytes bound to
@@ -220,20 +227,20 @@ hipError_t launch_slice_scan(const BatchDev& b, hipStream_t s);
 hipError_t launch_expand(const BatchDev& b, hipStream_t s);
 hipError_t launch_compact(const BatchDev& b, hipStream_t s);
 hipError_t launch_bind_serial(const BatchDev& b, const RailParams& rp, int mode, hipStream_t s);
-// `told` (host memory the device can write, or null): where the plan's totals go as well
-hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, PlanState* told, hipStream_t s);
+// `told`: where the plan's totals go as well
+hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, Report told, hipStream_t s);
 // A first plan in one workgroup, for batches small enough.
 bool plan_is_small(const BatchDev& b);
-hipError_t launch_plan_small(const BatchDev& b, const RailParams& rp, PlanState* told, hipStream_t s);
+hipError_t launch_plan_small(const BatchDev& b, const RailParams& rp, Report told, hipStream_t s);
 hipError_t launch_rotate(const BatchDev& b, const RotateParams& rot, hipStream_t s);
-hipError_t launch_fail(const BatchDev& b, const FailParams& fp, PlanState* told, hipStream_t s);
+hipError_t launch_fail(const BatchDev& b, const FailParams& fp, Report told, hipStream_t s);
 hipError_t launch_bounded_prepare(const BatchDev& b, uint64_t payload, uint64_t chunk_bytes, uint32_t n_chunks,
                                   uint64_t slot_bytes, uint32_t slots, uint8_t* arena, hipStream_t s);
 hipError_t launch_bounded_copy(const BatchDev& b, bool gather, uint32_t chunk, uint64_t payload, uint64_t chunk_bytes,
                                uint64_t slot_bytes, uint32_t slots, uint8_t* arena, hipStream_t s);
 hipError_t launch_mark_done_bounded(const BatchDev& b, hipStream_t s);
 hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, bool first_plan,
-                           PlanState* told, hipStream_t s);
+                           Report told, hipStream_t s);
 hipError_t launch_tile_tables(const BatchDev& b, hipStream_t s);
 hipError_t launch_finalize(const BatchDev& b, uint8_t* arena, bool compact, uint64_t max_tiles, hipStream_t s);
 hipError_t launch_copy(const BatchDev& b, bool gather, hipStream_t s);
@@ -242,11 +249,11 @@ hipError_t launch_copy_one_pass(const BatchDev& b, bool compact, uint64_t max_ti
 hipError_t launch_copy_ordered(const BatchDev& b, bool gather, hipStream_t s);
 hipError_t launch_copy_compact(const BatchDev& b, bool gather, uint64_t max_tiles, hipStream_t s);
 hipError_t launch_mark_done(const BatchDev& b, bool compact, hipStream_t s);
-hipError_t launch_retire(const BatchDev& b, const BudgetParams& bp, PlanState* told, hipStream_t s);
-hipError_t launch_count_remaining(const BatchDev& b, PlanState* told, hipStream_t s);
+hipError_t launch_retire(const BatchDev& b, const BudgetParams& bp, Report told, hipStream_t s);
+hipError_t launch_count_remaining(const BatchDev& b, Report told, hipStream_t s);
 hipError_t launch_reset(const BatchDev& b, hipStream_t s);
 hipError_t launch_sim_latency(const BatchDev& b, const LatencyParams& lp, hipStream_t s);
-hipError_t launch_probe(const BatchDev& b, const ProbeParams& pp, PlanState* told, hipStream_t s);
+hipError_t launch_probe(const BatchDev& b, const ProbeParams& pp, Report told, hipStream_t s);
 
 uint64_t scan_partials_capacity(uint64_t n);
 

@@ -5,7 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "tent_internal.h"
+#include "report.h"
 
 namespace tent {
 
@@ -102,22 +102,22 @@ __device__ __forceinline__ int argmax_cost(uint64_t cost, bool valid, int lane, 
 }
 
 // The totals a plan reports, by the first wavefront of one workgroup behind the chain's launch.
-__device__ __forceinline__ void tell_totals(const PlanState& ps, PlanState* told)
+__device__ __forceinline__ void tell_totals(const PlanState& ps, Report told)
 {
     const uint32_t d = threadIdx.x;
     if (d >= TENT_MAX_RAILS) return;
-    told->T[d] = ps.T[d];
-    told->cnt[d] = ps.cnt[d];
-    told->A_after[d] = ps.A_after[d];
-    told->base[d] = ps.base[d];
-    if (d == 0) {
-        told->n_pending = ps.n_pending;
-        told->n_bound = ps.n_bound;
-        told->n_mice = ps.n_mice;
-        told->n_elephant = ps.n_elephant;
-        told->n_deferred = ps.n_deferred;
-        told->rr_next = ps.rr_next;
-    }
+    tell(&told.to->T[d], ps.T[d]);
+    tell(&told.to->cnt[d], ps.cnt[d]);
+    tell(&told.to->A_after[d], ps.A_after[d]);
+    tell(&told.to->base[d], ps.base[d]);
+    if (d != 0) return;
+    tell(&told.to->n_pending, ps.n_pending);
+    tell(&told.to->n_bound, ps.n_bound);
+    tell(&told.to->n_mice, ps.n_mice);
+    tell(&told.to->n_elephant, ps.n_elephant);
+    tell(&told.to->n_deferred, ps.n_deferred);
+    tell(&told.to->rr_next, ps.rr_next);
+    tell_done(told);
 }
 
 }  // namespace tent

@@ -11,7 +11,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 MiB = 1 << 20
-LAUNCH, RECORD, WAIT = 1, 2, 3
+LAUNCH, RECORD, WAIT, HOST_WAIT = 1, 2, 3, 4
 STREAM_A, STREAM_B = 0xA0, 0xB0                      # never dereferenced
 
 
@@ -221,6 +221,35 @@ def timed_stages():
 def test_stages_that_one_launch_stands_for(fake):
     """A small batch's first plan is one interval under "bind", one-pass copies are one under "gather"."""
     run(fake, "timed_stages")
+
+
+def figures_that_do_not_come(captured):
+    h = Host(slice_bytes=4096)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    b = T.tent_declare(h.ctx, *h.extents(64, 4096))
+    T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+    asks = [lambda: T.tent_plan(h.ctx, b, rails, True, STREAM_A),
+            lambda: T.tent_plan_dispatch(h.ctx, b, rails, h.W.make_dispatch_params(1 << 18), None, True, STREAM_A),
+            lambda: T.tent_sim_fail(h.ctx, b, np.ones(2, dtype=np.uint8), True, STREAM_A),
+            lambda: T.tent_sim_advance(h.ctx, b, np.zeros(2, dtype=np.uint64), STREAM_A),
+            lambda: T.tent_update_bandwidth(h.ctx, b, h.W.make_probe_params([50000, 25000]), rails, STREAM_A),
+            lambda: T.tent_poll(h.ctx, b, STREAM_A)]
+    h.hip.fake_capture(STREAM_A if captured else 0)
+    for ask in asks:
+        h.log()
+        ask()
+        assert [x[:2] for x in h.log()].count((HOST_WAIT, STREAM_A)) == 1
+    h.hip.fake_capture(0)
+    h.hip.fake_fail_host_waits(1)
+    assert status_of(T, T.tent_poll, h.ctx, b, STREAM_A) == T.TENT_ERR_HIP
+    T.tent_destroy(h.ctx)
+
+
+@pytest.mark.parametrize("captured", [False, True])
+def test_a_call_whose_figures_do_not_come_waits_for_its_stream(fake, captured):
+    """Kernels store their figures to host memory; where none arrive in time (here launches do nothing), or the stream is being
+    captured, the call waits for the stream and passes on what that says."""
+    run(fake, "figures_that_do_not_come", captured)
 
 
 # The largest batches tent_declare_static accepts, in units of each kind: flags 0, no overlap check, bounded staging, both;
