@@ -186,12 +186,16 @@ __global__ void __launch_bounds__(256) dispatch_chain_tables_kernel(BatchDev b, 
 // the slot's rank in the merge and hands it to the request's rank-th pending slice.
 __global__ void __launch_bounds__(256) dispatch_emit_kernel(BatchDev b, RailParams rp, DispatchParams dp, Report told)
 {
-    if (told.to && blockIdx.x == 0) tell_totals(*b.plan, told);
+    const uint32_t blocks = told.to ? gridDim.x - 1 : gridDim.x;
+    if (blockIdx.x == blocks) {                                      // one more for the report
+        if (threadIdx.x < 64) tell_totals(*b.plan, told);
+        return;
+    }
     const uint32_t R = rp.n_rails;
     const uint32_t stride = b.run_stride;
     const uint64_t S = b.slice_bytes;
     const uint64_t n = b.scan_tmp[b.n_slices];                       // slices not DONE
-    const uint64_t gstride = (uint64_t)gridDim.x * blockDim.x;
+    const uint64_t gstride = (uint64_t)blocks * blockDim.x;
     for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gstride) {
         const uint32_t i_q = b.pending[q];
         const uint32_t j = b.s_desc[i_q];
@@ -281,7 +285,7 @@ hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const Dispat
         else if (rp.n_rails <= 32) hipLaunchKernelGGL(dispatch_chain_kernel<32>, dim3(1), dim3(64), 0, s, b, rp, dp);
         else                       hipLaunchKernelGGL(dispatch_chain_kernel<64>, dim3(1), dim3(64), 0, s, b, rp, dp);
     }
-    hipLaunchKernelGGL(dispatch_emit_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, rp, dp, told);
+    hipLaunchKernelGGL(dispatch_emit_kernel, dim3((uint32_t)blocks + (told.to ? 1u : 0u)), dim3(256), 0, s, b, rp, dp, told);
     return hipGetLastError();
 }
 

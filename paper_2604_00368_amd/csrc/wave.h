@@ -101,11 +101,11 @@ __device__ __forceinline__ int argmax_cost(uint64_t cost, bool valid, int lane, 
     return (int)(__builtin_amdgcn_readfirstlane((int)lo_max) & 63);
 }
 
-// The totals a plan reports, by the first wavefront of one workgroup behind the chain's launch.
+// The totals a plan reports, by one wavefront behind the chain's launch or barrier; it waits about 3 us for the host's memory.
 __device__ __forceinline__ void tell_totals(const PlanState& ps, Report told)
 {
-    const uint32_t d = threadIdx.x;
-    if (d >= TENT_MAX_RAILS) return;
+    static_assert(TENT_MAX_RAILS == 64, "lane = rail");
+    const uint32_t d = threadIdx.x & 63u;
     tell(&told.to->T[d], ps.T[d]);
     tell(&told.to->cnt[d], ps.cnt[d]);
     tell(&told.to->A_after[d], ps.A_after[d]);
