@@ -9,7 +9,7 @@
 // run takes the m smallest triples (f_d(k), d, k) in lexicographic order, and the slice at position
 // p of the run gets the triple of rank p.  Three steps follow from that:
 //   1. run table     maximal runs of equal-length pending slices: on a first plan written with the slice table, on a
-//                    re-plan from the pending list (flag heads, exclusive scan);
+//                    re-plan with the list of pending slices (split.hip);
 //   2. chain         one wavefront, lane = rail, walks the runs in order and finds, per run, how many
 //                    slots k_d each rail takes.  A second wavefront, the feeder, goes ahead of it and hands it one record
 //                    per run with everything that does not depend on the rails' state, among it the cost level at
@@ -82,50 +82,6 @@ __device__ __forceinline__ uint32_t slots_upto(const Rail& r, uint64_t A, uint32
     if (room > want) room = want;
     const uint64_t k = div_exact(room, l, inv_l);
     return (uint32_t)(k < m ? k : m);
-}
-
-// ---- step 1: run table of a re-plan ------------------------------------------------------------
-struct RunHead {
-    const uint32_t* s_len;
-    const uint32_t* pending;
-    const uint64_t* n_pending;    // device-resident count of positions
-    __device__ uint64_t operator()(uint64_t q) const
-    {
-        if (q >= *n_pending) return 0;
-        if (q == 0) return 1;
-        return s_len[pending[q]] != s_len[pending[q - 1]];
-    }
-};
-
-struct PendingLen {
-    const uint32_t* s_len;
-    const uint32_t* pending;
-    const uint64_t* n_pending;
-    __device__ uint64_t operator()(uint64_t q) const
-    {
-        if (q >= *n_pending) return 0;
-        return s_len[pending[q]];
-    }
-};
-
-__global__ void __launch_bounds__(256) run_table_kernel(BatchDev b)
-{
-    const uint64_t n = b.plan->n_pending;
-    RunHead head{b.s_len, b.pending, &b.plan->n_pending};
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += stride) {
-        const bool starts = head(q) != 0;
-        const uint64_t run = b.scan_tmp[q] - (starts ? 0 : 1);
-        b.s_run[q] = (uint32_t)run;
-        if (starts && run < b.run_capacity) b.run_start[run] = (uint32_t)q;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        // a transfer contributes at most two runs, so the capacity of 2 * n_desc always suffices
-        uint64_t n_runs = b.scan_tmp[b.n_slices];
-        if (n_runs > b.run_capacity) n_runs = b.run_capacity;
-        b.plan->n_runs = n_runs;
-        b.run_start[n_runs] = (uint32_t)n;
-    }
 }
 
 // ---- step 2: chain over runs: exact slot counts -----------------------------------------------
@@ -1624,14 +1580,6 @@ hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, R
     const int up = use_pending ? 1 : 0;
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 4096) blocks = 4096;
-    // A first plan has its run table from the slice table's expansion.  A re-plan finds run ids (a scan of the run heads) and
-    // the bytes bound before every pending position in the same launches.
-    if (use_pending) {
-        hipError_t e = run_scans(s, scan_job(RunHead{b.s_len, b.pending, &b.plan->n_pending}, b.n_slices, b.scan_tmp, b.scan_partials),
-                                 scan_job(PendingLen{b.s_len, b.pending, &b.plan->n_pending}, b.n_slices, b.len_pre, b.scan_partials2));
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(run_table_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);
-    }
     auto launch_chain = [&](auto wide) {
         constexpr int kW = decltype(wide)::value;
         if (mode & kBindBuildTables)

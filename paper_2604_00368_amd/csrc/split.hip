@@ -301,42 +301,166 @@ hipError_t launch_stage_and_mark(const BatchDev& b, uint8_t* arena, bool compact
     return hipGetLastError();
 }
 
-// ---- E1: ascending lists of slices that are not DONE ------------------------------------------
-// Two lists from one scan: slices that never failed (bound by predicted cost) are counted in the
-// low half of the scanned word, slices with a retry count (bound by rotation) in the high half.
-struct NotDoneSplit {
-    const uint8_t* state;
-    const uint8_t* retry;
-    __device__ uint64_t operator()(uint64_t i) const
-    {
-        if (state[i] == TENT_SLICE_DONE) return 0;
-        return retry[i] ? (1ull << 32) : 1ull;
-    }
+// ---- E1: what a re-plan starts from ------------------------------------------------------------
+// Ascending lists of the slices that are not DONE -- those that never failed (bound by predicted cost) and those with a retry
+// count (bound by rotation) -- and of the former the bytes before every position and the maximal runs of equal length
+// (bind_runs.hip).  A scan in two launches, as in scan.h: what each tile of the slice table holds, then every workgroup
+// combines the tiles before its own and writes its part.  A run starts where a pending slice's length differs from that of the
+// pending slice before it, which may lie any number of tiles back: a maximum over (place + 1, length) finds it.
+// What bounds it is launches: 20,000 slices took six (two scans of two, the lists, the run table) and 30 us on MI355X, and take two and
+// 11.  Every workgroup reads 32 bytes of every tile before its own, which up to 10^6 slices costs less than a launch.
+struct TileShare {                     // of scan_partials, scan_partials2, scan_partials3 and scan_tmp, an entry per tile
+    uint64_t counts;                   // pending | retried << 20 | runs that start inside << 40 (the first pending slice left out)
+    uint64_t bytes;                    // of the pending slices
+    uint64_t last;                     // (tile + 1) << 32 | length of the last pending slice, 0 if there is none
+    uint64_t first_len;                // length of the first pending slice
 };
 
-__global__ void __launch_bounds__(256) compact_kernel(BatchDev b)
+// A thread's kScanItems slices.
+struct PendingItems {
+    uint32_t len[kScanItems];
+    uint32_t pending = 0, retried = 0;                       // a bit per slice
+    __device__ PendingItems(const BatchDev& b, uint64_t base)
+    {
+        static_assert(kScanItems == 8, "a thread's slices are read as two words of states and retries and two of four lengths");
+        uint64_t state = 0, retry = 0;
+        if (base + kScanItems <= b.n_slices) {               // (the arrays start at multiples of 256 bytes)
+            state = *reinterpret_cast<const uint64_t*>(b.s_state + base);
+            retry = *reinterpret_cast<const uint64_t*>(b.s_retry + base);
+            const uint4 low = *reinterpret_cast<const uint4*>(b.s_len + base), high = *reinterpret_cast<const uint4*>(b.s_len + base + 4);
+            len[0] = low.x, len[1] = low.y, len[2] = low.z, len[3] = low.w;
+            len[4] = high.x, len[5] = high.y, len[6] = high.z, len[7] = high.w;
+        } else {
+#pragma unroll
+            for (uint32_t k = 0; k < kScanItems; ++k) {
+                const bool there = base + k < b.n_slices;
+                state |= (uint64_t)(there ? b.s_state[base + k] : TENT_SLICE_DONE) << (8 * k);
+                retry |= (uint64_t)(there ? b.s_retry[base + k] : 0) << (8 * k);
+                len[k] = there ? b.s_len[base + k] : 0;
+            }
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kScanItems; ++k) {
+            if ((uint8_t)(state >> (8 * k)) == TENT_SLICE_DONE) continue;
+            if ((uint8_t)(retry >> (8 * k))) retried |= 1u << k; else pending |= 1u << k;
+        }
+    }
+    // length of the last pending slice, behind one of length `before` (0: none)
+    __device__ uint32_t last(uint32_t before) const
+    {
+#pragma unroll
+        for (uint32_t k = 0; k < kScanItems; ++k) if ((pending >> k) & 1) before = len[k];
+        return before;
+    }
+    __device__ uint64_t bytes() const
+    {
+        uint64_t sum = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kScanItems; ++k) if ((pending >> k) & 1) sum += len[k];
+        return sum;
+    }
+    // a bit per slice that starts a run, behind a pending slice of length `before`
+    __device__ uint32_t heads(uint32_t before) const
+    {
+        uint32_t h = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kScanItems; ++k) {
+            if (!((pending >> k) & 1)) continue;
+            if (len[k] != before) h |= 1u << k;
+            before = len[k];
+        }
+        return h;
+    }
+};
+// (place of the thread + 1, length of its last pending slice), 0 if it has none
+__device__ __forceinline__ uint64_t last_of(const PendingItems& it)
 {
-    const uint64_t n = b.n_slices;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        if (b.s_state[i] == TENT_SLICE_DONE) continue;
-        const uint64_t at = b.scan_tmp[i];
-        if (b.s_retry[i]) b.retry_ids[at >> 32] = (uint32_t)i;
-        else              b.pending[at & 0xFFFFFFFFu] = (uint32_t)i;
+    return it.pending ? ((uint64_t)(threadIdx.x + 1) << 32) | it.last(0) : 0;
+}
+
+__global__ void __launch_bounds__(kScanBlock) pending_share_kernel(BatchDev b)
+{
+    const PendingItems it(b, (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems);
+    uint64_t last, counts, bytes;
+    const uint64_t before = block_exclusive_scan(last_of(it), &last, ScanMax{});
+    uint32_t heads = it.heads((uint32_t)before);
+    if (it.pending && before == 0) {                         // the tile's first pending slice: seen by the next kernel
+        const uint32_t k = (uint32_t)__ffs((int)it.pending) - 1;
+        heads &= ~(1u << k);
+        uint32_t first = 0;
+#pragma unroll
+        for (uint32_t e = 0; e < kScanItems; ++e) first = e == k ? it.len[e] : first;
+        b.scan_tmp[blockIdx.x] = first;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        b.plan->n_pending = b.scan_tmp[n] & 0xFFFFFFFFu;
-        b.plan->n_retry = b.scan_tmp[n] >> 32;
+    block_exclusive_scan((uint64_t)__popc(it.pending) | ((uint64_t)__popc(it.retried) << 20) | ((uint64_t)__popc(heads) << 40), &counts,
+                         ScanSum{});
+    block_exclusive_scan(it.bytes(), &bytes, ScanSum{});
+    if (threadIdx.x != 0) return;
+    b.scan_partials[blockIdx.x] = counts;
+    b.scan_partials2[blockIdx.x] = bytes;
+    b.scan_partials3[blockIdx.x] = last ? ((uint64_t)(blockIdx.x + 1) << 32) | (uint32_t)last : 0;
+}
+
+__global__ void __launch_bounds__(kScanBlock) pending_lists_kernel(BatchDev b)
+{
+    const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
+    const PendingItems it(b, base);
+    uint64_t lists = 0, runs = 0, bytes = 0, last = 0;       // of the tiles before: pending | retried << 32, runs, bytes, last
+    for (uint32_t lo = 0; lo < blockIdx.x; lo += kScanBlock) {
+        const uint32_t u = lo + threadIdx.x;
+        TileShare s{0, 0, 0, 0};
+        if (u < blockIdx.x) s = TileShare{b.scan_partials[u], b.scan_partials2[u], b.scan_partials3[u], b.scan_tmp[u]};
+        uint64_t row_last, row_lists, row_runs, row_bytes;
+        const uint64_t in_row = block_exclusive_scan(s.last, &row_last, ScanMax{});
+        const uint32_t len_before = (uint32_t)(in_row ? in_row : last);
+        const uint32_t starts = s.last != 0 && (uint32_t)s.first_len != len_before ? 1u : 0u;
+        block_exclusive_scan((s.counts & 0xFFFFFu) | (((s.counts >> 20) & 0xFFFFFu) << 32), &row_lists, ScanSum{});
+        block_exclusive_scan((s.counts >> 40) + starts, &row_runs, ScanSum{});
+        block_exclusive_scan(s.bytes, &row_bytes, ScanSum{});
+        lists += row_lists;
+        runs += row_runs;
+        bytes += row_bytes;
+        last = row_last ? row_last : last;
     }
+    uint64_t total, all_bytes;
+    const uint64_t in_tile = block_exclusive_scan(last_of(it), &total, ScanMax{});
+    const uint32_t heads = it.heads((uint32_t)(in_tile ? in_tile : last));
+    const uint64_t at = block_exclusive_scan(
+        (uint64_t)__popc(it.pending) | ((uint64_t)__popc(it.retried) << 20) | ((uint64_t)__popc(heads) << 40), &total, ScanSum{});
+    bytes += block_exclusive_scan(it.bytes(), &all_bytes, ScanSum{});
+    uint32_t q = (uint32_t)lists + (uint32_t)(at & 0xFFFFFu), r = (uint32_t)(lists >> 32) + (uint32_t)((at >> 20) & 0xFFFFFu);
+    uint64_t run = runs + (at >> 40);                        // runs that start before the slice
+#pragma unroll
+    for (uint32_t k = 0; k < kScanItems; ++k) {
+        if ((it.retried >> k) & 1) b.retry_ids[r++] = (uint32_t)(base + k);
+        if (!((it.pending >> k) & 1)) continue;
+        // a transfer contributes at most two runs, so the capacity of 2 * n_desc always suffices
+        if ((heads >> k) & 1) {
+            if (run < b.run_capacity) b.run_start[run] = q;
+            ++run;
+        }
+        b.pending[q] = (uint32_t)(base + k);
+        b.s_run[q] = (uint32_t)(run - 1);
+        b.len_pre[q] = bytes;
+        bytes += it.len[k];
+        ++q;
+    }
+    if (blockIdx.x != gridDim.x - 1 || threadIdx.x != 0) return;
+    const uint64_t n_pending = (lists & 0xFFFFFFFFu) + (total & 0xFFFFFu);
+    uint64_t n_runs = runs + (total >> 40);
+    if (n_runs > b.run_capacity) n_runs = b.run_capacity;
+    b.plan->n_pending = n_pending;
+    b.plan->n_retry = (lists >> 32) + ((total >> 20) & 0xFFFFFu);
+    b.plan->n_runs = n_runs;
+    b.run_start[n_runs] = (uint32_t)n_pending;
 }
 
 hipError_t launch_compact(const BatchDev& b, hipStream_t s)
 {
-    hipError_t e = exclusive_scan(NotDoneSplit{b.s_state, b.s_retry}, b.n_slices, b.scan_tmp, b.scan_partials, s);
-    if (e != hipSuccess) return e;
-    uint64_t blocks = (b.n_slices + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(compact_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);
+    const uint64_t tiles = scan_tiles(b.n_slices);
+    if (tiles == 0 || tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(pending_share_kernel, dim3((uint32_t)tiles), dim3(kScanBlock), 0, s, b);
+    hipLaunchKernelGGL(pending_lists_kernel, dim3((uint32_t)tiles), dim3(kScanBlock), 0, s, b);
     return hipGetLastError();
 }
 

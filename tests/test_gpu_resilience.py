@@ -272,3 +272,38 @@ def test_rotation_with_many_rails(H, oracle, R):
         assert list(info.rail_bytes)[:R] == b2.T.tolist() and list(info.stage_base)[:R] == b2.base.tolist()
         assert list(info.rail_slices)[:R] == b2.n_slices.tolist()
         assert int((retry > 0).sum()) == int(per.sum()) > 0
+
+
+@pytest.mark.parametrize("n", [1, 8, 2047, 2048, 2049, 6145, 256 * 2048 + 2049])
+def test_lists_of_a_replan_at_the_edges_of_their_tiles(H, oracle, n):
+    # 8 slices to a thread, 2048 to a tile, 256 tiles to a row: what every rail drained in half its bytes is done, which empties the
+    # first tiles; one rail's slices are retried; equal and unequal lengths meet across tiles
+    from paper_2604_00368_amd import binding as T
+    from test_gpu_chain import transfers
+    S = 64
+    rng = np.random.Generator(np.random.PCG64(n))
+    count = np.minimum(rng.integers(1, 80, size=n), 1 + rng.integers(0, 4000, size=n) // 40)
+    count = count[:np.searchsorted(np.cumsum(count), n) + 1]
+    count[-1] -= int(count.sum()) - n
+    lens = count * S - np.where(rng.random(count.shape[0]) < 0.5, 0, rng.integers(0, S, size=count.shape[0]))
+    w = transfers(lens, S, W.make_rails([20000, 50000, 35000, 80000, 50000], queued=rng.integers(0, 4096, 5)))
+    s = oracle.split(w.src_ptr, w.src_ext, w.slice_bytes)
+    assert s.n == n
+    with H.Engine(w) as eng:
+        eng.declare()
+        st, info = eng.plan()
+        for rnd in range(4):
+            T.tent_sim_fail(eng.ctx, eng.batch, np.array([0, rnd == 1, rnd == 0, 0, rnd < 2], dtype=np.uint8), True, eng.stream)
+            half = np.array(list(info.rail_bytes)[:5], dtype=np.uint64) // np.uint64(2)
+            T.tent_sim_advance(eng.ctx, eng.batch, w.rails["queued_bytes"] + half, eng.stream)
+            eng.execute()
+            pending = np.flatnonzero(eng.table()["state"] != 2).astype(np.uint32)
+            assert 0 < pending.shape[0] and (n < 2047 or pending.shape[0] < n)
+            b = oracle.plan(s.len, T.tent_get_retries(eng.ctx, eng.batch), w.rails, ids=pending)
+            st, info = eng.plan()
+            tab = eng.table()
+            assert info.n_slices == pending.shape[0]
+            assert np.array_equal(tab["rail"][pending], b.rail[pending])
+            assert np.array_equal(tab["stage_off"][pending], b.stage_off[pending])
+            assert list(info.rail_bytes)[:5] == b.T.tolist()
+            assert list(info.rail_slices)[:5] == b.n_slices.tolist()
