@@ -1493,6 +1493,7 @@ __global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, R
     __shared__ SmallPlan<kWide> sh;
     const uint32_t t = threadIdx.x, e0 = 2 * t, e1 = 2 * t + 1;
     const uint32_t ns = (uint32_t)b.n_src_ext, nd = (uint32_t)b.n_dst_ext, D = b.n_desc, N = (uint32_t)b.n_slices;
+    const SliceDiv div(b.slice_bytes);
     {   // extent prefixes of both sides, and in address order where a table goes by it
         const uint64_t s0 = e0 < ns ? b.src_ext[e0].len : 0, s1 = e1 < ns ? b.src_ext[e1].len : 0;
         const uint64_t d0 = e0 < nd ? b.dst_ext[e0].len : 0, d1 = e1 < nd ? b.dst_ext[e1].len : 0;
@@ -1517,7 +1518,7 @@ __global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, R
     }
     __syncthreads();
     {   // first slice and runs before every transfer
-        const TransferCounts counts{b.src_ptr, sh.src_pre, b.slice_bytes};
+        const TransferCounts counts{b.src_ptr, sh.src_pre, div};
         const uint64_t c0 = e0 < D ? counts(e0) : 0, c1 = e1 < D ? counts(e1) : 0;
         const uint64_t at = pair_prefix(c0, c1, sh.wave_out);
         auto one = [&](uint32_t j, uint64_t v) {
@@ -1538,7 +1539,7 @@ __global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, R
             const uint32_t mid = lo + ((hi - lo) >> 1);
             if (sh.first[mid] <= i) lo = mid; else hi = mid;
         }
-        write_slice(b, i, lo, sh.first[lo], sh.runs_before[lo], sh.src_pre, sh.dst_pre);
+        write_slice(b, div, i, lo, sh.first[lo], sh.runs_before[lo], sh.src_pre, sh.dst_pre);
     }
     if (t == 0) {
         const uint32_t n_runs = sh.runs_before[D];

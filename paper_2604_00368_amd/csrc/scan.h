@@ -84,15 +84,28 @@ inline uint64_t scan_tiles(uint64_t n) { return (n + kScanTile - 1) / kScanTile;
 
 // (everything below has internal linkage: the same instantiation may exist in several translation units, each
 // with its own code object)
+// A lane's items, 0 behind the last one.  Without a branch around f its loads are all in flight at once; a scan of 128 transfers,
+// whose f loads twice, was eight such pairs one after the other (MI355X: 9.3 -> 6.7 us).
+template <class J>
+static __device__ __forceinline__ void read_items(const J& job, uint64_t base, uint64_t (&v)[kScanItems])
+{
+#pragma unroll
+    for (int k = 0; k < (int)kScanItems; ++k) {
+        const uint64_t i = base + k;
+        const uint64_t x = job.f(i < job.n ? i : job.n - 1);
+        v[k] = i < job.n ? x : 0;
+    }
+}
+
 template <class J>
 static __device__ __forceinline__ void scan_reduce_job(const J& job)
 {
     const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
     if ((uint64_t)blockIdx.x * kScanTile >= job.n) return;
-    uint64_t sum = 0;
+    uint64_t v[kScanItems], sum = 0;
+    read_items(job, base, v);
 #pragma unroll
-    for (int k = 0; k < (int)kScanItems; ++k)
-        if (base + k < job.n) sum = job.op(sum, job.f(base + k));
+    for (int k = 0; k < (int)kScanItems; ++k) sum = job.op(sum, v[k]);
     uint64_t total;
     block_exclusive_scan(sum, &total, job.op);
     if (threadIdx.x == 0) job.partials[blockIdx.x] = total;
@@ -127,13 +140,10 @@ static __device__ __forceinline__ void scan_down_job(const J& job, bool spined)
         for (uint64_t t = threadIdx.x; t < blockIdx.x; t += kScanBlock) mine = job.op(mine, job.partials[t]);
         block_exclusive_scan(mine, &before, job.op);
     }
-    uint64_t v[kScanItems];
-    uint64_t sum = 0;
+    uint64_t v[kScanItems], sum = 0;
+    read_items(job, base, v);
 #pragma unroll
-    for (int k = 0; k < (int)kScanItems; ++k) {
-        v[k] = base + k < job.n ? job.f(base + k) : 0;
-        sum = job.op(sum, v[k]);
-    }
+    for (int k = 0; k < (int)kScanItems; ++k) sum = job.op(sum, v[k]);
     uint64_t total;
     uint64_t run = job.op(before, block_exclusive_scan(sum, &total, job.op));
 #pragma unroll
