@@ -258,8 +258,8 @@ int tent_declare_static(tent_ctx *ctx, uint32_t n_desc,
  * bound by rotation ahead of this pass; see there.
  * `rails` is host memory (n_rails <= TENT_MAX_RAILS).  `info` is host memory or
  * NULL; when it is non-NULL the call waits for the stream as far as the figures
- * and fills it (the last kernel may still be writing the slice table: work that is
- * enqueued on `stream` comes after it), when it is NULL the call only enqueues work
+ * and fills it (its last kernel may still be writing the slice table; the batch's
+ * next call comes after it, on whatever stream), when it is NULL the call only enqueues work
  * on `stream`.
  * Returns TENT_DEFER (and binds nothing) when every rail is excluded;
  * TENT_ERR_INVALID for a health value above 2 (and for a batch that failed its overlap check, see

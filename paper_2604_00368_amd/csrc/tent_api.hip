@@ -54,6 +54,9 @@ struct Batch {
     hipEvent_t replan_at = nullptr;          // what a re-plan on another stream waits for: prep_event, done_at, or nothing
     bool done_recorded = false;
     hipEvent_t done_at = nullptr;            // the event that ends the last execute: its stream's mark, or done_event
+    // A call that has reported something may have returned before its last kernel had quite ended, on this stream.
+    bool reported = false;
+    hipStream_t report_stream = nullptr;
     bool may_replan = false;                 // slices may be left over by the next execute: the simulator or a dispatch ran since the plan
     // The declaration's device work (descriptor upload, address sort, overlap check) runs on the
     // context's own stream and ends at decl_event; `verdict` (pinned host memory) then holds the
@@ -153,24 +156,6 @@ Report next_report(tent_ctx* ctx, bool wanted)
     return wanted ? Report{ctx->host_plan, ++ctx->reports} : Report{nullptr, 0};
 }
 
-// Waits until the figures of `told` are there: everything enqueued on `s` before the kernel that tells them has ended then, and
-// that kernel is past its last look at what it counts (a plan's goes on to write the slices' rails).  After kReportSpin, under
-// capture (where it is refused) and behind an error this is a wait for the stream: a call of more than a millisecond does not
-// notice the 4 us.
-constexpr std::chrono::microseconds kReportSpin{1000};
-hipError_t await_report(const Report& told, hipStream_t s)
-{
-    if (capturing(s)) return hipStreamSynchronize(s);
-    const auto until = std::chrono::steady_clock::now() + kReportSpin;
-    do {
-        for (int k = 0; k < 64; ++k) {
-            if (__atomic_load_n(&told.to->call, __ATOMIC_ACQUIRE) == told.call) return hipSuccess;
-            __builtin_ia32_pause();
-        }
-    } while (std::chrono::steady_clock::now() < until);
-    return hipStreamSynchronize(s);
-}
-
 // Remember that work of the batch was just enqueued on `s` (nothing is recorded into a stream that is
 // being captured into a graph: such work is only known to be over when the device is idle).
 StreamMark* note_stream(Batch& b, hipStream_t s)
@@ -199,6 +184,39 @@ struct StreamNote {
     StreamNote(Batch& batch, hipStream_t stream) : b(batch), s(stream) {}
     ~StreamNote() { if (b.alive && !noted) (void)note_stream(b, s); }
 };
+
+// Waits until the figures of `told` are there: everything enqueued on `s` before the kernel that tells them has ended then, and
+// that kernel is past its last look at what it counts (a plan's goes on to write the slices' rails).  After kReportSpin, under
+// capture (where it is refused) and behind an error this is a wait for the stream: a call of more than a millisecond does not
+// notice the 4 us.
+constexpr std::chrono::microseconds kReportSpin{1000};
+hipError_t await_report(Batch& b, const Report& told, hipStream_t s)
+{
+    if (capturing(s)) return hipStreamSynchronize(s);
+    const auto until = std::chrono::steady_clock::now() + kReportSpin;
+    do {
+        for (int k = 0; k < 64; ++k) {
+            if (__atomic_load_n(&told.to->call, __ATOMIC_ACQUIRE) == told.call) {
+                b.reported = true;
+                b.report_stream = s;
+                return hipSuccess;
+            }
+            __builtin_ia32_pause();
+        }
+    } while (std::chrono::steady_clock::now() < until);
+    return hipStreamSynchronize(s);
+}
+
+// Callers may go on with the batch on another stream without an event of their own behind a call that waits.  What is left of its last
+// kernel is waited for here then, on the host as that call would have.
+hipError_t order_after_report(Batch& b, hipStream_t s)
+{
+    if (!b.reported || s == b.report_stream) return hipSuccess;
+    b.reported = false;
+    for (const StreamMark& m : b.marks)
+        if (m.used && m.stream == b.report_stream) return hipEventSynchronize(m.event);
+    return hipStreamSynchronize(b.report_stream);
+}
 
 // Host-side wait for everything that was enqueued for the batch.
 void wait_batch_idle(Batch& b)
@@ -1113,6 +1131,7 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
         if (too_small) return TENT_ERR_RANGE;
     }
     const BatchDev& d = b->dev;
+    HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
     if (b->decl_pending) HIP_TRY(hipStreamWaitEvent(s, b->decl_event, 0));
     HIP_TRY(order_after_execute_bookkeeping(*b, s));
@@ -1189,7 +1208,7 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
             HIP_TRY(hipMemcpyAsync(ctx->host_plan, d.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
             HIP_TRY(hipStreamSynchronize(s));
         } else {
-            HIP_TRY(await_report(told, s));
+            HIP_TRY(await_report(*b, told, s));
         }
         const PlanState& ps = *ctx->host_plan;
         std::memset(info, 0, sizeof(*info));
@@ -1262,6 +1281,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     if (!g.ok) return TENT_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const BatchDev& d = b->dev;
+    HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
     HIP_TRY(order_after_execute_bookkeeping(*b, s));
     dp.all_high = priority ? 0u : 1u;
@@ -1294,7 +1314,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     for (uint32_t r = 0; r < n_rails; ++r) b->last_lat_ns[r] = rails[r].lat_ns;
 
     if (info) {
-        HIP_TRY(await_report(told, s));
+        HIP_TRY(await_report(*b, told, s));
         const PlanState& ps = *ctx->host_plan;
         std::memset(info, 0, sizeof(*info));
         b->bound_hint = ps.n_bound;
@@ -1343,6 +1363,7 @@ int tent_sim_advance(tent_ctx* ctx, tent_batch_t batch, const uint64_t* budget_b
         bp.queued[d] = b->last_rails.A[d];
         bp.budget[d] = budget_bytes[d];
     }
+    HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
     b->may_replan = true;
     const Report told = next_report(ctx, n_done != nullptr);
@@ -1354,7 +1375,7 @@ int tent_sim_advance(tent_ctx* ctx, tent_batch_t batch, const uint64_t* budget_b
         if (bp.budget[d] > bp.queued[d]) tiles += (bp.budget[d] - bp.queued[d]) / (b->dev.tile_bytes ? b->dev.tile_bytes : 1u);
     b->tile_hint = tiles;
     if (!n_done) return TENT_OK;
-    HIP_TRY(await_report(told, s));
+    HIP_TRY(await_report(*b, told, s));
     b->bound_hint = ctx->host_plan->n_done;
     *n_done = ctx->host_plan->n_done;
     return TENT_OK;
@@ -1378,6 +1399,7 @@ int tent_sim_fail(tent_ctx* ctx, tent_batch_t batch, const uint8_t* rail_failed,
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
     const Report told = next_report(ctx, any && failed_per_rail);
     if (any) {
@@ -1388,7 +1410,7 @@ int tent_sim_fail(tent_ctx* ctx, tent_batch_t batch, const uint8_t* rail_failed,
     if (failed_per_rail) {
         for (uint32_t d = 0; d < n_rails; ++d) failed_per_rail[d] = 0;
         if (any) {
-            HIP_TRY(await_report(told, s));
+            HIP_TRY(await_report(*b, told, s));
             for (uint32_t d = 0; d < n_rails; ++d) failed_per_rail[d] = ctx->host_plan->fail_cnt[d];
         }
     }
@@ -1428,6 +1450,7 @@ int tent_sim_latency(tent_ctx* ctx, tent_batch_t batch, const uint32_t* true_bw_
     if (max_q >= (1ull << 53) || b->payload >= (1ull << 53) || max_q + b->payload >= (1ull << 53)) return TENT_ERR_RANGE;
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
+    HIP_TRY(order_after_report(*b, static_cast<hipStream_t>(stream)));
     StreamNote note(*b, static_cast<hipStream_t>(stream));
     HIP_TRY(launch_sim_latency(b->dev, lp, static_cast<hipStream_t>(stream)));
     return TENT_OK;
@@ -1452,12 +1475,13 @@ int tent_update_bandwidth(tent_ctx* ctx, tent_batch_t batch, const tent_probe_pa
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    HIP_TRY(order_after_report(*b, s));
     const Report told = next_report(ctx, true);
     {
         StageTimer t(ctx, TENT_T_FEEDBACK, s);
         HIP_TRY(launch_probe(b->dev, pp, told, s));
     }
-    HIP_TRY(await_report(told, s));
+    HIP_TRY(await_report(*b, told, s));
     for (uint32_t d = 0; d < n_rails; ++d) {
         rails[d].bw_MBps = ctx->host_plan->bw_next[d];
         if (probe_MBps_out) probe_MBps_out[d] = ctx->host_plan->probe[d];
@@ -1489,6 +1513,7 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
     // When the host knows that only a small part of the batch is BOUND (after the rail simulator), the
     // copies run over a list of the tiles of the BOUND slices and their launches are sized by that part.
@@ -1538,6 +1563,7 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
     };
     b->has_done = true;
     b->bound_hint = 0;
+    b->reported = false;                 // what follows the execute follows the report
     if (copies() != hipSuccess) {
         (void)hipGetLastError();
         b->broken = true;
@@ -1563,6 +1589,7 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
     uint8_t* arena = static_cast<uint8_t*>(ctx->cfg.staging_arena);
     const uint64_t payload = b->payload;
@@ -1630,6 +1657,7 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     b->replan_at = nullptr;
     b->has_done = true;
     b->bound_hint = 0;
+    b->reported = false;
     HIP_TRY(record_execute_done(*b, s, note));
     // the range copies read what a re-plan rewrites, and the DONE marks come last: a re-plan on another stream waits for it all
     if (b->done_recorded) b->replan_at = b->done_at;
@@ -1646,12 +1674,13 @@ int tent_poll(tent_ctx* ctx, tent_batch_t batch, uint64_t* remaining, void* stre
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    HIP_TRY(order_after_report(*b, s));
     // slices are marked DONE ahead of their copies: completion is only reported once the last
     // execute's copies have ended, whichever stream the caller polls on
     if (b->done_recorded && s != b->exec_stream) HIP_TRY(hipStreamWaitEvent(s, b->done_at, 0));
     const Report told = next_report(ctx, true);
     HIP_TRY(launch_count_remaining(b->dev, told, s));
-    HIP_TRY(await_report(told, s));
+    HIP_TRY(await_report(*b, told, s));
     *remaining = ctx->host_plan->n_remaining;
     return TENT_OK;
 }
@@ -1664,6 +1693,7 @@ int tent_reset(tent_ctx* ctx, tent_batch_t batch, void* stream)
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    HIP_TRY(order_after_report(*b, s));
     if (b->planned) {
         StreamNote note(*b, s);
         // the reset must not overtake the copies of an execute that runs on another stream

@@ -12,6 +12,8 @@ static struct { int kind; void *stream, *what; } log_[MOST];
 static int n_log, n_kernels, fail_host_waits;
 static struct { const void *fn; const char *name; } kernel[KERNELS];
 static void *capturing_stream;
+static int answer, n_host;
+static struct { char *at; size_t n; } host[64];
 
 static void note(int kind, void *stream, void *what)
 {
@@ -34,6 +36,8 @@ const char *fake_kernel_name(const void *fn)
 }
 void fake_fail_host_waits(int n) { fail_host_waits = n; }
 void fake_capture(void *stream) { capturing_stream = stream; }
+/* a small plan's launch answers its report, a block of host memory and a number: the number goes to the block's last word */
+void fake_answer_reports(int on) { answer = on; }
 
 /* ---- the runtime ---- */
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -61,7 +65,13 @@ static void *map(size_t n)
 }
 hipError_t hipMalloc(void **p, size_t n) { *p = map(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void *p) { (void)p; return hipSuccess; }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned flags) { (void)flags; *p = calloc(n, 1); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned flags)
+{
+    (void)flags;
+    *p = calloc(n, 1);
+    if (n_host < 64) { host[n_host].at = *p; host[n_host].n = n; ++n_host; }
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
 hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *symbol)
 {
@@ -117,8 +127,13 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *sh, hipStream_t *
 }
 hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **args, size_t sh, hipStream_t s)
 {
-    (void)g; (void)b; (void)args; (void)sh;
+    (void)g; (void)b; (void)sh;
     note(LAUNCH, s, (void *)fn);
+    if (answer && strstr(fake_kernel_name(fn), "plan_small_kernel")) {
+        const struct { char *to; unsigned long long call; } *report = args[2];
+        for (int k = 0; k < n_host; ++k)
+            if (host[k].at == report->to) memcpy(host[k].at + host[k].n - 8, &report->call, 8);
+    }
     return hipSuccess;
 }
 void **__hipRegisterFatBinary(const void *data) { static void *handle; (void)data; return &handle; }

@@ -252,6 +252,37 @@ def test_a_call_whose_figures_do_not_come_waits_for_its_stream(fake, captured):
     run(fake, "figures_that_do_not_come", captured)
 
 
+def go_on_elsewhere():
+    h = Host(slice_bytes=4096)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    b = T.tent_declare(h.ctx, *h.extents(64, 4096))
+    calls = [lambda s: T.tent_plan(h.ctx, b, rails, False, s), lambda s: T.tent_sim_fail(h.ctx, b, np.ones(2, dtype=np.uint8), False, s),
+             lambda s: T.tent_sim_advance(h.ctx, b, np.zeros(2, dtype=np.uint64), s), lambda s: T.tent_execute(h.ctx, b, s),
+             lambda s: T.tent_sim_latency(h.ctx, b, np.array([5, 5], dtype=np.uint32), s), lambda s: T.tent_reset(h.ctx, b, s)]
+    T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+    for k, call in enumerate(calls):
+        h.hip.fake_answer_reports(1)
+        h.log()
+        T.tent_plan(h.ctx, b, rails, True, STREAM_A)
+        seen = h.log()
+        h.hip.fake_answer_reports(0)
+        assert not [x for x in seen if x[0] == HOST_WAIT and x[1] == STREAM_A]
+        mark = [x[2] for x in seen if x[0] == RECORD and x[1] == STREAM_A][-1]
+        call(STREAM_B)
+        log = h.log()
+        waits = [i for i, x in enumerate(log) if x[0] == HOST_WAIT and x[2] == mark]
+        launches = [i for i, x in enumerate(log) if x[0] == LAUNCH]
+        assert waits and waits[0] < launches[0], k
+        T.tent_reset(h.ctx, b, STREAM_A)
+        T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+    T.tent_destroy(h.ctx)
+
+
+def test_a_call_on_another_stream_waits_for_what_a_report_left(fake):
+    """A call that reports returns once its figures are there; its kernel may still be writing the tables."""
+    run(fake, "go_on_elsewhere")
+
+
 # The largest batches tent_declare_static accepts, in units of each kind: flags 0, no overlap check, bounded staging, both;
 # with 16 rails and with 64 each.  Found by bisection over a library whose limit was the space its tables took.
 STATIC_LIMITS = {
