@@ -883,8 +883,10 @@ __device__ __forceinline__ Int4 rank_next_slots(double u, double lc1, double Y0,
 //   `tight` see to that.  (Below zero both give 0.)
 //   Taken: the run takes the guessed slots and the m - sum cheapest of the rails' next ones, if no rail takes two of those:
 //   its second one costs more than the level by at least the smallest lc1, so keys below near_key are all in order.
-//   Single slice: after the split every rail's next slot ends above the level and some rail's last one below near_key, so by
-//   kMaxStep no key lies below the window, the least one lies inside it, and it is the cheapest.
+//   Single slice: where slots were only added every rail's next slot ends above the level and some rail's last one below near_key,
+//   so by kMaxStep no key lies below the window, the least one lies inside it, and it is the cheapest.  Behind dropped slots
+//   (walk_runs) and behind another single slice a key may lie below the window too, where all are 0 but for the rail: there
+//   a least key from either end of the window sends the record to odd_record.
 // MI355X: about 65 instructions and 310 clocks (125 ns) per transfer of a run and a tail, from 110 and 640 with one-by-one
 // repairs and the bytes bound kept here: reset, plan and execute of 24,576 transfers on 16 rails 15.5 -> 11.6 ms, of 4,096 2.68
 // -> 2.04 ms, of 2,048 shorter by partial pages 1.44 -> 1.06 ms.  What is not a stretch of equal slice lengths goes through
@@ -1146,7 +1148,7 @@ __device__ __forceinline__ void bind_chain16(const BatchDev& b, const RailParams
             if (__builtin_amdgcn_readfirstlane((int)(s.z + r.z)) != 0) {   // a single slice stands behind it
                 const double y = fma((double)(s.z + r.z), c1, X1);
                 const uint32_t mine = tagged_key(y, who), best = row_reduce32(mine, Min32{});
-                if (__builtin_amdgcn_ballot_w64(best >= kFarKey16) != 0) break;
+                if (__builtin_amdgcn_ballot_w64(best - 16u >= kFarKey16 - 16u) != 0) break;
                 X1 = mine == best ? y : X1;
                 word |= best << kBitsOfSlots;
             }

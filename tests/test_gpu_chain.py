@@ -137,3 +137,38 @@ def test_ways_of_taking_a_record(H, oracle, kind, singles, equal):
              "five_live": lambda: W.make_rails(g.integers(10000, 400000, size=6), lat_ns=g.integers(0, 20000, size=6),
                                                health=[0, 1, 2, 0, 0, 0])}[kind]()
     check_binding(H, oracle, transfers(stretches(g, S, 500 if S < 1 << 20 else 60, singles, equal), S, rails))
+
+
+# A run of slices much shorter than the last one meets rails that the longer one has left far apart: the guess of its split is
+# too high, the dearest slots are dropped again and some rail's next slot ends more than 134 us below the level.  The
+# slice behind the run must still go where it costs least.
+DROPPED = {
+    # three rails of 25 GB/s: 451 us on one of them, two slices of 35 us, one of 40 ns, which belongs on rail 2
+    "behind_one_slice": (16 << 20, [11287500, 875000, 875000, 1000], dict(bw_MBps=[25000] * 3, queued=[0, 1000, 0]), [0, 2, 1, 2]),
+    "behind_a_run": (5600000, [5600000] * 2 + [440000] * 2 + [10000],
+                     dict(bw_MBps=[10000] * 3, lat_ns=0, queued=[0, 5700000, 5605000]), [0, 0, 2, 1, 2]),
+}
+
+
+@pytest.mark.parametrize("case", sorted(DROPPED))
+def test_slice_behind_dropped_slots(H, oracle, case):
+    S, lens, rails, want = DROPPED[case]
+    w = transfers(lens, S, W.make_rails(**rails))
+    assert oracle.bind(oracle.split(w.src_ptr, w.src_ext, S).len, w.rails).rail.tolist() == want
+    check_binding(H, oracle, w)
+
+
+@pytest.mark.parametrize("R", [2, 3, 5, 8])
+@pytest.mark.parametrize("singles", [1, 3, 4])
+@pytest.mark.parametrize("seed", [0, 1, 2])
+def test_slices_behind_runs_of_dropped_slots(H, oracle, R, singles, seed):
+    # the same at random, over and over: a long slice or two, 2 - 8 equal ones of 20 - 60 us, then a few short ones, of which the
+    # first goes with the run and up to three more as runs of none
+    g = np.random.Generator(np.random.PCG64([R, singles, seed]))
+    S, bw = 16 << 20, g.integers(12500, 50001, size=R) if seed else np.full(R, 25000)
+    lens = []
+    for _ in range(24):
+        lens += [int(g.integers(1 << 20, S))] * int(g.integers(1, 3))
+        lens += [int(g.integers(20, 61) * bw.mean())] * int(g.integers(2, 9))
+        lens += g.permutation(np.arange(1, 40))[:singles].tolist()
+    check_binding(H, oracle, transfers(lens, S, W.make_rails(bw, queued=g.integers(0, 1 << 20, size=R))))
