@@ -1125,23 +1125,27 @@ __device__ __forceinline__ void bind_chain16(const BatchDev& b, const RailParams
             if (__builtin_amdgcn_ballot_w64((takes & (key >= near_key)) | ((int)lacking < 0)) == 0) {
                 kk += takes ? 1u : 0u;
             } else {
-                uint32_t last = 0;
+                uint32_t farthest = 0;                                     // of all keys used
                 int more = __builtin_amdgcn_readfirstlane((int)lacking);
                 for (; more > 0; --more) {
-                    last = row_reduce32(key, Min32{});
+                    const uint32_t up = row_reduce32(key, Min32{});
                     const double beyond = pn + lc1;
-                    kk += key == last ? 1u : 0u;
-                    pn = key == last ? beyond : pn;
+                    farthest = up > farthest ? up : farthest;
+                    kk += key == up ? 1u : 0u;
+                    pn = key == up ? beyond : pn;
                     key = tagged_key(pn, who);
                 }
-                for (; more < 0; ++more) {                                 // 1 - floor(ps) of the last slot taken, 1 and up
+                // 1 - floor(ps) of the last slot taken, 1 and up.  Where that is beyond the window on every rail with a slot, rails
+                // without one are taken for it too, and what follows has any key: the first such step must not be forgotten
+                for (; more < 0; ++more) {
                     const uint32_t down = kk != 0 ? tagged_key(kDownFrom + lc1 - pn, 15u - who) : ~0u;
                     const double before = pn - lc1;
-                    last = row_reduce32(down, Min32{});
-                    kk -= down == last ? 1u : 0u;
-                    pn = down == last ? before : pn;
+                    const uint32_t least = row_reduce32(down, Min32{});
+                    farthest = least > farthest ? least : farthest;
+                    kk -= down == least ? 1u : 0u;
+                    pn = down == least ? before : pn;
                 }
-                if (__builtin_amdgcn_ballot_w64(last >= kFarKey16) != 0) break;
+                if (__builtin_amdgcn_ballot_w64(farthest >= kFarKey16) != 0) break;
                 X1 = pn - lc1;
             }
             uint32_t word = kk;

@@ -147,6 +147,8 @@ DROPPED = {
     "behind_one_slice": (16 << 20, [11287500, 875000, 875000, 1000], dict(bw_MBps=[25000] * 3, queued=[0, 1000, 0]), [0, 2, 1, 2]),
     "behind_a_run": (5600000, [5600000] * 2 + [440000] * 2 + [10000],
                      dict(bw_MBps=[10000] * 3, lat_ns=0, queued=[0, 5700000, 5605000]), [0, 0, 2, 1, 2]),
+    # three slots to drop, of which the second ends beyond the window too, where the rail without a slot looks alike
+    "beyond_the_window": (8000000, [3000000] + [50000] * 3, dict(bw_MBps=[2000, 10000], lat_ns=0, queued=[500000, 2700000]), [1, 0, 0, 0]),
 }
 
 
