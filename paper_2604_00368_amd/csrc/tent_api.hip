@@ -208,10 +208,11 @@ hipError_t await_report(Batch& b, const Report& told, hipStream_t s)
 }
 
 // Callers may go on with the batch on another stream without an event of their own behind a call that waits.  What is left of its last
-// kernel is waited for here then, on the host as that call would have.
+// kernel is waited for here then, on the host as that call would have.  Not where `s` is being captured, which permits no wait for
+// work outside the graph: when the graph runs is its caller's to order.
 hipError_t order_after_report(Batch& b, hipStream_t s)
 {
-    if (!b.reported || s == b.report_stream) return hipSuccess;
+    if (!b.reported || s == b.report_stream || capturing(s)) return hipSuccess;
     b.reported = false;
     for (const StreamMark& m : b.marks)
         if (m.used && m.stream == b.report_stream) return hipEventSynchronize(m.event);

@@ -36,8 +36,11 @@ const char *fake_kernel_name(const void *fn)
 }
 void fake_fail_host_waits(int n) { fail_host_waits = n; }
 void fake_capture(void *stream) { capturing_stream = stream; }
-/* a small plan's launch answers its report, a block of host memory and a number: the number goes to the block's last word */
+/* a launch that reports answers its report, a block of host memory and a number: the number goes to the block's last word */
 void fake_answer_reports(int on) { answer = on; }
+static const struct { const char *name; int arg; } reporter[] = {
+    {"plan_small_kernel", 2}, {"dispatch_emit_kernel", 3}, {"retire_kernel", 2}, {"fail_kernel", 2}, {"probe_kernel", 2}, {"count_remaining_kernel", 1},
+};
 
 /* ---- the runtime ---- */
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -129,8 +132,9 @@ hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **args, size_t s
 {
     (void)g; (void)b; (void)sh;
     note(LAUNCH, s, (void *)fn);
-    if (answer && strstr(fake_kernel_name(fn), "plan_small_kernel")) {
-        const struct { char *to; unsigned long long call; } *report = args[2];
+    for (size_t r = 0; answer && r < sizeof(reporter) / sizeof(reporter[0]); ++r) {
+        if (!strstr(fake_kernel_name(fn), reporter[r].name)) continue;
+        const struct { char *to; unsigned long long call; } *report = args[reporter[r].arg];
         for (int k = 0; k < n_host; ++k)
             if (host[k].at == report->to) memcpy(host[k].at + host[k].n - 8, &report->call, 8);
     }

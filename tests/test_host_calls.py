@@ -283,6 +283,37 @@ def test_a_call_on_another_stream_waits_for_what_a_report_left(fake):
     run(fake, "go_on_elsewhere")
 
 
+def capture_elsewhere():
+    h = Host(slice_bytes=4096)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    b = T.tent_declare(h.ctx, *h.extents(64, 4096))
+    reports = [lambda: T.tent_plan(h.ctx, b, rails, True, STREAM_A),
+               lambda: T.tent_plan_dispatch(h.ctx, b, rails, h.W.make_dispatch_params(1 << 18), None, True, STREAM_A),
+               lambda: T.tent_sim_fail(h.ctx, b, np.ones(2, dtype=np.uint8), True, STREAM_A),
+               lambda: T.tent_sim_advance(h.ctx, b, np.zeros(2, dtype=np.uint64), STREAM_A),
+               lambda: T.tent_update_bandwidth(h.ctx, b, h.W.make_probe_params([50000, 25000]), rails, STREAM_A),
+               lambda: T.tent_poll(h.ctx, b, STREAM_A)]
+    for k, report in enumerate(reports):
+        T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+        h.hip.fake_answer_reports(1)
+        report()
+        h.hip.fake_answer_reports(0)
+        h.log()
+        h.hip.fake_capture(STREAM_B)
+        T.tent_reset(h.ctx, b, STREAM_B)
+        T.tent_plan(h.ctx, b, rails, False, STREAM_B)
+        T.tent_execute(h.ctx, b, STREAM_B)
+        h.hip.fake_capture(0)
+        seen = h.log()
+        assert {x[0] for x in seen} == {LAUNCH} and {x[1] for x in seen} == {STREAM_B}, (k, seen)
+    T.tent_destroy(h.ctx)
+
+
+def test_a_cycle_captured_behind_a_report_elsewhere(fake):
+    """Into a stream that is being captured a cycle is kernels only, whatever reported on another stream before."""
+    run(fake, "capture_elsewhere")
+
+
 # The largest batches tent_declare_static accepts, in units of each kind: flags 0, no overlap check, bounded staging, both;
 # with 16 rails and with 64 each.  Found by bisection over a library whose limit was the space its tables took.
 STATIC_LIMITS = {
