@@ -54,8 +54,9 @@ struct Batch {
     hipEvent_t replan_at = nullptr;          // what a re-plan on another stream waits for: prep_event, done_at, or nothing
     bool done_recorded = false;
     hipEvent_t done_at = nullptr;            // the event that ends the last execute: its stream's mark, or done_event
-    // A call that has reported something may have returned before its last kernel had quite ended, on this stream.
-    bool reported = false;
+    // A call that has reported something may have returned before its last kernel had quite ended: the mark that ends it, and its
+    // stream (which the caller may have destroyed since: it is only compared with).
+    hipEvent_t report_at = nullptr;
     hipStream_t report_stream = nullptr;
     bool may_replan = false;                 // slices may be left over by the next execute: the simulator or a dispatch ran since the plan
     // The declaration's device work (descriptor upload, address sort, overlap check) runs on the
@@ -190,21 +191,30 @@ struct StreamNote {
 // capture (where it is refused) and behind an error this is a wait for the stream: a call of more than a millisecond does not
 // notice the 4 us.
 constexpr std::chrono::microseconds kReportSpin{1000};
-hipError_t await_report(Batch& b, const Report& told, hipStream_t s)
+hipError_t await_figures(const Report& told, hipStream_t s)
 {
     if (capturing(s)) return hipStreamSynchronize(s);
     const auto until = std::chrono::steady_clock::now() + kReportSpin;
     do {
         for (int k = 0; k < 64; ++k) {
-            if (__atomic_load_n(&told.to->call, __ATOMIC_ACQUIRE) == told.call) {
-                b.reported = true;
-                b.report_stream = s;
-                return hipSuccess;
-            }
+            if (__atomic_load_n(&told.to->call, __ATOMIC_ACQUIRE) == told.call) return hipSuccess;
             __builtin_ia32_pause();
         }
     } while (std::chrono::steady_clock::now() < until);
     return hipStreamSynchronize(s);
+}
+
+// The same for a call that writes the batch's tables: what is left of it then ends at the stream's mark, which the call records itself,
+// while its kernels run.  Without a mark it waits for the stream.  (A call that only counts leaves nothing: its figures go out
+// behind its last access to the batch.)
+hipError_t await_report(Batch& b, const Report& told, hipStream_t s, StreamNote& note)
+{
+    const StreamMark* mark = note_stream(b, s);
+    note.noted = true;
+    if (!mark) return hipStreamSynchronize(s);
+    b.report_at = mark->event;
+    b.report_stream = s;
+    return await_figures(told, s);
 }
 
 // Callers may go on with the batch on another stream without an event of their own behind a call that waits.  What is left of its last
@@ -212,11 +222,10 @@ hipError_t await_report(Batch& b, const Report& told, hipStream_t s)
 // work outside the graph: when the graph runs is its caller's to order.
 hipError_t order_after_report(Batch& b, hipStream_t s)
 {
-    if (!b.reported || s == b.report_stream || capturing(s)) return hipSuccess;
-    b.reported = false;
-    for (const StreamMark& m : b.marks)
-        if (m.used && m.stream == b.report_stream) return hipEventSynchronize(m.event);
-    return hipStreamSynchronize(b.report_stream);
+    if (!b.report_at || s == b.report_stream || capturing(s)) return hipSuccess;
+    const hipEvent_t end = b.report_at;
+    b.report_at = nullptr;
+    return hipEventSynchronize(end);
 }
 
 // Host-side wait for everything that was enqueued for the batch.
@@ -295,6 +304,7 @@ void free_batch(tent_ctx* ctx, Batch& b)
     b.alive = false;
     b.decl_pending = false;
     b.replan_at = nullptr;
+    b.report_at = nullptr;
     b.done_recorded = false;
     b.marks_lost = false;
     for (StreamMark& m : b.marks) { m.used = false; m.stream = nullptr; }
@@ -660,6 +670,7 @@ hipError_t record_execute_done(Batch& b, hipStream_t s, StreamNote& note)
     }
     b.exec_stream = s;
     b.done_recorded = true;
+    b.report_at = nullptr;               // what follows the execute follows the report
     return hipSuccess;
 }
 
@@ -1209,7 +1220,7 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
             HIP_TRY(hipMemcpyAsync(ctx->host_plan, d.plan, sizeof(PlanState), hipMemcpyDeviceToHost, s));
             HIP_TRY(hipStreamSynchronize(s));
         } else {
-            HIP_TRY(await_report(*b, told, s));
+            HIP_TRY(await_report(*b, told, s, note));
         }
         const PlanState& ps = *ctx->host_plan;
         std::memset(info, 0, sizeof(*info));
@@ -1315,7 +1326,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     for (uint32_t r = 0; r < n_rails; ++r) b->last_lat_ns[r] = rails[r].lat_ns;
 
     if (info) {
-        HIP_TRY(await_report(*b, told, s));
+        HIP_TRY(await_report(*b, told, s, note));
         const PlanState& ps = *ctx->host_plan;
         std::memset(info, 0, sizeof(*info));
         b->bound_hint = ps.n_bound;
@@ -1376,7 +1387,7 @@ int tent_sim_advance(tent_ctx* ctx, tent_batch_t batch, const uint64_t* budget_b
         if (bp.budget[d] > bp.queued[d]) tiles += (bp.budget[d] - bp.queued[d]) / (b->dev.tile_bytes ? b->dev.tile_bytes : 1u);
     b->tile_hint = tiles;
     if (!n_done) return TENT_OK;
-    HIP_TRY(await_report(*b, told, s));
+    HIP_TRY(await_report(*b, told, s, note));
     b->bound_hint = ctx->host_plan->n_done;
     *n_done = ctx->host_plan->n_done;
     return TENT_OK;
@@ -1411,7 +1422,7 @@ int tent_sim_fail(tent_ctx* ctx, tent_batch_t batch, const uint8_t* rail_failed,
     if (failed_per_rail) {
         for (uint32_t d = 0; d < n_rails; ++d) failed_per_rail[d] = 0;
         if (any) {
-            HIP_TRY(await_report(*b, told, s));
+            HIP_TRY(await_report(*b, told, s, note));
             for (uint32_t d = 0; d < n_rails; ++d) failed_per_rail[d] = ctx->host_plan->fail_cnt[d];
         }
     }
@@ -1482,7 +1493,7 @@ int tent_update_bandwidth(tent_ctx* ctx, tent_batch_t batch, const tent_probe_pa
         StageTimer t(ctx, TENT_T_FEEDBACK, s);
         HIP_TRY(launch_probe(b->dev, pp, told, s));
     }
-    HIP_TRY(await_report(*b, told, s));
+    HIP_TRY(await_figures(told, s));
     for (uint32_t d = 0; d < n_rails; ++d) {
         rails[d].bw_MBps = ctx->host_plan->bw_next[d];
         if (probe_MBps_out) probe_MBps_out[d] = ctx->host_plan->probe[d];
@@ -1564,7 +1575,6 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
     };
     b->has_done = true;
     b->bound_hint = 0;
-    b->reported = false;                 // what follows the execute follows the report
     if (copies() != hipSuccess) {
         (void)hipGetLastError();
         b->broken = true;
@@ -1658,7 +1668,6 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     b->replan_at = nullptr;
     b->has_done = true;
     b->bound_hint = 0;
-    b->reported = false;
     HIP_TRY(record_execute_done(*b, s, note));
     // the range copies read what a re-plan rewrites, and the DONE marks come last: a re-plan on another stream waits for it all
     if (b->done_recorded) b->replan_at = b->done_at;
@@ -1681,7 +1690,7 @@ int tent_poll(tent_ctx* ctx, tent_batch_t batch, uint64_t* remaining, void* stre
     if (b->done_recorded && s != b->exec_stream) HIP_TRY(hipStreamWaitEvent(s, b->done_at, 0));
     const Report told = next_report(ctx, true);
     HIP_TRY(launch_count_remaining(b->dev, told, s));
-    HIP_TRY(await_report(*b, told, s));
+    HIP_TRY(await_figures(told, s));
     *remaining = ctx->host_plan->n_remaining;
     return TENT_OK;
 }

@@ -314,6 +314,38 @@ def test_a_cycle_captured_behind_a_report_elsewhere(fake):
     run(fake, "capture_elsewhere")
 
 
+def streams_that_are_gone():
+    h = Host(slice_bytes=4096)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    b = T.tent_declare(h.ctx, *h.extents(64, 4096))
+    T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+    reports = [lambda s: T.tent_plan(h.ctx, b, rails, True, s),
+               lambda s: T.tent_sim_fail(h.ctx, b, np.ones(2, dtype=np.uint8), True, s),
+               lambda s: T.tent_sim_advance(h.ctx, b, np.zeros(2, dtype=np.uint64), s),
+               lambda s: T.tent_update_bandwidth(h.ctx, b, h.W.make_probe_params([50000, 25000]), rails, s),
+               lambda s: T.tent_poll(h.ctx, b, s)]
+    goes_on = [lambda: T.tent_plan(h.ctx, b, rails, False, STREAM_A), lambda: T.tent_execute(h.ctx, b, STREAM_A),
+               lambda: T.tent_reset(h.ctx, b, STREAM_A)]
+    streams = iter(range(0x1000, 0x2000, 16))            # more of them than a batch has marks
+    for report in reports * 2:
+        for go_on in goes_on:
+            T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+            gone = next(streams)
+            h.hip.fake_answer_reports(1)
+            report(gone)
+            h.hip.fake_answer_reports(0)
+            h.log()                                      # the caller destroys the stream here
+            go_on()
+            assert gone not in [x[1] for x in h.log()]
+    T.tent_destroy(h.ctx)
+    assert all(s not in range(0x1000, 0x2000) for _, s, _ in h.log() if s)
+
+
+def test_a_stream_is_not_touched_once_a_call_has_reported_on_it(fake):
+    """A call that reports has waited for its stream: the caller may destroy it and go on with the batch on another."""
+    run(fake, "streams_that_are_gone")
+
+
 # The largest batches tent_declare_static accepts, in units of each kind: flags 0, no overlap check, bounded staging, both;
 # with 16 rails and with 64 each.  Found by bisection over a library whose limit was the space its tables took.
 STATIC_LIMITS = {
