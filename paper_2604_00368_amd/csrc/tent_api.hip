@@ -218,14 +218,14 @@ hipError_t await_report(Batch& b, const Report& told, hipStream_t s, StreamNote&
 }
 
 // Callers may go on with the batch on another stream without an event of their own behind a call that waits.  What is left of its last
-// kernel is waited for here then, on the host as that call would have.  Not where `s` is being captured, which permits no wait for
-// work outside the graph: when the graph runs is its caller's to order.
+// kernel is waited for there, on the device.  Not where `s` is being captured, which permits no wait for work outside the
+// graph: when the graph runs is its caller's to order.
 hipError_t order_after_report(Batch& b, hipStream_t s)
 {
     if (!b.report_at || s == b.report_stream || capturing(s)) return hipSuccess;
     const hipEvent_t end = b.report_at;
     b.report_at = nullptr;
-    return hipEventSynchronize(end);
+    return hipStreamWaitEvent(s, end, 0);
 }
 
 // Host-side wait for everything that was enqueued for the batch.

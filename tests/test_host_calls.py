@@ -257,7 +257,7 @@ def go_on_elsewhere():
     T, rails = h.T, h.W.make_rails([50000, 25000])
     b = T.tent_declare(h.ctx, *h.extents(64, 4096))
     calls = [lambda s: T.tent_plan(h.ctx, b, rails, False, s), lambda s: T.tent_sim_fail(h.ctx, b, np.ones(2, dtype=np.uint8), False, s),
-             lambda s: T.tent_sim_advance(h.ctx, b, np.zeros(2, dtype=np.uint64), s), lambda s: T.tent_execute(h.ctx, b, s),
+             lambda s: T.tent_sim_advance(h.ctx, b, np.zeros(2, dtype=np.uint64), s, False), lambda s: T.tent_execute(h.ctx, b, s),
              lambda s: T.tent_sim_latency(h.ctx, b, np.array([5, 5], dtype=np.uint32), s), lambda s: T.tent_reset(h.ctx, b, s)]
     T.tent_plan(h.ctx, b, rails, False, STREAM_A)
     for k, call in enumerate(calls):
@@ -268,10 +268,12 @@ def go_on_elsewhere():
         h.hip.fake_answer_reports(0)
         assert not [x for x in seen if x[0] == HOST_WAIT and x[1] == STREAM_A]
         mark = [x[2] for x in seen if x[0] == RECORD and x[1] == STREAM_A][-1]
+        T.tent_sim_latency(h.ctx, b, np.array([5, 5], dtype=np.uint32), STREAM_A)     # more of the batch's work there
         call(STREAM_B)
         log = h.log()
-        waits = [i for i, x in enumerate(log) if x[0] == HOST_WAIT and x[2] == mark]
-        launches = [i for i, x in enumerate(log) if x[0] == LAUNCH]
+        assert not [x for x in log if x[0] == HOST_WAIT], k
+        waits = [i for i, x in enumerate(log) if x == (WAIT, STREAM_B, mark)]
+        launches = [i for i, x in enumerate(log) if x[:2] == (LAUNCH, STREAM_B)]
         assert waits and waits[0] < launches[0], k
         T.tent_reset(h.ctx, b, STREAM_A)
         T.tent_plan(h.ctx, b, rails, False, STREAM_A)
@@ -279,7 +281,8 @@ def go_on_elsewhere():
 
 
 def test_a_call_on_another_stream_waits_for_what_a_report_left(fake):
-    """A call that reports returns once its figures are there; its kernel may still be writing the tables."""
+    """A call that reports returns once its figures are there; its kernel may still be writing the tables.  Who goes on elsewhere
+    waits for that on the device: calls that only enqueue do not hold up the host."""
     run(fake, "go_on_elsewhere")
 
 
