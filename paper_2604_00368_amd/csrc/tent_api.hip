@@ -191,13 +191,17 @@ struct StreamNote {
 // capture (where it is refused) and behind an error this is a wait for the stream: a call of more than a millisecond does not
 // notice the 4 us.
 constexpr std::chrono::microseconds kReportSpin{1000};
-hipError_t await_figures(const Report& told, hipStream_t s)
+hipError_t await_figures(const Report& told, hipStream_t s, bool* looked = nullptr)
 {
+    if (looked) *looked = false;                         // the figures were there before the stream had been waited for
     if (capturing(s)) return hipStreamSynchronize(s);
     const auto until = std::chrono::steady_clock::now() + kReportSpin;
     do {
         for (int k = 0; k < 64; ++k) {
-            if (__atomic_load_n(&told.to->call, __ATOMIC_ACQUIRE) == told.call) return hipSuccess;
+            if (__atomic_load_n(&told.to->call, __ATOMIC_ACQUIRE) == told.call) {
+                if (looked) *looked = true;
+                return hipSuccess;
+            }
             __builtin_ia32_pause();
         }
     } while (std::chrono::steady_clock::now() < until);
@@ -1690,8 +1694,13 @@ int tent_poll(tent_ctx* ctx, tent_batch_t batch, uint64_t* remaining, void* stre
     if (b->done_recorded && s != b->exec_stream) HIP_TRY(hipStreamWaitEvent(s, b->done_at, 0));
     const Report told = next_report(ctx, true);
     HIP_TRY(launch_count_remaining(b->dev, told, s));
-    HIP_TRY(await_figures(told, s));
-    *remaining = ctx->host_plan->n_remaining;
+    bool looked = false;
+    HIP_TRY(await_figures(told, s, &looked));
+    const uint64_t left = ctx->host_plan->n_remaining;
+    // The figure says that the copies have ended, not that what they wrote has left the caches: that is what the event behind them, or
+    // the stream's end, waits for.
+    if (left == 0 && looked) HIP_TRY(b->done_recorded && !b->marks_lost ? hipEventSynchronize(b->done_at) : hipStreamSynchronize(s));
+    *remaining = left;
     return TENT_OK;
 }
 

@@ -36,7 +36,8 @@ const char *fake_kernel_name(const void *fn)
 }
 void fake_fail_host_waits(int n) { fail_host_waits = n; }
 void fake_capture(void *stream) { capturing_stream = stream; }
-/* a launch that reports answers its report, a block of host memory and a number: the number goes to the block's last word */
+/* a launch that reports answers its report, a block of host memory and a number: the number goes to the block's last word (1), with
+ * figures that are not zero in front of it (2) */
 void fake_answer_reports(int on) { answer = on; }
 static const struct { const char *name; int arg; } reporter[] = {
     {"plan_small_kernel", 2}, {"dispatch_emit_kernel", 3}, {"retire_kernel", 2}, {"fail_kernel", 2}, {"probe_kernel", 2}, {"count_remaining_kernel", 1},
@@ -136,7 +137,10 @@ hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **args, size_t s
         if (!strstr(fake_kernel_name(fn), reporter[r].name)) continue;
         const struct { char *to; unsigned long long call; } *report = args[reporter[r].arg];
         for (int k = 0; k < n_host; ++k)
-            if (host[k].at == report->to) memcpy(host[k].at + host[k].n - 8, &report->call, 8);
+            if (host[k].at == report->to) {
+                memset(host[k].at, answer - 1, host[k].n - 8);
+                memcpy(host[k].at + host[k].n - 8, &report->call, 8);
+            }
     }
     return hipSuccess;
 }

@@ -349,6 +349,43 @@ def test_a_stream_is_not_touched_once_a_call_has_reported_on_it(fake):
     run(fake, "streams_that_are_gone")
 
 
+def complete(bounded):
+    h = Host(flags=8 if bounded else 0)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    b = T.tent_declare(h.ctx, *h.extents(8, 65536))
+    host_waits = lambda: [x[1:] for x in h.log() if x[0] == HOST_WAIT]
+
+    def move(stream):
+        T.tent_plan(h.ctx, b, rails, False, stream)
+        h.log()
+        T.tent_execute_bounded(h.ctx, b, MiB, stream) if bounded else T.tent_execute(h.ctx, b, stream)
+        log = h.log()
+        return [x[2] for x in log if x[0] == RECORD][-1:]
+
+    for stream in (STREAM_A, STREAM_B):
+        ends = move(STREAM_A)
+        h.hip.fake_answer_reports(2)
+        assert T.tent_poll(h.ctx, b, stream) != 0 and not host_waits()
+        h.hip.fake_answer_reports(1)
+        assert T.tent_poll(h.ctx, b, stream) == 0 and host_waits() == [(None, e) for e in ends]
+        h.hip.fake_answer_reports(0)
+        assert T.tent_poll(h.ctx, b, stream) == 0 and host_waits() == [(stream, None)]
+    # an execute in a graph has no mark
+    h.hip.fake_capture(STREAM_B)
+    assert move(STREAM_B) == []
+    h.hip.fake_capture(0)
+    h.hip.fake_answer_reports(1)
+    assert T.tent_poll(h.ctx, b, STREAM_A) == 0 and host_waits() == [(STREAM_A, None)]
+    T.tent_destroy(h.ctx)
+
+
+@pytest.mark.parametrize("bounded", [False, True])
+def test_complete_means_that_the_copies_have_been_waited_for(fake, bounded):
+    """Nothing left over is the caller's leave to read the destination from anywhere: the copies' end, with its release to the whole
+    system, is waited for.  Where slices are left over the figure is enough."""
+    run(fake, "complete", bounded)
+
+
 # The largest batches tent_declare_static accepts, in units of each kind: flags 0, no overlap check, bounded staging, both;
 # with 16 rails and with 64 each.  Found by bisection over a library whose limit was the space its tables took.
 STATIC_LIMITS = {
