@@ -328,7 +328,8 @@ hipError_t launch_stage_and_mark(const BatchDev& b, uint8_t* arena, bool compact
 // combines the tiles before its own and writes its part.  A run starts where a pending slice's length differs from that of the
 // pending slice before it, which may lie any number of tiles back: a maximum over (place + 1, length) finds it.
 // What bounds it is launches: 20,000 slices took six (two scans of two, the lists, the run table) and 30 us on MI355X, and take two and
-// 11.  Every workgroup reads 32 bytes of every tile before its own, which up to 10^6 slices costs less than a launch.
+// 11.  Every workgroup reads 32 bytes of every tile before its own, which up to kSelfSpine tiles (4.2 million slices, 78 us) costs no
+// more than a launch; beyond them one workgroup combines them in between: 16.8 million slices 437 -> 260 us, 67 million 5281 -> 982.
 struct TileShare {                     // of scan_partials, scan_partials2, scan_partials3 and scan_tmp, an entry per tile
     uint64_t counts;                   // pending | retried << 20 | runs that start inside << 40 (the first pending slice left out)
     uint64_t bytes;                    // of the pending slices
@@ -421,27 +422,64 @@ __global__ void __launch_bounds__(kScanBlock) pending_share_kernel(BatchDev b)
     b.scan_partials3[blockIdx.x] = last ? ((uint64_t)(blockIdx.x + 1) << 32) | (uint32_t)last : 0;
 }
 
-__global__ void __launch_bounds__(kScanBlock) pending_lists_kernel(BatchDev b)
+// What a stretch of tiles holds.
+struct TilesHold {
+    uint64_t lists = 0;                // pending | retried << 32
+    uint64_t runs = 0;
+    uint64_t bytes = 0;
+    uint64_t last = 0;                 // as in TileShare
+};
+// The tiles [lo, end), at most kScanBlock of them, a thread each, by a whole workgroup: adds them to `all`, which holds those before lo;
+// returns those before the thread's own.
+__device__ __forceinline__ TilesHold add_tiles(const BatchDev& b, uint32_t lo, uint32_t end, TilesHold& all)
+{
+    const uint32_t u = lo + threadIdx.x;
+    TileShare s{0, 0, 0, 0};
+    if (u < end) s = TileShare{b.scan_partials[u], b.scan_partials2[u], b.scan_partials3[u], b.scan_tmp[u]};
+    TilesHold row, own;
+    own.last = block_exclusive_scan(s.last, &row.last, ScanMax{});
+    own.last = own.last ? own.last : all.last;
+    const uint32_t starts = s.last != 0 && (uint32_t)s.first_len != (uint32_t)own.last ? 1u : 0u;
+    own.lists = all.lists + block_exclusive_scan((s.counts & 0xFFFFFu) | (((s.counts >> 20) & 0xFFFFFu) << 32), &row.lists, ScanSum{});
+    own.runs = all.runs + block_exclusive_scan((s.counts >> 40) + starts, &row.runs, ScanSum{});
+    own.bytes = all.bytes + block_exclusive_scan(s.bytes, &row.bytes, ScanSum{});
+    all.lists += row.lists;
+    all.runs += row.runs;
+    all.bytes += row.bytes;
+    all.last = row.last ? row.last : all.last;
+    return own;
+}
+
+// One workgroup: every tile's share -> what the tiles before it hold, in the same words (`runs` where the first length was).
+__global__ void __launch_bounds__(kScanBlock) pending_spine_kernel(BatchDev b, uint32_t tiles)
+{
+    TilesHold all;
+    for (uint32_t lo = 0; lo < tiles; lo += kScanBlock) {
+        const TilesHold own = add_tiles(b, lo, tiles, all);
+        const uint32_t u = lo + threadIdx.x;
+        if (u >= tiles) continue;
+        b.scan_partials[u] = own.lists;
+        b.scan_partials2[u] = own.bytes;
+        b.scan_partials3[u] = own.last;
+        b.scan_tmp[u] = own.runs;
+    }
+}
+
+__global__ void __launch_bounds__(kScanBlock) pending_lists_kernel(BatchDev b, int spined)
 {
     const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
     const PendingItems it(b, base);
-    uint64_t lists = 0, runs = 0, bytes = 0, last = 0;       // of the tiles before: pending | retried << 32, runs, bytes, last
-    for (uint32_t lo = 0; lo < blockIdx.x; lo += kScanBlock) {
-        const uint32_t u = lo + threadIdx.x;
-        TileShare s{0, 0, 0, 0};
-        if (u < blockIdx.x) s = TileShare{b.scan_partials[u], b.scan_partials2[u], b.scan_partials3[u], b.scan_tmp[u]};
-        uint64_t row_last, row_lists, row_runs, row_bytes;
-        const uint64_t in_row = block_exclusive_scan(s.last, &row_last, ScanMax{});
-        const uint32_t len_before = (uint32_t)(in_row ? in_row : last);
-        const uint32_t starts = s.last != 0 && (uint32_t)s.first_len != len_before ? 1u : 0u;
-        block_exclusive_scan((s.counts & 0xFFFFFu) | (((s.counts >> 20) & 0xFFFFFu) << 32), &row_lists, ScanSum{});
-        block_exclusive_scan((s.counts >> 40) + starts, &row_runs, ScanSum{});
-        block_exclusive_scan(s.bytes, &row_bytes, ScanSum{});
-        lists += row_lists;
-        runs += row_runs;
-        bytes += row_bytes;
-        last = row_last ? row_last : last;
+    TilesHold before;
+    if (spined) {
+        before.lists = b.scan_partials[blockIdx.x];
+        before.bytes = b.scan_partials2[blockIdx.x];
+        before.last = b.scan_partials3[blockIdx.x];
+        before.runs = b.scan_tmp[blockIdx.x];
+    } else {
+        for (uint32_t lo = 0; lo < blockIdx.x; lo += kScanBlock) add_tiles(b, lo, blockIdx.x, before);
     }
+    const uint64_t lists = before.lists, runs = before.runs, last = before.last;
+    uint64_t bytes = before.bytes;
     uint64_t total, all_bytes;
     const uint64_t in_tile = block_exclusive_scan(last_of(it), &total, ScanMax{});
     const uint32_t heads = it.heads((uint32_t)(in_tile ? in_tile : last));
@@ -480,7 +518,9 @@ hipError_t launch_compact(const BatchDev& b, hipStream_t s)
     const uint64_t tiles = scan_tiles(b.n_slices);
     if (tiles == 0 || tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
     hipLaunchKernelGGL(pending_share_kernel, dim3((uint32_t)tiles), dim3(kScanBlock), 0, s, b);
-    hipLaunchKernelGGL(pending_lists_kernel, dim3((uint32_t)tiles), dim3(kScanBlock), 0, s, b);
+    const bool spined = tiles > kSelfSpine;
+    if (spined) hipLaunchKernelGGL(pending_spine_kernel, dim3(1), dim3(kScanBlock), 0, s, b, (uint32_t)tiles);
+    hipLaunchKernelGGL(pending_lists_kernel, dim3((uint32_t)tiles), dim3(kScanBlock), 0, s, b, spined ? 1 : 0);
     return hipGetLastError();
 }
 
