@@ -19,6 +19,13 @@
  *     must be used by one host thread at a time.
  *   - `stream` arguments are hipStream_t values passed as void* (NULL = the
  *     default stream).  Calls that take a stream only enqueue work unless stated.
+ *   - Calls that report figures to the host (tent_plan and tent_plan_dispatch with info != NULL, tent_sim_advance with
+ *     n_done != NULL, tent_sim_fail with failed_per_rail != NULL, tent_update_bandwidth, tent_poll) return once the
+ *     figures are there: everything that was enqueued on `stream` before the call has ended then, while the call's own last
+ *     kernel may still be writing the batch's tables.  The batch's next call comes after that by itself, on whatever stream
+ *     (its stream is made to wait; nothing is waited for on one that is being captured), and so does tent_release.
+ *     They are no synchronisation of `stream`: who reads what other work on it wrote from outside the device (host, other GPU,
+ *     unordered copy engine) synchronises as without them.  tent_poll that reports 0 is one for the batch's bytes; see there.
  *   - Calls on one batch are ordered by the caller: on one stream, or across streams by events
  *     of the caller's.  One ordering the library provides by itself: tent_plan and
  *     tent_plan_dispatch on another stream than the batch's last tent_execute wait (on the
@@ -34,7 +41,8 @@
  *     nothing from or to the host and enqueue kernels only (no memset nodes), so a caller may
  *     record them on a capturing stream and replay the graph.  The host-side bookkeeping of a
  *     batch (planned / moved) changes when the call is made, i.e. at capture time, so a recorded
- *     sequence should be a whole cycle: tent_reset, tent_plan, tent_execute.  Calls that read
+ *     sequence should be a whole cycle: tent_reset, tent_plan, tent_execute.  A replay is ordered by its caller behind the
+ *     streams that the batch's earlier calls were given (an event, or a synchronisation, also where that call reported).  Calls that read
  *     results back (info != NULL, tent_poll, tent_get_*, tent_sim_advance, tent_update_bandwidth)
  *     or take host arrays per call (tent_plan_dispatch with priorities) are not for capture.
  */
@@ -257,10 +265,8 @@ int tent_declare_static(tent_ctx *ctx, uint32_t n_desc,
  * rail totals rounded up to 256 bytes.  Slices that failed on a rail (tent_sim_fail) are
  * bound by rotation ahead of this pass; see there.
  * `rails` is host memory (n_rails <= TENT_MAX_RAILS).  `info` is host memory or
- * NULL; when it is non-NULL the call waits for the stream as far as the figures
- * and fills it (its last kernel may still be writing the slice table; the batch's
- * next call comes after it, on whatever stream), when it is NULL the call only enqueues work
- * on `stream`.
+ * NULL; when it is non-NULL the call waits for the figures and fills it, when it is NULL the call
+ * only enqueues work on `stream`.
  * Returns TENT_DEFER (and binds nothing) when every rail is excluded;
  * TENT_ERR_INVALID for a health value above 2 (and for a batch that failed its overlap check, see
  * tent_declare); TENT_ERR_RANGE when n_rails exceeds the context's max_rails, bw_MBps = 0,
@@ -311,7 +317,7 @@ int tent_get_modes(tent_ctx *ctx, tent_batch_t batch, uint8_t *host_out, uint64_
  * queued_bytes_d + stage_off + len <= budget_bytes[d]; otherwise it returns to
  * PENDING and will be re-planned (Section 4.3, idempotent retry).
  * `budget_bytes` is host memory with n_rails entries.  With n_done != NULL the call waits for
- * the stream and *n_done (host) receives the number of slices that stayed BOUND; with
+ * the figure and *n_done (host) receives the number of slices that stayed BOUND; with
  * n_done == NULL it only enqueues.  Either way the next tent_execute sizes its copy launches by
  * what can have stayed BOUND (at most budget_d - queued_bytes_d bytes per rail, and the count
  * when it was read back).
@@ -325,7 +331,7 @@ int tent_sim_advance(tent_ctx *ctx, tent_batch_t batch, const uint64_t *budget_b
  * and its retry count goes up by one (saturating at 255).  Call it after tent_plan and before
  * tent_sim_advance / tent_execute.  `rail_failed` is host memory with one entry per rail of the last
  * tent_plan; `failed_per_rail` (host, same length, or NULL) receives the number of slices that failed
- * on each rail, and when it is non-NULL the call waits for the stream.
+ * on each rail, and when it is non-NULL the call waits for the figures.
  *
  * The next tent_plan treats slices with a retry count differently: they are issued first, in
  * ascending slice index, without the cost model -- slice i on its k-th retry takes candidate number
@@ -384,7 +390,7 @@ int tent_sim_latency(tent_ctx *ctx, tent_batch_t batch, const uint32_t *true_bw_
  * A rail without a BOUND slice keeps its estimate.  `params` (host, n_rails entries) is read,
  * `rails` (host, n_rails entries) has its bw_MBps fields updated in place, `probe_MBps_out` (host,
  * n_rails entries or NULL) receives B_probe_d, 0 where the rail had no sample.  n_rails must equal
- * the rail count of the last tent_plan.  Waits for `stream`.
+ * the rail count of the last tent_plan.  Waits for the figures.
  */
 int tent_update_bandwidth(tent_ctx *ctx, tent_batch_t batch, const tent_probe_params *params,
                           tent_rail_state *rails, uint32_t n_rails, uint32_t *probe_MBps_out, void *stream);
@@ -444,8 +450,11 @@ int tent_execute(tent_ctx *ctx, tent_batch_t batch, void *stream);
 int tent_execute_bounded(tent_ctx *ctx, tent_batch_t batch, uint64_t chunk_bytes, uint32_t slots, void *stream);
 
 /* Batch-level completion (Section 4.4): *remaining (host) receives the number of
- * slices not DONE.  Waits for `stream`, which is first made to wait for the copies of the batch's
- * last execute if that ran on another stream: 0 means every byte of the batch has landed. */
+ * slices not DONE.  Waits for the figure; `stream` is first made to wait for the copies of the batch's
+ * last execute if that ran on another stream, so slices are counted behind them.  0 means every byte of the
+ * batch has landed: the call then waits for the end of those copies, with its release to the whole system, and the
+ * destination may be read from any stream, device or the host.  Above 0 nothing is said about the bytes of the slices
+ * that are DONE to readers outside `stream`. */
 int tent_poll(tent_ctx *ctx, tent_batch_t batch, uint64_t *remaining, void *stream);
 
 /* Return every slice of the batch to PENDING (the next tent_plan rebuilds the table). */

@@ -277,8 +277,7 @@ def test_rotation_with_many_rails(H, oracle, R):
 @pytest.mark.parametrize("n", [1, 8, 2047, 2048, 2049, 6145, 256 * 2048 + 2049, 2048 * 2048, 2048 * 2048 + 2049])
 def test_lists_of_a_replan_at_the_edges_of_their_tiles(H, oracle, n):
     # 8 slices to a thread, 2048 to a tile, 256 tiles to a row, a spine beyond 2048 tiles: what every rail drained in half its bytes is
-    # done, which empties the
-    # first tiles; one rail's slices are retried; equal and unequal lengths meet across tiles
+    # done, which empties the first tiles; one rail's slices are retried; equal and unequal lengths meet across tiles
     from paper_2604_00368_amd import binding as T
     from test_gpu_chain import transfers
     S = 64
