@@ -169,9 +169,9 @@ __device__ __forceinline__ void build_level_model(LevelModel& lm, const BatchDev
             lm.min_c1 = min_c1;
             // What rounding takes off the slot counts is a sum of n_live fractions, n_live / 2 with a deviation of
             // sqrt(n_live / 12).  Three deviations leave next to no guess too high; half the slots that all rails take while the
-            // fastest takes one, if that is less, so that seldom a rail is short of two.  Of 6,000 runs of 8 - 72 slices on 16 rails
-            // in two speeds none is too high or short of two, on 8 rails of 12.5 - 100 GB/s 0.2 %, on 8 equal rails and one of eight
-            // times their speed 12 %.
+            // fastest takes one, if that is less, so that seldom a rail is short of two.  Of 24,000 runs of 8 - 72 slices (counted with
+            // this arithmetic redone on the CPU) 0.03 % are too high and none short of two on 16 rails in two speeds, 0.05 % each
+            // on 8 rails of 12.5 - 100 GB/s, 6 % each on 8 equal rails and one of eight times their speed.
             const double spread = sqrt(0.75 * (double)n_live), room = 0.5 * sum_G * min_c1 * (1.0 / 65536.0);
             lm.short_by = kWide > 16 ? 0.0 : spread < room ? spread : room;
         }
@@ -210,7 +210,8 @@ constexpr uint32_t kTakeOdd = 0u, kTakeSame = 1u, kTakeRun = 2u, kTakeSingle = 3
 constexpr uint32_t kRecTake = 6, kRecCount = 8;        // first bits of the two
 constexpr uint32_t kFeedBlock = 64;        // runs the feeder looks at a time, one per lane
 constexpr uint32_t kRingRecords = 256;     // ring of more than 16 rails, in records
-constexpr uint32_t kRingBlocks = 3;        // ring of up to 16 rails, in blocks of kFeedBlock records
+constexpr uint32_t kRingBlocks = 3;        // ring of up to 16 rails, in blocks of kFeedBlock records: one fed, one walked, one drained
+                                           // (4,096 transfers 553 us; with two 551, with four 543 and 9 KB more of LDS)
 
 // The chain keeps costs relative to the level in units of 2^-16 ps, as doubles that hold whole numbers below 2^53
 // exactly.  A rail 2^kFarBits ps or more above the level counts as infinitely far until the state is rebased, which
@@ -362,7 +363,9 @@ __device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const 
         const uint32_t prev_len = prev_run < 0 ? last_len : len_there;
         // Up to 16 rails a single slice can go as a run of no slices behind the last run: at that run's level, below which no slot
         // is free any more, as long as the slice's cost is not too far above it.  That costs twice what walk_singles takes for a
-        // slice, but a change from runs to single slices and back costs as much as two slices, so it is for up to three in a row.
+        // slice, but saves a change from runs to single slices and back, so it is for up to three in a row.  MI355X, plans of about
+        // 4,000 transfers with as many short ones behind every few long ones: one 1156 -> 636 us, two 1038 -> 633, three 1003 ->
+        // 640, four go the other way and take 909.
         bool no_run = false;
         if constexpr (kWide == 16) {
             const uint64_t runs_behind = run_mask & ~below;
@@ -409,7 +412,9 @@ __device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const 
             const bool same_fits = rise * kFineUnit < l_f * lm.min_c1 * kMaxSlots;
             uint32_t take = !follows ? kTakeOdd : no_run ? kTakeSame : single ? kTakeSingle : !run_fits ? kTakeOdd
                                 : flags == kRecShort && same_fits ? kTakeSame : kTakeRun;
-            // a stretch of few records goes with the runs around it: a change of the way costs as much as a record
+            // a stretch of few records goes with the runs around it: a change of the way costs as much as a record.  The same plans
+            // in stretches of two equal slice lengths 1262 us by walk_same, 1015 by walk_runs; of three 1162 and 1080, of four 1142
+            // either way, of five 1037 and 1174
             const uint64_t others = written_mask & ~__ballot(take == kTakeSame);
             const uint64_t other_before = others & below, other_behind = others & ~below;
             const uint64_t stretch = written_mask & (other_before ? ~((2ull << (63 - __clzll((long long)other_before))) - 1) : ~0ull) &
@@ -892,7 +897,8 @@ __device__ __forceinline__ Int4 rank_next_slots(double u, double lc1, double Y0,
 // -> 2.04 ms, of 2,048 shorter by partial pages 1.44 -> 1.06 ms.  What is not a stretch of equal slice lengths goes through
 // walk_runs (about 600 clocks a record) and walk_singles (290), and only the first record, one behind a rebase, and a guess
 // off by more than a few slots through odd_record (1,100); a change of the way costs about 250, a plan of 50 runs takes what
-// it took.
+// it took.  Where many guesses do not hold this is slower than repairing one by one throughout: 512 transfers on eight equal
+// rails and one of eight times their speed, 136 of whose 448 runs are too high or short of two, take 243 us and took 160.
 struct ChainState {
     double X, lc1, inv, kf0;
     uint32_t near_key;
