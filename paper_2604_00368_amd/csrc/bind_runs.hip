@@ -238,6 +238,11 @@ constexpr uint32_t kLastBlock = 0x80000000u, kSteepBlock = 0x40000000u;
 constexpr uint32_t kStepped = ~0u;         // StepRing::Record::single of a record that stepped
 constexpr uint32_t kWalkLast = 24;         // records of the last block the chain takes between two reports to the drainer
 constexpr uint32_t kBitsOfSlots = 28;      // of a word in found
+// A record whose guess does not hold costs a stretch of walk_same about what kMissWorth of its records save against walk_runs: where
+// more of them miss, kMissFew at least, the rest of the block goes through walk_runs.  MI355X, chain and emit: 448 records of
+// which a third miss 257 us without this and 180 with it (at two misses 170, at three 175), 1,792 of which 6 % miss 407 and 399 (403,
+// 400), 512 of which 6 % miss 133 and 139 (147, 143).
+constexpr uint32_t kMissFew = 4, kMissWorth = 8;
 
 struct RecordRing {                        // more than 16 rails
     // {m, flags, shift} {length of the single slice as a double, run} {level, l, that length} {1 / l}
@@ -897,8 +902,7 @@ __device__ __forceinline__ Int4 rank_next_slots(double u, double lc1, double Y0,
 // -> 2.04 ms, of 2,048 shorter by partial pages 1.44 -> 1.06 ms.  What is not a stretch of equal slice lengths goes through
 // walk_runs (about 600 clocks a record) and walk_singles (290), and only the first record, one behind a rebase, and a guess
 // off by more than a few slots through odd_record (1,100); a change of the way costs about 250, a plan of 50 runs takes what
-// it took.  Where many guesses do not hold this is slower than repairing one by one throughout: 512 transfers on eight equal
-// rails and one of eight times their speed, 136 of whose 448 runs are too high or short of two, take 243 us and took 160.
+// it took.
 struct ChainState {
     double X, lc1, inv, kf0;
     uint32_t near_key;
@@ -1196,7 +1200,8 @@ __device__ __forceinline__ void bind_chain16(const BatchDev& b, const RailParams
         const uint32_t slot = block % kRingBlocks, base = slot * kFeedBlock;
         const uint32_t told = (uint32_t)__builtin_amdgcn_readfirstlane((int)ring.count[slot]);
         const uint32_t n = told & ~(kLastBlock | kSteepBlock);
-        uint32_t flags = ring.rec[base].flags;
+        uint32_t flags = ring.rec[base].flags, missed = 0;
+        bool one_by_one = false;                               // the block's stretches of equal slices too
         for (uint32_t i = 0; i < n;) {
             // a rail far above the level counts as infinitely far: look again where it lies
             if (i == 0 || (told & kSteepBlock)) rebase = rebase || __builtin_amdgcn_ballot_w64(live && !(st.X < 1.0e300)) != 0;
@@ -1205,13 +1210,15 @@ __device__ __forceinline__ void bind_chain16(const BatchDev& b, const RailParams
             uint32_t count = rebase || take == kTakeOdd ? 0u : flags >> kRecCount, went = 0;
             if ((told & kLastBlock) && count > kWalkLast) count = kWalkLast;
             if (count != 0) {
-                if (take == kTakeSame && (tight || is_tight())) {
+                if (take == kTakeSame && !one_by_one && (tight || is_tight())) {
                     flags = ring.rec[base + i + count].flags;            // of the record behind, as a rule the next one to look at
                     went = walk_same(base + i, count);
                     tight = true;
                     if (went < count) {
                         flags = (kTakeRun << kRecTake) | (1u << kRecCount);   // not by ranks: with the repairs of walk_runs
                         i += went;
+                        ++missed;
+                        one_by_one = missed >= kMissFew && missed * kMissWorth > i;
                         continue;
                     }
                 } else if (take == kTakeSingle) {
@@ -1219,7 +1226,7 @@ __device__ __forceinline__ void bind_chain16(const BatchDev& b, const RailParams
                     went = walk_singles(base + i, count);
                     tight = false;
                 } else {
-                    count = take == kTakeSame ? 1u : count;
+                    count = take == kTakeSame && !one_by_one ? 1u : count;
                     flags = ring.rec[base + i + count].flags;
                     went = walk_runs(base + i, count);
                     tight = true;
