@@ -211,7 +211,7 @@ constexpr uint32_t kRecTake = 6, kRecCount = 8;        // first bits of the two
 constexpr uint32_t kFeedBlock = 64;        // runs the feeder looks at a time, one per lane
 constexpr uint32_t kRingRecords = 256;     // ring of more than 16 rails, in records
 constexpr uint32_t kRingBlocks = 3;        // ring of up to 16 rails, in blocks of kFeedBlock records: one fed, one walked, one drained
-                                           // (4,096 transfers 553 us; with two 551, with four 543 and 9 KB more of LDS)
+                                           // (4,096 transfers 553 us; with two 551, with four 543 and 8 KB more of LDS)
 
 // The chain keeps costs relative to the level in units of 2^-16 ps, as doubles that hold whole numbers below 2^53
 // exactly.  A rail 2^kFarBits ps or more above the level counts as infinitely far until the state is rebased, which
@@ -370,7 +370,7 @@ __device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const 
         // is free any more, as long as the slice's cost is not too far above it.  That costs twice what walk_singles takes for a
         // slice, but saves a change from runs to single slices and back, so it is for up to three in a row.  MI355X, plans of about
         // 4,000 transfers with as many short ones behind every few long ones: one 1156 -> 636 us, two 1038 -> 633, three 1003 ->
-        // 640, four go the other way and take 909.
+        // 640; rows of four and six take 909 and 847 the other way, and would take 629 and 624 as runs of none.
         bool no_run = false;
         if constexpr (kWide == 16) {
             const uint64_t runs_behind = run_mask & ~below;

@@ -2,7 +2,7 @@
 // the number (await_report in tent_api.hip).  Waiting for the stream costs a packet behind the kernel that releases the caches to
 // the whole system, and a plan's figures are there before its last kernel has ended.  MI355X, waiting -> looking: the serving
 // call of 64 short transfers, which asks twice, 119 -> 112 us; two requests' 82,000 pages, twice, 840 -> 829; sixteen telemetry
-// windows, 35 times, 6260 -> 6070.
+// windows, 35 times, 6260 -> 6070.  Figures are all that is there then: a poll that reports complete waits for the copies' release too.
 #pragma once
 
 #include "tent_internal.h"
