@@ -417,9 +417,9 @@ __device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const 
             const bool same_fits = rise * kFineUnit < l_f * lm.min_c1 * kMaxSlots;
             uint32_t take = !follows ? kTakeOdd : no_run ? kTakeSame : single ? kTakeSingle : !run_fits ? kTakeOdd
                                 : flags == kRecShort && same_fits ? kTakeSame : kTakeRun;
-            // a stretch of few records goes with the runs around it: a change of the way costs as much as a record.  The same plans
-            // in stretches of two equal slice lengths 1262 us by walk_same, 1015 by walk_runs; of three 1162 and 1080, of four 1142
-            // either way, of five 1037 and 1174
+            // a stretch of few records goes with the runs around it: a change of the way costs as much as a record.  MI355X, plans of
+            // 4,096 transfers in stretches of two equal slice lengths 1262 us by walk_same, 1015 by walk_runs; of three 1162 and
+            // 1080, of four 1142 either way, of five 1037 and 1174
             const uint64_t others = written_mask & ~__ballot(take == kTakeSame);
             const uint64_t other_before = others & below, other_behind = others & ~below;
             const uint64_t stretch = written_mask & (other_before ? ~((2ull << (63 - __clzll((long long)other_before))) - 1) : ~0ull) &
