@@ -16,6 +16,8 @@
 // chain only needs the number of slots K_d each rail takes among the first n merged elements (a
 // floating-point estimate of the cut level, repaired with exact integer comparisons), and a second,
 // fully parallel kernel gives every slot its rank in the merge in closed form (R integer divisions).
+#include <type_traits>
+
 #include "scan.h"
 #include "tile_tables.h"
 #include "wave.h"
@@ -162,10 +164,283 @@ __device__ __forceinline__ void dispatch_chain(const BatchDev& b, const RailPara
     }
 }
 
-template <int kWide>
-__global__ void __launch_bounds__(64) dispatch_chain_kernel(BatchDev b, RailParams rp, DispatchParams dp)
+// ---- the chain of up to 16 rails ---------------------------------------------------------------
+// The same decisions where every cost fits what is computed with here (dispatch_is_near).  What bounds it is one wavefront's
+// instruction latency, about 5 clocks an instruction whatever its kind and 40 for a branch on a fresh comparison, so:
+//   - costs are doubles that hold whole numbers; a slot's key is its cost times 16 plus its rail, below 2^53, so one
+//     comparison settles cost and tie;
+//   - the cut level comes from 32-bit reciprocals: any level will do, because the slots a rail takes are those that cost no
+//     more than it, which is checked with the exact products.  What costs no more than a level is the beginning of the merge,
+//     and stays so with every slot that is added cheapest first or dropped dearest first: no exchange of slots is needed;
+//   - the guess is meant to be half a slot low.  Where nothing or one slot is missing (three requests in four), the reduction that
+//     names the dearest slot taken or the cheapest free one is the only one, and only the check of all that is a branch;
+//   - a second wavefront looks up the requests a block of 64 ahead, and sums up the rails' bytes and writes the rows a block
+//     behind; they meet at a barrier per block.
+// All four rows of the wavefront hold the same state (lane % 16 = rail).
+// MI355X, chain and emit, against the chain above: 1,110 requests on three rails 815 -> 343 us, 512 on nine with priorities 431 -> 201, all
+// HIGH 431 -> 300 (eight of the nine move in step, so that more slots are missing or too many at a time), 64 on three 59 -> 41.
+typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+struct Request {
+    Quad a;                                // slices not DONE (0: nothing to do) with kMice, bytes that the last of them is shorter than a
+                                           // slice, and what Stage 2 counts: the request for mice, at most a slice for elephants
+    Quad b;                                // rails whose slot takes the request; elephants: the slots the cut level is for, as a float;
+                                           // mice: the round-robin counter modulo kTurns
+};
+constexpr uint32_t kMice = 1u << 31;
+constexpr uint32_t kRequests = 64;         // of a block
+constexpr uint32_t kTurns = 720720;        // a multiple of every number up to 16
+constexpr uint32_t kLast = 1u << 28;       // found: slots of the rail, and whether it takes the request's last one
+constexpr double kNoRail = 1125899906842624.0;   // 2^50: more than any cost, for rails that do not take the request
+
+struct RequestRing {
+    Request req[2][kRequests];
+    uint32_t found[2][kRequests][16];
+    uint64_t n_pending, n_deferred, n_mice, n_elephant, n_bound;
+};
+
+// Requests [64 blk, 64 blk + 64), one per lane.
+__device__ __forceinline__ void feed_requests(const BatchDev& b, const DispatchParams& dp, RequestRing& ring, uint32_t blk, uint32_t lane)
 {
-    dispatch_chain<kWide>(b, rp, dp);
+    const uint32_t j = blk * kRequests + lane;
+    uint32_t mode = 0, pending = 0, admitted = 0, short_by = 0;
+    uint64_t len = 0;
+    bool mice = false;
+    if (j < b.n_desc) {
+        const uint64_t f0 = b.first[j], f1 = b.first[j + 1];
+        len = b.src_pre[b.src_ptr[j + 1]] - b.src_pre[b.src_ptr[j]];
+        const uint32_t prio = dp.all_high ? 2u : b.priority[j];
+        pending = (uint32_t)(b.scan_tmp[f1] - b.scan_tmp[f0]);
+        admitted = (uint32_t)dp.adm[prio > 2 ? 2 : prio] & 0xFFFFu;
+        mice = len < dp.theta;
+        if (b.s_state[f1 - 1] != TENT_SLICE_DONE) short_by = (uint32_t)(b.slice_bytes - (len - (f1 - f0 - 1) * b.slice_bytes));
+        if (!mice && len > b.slice_bytes) len = b.slice_bytes;
+        mode = pending == 0 ? 0u : admitted == 0 ? 3u : mice ? 1u : 2u;
+        b.req_mode[j] = (uint8_t)mode;
+    }
+    const uint64_t mice_mask = __ballot(mode == 1);
+    const uint32_t n = mode == 1 || mode == 2 ? pending : 0;
+    const uint64_t turn = (dp.rr_start + ring.n_mice + (uint64_t)__popcll(mice_mask & ((1ull << lane) - 1))) % kTurns;
+    // half a slot per rail, because the counts are rounded down, less the half that the guess is meant to be low by
+    const float want = (float)n + 0.5f * ((float)__popc(admitted) - 1.0f);
+    ring.req[blk & 1][lane].a = Quad{n | (mode == 1 ? kMice : 0u), short_by, (uint32_t)len, (uint32_t)(len >> 32)};
+    ring.req[blk & 1][lane].b = Quad{admitted, mode == 1 ? (uint32_t)turn : __float_as_uint(want), 0u, 0u};
+    const uint64_t all = wave_reduce64(pending, 64, OpAdd{}), bound = wave_reduce64(n, 64, OpAdd{});
+    const uint64_t elephant = __popcll(__ballot(mode == 2)), deferred = __popcll(__ballot(mode == 3));
+    if (lane != 0) return;
+    ring.n_pending += all;
+    ring.n_bound += bound;
+    ring.n_mice += __popcll(mice_mask);
+    ring.n_elephant += elephant;
+    ring.n_deferred += deferred;
+}
+
+__device__ __forceinline__ double row_max_f64(double x)
+{
+    auto step = [](double v, uint64_t other) {
+        double r;
+        asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(v), "v"(__longlong_as_double((long long)other)));
+        return r;
+    };
+    x = step(x, dpp64<0xB1>((uint64_t)__double_as_longlong(x)));
+    x = step(x, dpp64<0x4E>((uint64_t)__double_as_longlong(x)));
+    x = step(x, dpp64<0x141>((uint64_t)__double_as_longlong(x)));
+    return step(x, dpp64<0x140>((uint64_t)__double_as_longlong(x)));
+}
+__device__ __forceinline__ float row_sum_f32(float x)
+{
+    x += __uint_as_float(dpp32<0xB1>(__float_as_uint(x)));
+    x += __uint_as_float(dpp32<0x4E>(__float_as_uint(x)));
+    x += __uint_as_float(dpp32<0x141>(__float_as_uint(x)));
+    return x + __uint_as_float(dpp32<0x140>(__float_as_uint(x)));
+}
+// a whole number below 2^52 as a double, and back
+__device__ __forceinline__ double whole_f64(uint64_t v)
+{
+    return __longlong_as_double((long long)(v | 0x4330000000000000ull)) - 4503599627370496.0;
+}
+__device__ __forceinline__ uint64_t f64_whole(double x)
+{
+    return (uint64_t)__double_as_longlong(x + 4503599627370496.0) & 0xFFFFFFFFFFFFFull;
+}
+
+// One request's slots by adding and dropping one at a time, from a guess.  Out of the loop's way: one request in four.
+struct Slots {
+    uint32_t K;
+    bool last;
+};
+__device__ __attribute__((noinline)) Slots settle_slots(uint32_t K, uint32_t n, double cost, double level, double rail)
+{
+    K += (double)(K + 1) * cost <= level ? 1u : 0u;              // (off by one at most, see walk_requests)
+    K -= (double)K * cost > level ? 1u : 0u;
+    int miss = __builtin_amdgcn_readfirstlane((int)(n - wave_reduce32(K, 16, Add32{})));
+    if (miss > 0) {
+        double key = fma((double)(K + 1) * cost, -16.0, -rail);
+        bool won;
+        do {                                                     // the cheapest free slot
+            won = key == row_max_f64(key);
+            K += won ? 1u : 0u;
+            key -= won ? cost * 16.0 : 0.0;
+        } while (--miss > 0);
+        return Slots{K, won};
+    }
+    double key = fma((double)K * cost, 16.0, rail);              // (a rail without slots: its number)
+    for (;; ++miss) {                                            // the dearest slot taken: the request's last one, or one too many
+        const bool won = key == row_max_f64(key);
+        if (miss == 0) return Slots{K, won};
+        K -= won ? 1u : 0u;
+        key -= won ? cost * 16.0 : 0.0;
+    }
+}
+
+// The block's requests; Q: cost of the rail's next byte in units of 2^-16 ps, (c0 << 16) + A c1, below 2^63.
+__device__ __forceinline__ void walk_requests(const BatchDev& b, const DispatchParams& dp, uint32_t c1, RequestRing& ring, uint32_t blk,
+                                              uint64_t& Q)
+{
+    const uint32_t who = threadIdx.x & 15u;
+    const uint64_t Sc1 = b.slice_bytes * c1;
+    const double rail = (double)who;
+    const Request* req = ring.req[blk & 1];
+    uint32_t* found = &ring.found[blk & 1][0][who];
+    const uint32_t m = b.n_desc - blk * kRequests < kRequests ? b.n_desc - blk * kRequests : kRequests;
+    Quad ra = req[0].a, rb = req[0].b;
+    for (uint32_t t = 0; t < m; ++t, found += 16) {
+        const Quad a = ra, w = rb;
+        const uint32_t head = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.x);
+        const uint32_t next_at = t + 1 < m ? t + 1 : t;
+        ra = req[next_at].a;
+        rb = req[next_at].b;
+        if (head == 0) continue;
+        const bool live = (w.x >> who) & 1;
+        const uint64_t len = ((uint64_t)a.w << 32) | a.z;
+        const uint64_t s = (Q + len * c1) >> 16;                             // Stage 2
+        const uint64_t short_c1 = (uint64_t)a.y * c1;
+        uint32_t K;
+        bool last;
+        double cost = whole_f64(s & 0xFFFFFFFFFFFFFull);                     // (rails that take nothing may cost anything)
+        if (head & kMice) {
+            const uint32_t n = head & ~kMice;
+            const uint64_t least = uniform64(f64_whole(-row_max_f64(live ? -cost : -kNoRail)));
+            const uint32_t cand = (uint32_t)__ballot(live && s <= least + ((least * dp.gamma_q8) >> 8)) & 0xFFFFu;
+            const uint32_t n_cand = (uint32_t)__popc(cand);
+            // turn % n_cand, whole numbers below 2^24 in floats
+            uint32_t idx = w.y - (uint32_t)((float)w.y * __builtin_amdgcn_rcpf((float)n_cand)) * n_cand;
+            idx += (int)idx < 0 ? n_cand : 0u;
+            idx -= idx >= n_cand ? n_cand : 0u;
+            last = ((cand >> who) & 1) && (uint32_t)__popc(cand & ((1u << who) - 1)) == idx;
+            K = last ? n : 0;
+        } else {
+            asm("v_max_f64 %0, %0, 1.0" : "+v"(cost));
+            cost = live ? cost : kNoRail;
+            const float inv = __builtin_amdgcn_rcpf((float)cost);
+            const float level_f = __uint_as_float(w.y) * __builtin_amdgcn_rcpf(row_sum_f32(inv));
+            const double level = (double)level_f;
+            K = (uint32_t)(level_f * inv);                                   // off by one at most below 2^20 slots
+            const double held = (double)K * cost, next = held + cost;
+            const uint32_t miss = head - wave_reduce32(K, 16, Add32{});
+            // the cheapest free slot, the dearest taken one otherwise
+            const bool add = miss == 1;
+            const double held_key = fma(held, 16.0, rail), next_key = fma(next, -16.0, -rail);
+            const double key = add ? next_key : held_key;
+            const bool guess_off = next <= level || held > level || miss > 1;
+            last = key == row_max_f64(key);
+            const uint32_t K_guess = K;
+            K += add && last ? 1u : 0u;
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(guess_off) != 0, 0)) {
+                const Slots r = settle_slots(K_guess, head, cost, level, rail);
+                K = r.K;
+                last = r.last;
+            }
+        }
+        // the request's last pending slice is the last element of the merge
+        Q += (uint64_t)K * Sc1 - (last ? short_c1 : 0);
+        *found = K | (last ? kLast : 0u);
+    }
+}
+
+// T, whole and below 2^53, is exact as a double.
+struct RailTotals {
+    double T;
+    uint64_t cnt;
+};
+__device__ __forceinline__ void drain_requests(const BatchDev& b, const RequestRing& ring, uint32_t blk, RailTotals& sum, uint32_t lane)
+{
+    const uint32_t who = lane & 15u;
+    const double S = (double)b.slice_bytes;
+    const uint32_t m = b.n_desc - blk * kRequests < kRequests ? b.n_desc - blk * kRequests : kRequests;
+    RunCell* cell = b.run_cell + (uint64_t)blk * kRequests * b.run_stride + who;
+#pragma unroll 4
+    for (uint32_t t = 0; t < m; ++t, cell += b.run_stride) {
+        const Quad r = ring.req[blk & 1][t].a;
+        const uint32_t word = ring.found[blk & 1][t][who];
+        if (r.x == 0) continue;
+        const uint32_t K = word & (kLast - 1);
+        if (lane < 16) *cell = RunCell{sum.T, K, 0u};
+        sum.T = fma((double)K, S, sum.T) - (double)(word & kLast ? r.y : 0u);
+        sum.cnt += K;
+    }
+}
+
+// By a whole workgroup of at least 192 threads, with barriers.
+__device__ __forceinline__ void dispatch_chain16(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, RequestRing& ring)
+{
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, who = lane & 15u;
+    const uint32_t blocks = (b.n_desc + kRequests - 1) / kRequests;
+    if (threadIdx.x == 0) ring.n_pending = ring.n_deferred = ring.n_mice = ring.n_elephant = ring.n_bound = 0;
+    __syncthreads();
+    const uint32_t c1 = (uint32_t)rp.c1[who];
+    uint64_t Q = (rp.c0[who] << 16) + rp.A[who] * c1;
+    RailTotals sum{0.0, 0};
+    if (wave == 0) __builtin_amdgcn_s_setprio(3);
+    if (wave == 1) feed_requests(b, dp, ring, 0, lane);
+    for (uint32_t k = 0; k < blocks; ++k) {                                  // block k walked, k + 1 fed, k - 1 drained
+        __syncthreads();
+        if (wave == 0) walk_requests(b, dp, c1, ring, k, Q);
+        // (block k - 1 is drained first: its records' place is the next block's)
+        if (wave == 1 && k > 0) drain_requests(b, ring, k - 1, sum, lane);
+        if (wave == 1 && k + 1 < blocks) feed_requests(b, dp, ring, k + 1, lane);
+    }
+    __syncthreads();
+    if (wave != 1) return;
+    drain_requests(b, ring, blocks - 1, sum, lane);
+    const uint64_t T = (uint64_t)sum.T, rounded = (T + 255) & ~255ull;
+    uint64_t inc = rounded;
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+        const uint64_t up = (uint64_t)__shfl_up((unsigned long long)inc, d, 16);
+        if ((int)who >= d) inc += up;
+    }
+    PlanState* ps = b.plan;
+    // (rails from 16 on: none, and behind all others)
+    const uint64_t all = (uint64_t)__shfl((unsigned long long)inc, 15, 64);
+    ps->T[lane] = lane < 16 ? T : 0;
+    ps->cnt[lane] = lane < 16 ? sum.cnt : 0;
+    ps->A_after[lane] = rp.A[lane] + (lane < 16 ? T : 0);
+    ps->base[lane] = lane < 16 ? inc - rounded : all;
+    if (lane != 0) return;
+    ps->n_bound = ring.n_bound;
+    ps->n_pending = ring.n_pending;
+    ps->n_mice = ring.n_mice;
+    ps->n_elephant = ring.n_elephant;
+    ps->n_deferred = ring.n_deferred;
+    ps->rr_next = dp.rr_start + ring.n_mice;
+}
+
+// kWide = 0: dispatch_chain16
+template <int kWide>
+__device__ __forceinline__ void dispatch_workgroup(const BatchDev& b, const RailParams& rp, const DispatchParams& dp)
+{
+    if constexpr (kWide == 0) {
+        __shared__ RequestRing ring;
+        dispatch_chain16(b, rp, dp, ring);
+    } else {
+        if (threadIdx.x < 64) dispatch_chain<kWide>(b, rp, dp);
+    }
+}
+
+template <int kWide>
+__global__ void __launch_bounds__(256) dispatch_chain_kernel(BatchDev b, RailParams rp, DispatchParams dp)
+{
+    dispatch_workgroup<kWide>(b, rp, dp);
 }
 
 // First plan of a batch: the tile tables of the copy kernels are built by the other workgroups of the
@@ -174,7 +449,7 @@ template <int kWide>
 __global__ void __launch_bounds__(256) dispatch_chain_tables_kernel(BatchDev b, RailParams rp, DispatchParams dp)
 {
     if (blockIdx.x == 0) {
-        if (threadIdx.x < 64) dispatch_chain<kWide>(b, rp, dp);
+        dispatch_workgroup<kWide>(b, rp, dp);
         return;
     }
     build_tile_tables_in(b, blockIdx.x - 1, gridDim.x - 1);
@@ -275,16 +550,17 @@ hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const Dispat
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(pending_list_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);
     }
-    if (first_plan) {
-        const dim3 grid(1 + tile_table_blocks(b)), block(256);
-        if (rp.n_rails <= 16)      hipLaunchKernelGGL(dispatch_chain_tables_kernel<16>, grid, block, 0, s, b, rp, dp);
-        else if (rp.n_rails <= 32) hipLaunchKernelGGL(dispatch_chain_tables_kernel<32>, grid, block, 0, s, b, rp, dp);
-        else                       hipLaunchKernelGGL(dispatch_chain_tables_kernel<64>, grid, block, 0, s, b, rp, dp);
-    } else {
-        if (rp.n_rails <= 16)      hipLaunchKernelGGL(dispatch_chain_kernel<16>, dim3(1), dim3(64), 0, s, b, rp, dp);
-        else if (rp.n_rails <= 32) hipLaunchKernelGGL(dispatch_chain_kernel<32>, dim3(1), dim3(64), 0, s, b, rp, dp);
-        else                       hipLaunchKernelGGL(dispatch_chain_kernel<64>, dim3(1), dim3(64), 0, s, b, rp, dp);
-    }
+    auto launch_chain = [&](auto wide) {
+        constexpr int kW = decltype(wide)::value;
+        if (first_plan)
+            hipLaunchKernelGGL(dispatch_chain_tables_kernel<kW>, dim3(1 + tile_table_blocks(b)), dim3(256), 0, s, b, rp, dp);
+        else
+            hipLaunchKernelGGL(dispatch_chain_kernel<kW>, dim3(1), dim3(kW == 0 ? 128 : 64), 0, s, b, rp, dp);
+    };
+    if (dp.near)               launch_chain(std::integral_constant<int, 0>{});
+    else if (rp.n_rails <= 16) launch_chain(std::integral_constant<int, 16>{});
+    else if (rp.n_rails <= 32) launch_chain(std::integral_constant<int, 32>{});
+    else                       launch_chain(std::integral_constant<int, 64>{});
     hipLaunchKernelGGL(dispatch_emit_kernel, dim3((uint32_t)blocks + (told.to ? 1u : 0u)), dim3(256), 0, s, b, rp, dp, told);
     return hipGetLastError();
 }

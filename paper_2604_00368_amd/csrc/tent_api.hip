@@ -1268,6 +1268,8 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
             if (priority[j] > 2) return TENT_ERR_INVALID;
     // The slot keys (m + 1) * s_d are packed with a 6-bit rail index and the tolerance multiplies a
     // cost by gamma: bound the largest cost any rail can show during this plan.
+    DispatchParams dp;
+    std::memset(&dp, 0, sizeof(dp));
     {
         unsigned __int128 worst = 0;
         for (uint32_t d = 0; d < n_rails; ++d) {
@@ -1278,9 +1280,8 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
         }
         if (worst * (b->max_req_slices + 1) >= ((unsigned __int128)1 << 57)) return TENT_ERR_RANGE;
         if (worst * (params->gamma_q8 + 1u) >= ((unsigned __int128)1 << 63)) return TENT_ERR_RANGE;
+        dp.near = n_rails <= 16 && dispatch_is_near(worst, b->max_req_slices) ? 1u : 0u;
     }
-    DispatchParams dp;
-    std::memset(&dp, 0, sizeof(dp));
     dp.theta = params->theta_bytes;
     dp.rr_start = params->rr_start;
     dp.gamma_q8 = params->gamma_q8;

@@ -54,6 +54,7 @@ struct DispatchParams {
     uint64_t adm[3];             // admitted-rail masks for priorities LOW, MID, HIGH
     uint32_t gamma_q8;           // cost tolerance of the mice candidate set, Q8.8
     uint32_t all_high;           // 1: no priority array was given, every request counts as HIGH
+    uint32_t near;               // 1: costs, slots and rails are few enough for the chain of up to 16 rails (dispatch.hip)
 };
 
 // Rails that report a hard error to the rail simulator.
@@ -239,6 +240,13 @@ hipError_t launch_bounded_prepare(const BatchDev& b, uint64_t payload, uint64_t 
 hipError_t launch_bounded_copy(const BatchDev& b, bool gather, uint32_t chunk, uint64_t payload, uint64_t chunk_bytes,
                                uint64_t slot_bytes, uint32_t slots, uint8_t* arena, hipStream_t s);
 hipError_t launch_mark_done_bounded(const BatchDev& b, hipStream_t s);
+// Whether the chain of up to 16 rails can compute a dispatch whose costs are below `worst` ps and whose transfers have at most
+// `most` slices: a slot's key (slots x cost x 16 + rail) is a whole number below 2^53, a cost in units of 2^-16 ps stays below
+// 2^63, and 32-bit reciprocals give a rail's slots to within one.
+inline bool dispatch_is_near(unsigned __int128 worst, uint64_t most)
+{
+    return most < (1ull << 20) && worst < (1ull << 46) && worst * (most + 64) < (1ull << 49);
+}
 hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, bool first_plan,
                            Report told, hipStream_t s);
 hipError_t launch_tile_tables(const BatchDev& b, hipStream_t s);

@@ -126,6 +126,27 @@ def test_small_configs_dispatch_bit_exact(H, oracle, name):
     assert done.all()
 
 
+@pytest.mark.parametrize("D", [1, 63, 64, 65, 129])
+@pytest.mark.parametrize("kind", ["mixed", "alike", "one fast", "far"])
+def test_request_chain_at_its_block_edges(H, oracle, D, kind):
+    # blocks of 64 requests; rails that move in step (exact ties), one that takes several slots while the others take one, and costs
+    # of 2^46 ps and more, which go through the chain of any width
+    rng = np.random.Generator(np.random.PCG64(D))
+    S = 64 * KiB
+    if kind == "mixed":
+        rails = W.make_rails(rng.integers(10000, 400000, 5), queued=rng.integers(0, 1 << 22, 5))
+    elif kind == "alike":
+        rails = W.make_rails([50000] * 16)
+    elif kind == "one fast":
+        rails = W.make_rails([50000] * 8 + [400000], queued=rng.integers(0, 1 << 18, 9))
+    else:
+        rails = W.make_rails(rng.integers(10000, 400000, 5), lat_ns=[1 << 31, 5000, 1 << 30, 1 << 31, 0], penalty_q8=[65535, 256, 65535, 65535, 256])
+    lens = np.where(rng.random(D) < 0.3, rng.integers(1, 4 * S, D), rng.integers(1, 80 * S, D))
+    w = contiguous_requests(lens, S, rails, D)
+    dispatch_windows_and_compare(H, oracle, w, theta=4 * S, gamma_q8=64, prio=W.make_priorities(D, D), windows=[0, 1, 2],
+                                 bytes_too=False, rr_start=(1 << 40) + 5)
+
+
 def test_dispatch_then_cost_model_replan(H, oracle):
     # a window of request-level dispatch, then the per-slice planner finishes what was deferred
     from paper_2604_00368_amd import binding as T
