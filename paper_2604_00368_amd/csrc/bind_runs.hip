@@ -244,6 +244,8 @@ constexpr uint32_t kBitsOfSlots = 28;      // of a word in found
 // 400), 512 of which 6 % miss 133 and 139 (147, 143).
 constexpr uint32_t kMissFew = 4, kMissWorth = 8;
 
+constexpr uint32_t kLeastStretch = 6;       // records of equal slice lengths that go by ranks
+
 struct RecordRing {                        // more than 16 rails
     // {m, flags, shift} {length of the single slice as a double, run} {level, l, that length} {1 / l}
     Quad rec[kRingRecords][4];
@@ -261,7 +263,7 @@ struct StepRing {
         uint32_t single;                   // key of the single slice (low four bits: its rail); kStepped: stands in found
         uint32_t pad[2];
     };
-    Record rec[kRingBlocks * kFeedBlock + 1];          // (the chain reads one record ahead)
+    Record rec[kRingBlocks * kFeedBlock + 8];          // (the chain reads up to eight records ahead)
     // per rail the slots of the run; a record that steps has fewer than 2^28, and the single slice's rail in the bits above
     uint32_t found[kRingBlocks * kFeedBlock][16];
     uint32_t count[kRingBlocks];           // records in the block; kLastBlock marks the last one
@@ -288,6 +290,15 @@ __device__ __forceinline__ uint32_t tagged_key(double x, uint32_t who)
     uint32_t r;
     asm("v_cvt_u32_f64_e32 %0, %1\n\tv_and_or_b32 %0, %0, -16, %2" : "=&v"(r) : "v"(x), "v"(who));
     return r;
+}
+
+// The records of `written` around the lane's own that are `alike`, up to the next ones that are not.
+__device__ __forceinline__ uint64_t stretch_of(uint64_t written, bool alike, uint32_t lane)
+{
+    const uint64_t others = written & ~__ballot(alike), below = (1ull << lane) - 1;
+    const uint64_t before = others & below, behind = others & ~below;
+    return written & (before ? ~((2ull << (63 - __clzll((long long)before))) - 1) : ~0ull) &
+           (behind ? (1ull << (__ffsll((long long)behind) - 1)) - 1 : ~0ull);
 }
 
 // Run records reach the chain through a ring in LDS.  A load that the chain issued itself would have to be
@@ -368,9 +379,10 @@ __device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const 
         const uint32_t prev_len = prev_run < 0 ? last_len : len_there;
         // Up to 16 rails a single slice can go as a run of no slices behind the last run: at that run's level, below which no slot
         // is free any more, as long as the slice's cost is not too far above it.  That costs twice what walk_singles takes for a
-        // slice, but saves a change from runs to single slices and back, so it is for up to three in a row.  MI355X, plans of about
-        // 4,000 transfers with as many short ones behind every few long ones: one 1156 -> 636 us, two 1038 -> 633, three 1003 ->
-        // 640; rows of four and six take 909 and 847 the other way, and would take 629 and 624 as runs of none.
+        // slice, but saves a change from runs to single slices and back, so it is for up to six in a row, in a stretch that goes by
+        // ranks.  MI355X, plans of about 4,000 transfers with as many short ones behind every few long ones: one 1109 -> 624 us,
+        // two 982 -> 623, four 834 -> 619, six 743 -> 610; rows of eight and ten take 704 and 646 the other way and would take
+        // 611 and 608 as runs of none, but 4,096 transfers of which most are single slices 502 -> 518 and 534.
         bool no_run = false;
         if constexpr (kWide == 16) {
             const uint64_t runs_behind = run_mask & ~below;
@@ -378,10 +390,13 @@ __device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const 
                                      (runs_behind ? (1ull << (__ffsll((long long)runs_behind) - 1)) - 1 : ~0ull);
             const double level_run = from_lane(level, prev_run < 0 ? 0 : prev_run);
             const double at_run = prev_run < 0 ? last_run_level : level_run;
-            no_run = single && __popcll(between) <= 3 && serves && prev_served && prev_len != 0 && (v - at_run) * (kUnit / kFineUnit) <= 0.5 * kMaxStep &&
+            no_run = single && __popcll(between) <= 6 && serves && prev_served && prev_len != 0 && (v - at_run) * (kUnit / kFineUnit) <= 0.5 * kMaxStep &&
                      (double)tail * lm.max_c1 <= 0.25 * kMaxStep * kFineUnit &&
                      (double)prev_len * (lm.max_c1 + lm.min_c1) <= kMaxStep * kFineUnit;
             if (run_mask) last_run_level = from_lane(level, 63 - __clzll((long long)run_mask));
+            // (only in a stretch that is likely to be long enough to go by ranks, see below)
+            const uint64_t likely = stretch_of(written_mask, no_run || (has_tail && serves && prev_len == run.len), lane);
+            no_run = no_run && __popcll(likely) >= (int)kLeastStretch;
             level = no_run ? at_run : level;
         }
         const double level_there = from_lane(level, prev < 0 ? 0 : prev);
@@ -418,13 +433,10 @@ __device__ __forceinline__ void feed_records(const BatchDev& b, int mode, const 
             uint32_t take = !follows ? kTakeOdd : no_run ? kTakeSame : single ? kTakeSingle : !run_fits ? kTakeOdd
                                 : flags == kRecShort && same_fits ? kTakeSame : kTakeRun;
             // a stretch of few records goes with the runs around it: a change of the way costs as much as a record.  MI355X, plans of
-            // 4,096 transfers in stretches of two equal slice lengths 1262 us by walk_same, 1015 by walk_runs; of three 1162 and
-            // 1080, of four 1142 either way, of five 1037 and 1174
-            const uint64_t others = written_mask & ~__ballot(take == kTakeSame);
-            const uint64_t other_before = others & below, other_behind = others & ~below;
-            const uint64_t stretch = written_mask & (other_before ? ~((2ull << (63 - __clzll((long long)other_before))) - 1) : ~0ull) &
-                                     (other_behind ? (1ull << (__ffsll((long long)other_behind) - 1)) - 1 : ~0ull);
-            if (take == kTakeSame && __popcll(stretch) < 4) take = kTakeRun;
+            // 4,096 transfers in stretches of four equal slice lengths 1128 us by walk_same, 952 by walk_runs; of five 1025 and 970, of
+            // six 947 and 942, of eight 942 and 964
+            const uint64_t stretch = stretch_of(written_mask, take == kTakeSame, lane);
+            if (take == kTakeSame && __popcll(stretch) < (int)kLeastStretch) take = kTakeRun;
             // how many records from here on may be taken the same way
             const uint64_t same = __ballot(take == kTakeSame), runs = __ballot(take == kTakeRun), singles = __ballot(take == kTakeSingle);
             const uint64_t alike = take == kTakeSame ? same : take == kTakeRun ? runs : take == kTakeSingle ? singles : 0;
@@ -900,9 +912,11 @@ __device__ __forceinline__ Int4 rank_next_slots(double u, double lc1, double Y0,
 // MI355X: about 65 instructions and 310 clocks (125 ns) per transfer of a run and a tail, from 110 and 640 with one-by-one
 // repairs and the bytes bound kept here: reset, plan and execute of 24,576 transfers on 16 rails 15.5 -> 11.6 ms, of 4,096 2.68
 // -> 2.04 ms, of 2,048 shorter by partial pages 1.44 -> 1.06 ms.  What is not a stretch of equal slice lengths goes through
-// walk_runs (about 600 clocks a record) and walk_singles (290), and only the first record, one behind a rebase, and a guess
-// off by more than a few slots through odd_record (1,100); a change of the way costs about 250, a plan of 50 runs takes what
-// it took.
+// walk_runs (about 600 clocks a record, 700 with what is added and dropped slot by slot) and walk_singles (180), and only the first
+// record, one behind a rebase, and a guess off by more than a few slots through odd_record (1,100); a change of the way costs about
+// 250, a plan of 50 runs takes what it took.  With a check and a branch for everything that may not hold, and the records read when
+// they were due, walk_runs took 850 and walk_singles 290: plans of 4,096 transfers of a slice 635 -> 502 us, of 4,054 pairs of one
+// or two slices of 1 MiB 1065 -> 819.
 struct ChainState {
     double X, lc1, inv, kf0;
     uint32_t near_key;
@@ -1113,31 +1127,44 @@ __device__ __forceinline__ void bind_chain16(const BatchDev& b, const RailParams
         return n - left;
     };
 
-    // Records of runs of any slice length, with a single slice behind them or not, one by one.  Where some rail lacks two slots
-    // they are added one by one, to the cheapest free one each time; where the guess took too many (rails that the last run left
-    // far above the level, in terms of this run's shorter slices, make the level too high) the dearest are dropped one by one.
+    // Records of runs of any slice length, with a single slice behind them or not, one by one: by ranks, with one check for all that may
+    // not hold, and otherwise slot by slot.  (Without a single slice one of no bytes is bound, which changes nothing; the drainer and the
+    // emit step do not look at its rail.)
     auto walk_runs = [&](uint32_t at, uint32_t n) -> uint32_t {
         const StepRing::Record* rec = &ring.rec[at];
         uint32_t* found = &ring.found[at][who];
+        const double inv_c1 = rail.inv_c1 * kFineUnit;
         uint32_t left = n;
-        for (; left != 0; --left, ++rec, found += 16) {
-            const Quad s = rec->step, r = rec->run;
-            const uint32_t near_key = r.w;
-            const double X0 = st.X + join_f64(s.x, s.y), len = (double)r.z;
-            const double lc1 = len * c1, inv = join_f64(r.x, r.y) * rail.inv_c1 * kFineUnit;
-            const double Y0 = X0 + lc1, kf0 = kGuessAt * inv;
+        Quad s = rec->step, r = rec->run;
+        for (; left != 0; --left, found += 16) {
+            const uint32_t near_key = r.w, m = s.w;
+            const double X0 = st.X + join_f64(s.x, s.y), lc1 = (double)r.z * c1, inv = join_f64(r.x, r.y) * inv_c1, len = (double)r.z;
+            const double Y0 = X0 + lc1, kf0 = kGuessAt * inv, tail = (double)(s.z + r.z);
             uint32_t kk, key, sum;
             double pn;
             const Int4 rank = rank_next_slots(fma(-X0, inv, kf0), lc1, Y0, who, kk, key, pn, sum);
-            const uint32_t lacking = s.w - sum;
-            // (a rail that does not take slices or lies far above the level has an infinite head)
-            const bool odd = (lacking + (uint32_t)kRepairMax > 15u + (uint32_t)kRepairMax) | !(kBias - X0 < kMaxShift) | (kk >= (uint32_t)kMaxSlots);
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) break;
+            const double held = pn - lc1, y_less = fma(tail, c1, held), y_more = fma(tail, c1, pn);
+            const uint32_t mine_less = tagged_key(y_less, who), mine_more = tagged_key(y_more, who);
+            ++rec;
+            s = rec->step;
+            r = rec->run;
+            const uint32_t lacking = m - sum;
             const bool takes = rank[0] < (int)lacking;
-            double X1 = takes ? pn : pn - lc1;
-            if (__builtin_amdgcn_ballot_w64((takes & (key >= near_key)) | ((int)lacking < 0)) == 0) {
+            asm volatile("" : : "v"(rank));                                // (its registers are not reused before: that would wait)
+            uint32_t mine = takes ? mine_more : mine_less;
+            double X1 = takes ? pn : held, y = takes ? y_more : y_less;
+            uint32_t best = row_reduce32(mine, Min32{});
+            // (a rail that does not take slices or lies far above the level has an infinite head)
+            const bool odd = (lacking > 15u) | !(kBias - X0 < kMaxShift) | (kk >= (uint32_t)kMaxSlots) | (takes & (key >= near_key)) |
+                             (best - 16u >= kFarKey16 - 16u);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) == 0, 1)) {
                 kk += takes ? 1u : 0u;
             } else {
+                // where some rail lacks two slots they are added one by one, to the cheapest free one each time; where the guess took too
+                // many (rails that the last run left far above the level, in terms of this run's shorter slices, make the level too high)
+                // the dearest are dropped one by one
+                const bool far = (lacking + (uint32_t)kRepairMax > 15u + (uint32_t)kRepairMax) | !(kBias - X0 < kMaxShift) | (kk >= (uint32_t)kMaxSlots);
+                if (__builtin_amdgcn_ballot_w64(far) != 0) break;
                 uint32_t farthest = 0;                                     // of all keys used
                 int more = __builtin_amdgcn_readfirstlane((int)lacking);
                 for (; more > 0; --more) {
@@ -1158,41 +1185,67 @@ __device__ __forceinline__ void bind_chain16(const BatchDev& b, const RailParams
                     kk -= down == least ? 1u : 0u;
                     pn = down == least ? before : pn;
                 }
-                if (__builtin_amdgcn_ballot_w64(farthest >= kFarKey16) != 0) break;
                 X1 = pn - lc1;
+                y = fma(tail, c1, X1);
+                mine = tagged_key(y, who);
+                best = row_reduce32(mine, Min32{});
+                // (without a single slice a least key outside the window means nothing)
+                if (__builtin_amdgcn_ballot_w64((farthest >= kFarKey16) | ((tail != 0.0) & (best - 16u >= kFarKey16 - 16u))) != 0) break;
             }
-            uint32_t word = kk;
-            if (__builtin_amdgcn_readfirstlane((int)(s.z + r.z)) != 0) {   // a single slice stands behind it
-                const double y = fma((double)(s.z + r.z), c1, X1);
-                const uint32_t mine = tagged_key(y, who), best = row_reduce32(mine, Min32{});
-                if (__builtin_amdgcn_ballot_w64(best - 16u >= kFarKey16 - 16u) != 0) break;
-                X1 = mine == best ? y : X1;
-                word |= best << kBitsOfSlots;
-            }
-            *found = word;
-            st = ChainState{X1, lc1, inv, kf0, near_key};
+            *found = kk | (best << kBitsOfSlots);
+            st = ChainState{mine == best ? y : X1, lc1, inv, kf0, near_key};
             l_f = len;
         }
         return n - left;
     };
 
-    // Single slices, one by one: a plain argmin by keys, unless they lie outside the window.
+    // Single slices, one by one: a plain argmin by keys, unless they lie outside the window.  Four records share a check, and each
+    // keeps the state it leaves, for the case that a later one does not pass; the next four are read meanwhile.
     auto walk_singles = [&](uint32_t at, uint32_t n) -> uint32_t {
         const StepRing::Record* rec = &ring.rec[at];
         uint32_t* found = &ring.found[at][who];
+        // One record: the state behind it and its key, less the least one inside the window (from kFarKey16 - 16 on: outside).
+        auto one = [&](const Quad& s, double X_in, double& X_out, uint32_t* out) -> uint32_t {
+            const double X0 = X_in + join_f64(s.x, s.y), y = fma((double)s.z, c1, X0);
+            const uint32_t mine = tagged_key(y, who), best = row_reduce32(mine, Min32{});
+            X_out = mine == best ? y : X0;
+            *out = best << kBitsOfSlots;
+            return best - 16u;
+        };
+        auto outside = [&](uint32_t key) { return __builtin_amdgcn_ballot_w64(key >= kFarKey16 - 16u) != 0; };
+        Quad s1 = rec[0].step, s2 = rec[1].step, s3 = rec[2].step, s4 = rec[3].step;
         uint32_t left = n;
-        Quad s = rec->step;
+        for (; left >= 4; left -= 4) {
+            const Quad n1 = rec[4].step, n2 = rec[5].step, n3 = rec[6].step, n4 = rec[7].step;
+            double X1, X2, X3, X4;
+            const uint32_t b1 = one(s1, st.X, X1, found), b2 = one(s2, X1, X2, found + 16);
+            const uint32_t b3 = one(s3, X2, X3, found + 32), b4 = one(s4, X3, X4, found + 48);
+            const uint32_t b12 = b1 > b2 ? b1 : b2, b34 = b3 > b4 ? b3 : b4;
+            if (__builtin_expect(outside(b12 > b34 ? b12 : b34), 0)) {
+                if (outside(b1)) return n - left;
+                st.X = X1;
+                if (outside(b2)) return n - left + 1;
+                st.X = X2;
+                if (outside(b3)) return n - left + 2;
+                st.X = X3;
+                return n - left + 3;
+            }
+            st.X = X4;
+            rec += 4;
+            found += 64;
+            s1 = n1;
+            s2 = n2;
+            s3 = n3;
+            s4 = n4;
+        }
         for (; left != 0; --left) {
-            const double X0 = st.X + join_f64(s.x, s.y), y = fma((double)s.z, c1, X0);
-            const uint32_t mine = tagged_key(y, who);
-            ++rec;
-            s = rec->step;
-            const uint32_t best = row_reduce32(mine, Min32{});
-            *found = best << kBitsOfSlots;
-            found += 16;
-            const double X1 = mine == best ? y : X0;
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(best - 16u >= kFarKey16 - 16u) != 0, 0)) break;
+            double X1;
+            const uint32_t b1 = one(s1, st.X, X1, found);
+            if (outside(b1)) break;
             st.X = X1;
+            found += 16;
+            s1 = s2;
+            s2 = s3;
         }
         return n - left;
     };

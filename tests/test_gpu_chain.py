@@ -174,3 +174,14 @@ def test_slices_behind_runs_of_dropped_slots(H, oracle, R, singles, seed):
         lens += [int(g.integers(20, 61) * bw.mean())] * int(g.integers(2, 9))
         lens += g.permutation(np.arange(1, 40))[:singles].tolist()
     check_binding(H, oracle, transfers(lens, S, W.make_rails(bw, queued=g.integers(0, 1 << 20, size=R))))
+
+
+@pytest.mark.parametrize("at", [1, 2, 3, 4, 5, 60, 61, 62, 63, 64])
+@pytest.mark.parametrize("n", [6, 65, 131])
+def test_a_slice_outside_the_window_among_single_slices(H, oracle, at, n):
+    # single slices are bound four to a check: one that costs 160 us and more lies outside the keys' window wherever it stands among them
+    g = np.random.Generator(np.random.PCG64([at, n]))
+    rails = W.make_rails([25000, 12500, 20000], queued=g.integers(0, 1 << 16, size=3))
+    lens = g.integers(1, 200000, size=n)
+    lens[at % n::64] = 4000000 + at
+    check_binding(H, oracle, transfers(lens, 1 << 22, rails))
