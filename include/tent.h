@@ -37,6 +37,12 @@
  *     tent_execute_bounded.  No such wait is recorded into a graph.  The next tent_execute must
  *     still come after that plan (the host-side wait of tent_sim_advance with n_done != NULL, or
  *     an event).
+ *   - On one stream the library does the same by itself: tent_reset, the plans and the rail simulator's calls move no byte, and
+ *     where they report no figures they may run on a stream of the context's own (default priority) while copies that they need
+ *     not wait for -- other batches', or those of the batch's last execute, under the same conditions as above -- still run on
+ *     `stream`.  They come behind the batch's earlier calls, and its next call behind them, whatever stream it is given (on one
+ *     that is being captured the host waits); only other work of the caller's on `stream` is not ordered behind them.  Batches that a
+ *     graph holds a call of, and those of tent_declare_static, stay on the streams they are given.
  *   - HIP graphs: tent_reset, tent_plan with info = NULL and tent_execute allocate nothing, copy
  *     nothing from or to the host and enqueue kernels only (no memset nodes), so a caller may
  *     record them on a capturing stream and replay the graph.  The host-side bookkeeping of a

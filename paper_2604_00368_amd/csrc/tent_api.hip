@@ -1,6 +1,7 @@
 // Host runtime behind the C ABI: argument validation, device tables, rail-state conversion and
 // kernel sequencing.  Every step of the hot path itself runs in the HIP kernels of this library.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cstring>
 #include <mutex>
@@ -12,6 +13,10 @@
 #include "tent_internal.h"
 
 using namespace tent;
+
+// Runtimes that lack them (stand-ins without a device) are taken to be idle.
+extern "C" hipError_t hipEventQuery(hipEvent_t) __attribute__((weak));
+extern "C" hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) __attribute__((weak));
 
 // Static workspace of tent_declare_static: callers that must not allocate get their batch's tables
 // here.  One copy per GPU, held until the process ends.  In host code the array's name is only a
@@ -33,7 +38,7 @@ struct StreamMark {
     hipEvent_t event = nullptr;
     bool used = false;
 };
-constexpr int kMarks = 4;
+constexpr int kMarks = 5;               // four streams of the caller's and the context's own
 
 struct Batch {
     bool alive = false;
@@ -58,6 +63,11 @@ struct Batch {
     // stream (which the caller may have destroyed since: it is only compared with).
     hipEvent_t report_at = nullptr;
     hipStream_t report_stream = nullptr;
+    // What the batch's tables were last worked on by: nothing yet (or only its declaration), a call on a stream of the caller's, an
+    // execute, or a call that ran beside earlier copies (see work_stream).
+    enum class Last { kNothing, kCaller, kExecute, kBeside } last = Last::kNothing;
+    uint64_t execute_no = 0;                 // which of all executes the last one was
+    hipStream_t beside = nullptr;            // the context's stream for such calls
     bool may_replan = false;                 // slices may be left over by the next execute: the simulator or a dispatch ran since the plan
     // The declaration's device work (descriptor upload, address sort, overlap check) runs on the
     // context's own stream and ends at decl_event; `verdict` (pinned host memory) then holds the
@@ -108,6 +118,9 @@ struct tent_ctx {
     hipEvent_t stage_event[2] = {nullptr, nullptr};
     bool stage_busy[2] = {false, false};
     uint32_t stage_turn = 0;
+    hipStream_t beside = nullptr;           // calls that only work on a batch's tables, beside earlier copies (work_stream)
+    hipEvent_t copies_end = nullptr;        // the event that ends the last execute, and its stream
+    hipStream_t copies_stream = nullptr;
     void* order_ws = nullptr;               // workspace of the address sort, grown when a declaration needs more
     uint64_t order_ws_bytes = 0;
     std::vector<Block> spare;               // table allocations of released batches, handed to later declarations
@@ -183,7 +196,16 @@ struct StreamNote {
     hipStream_t s;
     bool noted = false;          // an event recorded by the call itself covers its work
     StreamNote(Batch& batch, hipStream_t stream) : b(batch), s(stream) {}
-    ~StreamNote() { if (b.alive && !noted) (void)note_stream(b, s); }
+    ~StreamNote()
+    {
+        if (!b.alive || noted) return;
+        const StreamMark* mark = note_stream(b, s);
+        if (s != b.beside) return;
+        // who goes on with the batch on the caller's stream waits for it, as for what a report left
+        if (!mark) { (void)hipStreamSynchronize(s); return; }
+        b.report_at = mark->event;
+        b.report_stream = s;
+    }
 };
 
 // Waits until the figures of `told` are there: everything enqueued on `s` before the kernel that tells them has ended then, and
@@ -221,15 +243,28 @@ hipError_t await_report(Batch& b, const Report& told, hipStream_t s, StreamNote&
     return await_figures(told, s);
 }
 
+// Host calls on an event outside a graph that would invalidate a capture in progress, although what is captured does not depend on them.
+struct CaptureAside {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool set = false;
+    CaptureAside() { set = &hipThreadExchangeStreamCaptureMode && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess; }
+    ~CaptureAside() { if (set) (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 // Callers may go on with the batch on another stream without an event of their own behind a call that waits.  What is left of its last
-// kernel is waited for there, on the device.  Not where `s` is being captured, which permits no wait for work outside the
-// graph: when the graph runs is its caller's to order.
+// kernel is waited for there, on the device; so is a call that ran on the context's own stream.  A stream that is being
+// captured permits no wait for work outside the graph: when the graph runs is its caller's to order, but behind the context's own stream
+// the caller cannot order anything, so that is waited for by the host.
 hipError_t order_after_report(Batch& b, hipStream_t s)
 {
-    if (!b.report_at || s == b.report_stream || capturing(s)) return hipSuccess;
+    if (!b.report_at || s == b.report_stream) return hipSuccess;
+    const bool captured = capturing(s);
+    if (captured && b.report_stream != b.beside) return hipSuccess;
     const hipEvent_t end = b.report_at;
     b.report_at = nullptr;
-    return hipStreamWaitEvent(s, end, 0);
+    if (!captured) return hipStreamWaitEvent(s, end, 0);
+    const CaptureAside aside;
+    return hipEventSynchronize(end);
 }
 
 // Host-side wait for everything that was enqueued for the batch.
@@ -678,6 +713,62 @@ hipError_t record_execute_done(Batch& b, hipStream_t s, StreamNote& note)
     return hipSuccess;
 }
 
+// Executes so far, of all contexts: tells a batch whether other copies have been enqueued behind its own.
+std::atomic<uint64_t> g_executes{0};
+
+// An execute that was enqueued: what may run beside its copies.
+void note_execute(tent_ctx* ctx, Batch& b, hipStream_t s)
+{
+    b.last = b.done_recorded ? Batch::Last::kExecute : Batch::Last::kCaller;
+    b.execute_no = ++g_executes;
+    if (!b.done_recorded) return;
+    ctx->copies_end = b.done_at;
+    ctx->copies_stream = s;
+}
+
+// Whether the work behind which `end` was recorded has not ended.
+bool running(hipEvent_t end)
+{
+    if (!end || !&hipEventQuery) return false;
+    const CaptureAside aside;
+    const bool yes = hipEventQuery(end) == hipErrorNotReady;
+    if (yes) (void)hipGetLastError();
+    return yes;
+}
+
+// Where a call that only works on the batch's tables runs: a plan, a reset, the rail simulator and the probe read and write no byte
+// of a segment or the arena, so they need not wait for copies that were enqueued on the caller's stream before -- those of other batches,
+// and of the batch's own last execute as far as its bookkeeping.  Beside such copies they run on the context's own stream,
+// ordered among themselves and behind that bookkeeping (`whole`, a reset or a first plan, which rewrite what the copies read:
+// behind the batch's own copies); the next call of the batch on the caller's stream waits for them there.
+// Only while copies are known to run on `s` that the call does not have to wait for, because the change of streams costs two waits.
+// MI355X, cycles of three batches in turn: 4,096 transfers 2060 -> 1540 us, 24,576 11534 -> 9095, 256 ragged ones 262 -> 198, 74
+// slices (4 MB) 43 -> 37.  Beside the batch's own copies a re-plan has only those to hide behind: sixteen windows of 100 MB each 5808 ->
+// 4807 us, but nine of 2 MB 985 -> 1082, hence kBesideBytes.
+// Not a call that reports figures: everything that was enqueued on `s` before it has ended when it returns.
+// A batch that a graph holds a call of stays on its caller's streams, because replays are not seen here; so do batches in the
+// static workspace, whose next owner's declaration waits for the caller's streams, and contexts that time their stages.
+constexpr uint64_t kBesideBytes = 64ull << 20;
+hipStream_t work_stream(const tent_ctx* ctx, const Batch& b, hipStream_t s, bool whole, bool reports)
+{
+    if (reports || b.marks_lost || b.in_static || (ctx->cfg.flags & TENT_FLAG_PROFILE) || capturing(s)) return s;
+    if (b.last == Batch::Last::kBeside) return b.beside;
+    if (b.last == Batch::Last::kExecute) {
+        if (b.exec_stream != s || !b.replan_at) return s;
+        if (whole || b.replan_at == b.done_at) {
+            // (where nothing has been enqueued behind its copies, what has to wait for them runs beside nothing)
+            if (b.execute_no == g_executes.load()) return s;
+        } else if (b.payload < kBesideBytes) {
+            return s;
+        }
+        return running(b.done_at) ? b.beside : s;
+    }
+    if (ctx->copies_stream != s || !running(ctx->copies_end)) return s;
+    for (const StreamMark& m : b.marks)                  // (calls on the caller's streams that have not ended)
+        if (m.used && running(m.event)) return s;
+    return b.beside;
+}
+
 // The first call that needs the batch's tables waits (on the host) for the declaration's device work
 // and learns the verdict of the overlap check.  A batch that fails it is released.
 int finish_declare(tent_ctx* ctx, Batch& b)
@@ -806,6 +897,7 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     }
     Batch& b = *slot_b;
     renew_slot(b);
+    b.beside = ctx->beside;
     b.payload = payload;
     b.max_req_slices = max_req_slices;
     BatchDev& d = b.dev;
@@ -1044,6 +1136,7 @@ int tent_create(tent_ctx** out, const tent_config* cfg)
     ok = ok && hipMalloc((void**)&ctx->seg_base_dev, sizeof(uint64_t) * ctx->seg_capacity) == hipSuccess &&
          hipHostMalloc((void**)&ctx->host_plan, sizeof(PlanState), hipHostMallocCoherent) == hipSuccess &&
          hipStreamCreateWithFlags(&ctx->decl_stream, hipStreamNonBlocking) == hipSuccess &&
+         hipStreamCreateWithFlags(&ctx->beside, hipStreamNonBlocking) == hipSuccess &&
          init_slot(ctx->static_batch);
     if (ok) ctx->host_plan->call = 0;
     for (int k = 0; k < 2 && ok; ++k) {
@@ -1091,6 +1184,7 @@ int tent_destroy(tent_ctx* ctx)
     }
     if (ctx->order_ws) (void)hipFree(ctx->order_ws);
     if (ctx->decl_stream) (void)hipStreamDestroy(ctx->decl_stream);
+    if (ctx->beside) (void)hipStreamDestroy(ctx->beside);
     if (ctx->aux_stream) (void)hipStreamDestroy(ctx->aux_stream);
     if (ctx->seg_base_dev) (void)hipFree(ctx->seg_base_dev);
     if (ctx->host_plan) (void)hipHostFree(ctx->host_plan);
@@ -1147,10 +1241,12 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
         if (too_small) return TENT_ERR_RANGE;
     }
     const BatchDev& d = b->dev;
+    s = work_stream(ctx, *b, s, !b->has_done && !b->has_retry, info != nullptr);
     HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
     if (b->decl_pending) HIP_TRY(hipStreamWaitEvent(s, b->decl_event, 0));
     HIP_TRY(order_after_execute_bookkeeping(*b, s));
+    b->last = s == b->beside ? Batch::Last::kBeside : Batch::Last::kCaller;
 
     // Retry rotation (Section 4.3, "Link-Level Resilience"): candidates are the HEALTHY rails, else the
     // DEGRADED rails without topology penalty, else every DEGRADED rail, in ascending index.
@@ -1296,14 +1392,15 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
 
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
-    hipStream_t s = static_cast<hipStream_t>(stream);
+    const bool first_plan = !b->planned;
+    const hipStream_t s = work_stream(ctx, *b, static_cast<hipStream_t>(stream), first_plan, info != nullptr);
     const BatchDev& d = b->dev;
     HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
     HIP_TRY(order_after_execute_bookkeeping(*b, s));
+    b->last = s == b->beside ? Batch::Last::kBeside : Batch::Last::kCaller;
     dp.all_high = priority ? 0u : 1u;
     if (priority) HIP_TRY(hipMemcpyAsync(d.priority, priority, d.n_desc, hipMemcpyHostToDevice, s));
-    const bool first_plan = !b->planned;
     const Report told = next_report(ctx, info != nullptr);
     if (first_plan) {
         {
@@ -1373,7 +1470,7 @@ int tent_sim_advance(tent_ctx* ctx, tent_batch_t batch, const uint64_t* budget_b
     if (!b->planned) return TENT_ERR_STATE;
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
-    hipStream_t s = static_cast<hipStream_t>(stream);
+    const hipStream_t s = work_stream(ctx, *b, static_cast<hipStream_t>(stream), false, n_done != nullptr);
     BudgetParams bp;
     std::memset(&bp, 0, sizeof(bp));
     for (uint32_t d = 0; d < b->last_rails.n_rails; ++d) {
@@ -1382,6 +1479,8 @@ int tent_sim_advance(tent_ctx* ctx, tent_batch_t batch, const uint64_t* budget_b
     }
     HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
+    if (s == b->beside) HIP_TRY(order_after_execute_bookkeeping(*b, s));
+    b->last = s == b->beside ? Batch::Last::kBeside : Batch::Last::kCaller;
     b->may_replan = true;
     const Report told = next_report(ctx, n_done != nullptr);
     HIP_TRY(launch_retire(b->dev, bp, told, s));
@@ -1415,11 +1514,13 @@ int tent_sim_fail(tent_ctx* ctx, tent_batch_t batch, const uint8_t* rail_failed,
     }
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
-    hipStream_t s = static_cast<hipStream_t>(stream);
+    const hipStream_t s = work_stream(ctx, *b, static_cast<hipStream_t>(stream), false, any && failed_per_rail);
     HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
     const Report told = next_report(ctx, any && failed_per_rail);
     if (any) {
+        if (s == b->beside) HIP_TRY(order_after_execute_bookkeeping(*b, s));
+        b->last = s == b->beside ? Batch::Last::kBeside : Batch::Last::kCaller;
         b->may_replan = true;
         HIP_TRY(launch_fail(b->dev, fp, told, s));
         b->has_retry = true;
@@ -1467,9 +1568,12 @@ int tent_sim_latency(tent_ctx* ctx, tent_batch_t batch, const uint32_t* true_bw_
     if (max_q >= (1ull << 53) || b->payload >= (1ull << 53) || max_q + b->payload >= (1ull << 53)) return TENT_ERR_RANGE;
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
-    HIP_TRY(order_after_report(*b, static_cast<hipStream_t>(stream)));
-    StreamNote note(*b, static_cast<hipStream_t>(stream));
-    HIP_TRY(launch_sim_latency(b->dev, lp, static_cast<hipStream_t>(stream)));
+    const hipStream_t s = work_stream(ctx, *b, static_cast<hipStream_t>(stream), false, false);
+    HIP_TRY(order_after_report(*b, s));
+    StreamNote note(*b, s);
+    if (s == b->beside) HIP_TRY(order_after_execute_bookkeeping(*b, s));
+    b->last = s == b->beside ? Batch::Last::kBeside : Batch::Last::kCaller;
+    HIP_TRY(launch_sim_latency(b->dev, lp, s));
     return TENT_OK;
 }
 
@@ -1532,6 +1636,7 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
+    b->last = Batch::Last::kCaller;
     // When the host knows that only a small part of the batch is BOUND (after the rail simulator), the
     // copies run over a list of the tiles of the BOUND slices and their launches are sized by that part.
     uint64_t max_tiles = b->bound_hint * b->dev.tiles_per_slice;
@@ -1580,7 +1685,9 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
     };
     b->has_done = true;
     b->bound_hint = 0;
-    if (copies() != hipSuccess) {
+    const bool moved = copies() == hipSuccess;
+    note_execute(ctx, *b, s);
+    if (!moved) {
         (void)hipGetLastError();
         b->broken = true;
         return TENT_ERR_HIP;
@@ -1607,6 +1714,7 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIP_TRY(order_after_report(*b, s));
     StreamNote note(*b, s);
+    b->last = Batch::Last::kCaller;
     uint8_t* arena = static_cast<uint8_t*>(ctx->cfg.staging_arena);
     const uint64_t payload = b->payload;
     HIP_TRY(launch_bounded_prepare(d, payload, chunk_bytes, (uint32_t)n_chunks, slot_bytes, slots, arena, s));
@@ -1676,6 +1784,7 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     HIP_TRY(record_execute_done(*b, s, note));
     // the range copies read what a re-plan rewrites, and the DONE marks come last: a re-plan on another stream waits for it all
     if (b->done_recorded) b->replan_at = b->done_at;
+    note_execute(ctx, *b, s);
     return TENT_OK;
 }
 
@@ -1712,10 +1821,11 @@ int tent_reset(tent_ctx* ctx, tent_batch_t batch, void* stream)
     if (!b) return TENT_ERR_INVALID;
     DeviceGuard g(ctx->device);
     if (!g.ok) return TENT_ERR_HIP;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    HIP_TRY(order_after_report(*b, s));
+    const hipStream_t s = work_stream(ctx, *b, static_cast<hipStream_t>(stream), true, false);
+    if (b->planned || s != b->beside) HIP_TRY(order_after_report(*b, s));
     if (b->planned) {
         StreamNote note(*b, s);
+        b->last = s == b->beside ? Batch::Last::kBeside : Batch::Last::kCaller;
         // the reset must not overtake the copies of an execute that runs on another stream
         if (b->done_recorded && s != b->exec_stream && !capturing(s)) HIP_TRY(hipStreamWaitEvent(s, b->done_at, 0));
         HIP_TRY(launch_reset(b->dev, s));

@@ -12,7 +12,7 @@ static struct { int kind; void *stream, *what; } log_[MOST];
 static int n_log, n_kernels, fail_host_waits;
 static struct { const void *fn; const char *name; } kernel[KERNELS];
 static void *capturing_stream;
-static int answer, n_host;
+static int answer, n_host, busy;
 static struct { char *at; size_t n; } host[64];
 
 static void note(int kind, void *stream, void *what)
@@ -36,6 +36,8 @@ const char *fake_kernel_name(const void *fn)
 }
 void fake_fail_host_waits(int n) { fail_host_waits = n; }
 void fake_capture(void *stream) { capturing_stream = stream; }
+/* whether what has been enqueued has not ended yet */
+void fake_busy(int on) { busy = on; }
 /* a launch that reports answers its report, a block of host memory and a number: the number goes to the block's last word (1), with
  * figures that are not zero in front of it (2) */
 void fake_answer_reports(int on) { answer = on; }
@@ -100,6 +102,8 @@ hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b) { (void)a; (void)b; *ms = 0; return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { note(RECORD, s, e); return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags) { (void)flags; note(WAIT, s, e); return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t e) { (void)e; return busy ? hipErrorNotReady : hipSuccess; }
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *mode) { (void)mode; return hipSuccess; }
 static hipError_t host_wait(void *stream, void *what)
 {
     if (fail_host_waits > 0) { --fail_host_waits; return hipErrorUnknown; }

@@ -386,6 +386,127 @@ def test_complete_means_that_the_copies_have_been_waited_for(fake, bounded):
     run(fake, "complete", bounded)
 
 
+def beside_copies():
+    h = Host(slice_bytes=1 << 20)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    one, two = (T.tent_declare(h.ctx, *h.extents(3000, 65536)) for _ in range(2))
+    launched = lambda log: {x[1] for x in log if x[0] == LAUNCH}
+    index = lambda log, *what: [i for i, x in enumerate(log) if x[:len(what)] == what]
+
+    def cycle(b):
+        T.tent_reset(h.ctx, b, STREAM_A)
+        T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+        tables = h.log()
+        T.tent_execute(h.ctx, b, STREAM_A)
+        return tables, h.log()
+
+    h.log()
+    for b in (one, two, one, two):                       # nothing runs: everything on the caller's stream
+        tables, copies = cycle(b)
+        assert launched(tables) == launched(copies) == {STREAM_A}
+    h.hip.fake_busy(1)
+    end_of_one = [x[2] for x in cycle(one)[1] if x[0] == RECORD][-1]
+    tables, copies = cycle(two)                          # beside the copies of the other batch
+    assert launched(copies) == {STREAM_A} and len(launched(tables)) == 1 and STREAM_A not in launched(tables)
+    own = launched(tables).pop()
+    end = [x[2] for x in tables if x[0] == RECORD and x[1] == own][-1]
+    assert index(copies, WAIT, STREAM_A, end)[0] < index(copies, LAUNCH, STREAM_A)[0]
+    tables, copies = cycle(one)                          # behind its own copies, beside those of the other one
+    assert launched(tables) == {own} and index(tables, WAIT, own, end_of_one)[0] < index(tables, LAUNCH, own)[0]
+    for _ in range(2):                                   # nothing was enqueued behind its own copies: beside nothing
+        tables, copies = cycle(one)
+        assert launched(tables) == {STREAM_A}
+    # on another stream than the copies', and of a batch whose calls on the caller's stream have not ended: there
+    T.tent_reset(h.ctx, two, STREAM_B)
+    T.tent_plan(h.ctx, two, rails, False, STREAM_A)
+    assert launched(h.log()) == {STREAM_A, STREAM_B}
+    assert not [x for x in h.log() if x[0] == HOST_WAIT]
+    T.tent_destroy(h.ctx)
+
+
+def test_tables_are_worked_on_beside_earlier_copies(fake):
+    """A plan and a reset move no byte: while copies that they need not wait for run on the caller's stream they run on the
+    context's own, behind the batch's own copies, and the batch's next call on the caller's stream waits for them."""
+    run(fake, "beside_copies")
+
+
+def windows_beside_copies(payload):
+    h = Host(slice_bytes=1 << 20)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    n = payload // 65536
+    b = T.tent_declare(h.ctx, *h.extents(n, 65536))
+    T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+    T.tent_sim_advance(h.ctx, b, np.array([1 << 21, 1 << 21], dtype=np.uint64), STREAM_A, False)
+    h.log()
+    T.tent_execute(h.ctx, b, STREAM_A)
+    log = h.log()
+    bookkeeping, end = [x[2] for x in log if x[0] == RECORD][:2]
+    h.hip.fake_busy(1)
+    for call in (lambda: T.tent_plan(h.ctx, b, rails, False, STREAM_A), lambda: T.tent_sim_fail(h.ctx, b, np.ones(2, dtype=np.uint8), False, STREAM_A),
+                 lambda: T.tent_sim_latency(h.ctx, b, np.array([5, 5], dtype=np.uint32), STREAM_A)):
+        call()
+        log = h.log()
+        own = [x[1] for x in log if x[0] == LAUNCH][0]
+        assert (own == STREAM_A) == (payload < 64 * MiB)
+        assert not [x for x in log if x[0] == WAIT and x[2] == end]
+        if own != STREAM_A and bookkeeping:
+            first = [i for i, x in enumerate(log) if x[0] == LAUNCH][0]
+            assert (WAIT, own, bookkeeping) in log[:first]
+            bookkeeping = None                           # (what follows is ordered behind the plan)
+    # a call that reports figures has everything behind it that was enqueued on its stream, so that is where it runs
+    h.hip.fake_answer_reports(1)
+    T.tent_sim_advance(h.ctx, b, np.array([1 << 21, 1 << 21], dtype=np.uint64), STREAM_A)
+    h.hip.fake_answer_reports(0)
+    log = h.log()
+    assert {x[1] for x in log if x[0] == LAUNCH} == {STREAM_A}
+    assert bool([x for x in log if x[0] == WAIT and x[1] == STREAM_A]) == (own != STREAM_A)
+    T.tent_execute(h.ctx, b, STREAM_A)
+    log = h.log()
+    assert {x[1] for x in log if x[0] == LAUNCH} == {STREAM_A} and not [x for x in log if x[0] == WAIT]
+    T.tent_plan(h.ctx, b, rails, True, STREAM_A)
+    assert {x[1] for x in h.log() if x[0] == LAUNCH} == {STREAM_A}
+    T.tent_destroy(h.ctx)
+
+
+@pytest.mark.parametrize("payload", [64 * MiB - 65536, 64 * MiB])
+def test_windows_beside_their_own_copies(fake, payload):
+    """A re-plan and the rail simulator behind an execute wait for its bookkeeping only, where its copies are long enough."""
+    run(fake, "windows_beside_copies", payload)
+
+
+def capture_behind_beside():
+    h = Host(slice_bytes=1 << 20)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    one, two = (T.tent_declare(h.ctx, *h.extents(3000, 65536)) for _ in range(2))
+    T.tent_plan(h.ctx, one, rails, False, STREAM_A)
+    T.tent_execute(h.ctx, one, STREAM_A)
+    h.hip.fake_busy(1)
+    h.log()
+    T.tent_plan(h.ctx, two, rails, False, STREAM_A)
+    log = h.log()
+    own = [x[1] for x in log if x[0] == LAUNCH][0]
+    end = [x[2] for x in log if x[0] == RECORD and x[1] == own][-1]
+    assert own != STREAM_A
+    h.hip.fake_capture(STREAM_B)
+    T.tent_execute(h.ctx, two, STREAM_B)
+    h.hip.fake_capture(0)
+    log = h.log()
+    assert [x[0] for x in log if x[0] != LAUNCH] == [HOST_WAIT] and log[0] == (HOST_WAIT, None, end)
+    assert {x[1] for x in log if x[0] == LAUNCH} == {STREAM_B}
+    # a graph holds a call of the batch now: its tables are worked on where the caller can order its replays
+    T.tent_execute(h.ctx, one, STREAM_A)
+    h.log()
+    T.tent_reset(h.ctx, two, STREAM_A)
+    T.tent_plan(h.ctx, two, rails, False, STREAM_A)
+    assert {x[1] for x in h.log() if x[0] == LAUNCH} == {STREAM_A}
+    T.tent_destroy(h.ctx)
+
+
+def test_a_capture_behind_work_beside_copies(fake):
+    """A graph can wait for nothing outside it, and its caller cannot order it behind the context's own stream: the host waits."""
+    run(fake, "capture_behind_beside")
+
+
 # The largest batches tent_declare_static accepts, in units of each kind: flags 0, no overlap check, bounded staging, both;
 # with 16 rails and with 64 each.  Found by bisection over a library whose limit was the space its tables took.
 STATIC_LIMITS = {
