@@ -12,10 +12,9 @@
 // enumeration), so a chunk's launch touches only its own table entries.
 //
 // Geometry whose lengths are no multiple of the tile size has no such enumeration.  There the same
-// steps run over the payload in ranges of 1 KiB, one wavefront per range: the wavefront finds the
-// slice that holds the range's first byte (transfers are laid end to end, so a payload position
-// gives the transfer by a search over their first positions and the slice by a division), walks
-// the slices that intersect the range and moves each piece byte-exactly through the extent lists.
+// steps run over the payload in ranges of 1 KiB, one wavefront per range: the first step finds the
+// slice that holds the range's first byte (transfers are laid end to end, so slices start at ascending
+// payload positions) and keeps it, and the copies go through the slices that intersect the range, byte-exactly.
 #include "copy_generic.h"
 
 namespace tent {
@@ -149,82 +148,112 @@ __global__ void __launch_bounds__(kBothLanes) bounded_both_kernel(const uint64_t
 // ---- geometry without a tile enumeration: ranges of 1 KiB of the payload -----------------------
 constexpr uint32_t kRangeBytes = 1024;
 
-// Payload position of the first byte of transfer j (the source extent prefix runs over the whole batch).
-__device__ __forceinline__ uint64_t transfer_start(const BatchDev& b, uint32_t j) { return b.src_pre[b.src_ptr[j]]; }
-
-// Slice that holds payload position p (p < payload).
-__device__ __forceinline__ uint64_t slice_at(const BatchDev& b, uint64_t p)
-{
-    uint32_t lo = 0, hi = b.n_desc;                       // last transfer that starts at or before p
-    while (hi - lo > 1) {
-        const uint32_t mid = lo + ((hi - lo) >> 1);
-        if (transfer_start(b, mid) <= p) lo = mid; else hi = mid;
-    }
-    return b.first[lo] + (p - transfer_start(b, lo)) / b.slice_bytes;
-}
-
-// Per (chunk, rail): the interval of staging offsets that the BOUND bytes of the chunk touch.  A
-// workgroup covers four consecutive ranges, which lie in one chunk (chunks are multiples of 1 MiB).
-__global__ void __launch_bounds__(256) bounded_ranges_kernel(BatchDev b, uint64_t payload, uint64_t chunk_bytes)
+// Per range the slice of its first byte, and per (chunk, rail) the interval of staging offsets that the BOUND bytes of the chunk touch.
+// A workgroup takes kRangeSlices slices, a group of lanes (a power of two, up to a wavefront) one at a time.  Nearly all of them lie in
+// the first one's chunk, whose intervals are put together in LDS.  (By a wavefront per range, with a search for its slice and a
+// workgroup's intervals sent off every four ranges, 956 MB took 1640 us on MI355X, nearly all of it for atomics on the same few
+// words; now 9.)
+constexpr uint32_t kRangeSlices = 16;
+__global__ void __launch_bounds__(256) bounded_ranges_kernel(BatchDev b, uint64_t chunk_bytes, uint32_t group_shift)
 {
     __shared__ unsigned long long lo[TENT_MAX_RAILS], hi[TENT_MAX_RAILS];
     if (threadIdx.x < TENT_MAX_RAILS) { lo[threadIdx.x] = kNoTile; hi[threadIdx.x] = 0; }
     __syncthreads();
-    const uint64_t first = ((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) * (4ull * kRangeBytes);
-    const uint64_t p0 = first + (uint64_t)(threadIdx.x >> 6) * kRangeBytes;
-    if (p0 < payload) {
-        const uint64_t p1 = p0 + kRangeBytes < payload ? p0 + kRangeBytes : payload;
-        uint64_t i = slice_at(b, p0);
-        for (;;) {
-            const uint64_t at = transfer_start(b, b.s_desc[i]) + b.s_off[i];      // payload position of the slice
-            const uint64_t end = at + b.s_len[i];
-            if ((threadIdx.x & 63) == 0 && b.s_state[i] == TENT_SLICE_BOUND) {
-                const uint64_t from = at > p0 ? at : p0, to = end < p1 ? end : p1;
-                const uint64_t reg = b.s_stage_off[i] + (from - at);
-                const uint32_t d = b.s_rail[i];
-                atomicMin(&lo[d], (unsigned long long)reg);
-                atomicMax(&hi[d], (unsigned long long)(reg + (to - from)));
-            }
-            if (end >= p1) break;
-            ++i;
+    const uint64_t first = (uint64_t)blockIdx.x * kRangeSlices, c_first = b.s_pos[first] / chunk_bytes;
+    const uint32_t group = 1u << group_shift, t0 = threadIdx.x & (group - 1);
+    for (uint64_t i = first + (threadIdx.x >> group_shift); i < first + kRangeSlices && i < b.n_slices; i += 256u >> group_shift) {
+        const uint64_t at = b.s_pos[i], end = at + b.s_len[i];
+        for (uint64_t r = (at + kRangeBytes - 1) / kRangeBytes + t0; r * kRangeBytes < end; r += group) b.range_slice[r] = (uint32_t)i;
+        if (t0 != 0 || b.s_state[i] != TENT_SLICE_BOUND) continue;
+        const uint32_t d = b.s_rail[i];
+        const uint64_t off = b.s_stage_off[i];
+        for (uint64_t c = at / chunk_bytes; c * chunk_bytes < end; ++c) {
+            const uint64_t from = at > c * chunk_bytes ? at : c * chunk_bytes, to = end < (c + 1) * chunk_bytes ? end : (c + 1) * chunk_bytes;
+            unsigned long long* const row_lo = c == c_first ? lo : (unsigned long long*)&b.ch_lo[c * TENT_MAX_RAILS];
+            unsigned long long* const row_hi = c == c_first ? hi : (unsigned long long*)&b.ch_hi[c * TENT_MAX_RAILS];
+            atomicMin(&row_lo[d], (unsigned long long)(off + (from - at)));
+            atomicMax(&row_hi[d], (unsigned long long)(off + (to - at)));
         }
     }
     __syncthreads();
-    if (first < payload && threadIdx.x < TENT_MAX_RAILS && lo[threadIdx.x] != kNoTile) {
-        const uint64_t c = first / chunk_bytes;
-        atomicMin((unsigned long long*)&b.ch_lo[c * TENT_MAX_RAILS + threadIdx.x], lo[threadIdx.x]);
-        atomicMax((unsigned long long*)&b.ch_hi[c * TENT_MAX_RAILS + threadIdx.x], hi[threadIdx.x]);
+    if (threadIdx.x < TENT_MAX_RAILS && lo[threadIdx.x] != kNoTile) {
+        atomicMin((unsigned long long*)&b.ch_lo[c_first * TENT_MAX_RAILS + threadIdx.x], lo[threadIdx.x]);
+        atomicMax((unsigned long long*)&b.ch_hi[c_first * TENT_MAX_RAILS + threadIdx.x], hi[threadIdx.x]);
     }
 }
 
+// Where bytes [x0, x1) of a slice, at most kRangeBytes of them, start on a side whose tile table this is; false if they may be cut into
+// several extents.
+__device__ __forceinline__ bool one_piece(const uint64_t* tiles, uint32_t x0, uint32_t x1, uint64_t* paged)
+{
+    const uint32_t t0 = x0 / kRangeBytes, t1 = (x1 - 1) / kRangeBytes;
+    const uint64_t a = tiles[t0], z = tiles[t1];
+    *paged = a + x0 % kRangeBytes;
+    return ((a | z) & kTileSlow) == 0 && z - a == (uint64_t)(t1 - t0) * kRangeBytes;
+}
+
 // Move the BOUND bytes of payload positions [c_lo, c_hi) -- one chunk -- between their paged side and the
-// chunk's slot, one wavefront per range of 1 KiB.  kBoth (one-pass copies): the wavefront that gathered a piece scatters
-// it at once, reading back what it has just written.
-template <bool kGather, bool kBoth>
+// chunk's slot, one wavefront per range of 1 KiB (one-pass copies: both ways at once).  A piece of the range that has one address on
+// either side goes straight through registers; otherwise its bytes pass through 1 KiB of LDS, and the side that is cut into
+// several extents is walked piece by piece.
+// What bounds it is loads that wait for one another, then memory.  When every range searched the transfers by halves, copied at
+// the arena's alignment and read back from the arena what it had just written there, 956 MB of transfers of 256-byte tokens took
+// 2920 us on MI355X; with the range's slice from a table, the slices' tile tables and LDS 1050.
+template <bool kGather, bool kScatter>
 __global__ void __launch_bounds__(256) bounded_ranges_copy_kernel(BatchDev b, uint64_t c_lo, uint64_t c_hi,
                                                                   uint8_t* slot, uint64_t row)
 {
+    __shared__ vec4u bounce[256];
     const uint64_t w = ((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6);
     const uint64_t p0 = c_lo + w * kRangeBytes;
     if (p0 >= c_hi || b.plan->bounded_overflow != 0) return;
     const uint64_t p1 = p0 + kRangeBytes < c_hi ? p0 + kRangeBytes : c_hi;
-    uint64_t i = slice_at(b, p0);
-    for (;;) {
-        const uint64_t at = transfer_start(b, b.s_desc[i]) + b.s_off[i];
-        const uint64_t end = at + b.s_len[i];
+    vec4u* mine = &bounce[threadIdx.x & ~63u];                    // this wavefront's 1 KiB
+    uint8_t* my_bytes = (uint8_t*)mine;
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint64_t i = b.range_slice[p0 / kRangeBytes];; ++i) {
+        const uint64_t at = b.s_pos[i], end = at + b.s_len[i];
         if (b.s_state[i] == TENT_SLICE_BOUND) {
-            const uint64_t from = at > p0 ? at : p0, to = end < p1 ? end : p1;
-            const uint64_t x = from - at;                                         // offset inside the slice
+            const uint32_t x0 = (uint32_t)((at > p0 ? at : p0) - at), x1 = (uint32_t)((end < p1 ? end : p1) - at);
             const uint32_t d = b.s_rail[i];
-            uint8_t* staged = slot + b.ch_base[row + d] + (b.s_stage_off[i] + x - b.ch_lo[row + d]);
-            copy_range_generic<kGather>(b, i, x, x + (to - from), staged);
-            if (kBoth) {
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-                copy_range_generic<false>(b, i, x, x + (to - from), staged);
+            const uint64_t staged = (uint64_t)slot + b.ch_base[row + d] + (b.s_stage_off[i] + x0 - b.ch_lo[row + d]);
+            uint64_t src = staged, dst = 0;
+            const bool src_cut = kGather && !one_piece(b.src_tile + i * b.tiles_per_slice, x0, x1, &src);
+            const bool dst_cut = kScatter && !one_piece(b.dst_tile + i * b.tiles_per_slice, x0, x1, &dst);
+            // whole vectors, one per lane, and the bytes behind them
+            const uint32_t n = x1 - x0, o = lane * 16, o_tail = (n & ~15u) + lane;
+            const bool whole = o + 16 <= n, tail = o_tail < n;
+            vec4u v;
+            uint8_t t = 0;
+            if (src_cut) {
+                walk_cut_side<true>(b, i, x0, x1, mine);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                v = mine[lane];
+                if (tail) t = my_bytes[o_tail];
+            } else {
+                if (whole) v = *(const vec4u_dev*)(src + o);
+                if (tail) t = *(const byte_dev*)(src + o_tail);
+                if (dst_cut) {
+                    if (whole) mine[lane] = v;
+                    if (tail) my_bytes[o_tail] = t;
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                }
+            }
+            if (kGather) {
+                // (alone, the arena is written with ordinary stores: a slot small enough for the memory-side cache is then
+                // served from it when the chunk is scattered)
+                if (whole) { if (kScatter) __builtin_nontemporal_store(v, (vec4u_dev*)(staged + o)); else *(vec4u_dev*)(staged + o) = v; }
+                if (tail) *(byte_dev*)(staged + o_tail) = t;
+            }
+            if (kScatter && dst_cut) {
+                walk_cut_side<false>(b, i, x0, x1, mine);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");           // (before the next piece is written over it)
+            } else if (kScatter) {
+                if (whole) __builtin_nontemporal_store(v, (vec4u_dev*)(dst + o));
+                if (tail) *(byte_dev*)(dst + o_tail) = t;
             }
         }
         if (end >= p1) break;
-        ++i;
     }
 }
 
@@ -247,15 +276,18 @@ bool grid_for(uint64_t blocks, dim3* grid)
 
 }  // namespace
 
-hipError_t launch_bounded_prepare(const BatchDev& b, uint64_t payload, uint64_t chunk_bytes, uint32_t n_chunks,
-                                  uint64_t slot_bytes, uint32_t slots, uint8_t* arena, hipStream_t s)
+hipError_t launch_bounded_prepare(const BatchDev& b, uint64_t chunk_bytes, uint32_t n_chunks, uint64_t slot_bytes,
+                                  uint32_t slots, uint8_t* arena, hipStream_t s)
 {
     const uint32_t cells = n_chunks * TENT_MAX_RAILS;
     hipLaunchKernelGGL(bounded_clear_kernel, dim3((cells + 255) / 256), dim3(256), 0, s, b, n_chunks);
     dim3 grid;
     if (b.n_sc_tiles == 0) {                                  // no tile enumeration: ranges of the payload
-        if (!grid_for((payload + 4 * kRangeBytes - 1) / (4 * kRangeBytes), &grid)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(bounded_ranges_kernel, grid, dim3(256), 0, s, b, payload, chunk_bytes);
+        uint32_t group_shift = 0;
+        while (group_shift < 6 && (1u << group_shift) < b.tiles_per_slice) ++group_shift;
+        const uint64_t blocks = (b.n_slices + kRangeSlices - 1) / kRangeSlices;
+        if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(bounded_ranges_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b, chunk_bytes, group_shift);
         hipLaunchKernelGGL(bounded_bases_kernel, dim3(n_chunks), dim3(64), 0, s, b, slot_bytes);
         return hipGetLastError();
     }
@@ -284,7 +316,7 @@ hipError_t launch_bounded_copy(const BatchDev& b, bool gather, uint32_t chunk, u
         else if (gather)
             hipLaunchKernelGGL((bounded_ranges_copy_kernel<true, false>), grid, dim3(256), 0, s, b, c_lo, c_hi, slot, row);
         else
-            hipLaunchKernelGGL((bounded_ranges_copy_kernel<false, false>), grid, dim3(256), 0, s, b, c_lo, c_hi, slot, row);
+            hipLaunchKernelGGL((bounded_ranges_copy_kernel<false, true>), grid, dim3(256), 0, s, b, c_lo, c_hi, slot, row);
         return hipGetLastError();
     }
     uint32_t tile_shift = 0;

@@ -212,55 +212,6 @@ __global__ void __launch_bounds__(kOnePassLanes) one_pass_list_copy_kernel(const
     copy_to_both(from, mid, to, *n_act, tile_shift);
 }
 
-typedef __attribute__((address_space(1))) uint8_t byte_dev;
-
-// Bytes [lo, hi) of slice i, at most 1 KiB, between the extents they lie in and a wavefront's 1 KiB of LDS (offset
-// 0 = byte lo).  Every piece is one round of loads: bytes up to the next 16-byte boundary of the LDS side, whole
-// vectors (aligned in LDS, at any address in the extent), bytes behind them.
-template <bool kToLds>
-__device__ __forceinline__ void walk_cut_side(const BatchDev& b, uint64_t i, uint32_t lo, uint32_t hi, vec4u* lds)
-{
-    const uint32_t*    ptr = kToLds ? b.src_ptr : b.dst_ptr;
-    const tent_extent* ext = kToLds ? b.src_ext : b.dst_ext;
-    const uint64_t*    pre = kToLds ? b.src_pre : b.dst_pre;
-    const uint32_t     e0  = kToLds ? b.s_src_e0[i] : b.s_dst_e0[i];
-    const uint32_t j = b.s_desc[i];
-    uint64_t pos = pre[ptr[j]] + b.s_off[i] + lo;                // position in the batch-wide extent prefix
-    const uint64_t end = pos + (hi - lo);
-    uint32_t e = last_not_above32(pre, e0, ptr[j + 1], pos);
-    uint8_t* bytes = (uint8_t*)lds;
-    const uint32_t lane = threadIdx.x & 63u;
-    uint32_t at = 0;
-    while (pos < end) {
-        const uint64_t e_end = pre[e + 1];
-        const uint32_t n = (uint32_t)((e_end < end ? e_end : end) - pos);
-        const tent_extent x = ext[e];
-        const uint64_t paged = b.seg_base[x.seg] + x.off + (pos - pre[e]);
-        uint32_t head = (16u - (at & 15u)) & 15u;
-        if (head > n) head = n;
-        const uint32_t n_vec = (n - head) >> 4, tail = (n - head) & 15u;
-        const bool do_head = lane < head, do_vec = lane < n_vec, do_tail = lane < tail;
-        const uint32_t o_head = lane, o_vec = head + lane * 16u, o_tail = n - tail + lane;
-        if (kToLds) {
-            uint8_t h = 0, g = 0;
-            vec4u v;
-            if (do_head) h = *(const byte_dev*)(paged + o_head);
-            if (do_vec) v = *(const vec4u_dev*)(paged + o_vec);
-            if (do_tail) g = *(const byte_dev*)(paged + o_tail);
-            if (do_head) bytes[at + o_head] = h;
-            if (do_vec) lds[(at + o_vec) >> 4] = v;
-            if (do_tail) bytes[at + o_tail] = g;
-        } else {
-            if (do_head) *(byte_dev*)(paged + o_head) = bytes[at + o_head];
-            if (do_vec) *(vec4u_dev*)(paged + o_vec) = lds[(at + o_vec) >> 4];
-            if (do_tail) *(byte_dev*)(paged + o_tail) = bytes[at + o_tail];
-        }
-        at += n;
-        pos += n;
-        ++e;
-    }
-}
-
 // Geometry whose tiles cross extent boundaries, slice by slice as copy_kernel: a wavefront whose 1 KiB has one
 // address on each side copies straight through registers.  Otherwise its bytes pass through 1 KiB of LDS: the
 // side that is cut into several extents is walked piece by piece, the other side and the staging address keep their

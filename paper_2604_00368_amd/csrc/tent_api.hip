@@ -999,6 +999,7 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
         cv.want(&d.ch_lo, (uint64_t)kMaxChunks * TENT_MAX_RAILS);
         cv.want(&d.ch_hi, (uint64_t)kMaxChunks * TENT_MAX_RAILS);
         cv.want(&d.ch_base, (uint64_t)kMaxChunks * TENT_MAX_RAILS);
+        if (d.n_sc_tiles == 0) cv.want(&d.range_slice, payload / 1024 + 1);
     }
     cv.want(&d.pending, n_slices);
     cv.want(&d.retry_ids, n_slices);
@@ -1717,7 +1718,7 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     b->last = Batch::Last::kCaller;
     uint8_t* arena = static_cast<uint8_t*>(ctx->cfg.staging_arena);
     const uint64_t payload = b->payload;
-    HIP_TRY(launch_bounded_prepare(d, payload, chunk_bytes, (uint32_t)n_chunks, slot_bytes, slots, arena, s));
+    HIP_TRY(launch_bounded_prepare(d, chunk_bytes, (uint32_t)n_chunks, slot_bytes, slots, arena, s));
     if (d.one_pass) {
         // both directions of a chunk in one launch; a chunk's launch ends before the next one may reuse its slot
         for (uint32_t c = 0; c < n_chunks; ++c) {

@@ -168,6 +168,7 @@ struct BatchDev {
     uint64_t* ch_lo;               // [kMaxChunks * TENT_MAX_RAILS] bounded staging: first staging offset per chunk and rail
     uint64_t* ch_hi;               // same shape: end of the interval
     uint64_t* ch_base;             // same shape: region base inside the arena
+    uint32_t* range_slice;         // [payload / 1 KiB + 1] bounded staging without tiles: slice of every KiB's first byte
     uint64_t* tile_scan;           // [n_slices+1] two-pass tile list: tiles of the BOUND slices before slice i
     uint64_t* tile_partials;       // its per-block partial sums
     // Tiles of a partial execute (two passes: BOUND slices in ascending index; one pass: groups of 16 slices in any order)
@@ -235,8 +236,8 @@ bool plan_is_small(const BatchDev& b);
 hipError_t launch_plan_small(const BatchDev& b, const RailParams& rp, Report told, hipStream_t s);
 hipError_t launch_rotate(const BatchDev& b, const RotateParams& rot, hipStream_t s);
 hipError_t launch_fail(const BatchDev& b, const FailParams& fp, Report told, hipStream_t s);
-hipError_t launch_bounded_prepare(const BatchDev& b, uint64_t payload, uint64_t chunk_bytes, uint32_t n_chunks,
-                                  uint64_t slot_bytes, uint32_t slots, uint8_t* arena, hipStream_t s);
+hipError_t launch_bounded_prepare(const BatchDev& b, uint64_t chunk_bytes, uint32_t n_chunks, uint64_t slot_bytes,
+                                  uint32_t slots, uint8_t* arena, hipStream_t s);
 hipError_t launch_bounded_copy(const BatchDev& b, bool gather, uint32_t chunk, uint64_t payload, uint64_t chunk_bytes,
                                uint64_t slot_bytes, uint32_t slots, uint8_t* arena, hipStream_t s);
 hipError_t launch_mark_done_bounded(const BatchDev& b, hipStream_t s);

@@ -169,6 +169,17 @@ def test_bounded_execute_ragged_geometry_bit_exact(H, oracle, seed, kw, slots, f
 
 
 @passes
+@pytest.mark.parametrize("seed,kw", [(21, dict(n_desc=17, max_len=500_000, slice_bytes=1023, max_ext=1500)),
+                                     (22, dict(n_desc=17, max_len=500_000, slice_bytes=1025, max_ext=90_000)),
+                                     (23, dict(n_desc=3, max_len=4_000_000, slice_bytes=(1 << 20) + 1, max_ext=1 << 20)),
+                                     (24, dict(n_desc=300, max_len=9_000, slice_bytes=1 << 20, max_ext=1 << 16))])
+def test_ranges_at_the_edges_of_slices_and_chunks(H, oracle, seed, kw, flags):
+    # slices a byte shorter and longer than a range, longer than a chunk, and many of them in a workgroup; extents that hold whole ranges
+    # on one side or both, so that a piece goes through registers as well as through LDS
+    test_bounded_execute_ragged_geometry_bit_exact(H, oracle, seed, kw, 1, flags)
+
+
+@passes
 def test_bounded_execute_ragged_partial_sets(H, oracle, flags):
     # re-planning epochs on ragged geometry: only the slices that stayed bound move, the rest is re-planned
     from paper_2604_00368_amd import binding as T
