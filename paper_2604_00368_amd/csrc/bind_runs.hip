@@ -1534,14 +1534,23 @@ __global__ void __launch_bounds__(256) bind_emit_kernel(BatchDev b, RailParams r
 // 182 slices took five launches and 44 us of device time in a graph and take one of 32 us.
 constexpr uint32_t kSmallThreads = 1024;
 constexpr uint32_t kSmallExtents = 2048;         // per side; two per thread
+constexpr uint32_t kSmallDescs = 2048;           // two per thread
 constexpr uint32_t kSmallSlices = 2048;
+constexpr uint32_t kFrontExtents = 4096;         // per side; four per thread
+constexpr uint32_t kFrontSlices = 4096;
 constexpr uint64_t kSmallTiles = 16384;          // 20 per thread that the chain, its feeder and its drainer leave over
+
+// What the front part of a plan keeps in LDS: extent prefixes of both sides, first slice and runs before every transfer.
+template <int kItems>
+struct FrontTables {
+    uint64_t src_pre[kSmallThreads * kItems + 1], dst_pre[kSmallThreads * kItems + 1];
+    uint32_t first[kSmallDescs + 1], runs_before[kSmallDescs + 1];
+    uint64_t wave_out[kSmallThreads / 64];
+};
 
 template <int kWide>
 struct SmallPlan {
-    uint64_t src_pre[kSmallExtents + 1], dst_pre[kSmallExtents + 1];
-    uint32_t first[kSmallExtents + 1], runs_before[kSmallExtents + 1];
-    uint64_t wave_out[kSmallThreads / 64];
+    FrontTables<2> front;
     union {
         Ring<kWide> ring;
         EmitRails er;
@@ -1549,53 +1558,66 @@ struct SmallPlan {
     LevelModel lm;
 };
 
-// Exclusive prefix of two values per thread (elements 2 t and 2 t + 1) over the workgroup.
-__device__ __forceinline__ uint64_t pair_prefix(uint64_t v0, uint64_t v1, uint64_t* wave_out)
+// Exclusive prefix of a thread's value over the workgroup.
+__device__ __forceinline__ uint64_t thread_prefix(uint64_t v, uint64_t* wave_out)
 {
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint64_t inc = wave_inclusive_scan(v0 + v1);
+    const uint64_t inc = wave_inclusive_scan(v);
     __syncthreads();
     if (lane == 63) wave_out[wave] = inc;
     __syncthreads();
     uint64_t before = 0;
     for (uint32_t w = 0; w < wave; ++w) before += wave_out[w];
-    return before + inc - (v0 + v1);
+    return before + inc - v;
 }
 
-template <int kWide>
-__global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, RailParams rp, Report told)
+// Prefixes, slice table and run table by one workgroup of kSmallThreads, with barriers; kItems extents a side and two transfers per
+// thread.  A barrier follows before anyone else reads what it leaves.
+template <int kItems>
+__device__ __forceinline__ void plan_front(const BatchDev& b, FrontTables<kItems>& sh)
 {
-    __shared__ SmallPlan<kWide> sh;
-    const uint32_t t = threadIdx.x, e0 = 2 * t, e1 = 2 * t + 1;
+    const uint32_t t = threadIdx.x, base = kItems * t;
     const uint32_t ns = (uint32_t)b.n_src_ext, nd = (uint32_t)b.n_dst_ext, D = b.n_desc, N = (uint32_t)b.n_slices;
     const SliceDiv div(b.slice_bytes);
     {   // extent prefixes of both sides, and in address order where a table goes by it
-        const uint64_t s0 = e0 < ns ? b.src_ext[e0].len : 0, s1 = e1 < ns ? b.src_ext[e1].len : 0;
-        const uint64_t d0 = e0 < nd ? b.dst_ext[e0].len : 0, d1 = e1 < nd ? b.dst_ext[e1].len : 0;
-        uint64_t o0 = 0, o1 = 0;
-        if (b.ord_pre) {
-            o0 = e0 < nd ? b.dst_ext[b.dst_order[e0]].len : 0;
-            o1 = e1 < nd ? b.dst_ext[b.dst_order[e1]].len : 0;
+        uint64_t s[kItems], d[kItems], o[kItems];
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const uint32_t e = base + k;
+            s[k] = e < ns ? b.src_ext[e].len : 0;
+            d[k] = e < nd ? b.dst_ext[e].len : 0;
+            o[k] = b.ord_pre && e < nd ? b.dst_order[e] : 0;
         }
-        auto put = [&](uint64_t* out, uint64_t* in_lds, uint32_t n, uint64_t at, uint64_t v0, uint64_t v1) {
-            auto one = [&](uint32_t e, uint64_t v) {
-                if (e > n) return;
-                out[e] = v;
-                if (in_lds) in_lds[e] = v;
-            };
-            one(e0, at);
-            one(e1, at + v0);
-            if (e1 + 1 == n) one(n, at + v0 + v1);                   // (entry n otherwise comes from the thread behind)
+        if (b.ord_pre) {
+#pragma unroll
+            for (int k = 0; k < kItems; ++k) o[k] = base + k < nd ? b.dst_ext[o[k]].len : 0;
+        }
+        auto put = [&](uint64_t* out, uint64_t* in_lds, uint32_t n, const uint64_t (&v)[kItems]) {
+            uint64_t sum = 0;
+#pragma unroll
+            for (int k = 0; k < kItems; ++k) sum += v[k];
+            uint64_t at = thread_prefix(sum, sh.wave_out);
+#pragma unroll
+            for (int k = 0; k <= kItems; ++k) {
+                const uint32_t e = base + k;
+                if (k == kItems && e != n) break;                    // (entry n otherwise comes from the thread behind)
+                if (e <= n) {
+                    out[e] = at;
+                    if (in_lds) in_lds[e] = at;
+                }
+                if (k < kItems) at += v[k];
+            }
         };
-        put(b.src_pre, sh.src_pre, ns, pair_prefix(s0, s1, sh.wave_out), s0, s1);
-        put(b.dst_pre, sh.dst_pre, nd, pair_prefix(d0, d1, sh.wave_out), d0, d1);
-        if (b.ord_pre) put(b.ord_pre, nullptr, nd, pair_prefix(o0, o1, sh.wave_out), o0, o1);
+        put(b.src_pre, sh.src_pre, ns, s);
+        put(b.dst_pre, sh.dst_pre, nd, d);
+        if (b.ord_pre) put(b.ord_pre, nullptr, nd, o);
     }
     __syncthreads();
     {   // first slice and runs before every transfer
+        const uint32_t e0 = 2 * t, e1 = 2 * t + 1;
         const TransferCounts counts{b.src_ptr, sh.src_pre, div};
         const uint64_t c0 = e0 < D ? counts(e0) : 0, c1 = e1 < D ? counts(e1) : 0;
-        const uint64_t at = pair_prefix(c0, c1, sh.wave_out);
+        const uint64_t at = thread_prefix(c0 + c1, sh.wave_out);
         auto one = [&](uint32_t j, uint64_t v) {
             if (j > D) return;
             b.first[j] = v & 0xFFFFFFFFu;
@@ -1621,8 +1643,27 @@ __global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, R
         b.run_start[n_runs] = N;
         b.plan->n_runs = n_runs;
         b.plan->n_pending = N;
-        start_ring(sh.ring);
     }
+}
+
+// The front part alone, for batches whose tile tables or slices are too many for one workgroup: in place of three to five launches in
+// a row (extent prefixes, counts, slices).  MI355X: a recorded cycle of 2,427 extents a side and 615 slices 134 -> 129.5 us, a life of
+// 2,768 and 768 155 -> 149, cycles in turn of 3,347 and 261 65 -> 56; with eight extents a thread, cycles of 4,224 and 2,112 take
+// 144 us against 137.
+template <int kItems>
+__global__ void __launch_bounds__(kSmallThreads) plan_front_kernel(BatchDev b)
+{
+    __shared__ FrontTables<kItems> sh;
+    plan_front(b, sh);
+}
+
+template <int kWide>
+__global__ void __launch_bounds__(kSmallThreads) plan_small_kernel(BatchDev b, RailParams rp, Report told)
+{
+    __shared__ SmallPlan<kWide> sh;
+    const uint32_t t = threadIdx.x;
+    plan_front(b, sh.front);
+    if (t == 0) start_ring(sh.ring);
     __syncthreads();
     build_level_model<kWide>(sh.lm, b, rp, kBindBuildTables);
     if (t < kChainThreads) chain_waves<kWide>(b, rp, kBindBuildTables, sh.ring, sh.lm);
@@ -1639,6 +1680,19 @@ bool plan_is_small(const BatchDev& b)
 {
     return b.n_src_ext <= kSmallExtents && b.n_dst_ext <= kSmallExtents && b.n_slices <= kSmallSlices &&
            b.n_slices * (uint64_t)b.tiles_per_slice <= kSmallTiles;
+}
+
+bool plan_front_fits(const BatchDev& b)
+{
+    return b.n_src_ext <= kFrontExtents && b.n_dst_ext <= kFrontExtents && b.n_desc <= kSmallDescs && b.n_slices <= kFrontSlices;
+}
+
+hipError_t launch_plan_front(const BatchDev& b, hipStream_t s)
+{
+    const uint64_t most = b.n_src_ext > b.n_dst_ext ? b.n_src_ext : b.n_dst_ext;
+    if (most <= 2 * kSmallThreads) hipLaunchKernelGGL(plan_front_kernel<2>, dim3(1), dim3(kSmallThreads), 0, s, b);
+    else                           hipLaunchKernelGGL(plan_front_kernel<4>, dim3(1), dim3(kSmallThreads), 0, s, b);
+    return hipGetLastError();
 }
 
 hipError_t launch_plan_small(const BatchDev& b, const RailParams& rp, Report told, hipStream_t s)

@@ -769,6 +769,29 @@ hipStream_t work_stream(const tent_ctx* ctx, const Batch& b, hipStream_t s, bool
     return b.beside;
 }
 
+// Prefixes, slice and run table of a first plan, and with `tables` the tile tables (where no chain's launch builds them).  A caller that
+// asks for the time of every stage gets the launches of a large batch.
+int split(tent_ctx* ctx, const BatchDev& d, bool tables, hipStream_t s)
+{
+    if (!(ctx->cfg.flags & TENT_FLAG_PROFILE) && plan_front_fits(d)) {
+        HIP_TRY(launch_plan_front(d, s));
+        if (tables) HIP_TRY(launch_tile_tables(d, s));
+        return TENT_OK;
+    }
+    {
+        StageTimer t(ctx, TENT_T_EXTENT_SCAN, s);
+        HIP_TRY(launch_extent_scans(d, s));
+    }
+    {
+        StageTimer t(ctx, TENT_T_SLICE_SCAN, s);
+        HIP_TRY(launch_slice_scan(d, s));
+    }
+    StageTimer t(ctx, TENT_T_EXPAND, s);
+    HIP_TRY(launch_expand(d, s));
+    if (tables) HIP_TRY(launch_tile_tables(d, s));
+    return TENT_OK;
+}
+
 // The first call that needs the batch's tables waits (on the host) for the declaration's device work
 // and learns the verdict of the overlap check.  A batch that fails it is released.
 int finish_declare(tent_ctx* ctx, Batch& b)
@@ -1276,21 +1299,10 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
         StageTimer t(ctx, TENT_T_BIND, s);
         HIP_TRY(launch_plan_small(d, rp, told, s));
     } else if (!replan) {
-        {
-            StageTimer t(ctx, TENT_T_EXTENT_SCAN, s);
-            HIP_TRY(launch_extent_scans(d, s));
-        }
-        {
-            StageTimer t(ctx, TENT_T_SLICE_SCAN, s);
-            HIP_TRY(launch_slice_scan(d, s));
-        }
-        {
-            // the tile tables of the copy kernels are built beside the binding chain, in its launch
-            // (the slice-by-slice binder has no such launch: there they are built here)
-            StageTimer t(ctx, TENT_T_EXPAND, s);
-            HIP_TRY(launch_expand(d, s));
-            if (serial) HIP_TRY(launch_tile_tables(d, s));
-        }
+        // the tile tables of the copy kernels are built beside the binding chain, in its launch
+        // (the slice-by-slice binder has no such launch: there they are built here)
+        rc = split(ctx, d, serial, s);
+        if (rc != TENT_OK) return rc;
     } else {
         StageTimer t(ctx, TENT_T_COMPACT, s);
         HIP_TRY(launch_compact(d, s));
@@ -1404,18 +1416,8 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     if (priority) HIP_TRY(hipMemcpyAsync(d.priority, priority, d.n_desc, hipMemcpyHostToDevice, s));
     const Report told = next_report(ctx, info != nullptr);
     if (first_plan) {
-        {
-            StageTimer t(ctx, TENT_T_EXTENT_SCAN, s);
-            HIP_TRY(launch_extent_scans(d, s));
-        }
-        {
-            StageTimer t(ctx, TENT_T_SLICE_SCAN, s);
-            HIP_TRY(launch_slice_scan(d, s));
-        }
-        {
-            StageTimer t(ctx, TENT_T_EXPAND, s);
-            HIP_TRY(launch_expand(d, s));
-        }
+        rc = split(ctx, d, false, s);
+        if (rc != TENT_OK) return rc;
     }
     {
         StageTimer t(ctx, TENT_T_BIND, s);

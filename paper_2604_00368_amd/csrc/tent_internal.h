@@ -233,6 +233,9 @@ hipError_t launch_bind_serial(const BatchDev& b, const RailParams& rp, int mode,
 hipError_t launch_bind_runs(const BatchDev& b, const RailParams& rp, int mode, Report told, hipStream_t s);
 // A first plan in one workgroup, for batches small enough.
 bool plan_is_small(const BatchDev& b);
+// The part of a first plan up to the slice table in one workgroup, in place of the three launch functions above.
+bool plan_front_fits(const BatchDev& b);
+hipError_t launch_plan_front(const BatchDev& b, hipStream_t s);
 hipError_t launch_plan_small(const BatchDev& b, const RailParams& rp, Report told, hipStream_t s);
 hipError_t launch_rotate(const BatchDev& b, const RotateParams& rot, hipStream_t s);
 hipError_t launch_fail(const BatchDev& b, const FailParams& fp, Report told, hipStream_t s);

@@ -111,6 +111,39 @@ def test_plan_in_one_workgroup_and_beyond(H, oracle, n, what):
         check_binding(H, oracle, transfers([8 * 1024 * n - 1024 * (n > 2)], 8 * 1024, rails))
 
 
+@pytest.mark.parametrize("n", [2049, 4095, 4096, 4097])
+@pytest.mark.parametrize("what", ["extents", "slices", "transfers", "dispatch"])
+def test_front_part_in_one_workgroup_and_beyond(H, oracle, n, what):
+    # one workgroup writes the slice table of up to 4096 extents a side, 4096 slices and 2048 transfers
+    from paper_2604_00368_amd import binding as T
+    g = np.random.Generator(np.random.PCG64([n, len(what)]))
+    rails = W.make_rails([25000, 50000, 40000, 10000], queued=g.integers(0, 5000, size=4))
+    if what == "slices":
+        return check_binding(H, oracle, transfers([1024 * (n // 3) - 5, 1024 * (n // 3), 1024 * (n - 2 * (n // 3))], 1024, rails))
+    if what == "transfers":
+        return check_binding(H, oracle, transfers(g.integers(1, 5000, size=n // 2), 4096, rails))
+    # transfers of several extents, cut differently on either side; whole tiles or not
+    for unit in (1024, 1000):
+        sizes = unit * g.integers(1, 9, size=n)
+        starts = np.unique(np.concatenate([[0], g.integers(1, n, size=60)]))
+        w = transfers(sizes, 16384, rails)
+        w.src_ptr = np.append(starts, n).astype(np.uint32)
+        merged = np.add.reduceat(sizes, starts)
+        w.dst_ext = w.dst_ext[:len(starts)].copy()
+        w.dst_ext["len"], w.dst_ext["off"] = merged, np.concatenate([[0], np.cumsum(merged)[:-1]])
+        w.dst_ptr = np.arange(len(starts) + 1, dtype=np.uint32)
+        if what == "extents":
+            check_binding(H, oracle, w)
+            continue
+        s = oracle.split(w.src_ptr, w.src_ext, w.slice_bytes)
+        dp = W.make_dispatch_params(1 << 15)
+        r = oracle.dispatch(s, w.rails, dp)
+        with H.Engine(w) as eng:
+            eng.declare()
+            assert T.tent_plan_dispatch(eng.ctx, eng.batch, w.rails, dp, None, True, eng.stream)[0] == 0
+            H.assert_plan_equal(eng.table(), s, r.binding)
+
+
 def stretches(g, S, n, singles, equal):
     """Stretches of `equal` transfers of whole slices and a tail, `singles` transfers shorter than a slice, and one whose
     slices are short (a run of its own slice length when repeated) in turn."""
