@@ -7,7 +7,7 @@
 // retried slice is therefore a pure function of (i, k); what needs work is its staging offset, the
 // bytes of the earlier retried slices on the same rail -- one prefix sum per rail over the retry
 // list.  Three launches: per-chunk byte and slice counts per rail, an exclusive scan of those
-// over the chunks (one lane per rail), and the in-order walk of every chunk by one wavefront.
+// over the chunks (one lane per rail), and the in-order walk of every chunk by one wavefront; one for a small batch.
 #include "finish.h"
 
 namespace tent {
@@ -79,14 +79,9 @@ __global__ void __launch_bounds__(64) rotate_spine_kernel(BatchDev b)
 // Step 3: one wavefront walks its chunk in order, 64 retried slices at a time.  Lane d keeps the
 // running byte count of rail d; for every rail present among the 64 slices a wave-wide inclusive
 // scan over the lengths of that rail's slices gives each its offset.
-__global__ void __launch_bounds__(64) rotate_emit_kernel(BatchDev b, RotateParams rot)
+__device__ __forceinline__ void bind_retried(const BatchDev& b, const RotateParams& rot, uint64_t begin, uint64_t end, uint64_t my_base)
 {
-    const uint64_t n = b.plan->n_retry;
-    const uint64_t begin = (uint64_t)blockIdx.x * kRotChunk;
-    if (begin >= n) return;
-    const int lane = threadIdx.x;
-    uint64_t my_base = b.rot_bytes[(uint64_t)blockIdx.x * TENT_MAX_RAILS + lane];
-    const uint64_t end = begin + kRotChunk < n ? begin + kRotChunk : n;
+    const int lane = threadIdx.x & 63;
     for (uint64_t blk = begin; blk < end; blk += 64) {
         const uint64_t q = blk + lane;
         const bool valid = q < end;
@@ -120,6 +115,50 @@ __global__ void __launch_bounds__(64) rotate_emit_kernel(BatchDev b, RotateParam
             b.s_state[id] = TENT_SLICE_BOUND;
         }
     }
+}
+
+__global__ void __launch_bounds__(64) rotate_emit_kernel(BatchDev b, RotateParams rot)
+{
+    const uint64_t n = b.plan->n_retry;
+    const uint64_t begin = (uint64_t)blockIdx.x * kRotChunk;
+    if (begin >= n) return;
+    bind_retried(b, rot, begin, begin + kRotChunk < n ? begin + kRotChunk : n, b.rot_bytes[(uint64_t)blockIdx.x * TENT_MAX_RAILS + threadIdx.x]);
+}
+
+// The three steps in one launch, by one workgroup of a wavefront per chunk, for batches of up to kRotateSmall slices: there launches cost
+// more than the work.  MI355X, lists, rotation and chain of 2,000 slices on 9 rails with what one of them had failed 60.6 -> 53.0 us, with
+// all of it failed 41.6 -> 34.8, on 64 rails 106.3 -> 105.9; 20,000 slices in rounds of 4,096 would take 129.9 us for 133.0, but 141 for
+// 64 where all have failed.
+constexpr uint32_t kRotateWaves = 8;
+constexpr uint64_t kRotateSmall = (uint64_t)kRotateWaves * kRotChunk;
+
+__global__ void __launch_bounds__(64 * kRotateWaves) rotate_small_kernel(BatchDev b, RotateParams rot)
+{
+    __shared__ unsigned long long bytes[kRotateWaves][TENT_MAX_RAILS];
+    __shared__ uint32_t cnt[kRotateWaves][TENT_MAX_RAILS];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint64_t n = b.plan->n_retry;                          // at most n_slices
+    const uint64_t begin = (uint64_t)wave * kRotChunk, end = begin + kRotChunk < n ? begin + kRotChunk : n;
+    bytes[wave][lane] = 0;
+    cnt[wave][lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    for (uint64_t q = begin + lane; q < end; q += 64) {
+        const uint32_t id = b.retry_ids[q];
+        const uint32_t d = rotation_rail(rot, id, b.s_retry[id]);
+        atomicAdd(&bytes[wave][d], (unsigned long long)b.s_len[id]);
+        atomicAdd(&cnt[wave][d], 1u);
+    }
+    __syncthreads();
+    uint64_t before = 0, all = 0, slices = 0;                    // lane = rail
+    for (uint32_t w = 0; w < kRotateWaves; ++w) {
+        if (w == wave) before = all;
+        all += bytes[w][lane];
+        slices += cnt[w][lane];
+    }
+    if (begin < n) bind_retried(b, rot, begin, end, before);
+    if (wave != 0) return;
+    b.plan->Tr[lane] = all;
+    b.plan->cr[lane] = slices;
 }
 
 // Rail simulator: every BOUND slice on a failed rail returns to the pending set with one more retry.
@@ -156,6 +195,10 @@ hipError_t launch_rotate(const BatchDev& b, const RotateParams& rot, hipStream_t
     if (rot.n_cand == 0 || rot.n_cand > TENT_MAX_RAILS) return hipErrorInvalidValue;
     const uint64_t chunks = (b.n_slices + kRotChunk - 1) / kRotChunk;          // upper bound; idle chunks exit at once
     if (chunks == 0 || chunks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    if (b.n_slices <= kRotateSmall) {
+        hipLaunchKernelGGL(rotate_small_kernel, dim3(1), dim3(64 * kRotateWaves), 0, s, b, rot);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(rotate_count_kernel, dim3((uint32_t)chunks), dim3(64), 0, s, b, rot);
     hipLaunchKernelGGL(rotate_spine_kernel, dim3(1), dim3(64), 0, s, b);
     hipLaunchKernelGGL(rotate_emit_kernel, dim3((uint32_t)chunks), dim3(64), 0, s, b, rot);

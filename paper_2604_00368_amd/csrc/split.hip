@@ -517,7 +517,8 @@ hipError_t launch_compact(const BatchDev& b, hipStream_t s)
 {
     const uint64_t tiles = scan_tiles(b.n_slices);
     if (tiles == 0 || tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(pending_share_kernel, dim3((uint32_t)tiles), dim3(kScanBlock), 0, s, b);
+    // (one tile alone needs no other's share)
+    if (tiles > 1) hipLaunchKernelGGL(pending_share_kernel, dim3((uint32_t)tiles), dim3(kScanBlock), 0, s, b);
     const bool spined = tiles > kSelfSpine;
     if (spined) hipLaunchKernelGGL(pending_spine_kernel, dim3(1), dim3(kScanBlock), 0, s, b, (uint32_t)tiles);
     hipLaunchKernelGGL(pending_lists_kernel, dim3((uint32_t)tiles), dim3(kScanBlock), 0, s, b, spined ? 1 : 0);

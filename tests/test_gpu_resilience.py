@@ -307,3 +307,25 @@ def test_lists_of_a_replan_at_the_edges_of_their_tiles(H, oracle, n):
             assert np.array_equal(tab["stage_off"][pending], b.stage_off[pending])
             assert list(info.rail_bytes)[:5] == b.T.tolist()
             assert list(info.rail_slices)[:5] == b.n_slices.tolist()
+
+
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 2047, 2048, 2049])
+@pytest.mark.parametrize("R", [3, 64])
+def test_rotation_of_everything_in_one_launch_and_beyond(H, oracle, n, R):
+    # chunks of 256 retried slices; up to 2048 slices one workgroup takes them all
+    from paper_2604_00368_amd import binding as T
+    from test_gpu_chain import transfers
+    S = 64
+    rng = np.random.Generator(np.random.PCG64([n, R]))
+    w = transfers([S * (n // 2) + 1, S * (n - n // 2 - 1) - 3] if n > 2 else [S * n], S, W.make_rails(rng.integers(20000, 90000, R)))
+    s = oracle.split(w.src_ptr, w.src_ext, w.slice_bytes)
+    assert s.n == n
+    with H.Engine(w) as eng:
+        eng.declare()
+        assert eng.plan()[0] == 0
+        for _ in range(2):
+            T.tent_sim_fail(eng.ctx, eng.batch, np.ones(R, dtype=np.uint8), True, eng.stream)
+            b = oracle.plan(s.len, T.tent_get_retries(eng.ctx, eng.batch), w.rails, ids=np.arange(n, dtype=np.uint32))
+            st, info = eng.plan()
+            assert st == 0
+            H.assert_plan_equal(eng.table(), s, b, info)
