@@ -51,7 +51,7 @@ __device__ __forceinline__ void dispatch_chain(const BatchDev& b, const RailPara
         uint64_t my_len = 0;
         if (jl < D) {
             const uint64_t f0 = b.first[jl], f1 = b.first[jl + 1];
-            my_n = (uint32_t)(b.scan_tmp[f1] - b.scan_tmp[f0]);              // slices of the request not DONE
+            my_n = (uint32_t)(dp.all_pending ? f1 - f0 : b.scan_tmp[f1] - b.scan_tmp[f0]);       // slices of the request not DONE
             my_len = b.src_pre[b.src_ptr[jl + 1]] - b.src_pre[b.src_ptr[jl]];
             const uint64_t last_len = my_len - (f1 - f0 - 1) * S;
             if (b.s_state[f1 - 1] != TENT_SLICE_DONE) my_short = (uint32_t)(S - last_len);
@@ -209,7 +209,7 @@ __device__ __forceinline__ void feed_requests(const BatchDev& b, const DispatchP
         const uint64_t f0 = b.first[j], f1 = b.first[j + 1];
         len = b.src_pre[b.src_ptr[j + 1]] - b.src_pre[b.src_ptr[j]];
         const uint32_t prio = dp.all_high ? 2u : b.priority[j];
-        pending = (uint32_t)(b.scan_tmp[f1] - b.scan_tmp[f0]);
+        pending = (uint32_t)(dp.all_pending ? f1 - f0 : b.scan_tmp[f1] - b.scan_tmp[f0]);
         admitted = (uint32_t)dp.adm[prio > 2 ? 2 : prio] & 0xFFFFu;
         mice = len < dp.theta;
         if (b.s_state[f1 - 1] != TENT_SLICE_DONE) short_by = (uint32_t)(b.slice_bytes - (len - (f1 - f0 - 1) * b.slice_bytes));
@@ -469,14 +469,14 @@ __global__ void __launch_bounds__(256) dispatch_emit_kernel(BatchDev b, RailPara
     const uint32_t R = rp.n_rails;
     const uint32_t stride = b.run_stride;
     const uint64_t S = b.slice_bytes;
-    const uint64_t n = b.scan_tmp[b.n_slices];                       // slices not DONE
+    const uint64_t n = dp.all_pending ? b.n_slices : b.scan_tmp[b.n_slices];         // slices not DONE
     const uint64_t gstride = (uint64_t)blocks * blockDim.x;
     for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gstride) {
-        const uint32_t i_q = b.pending[q];
+        const uint32_t i_q = dp.all_pending ? (uint32_t)q : b.pending[q];
         const uint32_t j = b.s_desc[i_q];
         const uint32_t mode = b.req_mode[j];
         if (mode != 1 && mode != 2) continue;                        // deferred
-        const uint64_t q0 = b.scan_tmp[b.first[j]];                  // first pending position of the request
+        const uint64_t q0 = dp.all_pending ? b.first[j] : b.scan_tmp[b.first[j]];    // first pending position of the request
         const uint64_t row = (uint64_t)j * stride;
         uint32_t t = (uint32_t)(q - q0), d = 0;
         for (; d < R; ++d) {
@@ -503,7 +503,7 @@ __global__ void __launch_bounds__(256) dispatch_emit_kernel(BatchDev b, RailPara
                 rank += before < ko ? before : ko;
             }
         }
-        const uint32_t id = b.pending[q0 + rank];
+        const uint32_t id = dp.all_pending ? (uint32_t)(q0 + rank) : b.pending[q0 + rank];
         b.s_rail[id] = d;
         b.s_stage_off[id] = (uint64_t)b.run_cell[row + d].T + (uint64_t)k * S;
         b.s_state[id] = TENT_SLICE_BOUND;
@@ -514,16 +514,6 @@ struct NotDone {
     const uint8_t* state;
     __device__ uint64_t operator()(uint64_t i) const { return state[i] != TENT_SLICE_DONE; }
 };
-
-__global__ void __launch_bounds__(256) all_pending_kernel(BatchDev b)
-{
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < b.n_slices; i += stride) {
-        b.pending[i] = (uint32_t)i;
-        b.scan_tmp[i] = i;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) b.scan_tmp[b.n_slices] = b.n_slices;
-}
 
 __global__ void __launch_bounds__(256) pending_list_kernel(BatchDev b)
 {
@@ -542,10 +532,7 @@ hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const Dispat
 {
     uint64_t blocks = (b.n_slices + 255) / 256;
     if (blocks > 4096) blocks = 4096;
-    if (first_plan) {
-        // nothing is DONE yet: every slice is its own pending position
-        hipLaunchKernelGGL(all_pending_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);
-    } else {
+    if (!first_plan) {
         hipError_t e = exclusive_scan(NotDone{b.s_state}, b.n_slices, b.scan_tmp, b.scan_partials, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(pending_list_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, b);

@@ -1413,6 +1413,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     HIP_TRY(order_after_execute_bookkeeping(*b, s));
     b->last = s == b->beside ? Batch::Last::kBeside : Batch::Last::kCaller;
     dp.all_high = priority ? 0u : 1u;
+    dp.all_pending = first_plan ? 1u : 0u;
     if (priority) HIP_TRY(hipMemcpyAsync(d.priority, priority, d.n_desc, hipMemcpyHostToDevice, s));
     const Report told = next_report(ctx, info != nullptr);
     if (first_plan) {

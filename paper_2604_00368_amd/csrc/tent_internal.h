@@ -54,6 +54,7 @@ struct DispatchParams {
     uint64_t adm[3];             // admitted-rail masks for priorities LOW, MID, HIGH
     uint32_t gamma_q8;           // cost tolerance of the mice candidate set, Q8.8
     uint32_t all_high;           // 1: no priority array was given, every request counts as HIGH
+    uint32_t all_pending;        // 1: a first plan, every slice is its own pending position (no list)
     uint32_t near;               // 1: costs, slots and rails are few enough for the chain of up to 16 rails (dispatch.hip)
 };
 
