@@ -417,7 +417,7 @@ def beside_copies():
         tables, copies = cycle(one)
         assert launched(tables) == {STREAM_A}
     # on another stream than the copies', and of a batch whose calls on the caller's stream have not ended: there
-    T.tent_reset(h.ctx, two, STREAM_B)
+    T.tent_plan(h.ctx, two, rails, False, STREAM_B)
     T.tent_plan(h.ctx, two, rails, False, STREAM_A)
     assert launched(h.log()) == {STREAM_A, STREAM_B}
     assert not [x for x in h.log() if x[0] == HOST_WAIT]
@@ -428,6 +428,47 @@ def test_tables_are_worked_on_beside_earlier_copies(fake):
     """A plan and a reset move no byte: while copies that they need not wait for run on the caller's stream they run on the
     context's own, behind the batch's own copies, and the batch's next call on the caller's stream waits for them."""
     run(fake, "beside_copies")
+
+
+def resets():
+    h = Host(slice_bytes=4096)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    b = T.tent_declare(h.ctx, *h.extents(64, 4096))
+
+    def reset(stream=STREAM_A):
+        h.log()
+        T.tent_reset(h.ctx, b, stream)
+        assert T.tent_poll(h.ctx, b, stream) == 64
+        return h.log()
+
+    T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+    T.tent_execute(h.ctx, b, STREAM_A)
+    end = [x[2] for x in h.log() if x[0] == RECORD][-1]
+    assert reset() == []
+    T.tent_plan(h.ctx, b, rails, False, STREAM_B)                  # rewrites what the copies read
+    log = h.log()
+    assert log.index((WAIT, STREAM_B, end)) < [x[0] for x in log].index(LAUNCH)
+    T.tent_execute(h.ctx, b, STREAM_A)
+    end = [x[2] for x in h.log() if x[0] == RECORD][-1]
+    assert reset(STREAM_B) == [(WAIT, STREAM_B, end)]
+    for fail in (1, 0):                                            # retry counts are cleared, once
+        T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+        if fail:
+            T.tent_sim_fail(h.ctx, b, np.ones(2, dtype=np.uint8), False, STREAM_A)
+        assert [x[0] for x in reset()].count(LAUNCH) == fail
+    T.tent_plan(h.ctx, b, rails, False, STREAM_A)                  # in a graph there may be some when it is replayed
+    h.hip.fake_capture(STREAM_A)
+    for _ in range(2):
+        assert [x[:2] for x in reset()] == [(LAUNCH, STREAM_A)]
+        T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+        h.hip.fake_capture(0) if _ else None
+    assert [x[0] for x in reset()].count(LAUNCH) == 1
+    T.tent_destroy(h.ctx)
+
+
+def test_a_reset_launches_only_where_something_is_to_be_cleared(fake):
+    """The next plan writes the slice table afresh; without retry counts a reset is the host's bookkeeping."""
+    run(fake, "resets")
 
 
 def windows_beside_copies(payload):
