@@ -27,12 +27,17 @@ namespace {
 
 constexpr uint64_t kNoKey = ~0ull;
 
+__device__ __forceinline__ uint32_t priority_of(const BatchDev& b, const DispatchParams& dp, const PriorityBits& bits, uint32_t j)
+{
+    return dp.all_high ? 2u : dp.by_bits ? (bits.word[j / 16] >> (2 * (j % 16))) & 3u : b.priority[j];
+}
+
 // ---- the chain over requests -------------------------------------------------------------------
 // kWide = 16, 32 or 64: smallest of these that covers the rails; lanes beyond the rails only tag along
 // (uniform decisions are read from lane 0's row).
 // Runs in the first wavefront of a workgroup (lane = threadIdx.x < 64).
 template <int kWide>
-__device__ __forceinline__ void dispatch_chain(const BatchDev& b, const RailParams& rp, const DispatchParams& dp)
+__device__ __forceinline__ void dispatch_chain(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, const PriorityBits& bits)
 {
     const int lane = threadIdx.x;
     const uint64_t S = b.slice_bytes;
@@ -55,7 +60,7 @@ __device__ __forceinline__ void dispatch_chain(const BatchDev& b, const RailPara
             my_len = b.src_pre[b.src_ptr[jl + 1]] - b.src_pre[b.src_ptr[jl]];
             const uint64_t last_len = my_len - (f1 - f0 - 1) * S;
             if (b.s_state[f1 - 1] != TENT_SLICE_DONE) my_short = (uint32_t)(S - last_len);
-            if (!dp.all_high) my_prio = b.priority[jl];
+            my_prio = priority_of(b, dp, bits, jl);
         }
         const int m = (int)(D - blk < 64 ? D - blk : 64);
         uint32_t my_mode = 0;
@@ -199,7 +204,7 @@ struct RequestRing {
 };
 
 // Requests [64 blk, 64 blk + 64), one per lane.
-__device__ __forceinline__ void feed_requests(const BatchDev& b, const DispatchParams& dp, RequestRing& ring, uint32_t blk, uint32_t lane)
+__device__ __forceinline__ void feed_requests(const BatchDev& b, const DispatchParams& dp, const PriorityBits& bits, RequestRing& ring, uint32_t blk, uint32_t lane)
 {
     const uint32_t j = blk * kRequests + lane;
     uint32_t mode = 0, pending = 0, admitted = 0, short_by = 0;
@@ -208,7 +213,7 @@ __device__ __forceinline__ void feed_requests(const BatchDev& b, const DispatchP
     if (j < b.n_desc) {
         const uint64_t f0 = b.first[j], f1 = b.first[j + 1];
         len = b.src_pre[b.src_ptr[j + 1]] - b.src_pre[b.src_ptr[j]];
-        const uint32_t prio = dp.all_high ? 2u : b.priority[j];
+        const uint32_t prio = priority_of(b, dp, bits, j);
         pending = (uint32_t)(dp.all_pending ? f1 - f0 : b.scan_tmp[f1] - b.scan_tmp[f0]);
         admitted = (uint32_t)dp.adm[prio > 2 ? 2 : prio] & 0xFFFFu;
         mice = len < dp.theta;
@@ -381,7 +386,8 @@ __device__ __forceinline__ void drain_requests(const BatchDev& b, const RequestR
 }
 
 // By a whole workgroup of at least 192 threads, with barriers.
-__device__ __forceinline__ void dispatch_chain16(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, RequestRing& ring)
+__device__ __forceinline__ void dispatch_chain16(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, const PriorityBits& bits,
+                                                 RequestRing& ring)
 {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, who = lane & 15u;
     const uint32_t blocks = (b.n_desc + kRequests - 1) / kRequests;
@@ -391,13 +397,13 @@ __device__ __forceinline__ void dispatch_chain16(const BatchDev& b, const RailPa
     uint64_t Q = (rp.c0[who] << 16) + rp.A[who] * c1;
     RailTotals sum{0.0, 0};
     if (wave == 0) __builtin_amdgcn_s_setprio(3);
-    if (wave == 1) feed_requests(b, dp, ring, 0, lane);
+    if (wave == 1) feed_requests(b, dp, bits, ring, 0, lane);
     for (uint32_t k = 0; k < blocks; ++k) {                                  // block k walked, k + 1 fed, k - 1 drained
         __syncthreads();
         if (wave == 0) walk_requests(b, dp, c1, ring, k, Q);
         // (block k - 1 is drained first: its records' place is the next block's)
         if (wave == 1 && k > 0) drain_requests(b, ring, k - 1, sum, lane);
-        if (wave == 1 && k + 1 < blocks) feed_requests(b, dp, ring, k + 1, lane);
+        if (wave == 1 && k + 1 < blocks) feed_requests(b, dp, bits, ring, k + 1, lane);
     }
     __syncthreads();
     if (wave != 1) return;
@@ -427,29 +433,29 @@ __device__ __forceinline__ void dispatch_chain16(const BatchDev& b, const RailPa
 
 // kWide = 0: dispatch_chain16
 template <int kWide>
-__device__ __forceinline__ void dispatch_workgroup(const BatchDev& b, const RailParams& rp, const DispatchParams& dp)
+__device__ __forceinline__ void dispatch_workgroup(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, const PriorityBits& bits)
 {
     if constexpr (kWide == 0) {
         __shared__ RequestRing ring;
-        dispatch_chain16(b, rp, dp, ring);
+        dispatch_chain16(b, rp, dp, bits, ring);
     } else {
-        if (threadIdx.x < 64) dispatch_chain<kWide>(b, rp, dp);
+        if (threadIdx.x < 64) dispatch_chain<kWide>(b, rp, dp, bits);
     }
 }
 
 template <int kWide>
-__global__ void __launch_bounds__(256) dispatch_chain_kernel(BatchDev b, RailParams rp, DispatchParams dp)
+__global__ void __launch_bounds__(256) dispatch_chain_kernel(BatchDev b, RailParams rp, DispatchParams dp, PriorityBits bits)
 {
-    dispatch_workgroup<kWide>(b, rp, dp);
+    dispatch_workgroup<kWide>(b, rp, dp, bits);
 }
 
 // First plan of a batch: the tile tables of the copy kernels are built by the other workgroups of the
 // chain's launch (they depend on the slice table only).
 template <int kWide>
-__global__ void __launch_bounds__(256) dispatch_chain_tables_kernel(BatchDev b, RailParams rp, DispatchParams dp)
+__global__ void __launch_bounds__(256) dispatch_chain_tables_kernel(BatchDev b, RailParams rp, DispatchParams dp, PriorityBits bits)
 {
     if (blockIdx.x == 0) {
-        dispatch_workgroup<kWide>(b, rp, dp);
+        dispatch_workgroup<kWide>(b, rp, dp, bits);
         return;
     }
     build_tile_tables_in(b, blockIdx.x - 1, gridDim.x - 1);
@@ -527,7 +533,7 @@ __global__ void __launch_bounds__(256) pending_list_kernel(BatchDev b)
 
 }  // namespace
 
-hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, bool first_plan,
+hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, const PriorityBits& bits, bool first_plan,
                            Report told, hipStream_t s)
 {
     uint64_t blocks = (b.n_slices + 255) / 256;
@@ -540,9 +546,9 @@ hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const Dispat
     auto launch_chain = [&](auto wide) {
         constexpr int kW = decltype(wide)::value;
         if (first_plan)
-            hipLaunchKernelGGL(dispatch_chain_tables_kernel<kW>, dim3(1 + tile_table_blocks(b)), dim3(256), 0, s, b, rp, dp);
+            hipLaunchKernelGGL(dispatch_chain_tables_kernel<kW>, dim3(1 + tile_table_blocks(b)), dim3(256), 0, s, b, rp, dp, bits);
         else
-            hipLaunchKernelGGL(dispatch_chain_kernel<kW>, dim3(1), dim3(kW == 0 ? 128 : 64), 0, s, b, rp, dp);
+            hipLaunchKernelGGL(dispatch_chain_kernel<kW>, dim3(1), dim3(kW == 0 ? 128 : 64), 0, s, b, rp, dp, bits);
     };
     if (dp.near)               launch_chain(std::integral_constant<int, 0>{});
     else if (rp.n_rails <= 16) launch_chain(std::integral_constant<int, 16>{});

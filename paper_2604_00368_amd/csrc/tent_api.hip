@@ -1374,9 +1374,15 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     if (rp.admitted == 0) return TENT_DEFER;
     if (!(ctx->cfg.flags & TENT_FLAG_BOUNDED_STAGING) && b->payload + 256ull * n_rails > ctx->cfg.staging_bytes)
         return TENT_ERR_RANGE;
+    const uint32_t n_desc = b->dev.n_desc;
+    const bool by_bits = priority && n_desc <= kPriorityBits;
+    PriorityBits bits;
+    std::memset(&bits, 0, sizeof(bits));
     if (priority)
-        for (uint32_t j = 0; j < b->dev.n_desc; ++j)
+        for (uint32_t j = 0; j < n_desc; ++j) {
             if (priority[j] > 2) return TENT_ERR_INVALID;
+            if (by_bits) bits.word[j / 16] |= (uint32_t)priority[j] << (2 * (j % 16));
+        }
     // The slot keys (m + 1) * s_d are packed with a 6-bit rail index and the tolerance multiplies a
     // cost by gamma: bound the largest cost any rail can show during this plan.
     DispatchParams dp;
@@ -1416,7 +1422,8 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     b->last = s == b->beside ? Batch::Last::kBeside : Batch::Last::kCaller;
     dp.all_high = priority ? 0u : 1u;
     dp.all_pending = first_plan ? 1u : 0u;
-    if (priority) HIP_TRY(hipMemcpyAsync(d.priority, priority, d.n_desc, hipMemcpyHostToDevice, s));
+    dp.by_bits = by_bits ? 1u : 0u;
+    if (priority && !by_bits) HIP_TRY(hipMemcpyAsync(d.priority, priority, d.n_desc, hipMemcpyHostToDevice, s));
     const Report told = next_report(ctx, info != nullptr);
     if (first_plan) {
         rc = split(ctx, d, false, s);
@@ -1424,7 +1431,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     }
     {
         StageTimer t(ctx, TENT_T_BIND, s);
-        HIP_TRY(launch_dispatch(d, rp, dp, first_plan, told, s));
+        HIP_TRY(launch_dispatch(d, rp, dp, bits, first_plan, told, s));
     }
     b->planned = true;
     b->may_replan = true;                                     // deferred transfers stay pending

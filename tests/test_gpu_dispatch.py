@@ -147,6 +147,16 @@ def test_request_chain_at_its_block_edges(H, oracle, D, kind):
                                  bytes_too=False, rr_start=(1 << 40) + 5)
 
 
+@pytest.mark.parametrize("R", [4, 20])
+@pytest.mark.parametrize("D", [15, 16, 17, 2047, 2048, 2049])
+def test_priorities_with_the_arguments_and_in_memory(H, oracle, D, R):
+    # two bits each, sixteen to a word, for up to 2048 transfers
+    rng = np.random.Generator(np.random.PCG64(D))
+    S = 4 * KiB
+    w = contiguous_requests(rng.integers(1, 6 * S, D), S, W.make_rails(rng.integers(10000, 400000, R)), D)
+    dispatch_windows_and_compare(H, oracle, w, theta=2 * S, gamma_q8=64, prio=W.make_priorities(D, D), windows=[0, 1, 2], bytes_too=False)
+
+
 def test_dispatch_then_cost_model_replan(H, oracle):
     # a window of request-level dispatch, then the per-slice planner finishes what was deferred
     from paper_2604_00368_amd import binding as T
