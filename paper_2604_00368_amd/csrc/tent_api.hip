@@ -718,12 +718,13 @@ hipError_t record_execute_done(Batch& b, hipStream_t s, StreamNote& note)
 // Executes so far, of all contexts: tells a batch whether other copies have been enqueued behind its own.
 std::atomic<uint64_t> g_executes{0};
 
-// An execute that was enqueued: what may run beside its copies.
-void note_execute(tent_ctx* ctx, Batch& b, hipStream_t s)
+// An execute that was enqueued: what may run beside its copies (with `apart`, nothing).
+void note_execute(tent_ctx* ctx, Batch& b, hipStream_t s, bool apart = false)
 {
-    b.last = b.done_recorded ? Batch::Last::kExecute : Batch::Last::kCaller;
+    b.last = b.done_recorded && !apart ? Batch::Last::kExecute : Batch::Last::kCaller;
     b.execute_no = ++g_executes;
-    if (!b.done_recorded) return;
+    if (apart) ctx->copies_end = nullptr;
+    if (!b.done_recorded || apart) return;
     ctx->copies_end = b.done_at;
     ctx->copies_stream = s;
 }
@@ -751,6 +752,11 @@ bool running(hipEvent_t end)
 // A batch that a graph holds a call of stays on its caller's streams, because replays are not seen here; so do batches in the
 // static workspace, whose next owner's declaration waits for the caller's streams, and contexts that time their stages.
 constexpr uint64_t kBesideBytes = 64ull << 20;
+// A launch per chunk drains and ramps up with another stream's kernels between them at 2 - 5 us more, so a plan goes beside a
+// bounded execute where its chain is worth that: MI355X, cycles of 4,096 transfers in 28 chunks 1157 -> 447 us, of 2,280 in 8 1505 -> 1273,
+// of 512 in 20 3255 -> 3121, of 128 in 3 276 -> 238, but of 65 in 53 680 -> 719, 254 in 84 1183 -> 1214, 512 in 76 1005 -> 1071 and
+// 728 in 67 1064 -> 1093.
+constexpr uint64_t kBesideChunks = 16;
 hipStream_t work_stream(const tent_ctx* ctx, const Batch& b, hipStream_t s, bool whole, bool reports)
 {
     if (reports || b.marks_lost || b.in_static || (ctx->cfg.flags & TENT_FLAG_PROFILE) || capturing(s)) return s;
@@ -1797,7 +1803,7 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     HIP_TRY(record_execute_done(*b, s, note));
     // the range copies read what a re-plan rewrites, and the DONE marks come last: a re-plan on another stream waits for it all
     if (b->done_recorded) b->replan_at = b->done_at;
-    note_execute(ctx, *b, s);
+    note_execute(ctx, *b, s, n_chunks > kBesideChunks + b->dev.n_desc / 16);
     return TENT_OK;
 }
 
