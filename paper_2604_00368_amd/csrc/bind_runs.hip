@@ -240,8 +240,8 @@ constexpr uint32_t kWalkLast = 24;         // records of the last block the chai
 constexpr uint32_t kBitsOfSlots = 28;      // of a word in found
 // A record whose guess does not hold costs a stretch of walk_same about what kMissWorth of its records save against walk_runs: where
 // more of them miss, kMissFew at least, the rest of the block goes through walk_runs.  MI355X, chain and emit: 448 records of
-// which a third miss 257 us without this and 180 with it (at two misses 170, at three 175), 1,792 of which 6 % miss 407 and 399 (403,
-// 400), 512 of which 6 % miss 133 and 139 (147, 143).
+// which a third miss 257 us without this and 171 with it (at two misses 158, at three 165), 1,792 of which 6 % miss 403 and 380 (372,
+// 376), 512 of which 6 % miss 133 either way.
 constexpr uint32_t kMissFew = 4, kMissWorth = 8;
 
 constexpr uint32_t kLeastStretch = 6;       // records of equal slice lengths that go by ranks
@@ -1537,7 +1537,7 @@ constexpr uint32_t kSmallExtents = 2048;         // per side; two per thread
 constexpr uint32_t kSmallDescs = 2048;           // two per thread
 constexpr uint32_t kSmallSlices = 2048;
 constexpr uint32_t kFrontExtents = 4096;         // per side; four per thread
-constexpr uint32_t kFrontSlices = 4096;
+constexpr uint32_t kFrontSlices = 3072;          // three per thread; two beside four extents
 constexpr uint64_t kSmallTiles = 16384;          // 20 per thread that the chain, its feeder and its drainer leave over
 
 // What the front part of a plan keeps in LDS: extent prefixes of both sides, first slice and runs before every transfer.
@@ -1649,7 +1649,9 @@ __device__ __forceinline__ void plan_front(const BatchDev& b, FrontTables<kItems
 // The front part alone, for batches whose tile tables or slices are too many for one workgroup: in place of three to five launches in
 // a row (extent prefixes, counts, slices).  MI355X: a recorded cycle of 2,427 extents a side and 615 slices 134 -> 129.5 us, a life of
 // 2,768 and 768 155 -> 149, cycles in turn of 3,347 and 261 65 -> 56; with eight extents a thread, cycles of 4,224 and 2,112 take
-// 144 us against 137.
+// 144 us against 137.  A slice costs one thread what it costs a thread of a whole launch, so beyond a few per thread the launches win again:
+// recorded cycles of 3,000 extents and 3,480 slices 89.8 us against 87.4, of 3,860 and 2,868 88.8 against 87.6; cycles on their own of
+// 2,048 and 2,608 191 against 199, of 1,792 and 3,584 175 against 180 and in turn 163.2 against 162.3.
 template <int kItems>
 __global__ void __launch_bounds__(kSmallThreads) plan_front_kernel(BatchDev b)
 {
@@ -1684,7 +1686,8 @@ bool plan_is_small(const BatchDev& b)
 
 bool plan_front_fits(const BatchDev& b)
 {
-    return b.n_src_ext <= kFrontExtents && b.n_dst_ext <= kFrontExtents && b.n_desc <= kSmallDescs && b.n_slices <= kFrontSlices;
+    const uint64_t most = b.n_src_ext > b.n_dst_ext ? b.n_src_ext : b.n_dst_ext;
+    return most <= kFrontExtents && b.n_desc <= kSmallDescs && b.n_slices <= (most <= kSmallExtents ? kFrontSlices : kSmallSlices);
 }
 
 hipError_t launch_plan_front(const BatchDev& b, hipStream_t s)

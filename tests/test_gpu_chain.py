@@ -111,10 +111,10 @@ def test_plan_in_one_workgroup_and_beyond(H, oracle, n, what):
         check_binding(H, oracle, transfers([8 * 1024 * n - 1024 * (n > 2)], 8 * 1024, rails))
 
 
-@pytest.mark.parametrize("n", [2049, 4095, 4096, 4097])
+@pytest.mark.parametrize("n", [2049, 3071, 3072, 3073, 4095, 4096, 4097])
 @pytest.mark.parametrize("what", ["extents", "slices", "transfers", "dispatch"])
 def test_front_part_in_one_workgroup_and_beyond(H, oracle, n, what):
-    # one workgroup writes the slice table of up to 4096 extents a side, 4096 slices and 2048 transfers
+    # one workgroup writes the slice table of up to 4096 extents a side, 2048 transfers and 2048 slices (3072 with up to 2048 extents)
     from paper_2604_00368_amd import binding as T
     g = np.random.Generator(np.random.PCG64([n, len(what)]))
     rails = W.make_rails([25000, 50000, 40000, 10000], queued=g.integers(0, 5000, size=4))
