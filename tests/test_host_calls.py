@@ -424,6 +424,39 @@ def beside_copies():
     T.tent_destroy(h.ctx)
 
 
+def two_streams():
+    h = Host(slice_bytes=1 << 20)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    other = T.tent_create(1 << 20, 1 << 53, 1 << 60)
+    for base in (1 << 44, 1 << 46):
+        T.tent_register_segment(other, base, 1 << 40)
+    one, two = T.tent_declare(h.ctx, *h.extents(3000, 65536)), T.tent_declare(other, *h.extents(3000, 65536))
+    h.hip.fake_busy(1)
+
+    def plan_streams(ctx, b, stream):
+        T.tent_reset(ctx, b, stream)
+        h.log()
+        T.tent_plan(ctx, b, rails, False, stream)
+        streams = {x[1] for x in h.log() if x[0] == LAUNCH}
+        T.tent_execute(ctx, b, stream)
+        return streams
+
+    for _ in range(3):                                   # on a stream each: nothing but its own copies is ahead of a plan
+        assert plan_streams(h.ctx, one, STREAM_A) == {STREAM_A}
+        assert plan_streams(other, two, STREAM_B) == {STREAM_B}
+    plan_streams(other, two, STREAM_A)                   # on one stream: beside the copies of the other context's batch
+    for _ in range(2):
+        assert STREAM_A not in plan_streams(h.ctx, one, STREAM_A)
+        assert STREAM_A not in plan_streams(other, two, STREAM_A)
+    T.tent_destroy(other)
+    T.tent_destroy(h.ctx)
+
+
+def test_copies_on_another_stream_are_none_to_run_beside(fake):
+    """A plan that waits for its own copies leaves the caller's stream only where other copies have been enqueued on it since."""
+    run(fake, "two_streams")
+
+
 def test_tables_are_worked_on_beside_earlier_copies(fake):
     """A plan and a reset move no byte: while copies that they need not wait for run on the caller's stream they run on the
     context's own, behind the batch's own copies, and the batch's next call on the caller's stream waits for them."""
