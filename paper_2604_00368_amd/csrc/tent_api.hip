@@ -342,6 +342,7 @@ void free_batch(tent_ctx* ctx, Batch& b)
     b.block_bytes = 0;
     b.alive = false;
     b.decl_pending = false;
+    if (ctx->copies_end == b.done_at) ctx->copies_end = nullptr;       // (it has ended, and the slot's next batch records the event anew)
     b.replan_at = nullptr;
     b.report_at = nullptr;
     b.done_recorded = false;

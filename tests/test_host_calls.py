@@ -457,6 +457,28 @@ def test_copies_on_another_stream_are_none_to_run_beside(fake):
     run(fake, "two_streams")
 
 
+def released_copies():
+    h = Host(slice_bytes=1 << 20)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    declare = lambda: T.tent_declare(h.ctx, *h.extents(3000, 65536))
+    old, other = declare(), declare()
+    T.tent_plan(h.ctx, old, rails, False, STREAM_A)
+    T.tent_execute(h.ctx, old, STREAM_A)
+    T.tent_release(h.ctx, old)
+    new = declare()                                      # in the slot of the one that has gone, with its events
+    T.tent_plan(h.ctx, new, rails, False, STREAM_B)
+    h.hip.fake_busy(1)                                   # what runs is on the other stream
+    h.log()
+    T.tent_plan(h.ctx, other, rails, False, STREAM_A)
+    assert {x[1] for x in h.log() if x[0] == LAUNCH} == {STREAM_A}
+    T.tent_destroy(h.ctx)
+
+
+def test_copies_of_a_released_batch_are_none_to_run_beside(fake):
+    """A release has waited for them; what the slot's next batch records its event behind are not the copies that it stood for."""
+    run(fake, "released_copies")
+
+
 def test_tables_are_worked_on_beside_earlier_copies(fake):
     """A plan and a reset move no byte: while copies that they need not wait for run on the caller's stream they run on the
     context's own, behind the batch's own copies, and the batch's next call on the caller's stream waits for them."""
