@@ -67,6 +67,7 @@ struct Batch {
     // execute, or a call that ran beside earlier copies (see work_stream).
     enum class Last { kNothing, kCaller, kExecute, kBeside } last = Last::kNothing;
     uint64_t execute_no = 0;                 // which of its stream's executes the last one was
+    uint64_t execute_bytes = 0;              // what it moved at most, as far as the host knows
     hipStream_t beside = nullptr;            // the context's stream for such calls
     bool may_replan = false;                 // slices may be left over by the next execute: the simulator or a dispatch ran since the plan
     // The declaration's device work (descriptor upload, address sort, overlap check) runs on the
@@ -757,8 +758,10 @@ bool running(hipEvent_t end)
 // Only while copies are known to run on `s` that the call does not have to wait for, because the change of streams costs two waits:
 // where executes on any stream counted as such, two contexts on a stream each, with 10 MB cycles, took 80 us for both instead of 60.
 // MI355X, cycles of three batches in turn: 4,096 transfers 2060 -> 1540 us, 24,576 11534 -> 9095, 256 ragged ones 262 -> 198, 74
-// slices (4 MB) 43 -> 37.  Beside the batch's own copies a re-plan has only those to hide behind: sixteen windows of 100 MB each 5808 ->
-// 4807 us, but nine of 2 MB 985 -> 1082, hence kBesideBytes.
+// slices (4 MB) 43 -> 37.  Beside the batch's own copies a re-plan has only those to hide behind, hence kBesideBytes: sixteen windows of
+// 100 MB each 5808 -> 4807 us, and of a batch of 1 GiB three of 96 MiB 2263 -> 2210 and three of 64 2314 -> 2319 (2352 -> 2324 where the
+// simulator's figures are read), but three of 32 2341 -> 2394, six of 2 2371 -> 2485, and of one of 70 MiB six of 2 440 -> 548.  Where
+// other batches' copies lie behind them as well it is worth it in any case: two such batches in turn 877 -> 731.
 // Not a call that reports figures: everything that was enqueued on `s` before it has ended when it returns.
 // A batch that a graph holds a call of stays on its caller's streams, because replays are not seen here; so do batches in the
 // static workspace, whose next owner's declaration waits for the caller's streams, and contexts that time their stages.
@@ -774,10 +777,11 @@ hipStream_t work_stream(const tent_ctx* ctx, const Batch& b, hipStream_t s, bool
     if (b.last == Batch::Last::kBeside) return b.beside;
     if (b.last == Batch::Last::kExecute) {
         if (b.exec_stream != s || !b.replan_at) return s;
+        // where nothing has been enqueued behind its copies, what has to wait for them runs beside nothing
+        const bool alone = b.execute_no == executes_on(ctx, s).load();
         if (whole || b.replan_at == b.done_at) {
-            // (where nothing has been enqueued behind its copies, what has to wait for them runs beside nothing)
-            if (b.execute_no == executes_on(ctx, s).load()) return s;
-        } else if (b.payload < kBesideBytes) {
+            if (alone) return s;
+        } else if (b.payload < kBesideBytes || (alone && b.execute_bytes < kBesideBytes)) {
             return s;
         }
         return running(b.done_at) ? b.beside : s;
@@ -1715,6 +1719,7 @@ int tent_execute(tent_ctx* ctx, tent_batch_t batch, void* stream)
     };
     b->has_done = true;
     b->bound_hint = 0;
+    b->execute_bytes = max_tiles < b->payload / b->dev.tile_bytes ? max_tiles * b->dev.tile_bytes : b->payload;
     const bool moved = copies() == hipSuccess;
     note_execute(ctx, *b, s);
     if (!moved) {

@@ -111,7 +111,7 @@ def test_batches_in_turn(T, kind, flags):
 
 def windows(T, kind, flags, wait):
     g = np.random.Generator(np.random.PCG64(4))
-    p = Pools(T, geometry(kind, 72 * MiB, g), 65536, flags, 6)
+    p = Pools(T, geometry(kind, 320 * MiB, g), 65536, flags, 6)
     pause = torch.cuda.synchronize if wait else (lambda: None)
     told = []
     try:
@@ -124,7 +124,8 @@ def windows(T, kind, flags, wait):
                 if st != 0:
                     continue
                 told.append(T.tent_sim_fail(p.ctx, b, (g.random(6) < 0.2).astype(np.uint8), e % 2 == 0, p.stream)); pause()
-                told.append(T.tent_sim_advance(p.ctx, b, rails["queued_bytes"] + np.uint64(3 * MiB), p.stream, e % 2 == 1)); pause()
+                budget = rails["queued_bytes"] + np.uint64((3 if e == 2 else 11) * MiB)      # 66 MiB a window: beside; 18: not
+                told.append(T.tent_sim_advance(p.ctx, b, budget, p.stream, e % 2 == 1)); pause()
                 T.tent_sim_latency(p.ctx, b, rails["bw_MBps"], p.stream); pause()
                 if e == 3:
                     told.append(T.tent_update_bandwidth(p.ctx, b, W.make_probe_params([50000] * 6), rails, p.stream)[1]); pause()

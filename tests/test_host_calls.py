@@ -549,24 +549,31 @@ def test_a_reset_launches_only_where_something_is_to_be_cleared(fake):
     run(fake, "resets")
 
 
-def windows_beside_copies(payload):
+def windows_beside_copies(payload, window, others, beside):
     h = Host(slice_bytes=1 << 20)
     T, rails = h.T, h.W.make_rails([50000, 25000])
-    n = payload // 65536
-    b = T.tent_declare(h.ctx, *h.extents(n, 65536))
+    b, other = (T.tent_declare(h.ctx, *h.extents(n // 65536, 65536)) for n in (payload, 4 * MiB))
     T.tent_plan(h.ctx, b, rails, False, STREAM_A)
-    T.tent_sim_advance(h.ctx, b, np.array([1 << 21, 1 << 21], dtype=np.uint64), STREAM_A, False)
+    budget = np.array([window // 2, window // 2], dtype=np.uint64)
+    if window < payload:
+        T.tent_sim_advance(h.ctx, b, budget, STREAM_A, False)
+    else:
+        T.tent_plan_dispatch(h.ctx, b, rails, h.W.make_dispatch_params(1 << 18), None, False, STREAM_A)
     h.log()
     T.tent_execute(h.ctx, b, STREAM_A)
     log = h.log()
     bookkeeping, end = [x[2] for x in log if x[0] == RECORD][:2]
+    if others:
+        T.tent_plan(h.ctx, other, rails, False, STREAM_A)
+        T.tent_execute(h.ctx, other, STREAM_A)
+        h.log()
     h.hip.fake_busy(1)
     for call in (lambda: T.tent_plan(h.ctx, b, rails, False, STREAM_A), lambda: T.tent_sim_fail(h.ctx, b, np.ones(2, dtype=np.uint8), False, STREAM_A),
                  lambda: T.tent_sim_latency(h.ctx, b, np.array([5, 5], dtype=np.uint32), STREAM_A)):
         call()
         log = h.log()
         own = [x[1] for x in log if x[0] == LAUNCH][0]
-        assert (own == STREAM_A) == (payload < 64 * MiB)
+        assert (own != STREAM_A) == beside
         assert not [x for x in log if x[0] == WAIT and x[2] == end]
         if own != STREAM_A and bookkeeping:
             first = [i for i, x in enumerate(log) if x[0] == LAUNCH][0]
@@ -574,7 +581,7 @@ def windows_beside_copies(payload):
             bookkeeping = None                           # (what follows is ordered behind the plan)
     # a call that reports figures has everything behind it that was enqueued on its stream, so that is where it runs
     h.hip.fake_answer_reports(1)
-    T.tent_sim_advance(h.ctx, b, np.array([1 << 21, 1 << 21], dtype=np.uint64), STREAM_A)
+    T.tent_sim_advance(h.ctx, b, budget, STREAM_A)
     h.hip.fake_answer_reports(0)
     log = h.log()
     assert {x[1] for x in log if x[0] == LAUNCH} == {STREAM_A}
@@ -587,10 +594,13 @@ def windows_beside_copies(payload):
     T.tent_destroy(h.ctx)
 
 
-@pytest.mark.parametrize("payload", [64 * MiB - 65536, 64 * MiB])
-def test_windows_beside_their_own_copies(fake, payload):
-    """A re-plan and the rail simulator behind an execute wait for its bookkeeping only, where its copies are long enough."""
-    run(fake, "windows_beside_copies", payload)
+@pytest.mark.parametrize("payload,window,others,beside", [
+    (64 * MiB, 64 * MiB, False, True), (64 * MiB - 65536, 64 * MiB - 65536, False, False), (1024 * MiB, 64 * MiB, False, True),
+    (1024 * MiB, 64 * MiB - 65536, False, False), (1024 * MiB, 2 * MiB, True, True), (64 * MiB - 65536, 2 * MiB, True, False)])
+def test_windows_beside_their_own_copies(fake, payload, window, others, beside):
+    """A re-plan and the rail simulator behind an execute wait for its bookkeeping only, where that execute's copies are long enough, or
+    those of others have been enqueued behind them."""
+    run(fake, "windows_beside_copies", payload, window, others, beside)
 
 
 def capture_behind_beside():
