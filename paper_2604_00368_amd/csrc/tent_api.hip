@@ -51,6 +51,8 @@ struct Batch {
     uint32_t generation = 0;
     uint64_t payload = 0;
     uint64_t max_req_slices = 0; // most slices any one transfer has
+    uint64_t records = 0;        // transfers that start with a slice of another length than the one before ends with
+    uint64_t chain_steps = 0;    // what the last plan's chain went through one by one: such transfers, or all of them (a dispatch)
     RailParams last_rails{};     // telemetry of the last plan (for the rail simulator)
     uint32_t last_lat_ns[TENT_MAX_RAILS] = {};
     // The last execute's bookkeeping (staging addresses, tile lists, DONE marks) ends on exec_stream; its
@@ -525,7 +527,7 @@ bool pointers_ok(uint32_t n_desc, const uint32_t* p)
 // copied to `se_out` / `de_out` (if not null) on the way.
 struct WalkResult {
     int rc = TENT_OK;
-    uint64_t total = 0, slices = 0, bits = 0, most = 0;
+    uint64_t total = 0, slices = 0, bits = 0, most = 0, records = 0;
     uint64_t dst_apart = 0;                     // address bits in which a destination extent differs from the first one
 };
 
@@ -570,6 +572,7 @@ void validate_range(const tent_ctx* ctx, uint32_t j0, uint32_t j1, const uint32_
     const uint64_t origin = de[0].seg < ctx->segments.size() ? (uint64_t)ctx->segments[de[0].seg].base + de[0].off : 0;
     WalkResult r;
     SideWalk src(ctx, origin), dst(ctx, origin);
+    uint64_t last = 0;                          // length of the slice before
     for (uint32_t j = j0; j < j1; ++j) {
         uint64_t ls = 0, ld = 0;
         if (!src(se, se_out, sp[j], sp[j + 1], &ls) || !dst(de, de_out, dp[j], dp[j + 1], &ld) || ls != ld) {
@@ -580,6 +583,8 @@ void validate_range(const tent_ctx* ctx, uint32_t j0, uint32_t j1, const uint32_
         const uint64_t cnt = (ls + S - 1) / S;
         r.slices += cnt;
         r.most = std::max(r.most, cnt);
+        r.records += last != std::min(ls, S);
+        last = ls - (cnt - 1) * S;
     }
     r.bits = src.bits | dst.bits;
     r.dst_apart = dst.apart;
@@ -639,6 +644,7 @@ int validate(const tent_ctx* ctx, uint32_t n_desc, const uint32_t* sp, const ten
         all->slices += part[k].slices;
         all->bits |= part[k].bits;
         all->most = std::max(all->most, part[k].most);
+        all->records += part[k].records;
         all->dst_apart |= part[k].dst_apart;
     }
     return TENT_OK;
@@ -766,11 +772,13 @@ bool running(hipEvent_t end)
 // A batch that a graph holds a call of stays on its caller's streams, because replays are not seen here; so do batches in the
 // static workspace, whose next owner's declaration waits for the caller's streams, and contexts that time their stages.
 constexpr uint64_t kBesideBytes = 64ull << 20;
-// A launch per chunk drains and ramps up with another stream's kernels between them at 2 - 5 us more, so a plan goes beside a
-// bounded execute where its chain is worth that: MI355X, cycles of 4,096 transfers in 28 chunks 1157 -> 447 us, of 2,280 in 8 1505 -> 1273,
-// of 512 in 20 3255 -> 3121, of 128 in 3 276 -> 238, but of 65 in 53 680 -> 719, 254 in 84 1183 -> 1214, 512 in 76 1005 -> 1071 and
-// 728 in 67 1064 -> 1093.
-constexpr uint64_t kBesideChunks = 16;
+// Launches in a row lose up to 0.4 us each while another stream's kernels run or wait beside them, so a plan goes beside a bounded
+// execute where its chain is worth that: kBesideChunks chunks, and one more for every kChunkSteps steps of the chain.  MI355X, cycles
+// of three batches in turn, us a batch: 4,096 transfers of which three in four end in a short slice, in 16 chunks of 16 MiB 720 -> 403,
+// in 126 2175 -> 1923, in 247 of 4 MiB 1765 -> 1591; 1,024 in 79 of 16 MiB 1215 -> 1165 and in 127 1846 -> 1817 (behind the line); 256 in
+// 25 405 -> 373, in 65 935 -> 931, in 81 1144 -> 1154; 64 in 16 217 -> 202, in 47 674 -> 677, in 124 1698 -> 1742.  4,096 of whole slices,
+// a single step, in 16 247 -> 225, in 32 485 -> 483, in 64 909 -> 923, in 128 1768 -> 1814.
+constexpr uint64_t kBesideChunks = 16, kChunkSteps = 8;
 hipStream_t work_stream(const tent_ctx* ctx, const Batch& b, hipStream_t s, bool whole, bool reports)
 {
     if (reports || b.marks_lost || b.in_static || (ctx->cfg.flags & TENT_FLAG_PROFILE) || capturing(s)) return s;
@@ -946,6 +954,7 @@ int declare_impl(tent_ctx* ctx, uint32_t n_desc, const uint32_t* src_ptr, const 
     b.beside = ctx->beside;
     b.payload = payload;
     b.max_req_slices = max_req_slices;
+    b.records = walk.records;
     BatchDev& d = b.dev;
     d.n_desc = n_desc;
     d.n_src_ext = ns;
@@ -1346,6 +1355,7 @@ int tent_plan(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state* rails, u
     if (rc != TENT_OK) return rc;
     b->planned = true;
     b->may_replan = false;                                    // every pending slice is BOUND now
+    b->chain_steps = b->records;
     b->bound_hint = b->dev.n_slices;
     b->tile_hint = ~0ull;
     b->last_rails = rp;
@@ -1456,6 +1466,7 @@ int tent_plan_dispatch(tent_ctx* ctx, tent_batch_t batch, const tent_rail_state*
     }
     b->planned = true;
     b->may_replan = true;                                     // deferred transfers stay pending
+    b->chain_steps = n_desc;
     b->bound_hint = b->dev.n_slices;
     b->tile_hint = ~0ull;
     b->last_rails = rp;
@@ -1819,7 +1830,7 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     HIP_TRY(record_execute_done(*b, s, note));
     // the range copies read what a re-plan rewrites, and the DONE marks come last: a re-plan on another stream waits for it all
     if (b->done_recorded) b->replan_at = b->done_at;
-    note_execute(ctx, *b, s, n_chunks > kBesideChunks + b->dev.n_desc / 16);
+    note_execute(ctx, *b, s, n_chunks > kBesideChunks + b->chain_steps / kChunkSteps);
     return TENT_OK;
 }
 

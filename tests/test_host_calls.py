@@ -485,27 +485,37 @@ def test_tables_are_worked_on_beside_earlier_copies(fake):
     run(fake, "beside_copies")
 
 
-def beside_chunks(n, chunks, beside):
+def beside_chunks(n, chunks, kind, beside):
     h = Host(slice_bytes=1 << 16, flags=8)
     T, rails = h.T, h.W.make_rails([50000, 25000])
-    ext = h.extents(n, chunks * 256 * MiB // n)
-    one, two = (T.tent_declare(h.ctx, *ext) for _ in range(2))
+    # whole slices, a short slice at the end of every transfer, or one at the end of every eighth
+    short = {"whole": np.zeros(n), "dispatch": np.zeros(n), "short": np.ones(n), "some": np.arange(n) % 8 == 7}[kind].astype(np.uint32)
+    ptr, src, _, dst = h.extents(n, chunks * 256 * MiB // n)
+    src["len"] -= 1024 * short
+    dst["len"] = src["len"]
+    one, two = (T.tent_declare(h.ctx, ptr, src, ptr, dst) for _ in range(2))
     h.hip.fake_busy(1)
     streams = []
     for b in (one, two, one):
         T.tent_reset(h.ctx, b, STREAM_A)
         h.log()
-        T.tent_plan(h.ctx, b, rails, False, STREAM_A)
+        if kind == "dispatch":
+            T.tent_plan_dispatch(h.ctx, b, rails, h.W.make_dispatch_params(1 << 18), None, False, STREAM_A)
+        else:
+            T.tent_plan(h.ctx, b, rails, False, STREAM_A)
         streams.append({x[1] for x in h.log() if x[0] == LAUNCH})
         T.tent_execute_bounded(h.ctx, b, 256 * MiB, STREAM_A)
     assert streams[0] == {STREAM_A} and all((s != {STREAM_A}) == beside for s in streams[1:]), streams
     T.tent_destroy(h.ctx)
 
 
-@pytest.mark.parametrize("n,chunks,beside", [(64, 20, True), (64, 21, False), (4096, 28, True), (256, 32, True), (256, 33, False)])
-def test_plans_stay_behind_copies_in_many_chunks(fake, n, chunks, beside):
-    """Every chunk is a launch, and launches in a row lose time with another stream's beside them: only a long chain is worth it."""
-    run(fake, "beside_chunks", n, chunks, beside)
+@pytest.mark.parametrize("n,chunks,kind,beside", [
+    (64, 24, "short", True), (64, 25, "short", False), (256, 48, "short", True), (256, 49, "short", False), (256, 20, "some", True),
+    (256, 21, "some", False), (4096, 16, "whole", True), (4096, 17, "whole", False), (64, 24, "dispatch", True), (64, 25, "dispatch", False)])
+def test_plans_stay_behind_copies_in_many_chunks(fake, n, chunks, kind, beside):
+    """Every chunk is a launch, and launches in a row lose time with another stream's beside them: only a long chain is worth it, one
+    that goes through many transfers one by one."""
+    run(fake, "beside_chunks", n, chunks, kind, beside)
 
 
 def resets():
