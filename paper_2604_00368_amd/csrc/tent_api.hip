@@ -14,10 +14,6 @@
 
 using namespace tent;
 
-// Runtimes that lack them (stand-ins without a device) are taken to be idle.
-extern "C" hipError_t hipEventQuery(hipEvent_t) __attribute__((weak));
-extern "C" hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) __attribute__((weak));
-
 // Static workspace of tent_declare_static: callers that must not allocate get their batch's tables
 // here.  One copy per GPU, held until the process ends.  In host code the array's name is only a
 // stand-in: its address on a GPU is looked up once, with that GPU current, and host code uses the
@@ -250,7 +246,7 @@ hipError_t await_report(Batch& b, const Report& told, hipStream_t s, StreamNote&
 struct CaptureAside {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     bool set = false;
-    CaptureAside() { set = &hipThreadExchangeStreamCaptureMode && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess; }
+    CaptureAside() { set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess; }
     ~CaptureAside() { if (set) (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
@@ -749,7 +745,7 @@ void note_execute(tent_ctx* ctx, Batch& b, hipStream_t s, bool apart = false)
 // Whether the work behind which `end` was recorded has not ended.
 bool running(hipEvent_t end)
 {
-    if (!end || !&hipEventQuery) return false;
+    if (!end) return false;
     const CaptureAside aside;
     const bool yes = hipEventQuery(end) == hipErrorNotReady;
     if (yes) (void)hipGetLastError();

@@ -37,6 +37,12 @@ def test_library_exports_every_declared_symbol(T):
     assert sorted(T.EXPORTS) == names                       # the binding covers the whole header
 
 
+def test_runtime_functions_are_all_required(T):
+    # a runtime without one of them is refused when the library is loaded, not found out by what does not happen
+    names = subprocess.run(["nm", "-D", "--undefined-only", T.LIB_PATH], capture_output=True, text=True, check=True).stdout.split("\n")
+    assert any(" U hip" in n for n in names) and not [n for n in names if " w hip" in n]
+
+
 def test_binding_has_the_same_names(T):
     for n in declared_functions():
         assert callable(getattr(T, n)), n
