@@ -42,7 +42,8 @@
  *     not wait for -- other batches', or those of the batch's last execute, under the same conditions as above -- still run on
  *     `stream`.  They come behind the batch's earlier calls, and its next call behind them, whatever stream it is given (on one
  *     that is being captured the host waits); only other work of the caller's on `stream` is not ordered behind them.  Batches that a
- *     graph holds a call of, and those of tent_declare_static, stay on the streams they are given.
+ *     graph holds a call of, those of tent_declare_static and of a context with TENT_FLAG_PROFILE, and calls on a stream with a priority
+ *     or a mask of compute units, stay on the streams they are given.
  *   - HIP graphs: tent_reset, tent_plan with info = NULL and tent_execute allocate nothing, copy
  *     nothing from or to the host and enqueue kernels only (no memset nodes), so a caller may
  *     record them on a capturing stream and replay the graph.  The host-side bookkeeping of a

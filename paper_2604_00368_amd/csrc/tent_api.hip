@@ -94,6 +94,14 @@ struct Timing {
 
 struct Block { void* ptr; uint64_t bytes; };
 
+// What a stream's work is given: its priority, and the compute units that it may run on, a bit each.
+struct StreamTerms {
+    static constexpr uint32_t kWords = 16;
+    int priority = 0;
+    uint32_t cu_mask[kWords] = {};
+    bool operator==(const StreamTerms& o) const { return priority == o.priority && std::memcmp(cu_mask, o.cu_mask, sizeof(cu_mask)) == 0; }
+};
+
 }  // namespace
 
 struct tent_ctx {
@@ -118,6 +126,8 @@ struct tent_ctx {
     bool stage_busy[2] = {false, false};
     uint32_t stage_turn = 0;
     hipStream_t beside = nullptr;           // calls that only work on a batch's tables, beside earlier copies (work_stream)
+    StreamTerms beside_terms;               // of that stream
+    uint32_t cu_words = 0;                  // words that hold a bit per compute unit of the device
     hipEvent_t copies_end = nullptr;        // the event that ends the last execute, and its stream
     hipStream_t copies_stream = nullptr;
     void* order_ws = nullptr;               // workspace of the address sort, grown when a declaration needs more
@@ -752,6 +762,13 @@ bool running(hipEvent_t end)
     return yes;
 }
 
+bool stream_terms(hipStream_t s, uint32_t cu_words, StreamTerms* out)
+{
+    if (hipStreamGetPriority(s, &out->priority) == hipSuccess && hipExtStreamGetCUMask(s, cu_words, out->cu_mask) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Where a call that only works on the batch's tables runs: a plan, a reset, the rail simulator and the probe read and write no byte
 // of a segment or the arena, so they need not wait for copies that were enqueued on the caller's stream before -- those of other batches,
 // and of the batch's own last execute as far as its bookkeeping.  Beside such copies they run on the context's own stream,
@@ -766,7 +783,8 @@ bool running(hipEvent_t end)
 // other batches' copies lie behind them as well it is worth it in any case: two such batches in turn 877 -> 731.
 // Not a call that reports figures: everything that was enqueued on `s` before it has ended when it returns.
 // A batch that a graph holds a call of stays on its caller's streams, because replays are not seen here; so do batches in the
-// static workspace, whose next owner's declaration waits for the caller's streams, and contexts that time their stages.
+// static workspace, whose next owner's declaration waits for the caller's streams, and contexts that time their stages.  So do calls on a
+// stream that its caller gave a priority or a share of the compute units (asking for both takes 0.4 us): they hold for what is enqueued there.
 constexpr uint64_t kBesideBytes = 64ull << 20;
 // Launches in a row lose up to 0.4 us each while another stream's kernels run or wait beside them, so a plan goes beside a bounded
 // execute where its chain is worth that: kBesideChunks chunks, and one more for every kChunkSteps steps of the chain.  MI355X, cycles
@@ -775,25 +793,31 @@ constexpr uint64_t kBesideBytes = 64ull << 20;
 // 25 405 -> 373, in 65 935 -> 931, in 81 1144 -> 1154; 64 in 16 217 -> 202, in 47 674 -> 677, in 124 1698 -> 1742.  4,096 of whole slices,
 // a single step, in 16 247 -> 225, in 32 485 -> 483, in 64 909 -> 923, in 128 1768 -> 1814.
 constexpr uint64_t kBesideChunks = 16, kChunkSteps = 8;
-hipStream_t work_stream(const tent_ctx* ctx, const Batch& b, hipStream_t s, bool whole, bool reports)
+bool worth_beside(const tent_ctx* ctx, const Batch& b, hipStream_t s, bool whole)
 {
-    if (reports || b.marks_lost || b.in_static || (ctx->cfg.flags & TENT_FLAG_PROFILE) || capturing(s)) return s;
-    if (b.last == Batch::Last::kBeside) return b.beside;
+    if (b.last == Batch::Last::kBeside) return true;
     if (b.last == Batch::Last::kExecute) {
-        if (b.exec_stream != s || !b.replan_at) return s;
+        if (b.exec_stream != s || !b.replan_at) return false;
         // where nothing has been enqueued behind its copies, what has to wait for them runs beside nothing
         const bool alone = b.execute_no == executes_on(ctx, s).load();
         if (whole || b.replan_at == b.done_at) {
-            if (alone) return s;
+            if (alone) return false;
         } else if (b.payload < kBesideBytes || (alone && b.execute_bytes < kBesideBytes)) {
-            return s;
+            return false;
         }
-        return running(b.done_at) ? b.beside : s;
+        return running(b.done_at);
     }
-    if (ctx->copies_stream != s || !running(ctx->copies_end)) return s;
+    if (ctx->copies_stream != s || !running(ctx->copies_end)) return false;
     for (const StreamMark& m : b.marks)                  // (calls on the caller's streams that have not ended)
-        if (m.used && running(m.event)) return s;
-    return b.beside;
+        if (m.used && running(m.event)) return false;
+    return true;
+}
+
+hipStream_t work_stream(const tent_ctx* ctx, const Batch& b, hipStream_t s, bool whole, bool reports)
+{
+    if (reports || b.marks_lost || b.in_static || (ctx->cfg.flags & TENT_FLAG_PROFILE) || capturing(s) || !worth_beside(ctx, b, s, whole)) return s;
+    StreamTerms terms;
+    return stream_terms(s, ctx->cu_words, &terms) && terms == ctx->beside_terms ? b.beside : s;
 }
 
 // Prefixes, slice and run table of a first plan, and with `tables` the tile tables (where no chain's launch builds them).  A caller that
@@ -1190,7 +1214,13 @@ int tent_create(tent_ctx** out, const tent_config* cfg)
          hipStreamCreateWithFlags(&ctx->decl_stream, hipStreamNonBlocking) == hipSuccess &&
          hipStreamCreateWithFlags(&ctx->beside, hipStreamNonBlocking) == hipSuccess &&
          init_slot(ctx->static_batch);
-    if (ok) ctx->host_plan->call = 0;
+    if (ok) {
+        int n_cu = 0;
+        ok = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device) == hipSuccess;
+        ctx->cu_words = std::min<uint32_t>((n_cu + 31) / 32, StreamTerms::kWords);
+        (void)stream_terms(ctx->beside, ctx->cu_words, &ctx->beside_terms);
+        ctx->host_plan->call = 0;
+    }
     for (int k = 0; k < 2 && ok; ++k) {
         ok = hipHostMalloc((void**)&ctx->stage[k], kStageInitial, hipHostMallocDefault) == hipSuccess &&
              hipEventCreateWithFlags(&ctx->stage_event[k], hipEventDisableTiming) == hipSuccess;

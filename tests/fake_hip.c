@@ -11,7 +11,9 @@ enum { MOST = 1 << 16, KERNELS = 512 };
 static struct { int kind; void *stream, *what; } log_[MOST];
 static int n_log, n_kernels, fail_host_waits;
 static struct { const void *fn; const char *name; } kernel[KERNELS];
-static void *capturing_stream;
+static void *capturing_stream, *termed_stream;
+static int termed_priority;
+static uint32_t termed_mask;
 static int answer, n_host, busy;
 static struct { char *at; size_t n; } host[64];
 
@@ -36,6 +38,8 @@ const char *fake_kernel_name(const void *fn)
 }
 void fake_fail_host_waits(int n) { fail_host_waits = n; }
 void fake_capture(void *stream) { capturing_stream = stream; }
+/* the one stream that has a priority or whose first word of compute units is not full */
+void fake_terms(void *stream, int priority, unsigned mask) { termed_stream = stream; termed_priority = priority; termed_mask = mask; }
 /* whether what has been enqueued has not ended yet */
 void fake_busy(int on) { busy = on; }
 /* a launch that reports answers its report, a block of host memory and a number: the number goes to the block's last word (1), with
@@ -114,6 +118,25 @@ hipError_t hipEventSynchronize(hipEvent_t e) { return host_wait(NULL, e); }
 hipError_t hipStreamSynchronize(hipStream_t s) { return host_wait(s, NULL); }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned flags) { (void)flags; *s = (hipStream_t)malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
+hipError_t hipStreamGetPriority(hipStream_t s, int *priority)
+{
+    *priority = s && s == termed_stream ? termed_priority : 0;
+    return hipSuccess;
+}
+hipError_t hipExtStreamGetCUMask(hipStream_t s, uint32_t words, uint32_t *mask)
+{
+    if (words * 32 < 256) return hipErrorInvalidValue;
+    for (uint32_t k = 0; k < words; ++k) mask[k] = 0xFFFFFFFFu;
+    if (s && s == termed_stream) mask[0] = termed_mask;
+    return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int *to, hipDeviceAttribute_t what, int d)
+{
+    (void)d;
+    if (what != hipDeviceAttributeMultiprocessorCount) return hipErrorInvalidValue;
+    *to = 256;
+    return hipSuccess;
+}
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st)
 {
     *st = s && s == capturing_stream ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;

@@ -47,6 +47,7 @@ class Host:
         self.hip.fake_kernel_name.restype = C.c_char_p
         self.hip.fake_kernel_name.argtypes = [C.c_void_p]
         self.hip.fake_capture.argtypes = [C.c_void_p]
+        self.hip.fake_terms.argtypes = [C.c_void_p, C.c_int, C.c_uint]
         self.ctx = T.tent_create(slice_bytes, 1 << 52, 1 << 60, flags, max_rails)
         T.tent_register_segment(self.ctx, 1 << 44, pool)
         T.tent_register_segment(self.ctx, 1 << 46, pool)
@@ -477,6 +478,37 @@ def released_copies():
 def test_copies_of_a_released_batch_are_none_to_run_beside(fake):
     """A release has waited for them; what the slot's next batch records its event behind are not the copies that it stood for."""
     run(fake, "released_copies")
+
+
+def streams_with_terms(priority, mask):
+    h = Host(slice_bytes=1 << 20)
+    T, rails = h.T, h.W.make_rails([50000, 25000])
+    batches = [T.tent_declare(h.ctx, *h.extents(3000, 65536)) for _ in range(3)]
+
+    def plan(b, stream):
+        h.log()
+        T.tent_plan(h.ctx, b, rails, False, stream)
+        log = h.log()
+        return {x[1] for x in log if x[0] == LAUNCH}, log
+
+    plan(batches[0], STREAM_A)
+    T.tent_execute(h.ctx, batches[0], STREAM_A)
+    h.hip.fake_busy(1)
+    own, log = plan(batches[1], STREAM_A)
+    assert STREAM_A not in own
+    end = [x[2] for x in log if x[0] == RECORD][-1]
+    h.hip.fake_terms(STREAM_A, priority, mask)
+    assert plan(batches[2], STREAM_A)[0] == {STREAM_A}
+    streams, log = plan(batches[1], STREAM_A)            # behind what ran beside the copies
+    assert streams == {STREAM_A}
+    assert log.index((WAIT, STREAM_A, end)) < [x[0] for x in log].index(LAUNCH)
+    T.tent_destroy(h.ctx)
+
+
+@pytest.mark.parametrize("priority,mask", [(-1, 0xFFFFFFFF), (1, 0xFFFFFFFF), (0, 0x0000FFFF)])
+def test_calls_stay_on_a_stream_with_a_priority_or_a_share_of_the_device(fake, priority, mask):
+    """The caller gave these terms to what is enqueued there; the context's own stream has the default ones."""
+    run(fake, "streams_with_terms", priority, mask)
 
 
 def test_tables_are_worked_on_beside_earlier_copies(fake):
