@@ -218,3 +218,15 @@ def test_a_slice_outside_the_window_among_single_slices(H, oracle, at, n):
     lens = g.integers(1, 200000, size=n)
     lens[at % n::64] = 4000000 + at
     check_binding(H, oracle, transfers(lens, 1 << 22, rails))
+
+
+@pytest.mark.parametrize("row", [1, 2, 3, 5, 64])
+@pytest.mark.parametrize("between", [0, 1, 4, 5])
+def test_slices_outside_the_window_in_a_row(H, oracle, row, between):
+    # the first of a row of single slices has a check of its own, the next four share one; each row here begins with slices outside
+    g = np.random.Generator(np.random.PCG64([row, between]))
+    rails = W.make_rails([25000, 12500, 20000], queued=g.integers(0, 1 << 16, size=3))
+    lens = []
+    while len(lens) < 200:
+        lens += g.integers(3500000, 4100000, size=row).tolist() + g.integers(1, 200000, size=between).tolist()
+    check_binding(H, oracle, transfers(lens, 1 << 22, rails))
