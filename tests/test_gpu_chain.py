@@ -209,6 +209,23 @@ def test_slices_behind_runs_of_dropped_slots(H, oracle, R, singles, seed):
     check_binding(H, oracle, transfers(lens, S, W.make_rails(bw, queued=g.integers(0, 1 << 20, size=R))))
 
 
+@pytest.mark.parametrize("row", [1, 3, 5, 6, 7])
+@pytest.mark.parametrize("longest", [1.0, 2.0, 9.0])
+@pytest.mark.parametrize("runs", ["first", "alike"])
+def test_rows_of_single_slices_behind_short_runs(H, oracle, row, longest, runs):
+    # rows of up to six go as runs of none where runs of one slice length stand around them; not behind the first run of a length, and
+    # not if they are longer than two of its slices
+    g = np.random.Generator(np.random.PCG64([row, int(longest), len(runs)]))
+    S, lens = 400000, []
+    for _ in range(40):
+        if runs == "first":
+            lens += (S * g.integers(1, 4, size=2)).tolist()
+        l = 7000 if runs == "alike" else int(g.integers(5000, 9001))
+        lens += [l] * int(g.integers(2, 5)) + g.integers(1, int(longest * l) + 1, size=row).tolist()
+    rails = W.make_rails(g.integers(10000, 90000, size=8), queued=g.integers(0, 1 << 18, size=8))
+    check_binding(H, oracle, transfers(lens, S, rails))
+
+
 @pytest.mark.parametrize("at", [1, 2, 3, 4, 5, 60, 61, 62, 63, 64])
 @pytest.mark.parametrize("n", [6, 65, 131])
 def test_a_slice_outside_the_window_among_single_slices(H, oracle, at, n):
