@@ -385,7 +385,8 @@ __device__ __forceinline__ void drain_requests(const BatchDev& b, const RequestR
     }
 }
 
-// By a whole workgroup of at least 192 threads, with barriers.
+// By a whole workgroup of at least kChainThreads16, with barriers: the first wavefront walks, the second feeds and drains.
+constexpr uint32_t kChainThreads16 = 128;
 __device__ __forceinline__ void dispatch_chain16(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, const PriorityBits& bits,
                                                  RequestRing& ring)
 {
@@ -548,7 +549,7 @@ hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const Dispat
         if (first_plan)
             hipLaunchKernelGGL(dispatch_chain_tables_kernel<kW>, dim3(1 + tile_table_blocks(b)), dim3(256), 0, s, b, rp, dp, bits);
         else
-            hipLaunchKernelGGL(dispatch_chain_kernel<kW>, dim3(1), dim3(kW == 0 ? 128 : 64), 0, s, b, rp, dp, bits);
+            hipLaunchKernelGGL(dispatch_chain_kernel<kW>, dim3(1), dim3(kW == 0 ? kChainThreads16 : 64), 0, s, b, rp, dp, bits);
     };
     if (dp.near)               launch_chain(std::integral_constant<int, 0>{});
     else if (rp.n_rails <= 16) launch_chain(std::integral_constant<int, 16>{});

@@ -255,11 +255,12 @@ hipError_t launch_bounded_copy(const BatchDev& b, bool gather, uint32_t chunk, u
                                uint64_t slot_bytes, uint32_t slots, uint8_t* arena, hipStream_t s);
 hipError_t launch_mark_done_bounded(const BatchDev& b, hipStream_t s);
 // Whether the chain of up to 16 rails can compute a dispatch whose costs are below `worst` ps and whose transfers have at most
-// `most` slices: a slot's key (slots x cost x 16 + rail) is a whole number below 2^53, a cost in units of 2^-16 ps stays below
-// 2^63, and 32-bit reciprocals give a rail's slots to within one.
+// `most` slices.  Below 2^20 slices 32-bit reciprocals and a 32-bit level give a rail's slots to within one (their error is below 2^-22
+// of it).  The product keeps a slot's key (slots x cost x 16 + rail, for up to 64 slots more than there are) a whole number below 2^53,
+// and, as there are 65 slots at least, a cost below 2^43 ps, which in units of 2^-16 ps is below 2^63.
 inline bool dispatch_is_near(unsigned __int128 worst, uint64_t most)
 {
-    return most < (1ull << 20) && worst < (1ull << 46) && worst * (most + 64) < (1ull << 49);
+    return most < (1ull << 20) && worst * (most + 64) < (1ull << 49);
 }
 hipError_t launch_dispatch(const BatchDev& b, const RailParams& rp, const DispatchParams& dp, const PriorityBits& bits, bool first_plan,
                            Report told, hipStream_t s);

@@ -130,7 +130,7 @@ def test_small_configs_dispatch_bit_exact(H, oracle, name):
 @pytest.mark.parametrize("kind", ["mixed", "alike", "one fast", "far"])
 def test_request_chain_at_its_block_edges(H, oracle, D, kind):
     # blocks of 64 requests; rails that move in step (exact ties), one that takes several slots while the others take one, and costs
-    # of 2^46 ps and more, which go through the chain of any width
+    # too large for the chain of up to 16 rails, which go through that of any width
     rng = np.random.Generator(np.random.PCG64(D))
     S = 64 * KiB
     if kind == "mixed":
@@ -145,6 +145,55 @@ def test_request_chain_at_its_block_edges(H, oracle, D, kind):
     w = contiguous_requests(lens, S, rails, D)
     dispatch_windows_and_compare(H, oracle, w, theta=4 * S, gamma_q8=64, prio=W.make_priorities(D, D), windows=[0, 1, 2],
                                  bytes_too=False, rr_start=(1 << 40) + 5)
+
+
+def largest_cost(rails, payload):
+    """What a rail's cost can reach in a plan of `payload` bytes, ps."""
+    c1 = [10**6 * int(r["beta1_q8"]) * int(r["penalty_q8"]) // int(r["bw_MBps"]) for r in rails]
+    return max((int(r["lat_ns"]) * 1000 * int(r["penalty_q8"]) >> 8) + ((int(r["queued_bytes"]) + payload) * c >> 16) for r, c in zip(rails, c1))
+
+
+def dispatch_and_compare(H, oracle, w, dp):
+    from paper_2604_00368_amd import binding as T
+    s = oracle.split(w.src_ptr, w.src_ext, w.slice_bytes)
+    r = oracle.dispatch(s, w.rails, dp)
+    with H.Engine(w) as eng:
+        eng.declare()
+        st, info = T.tent_plan_dispatch(eng.ctx, eng.batch, w.rails, dp, None, True, eng.stream)
+        assert st == r.binding.status == 0
+        tab = eng.table()
+        assert np.array_equal(tab["rail"], r.binding.rail) and np.array_equal(tab["stage_off"], r.binding.stage_off)
+        assert list(info.plan.rail_slices)[:w.rails.shape[0]] == r.binding.n_slices.tolist()
+        assert info.rr_next == r.rr_end
+
+
+@pytest.mark.parametrize("most", [(1 << 20) - 1, 1 << 20])
+@pytest.mark.parametrize("kind", ["one", "alike", "wide"])
+def test_requests_of_as_many_slices_as_the_chain_takes(H, oracle, most, kind):
+    # the chain of up to 16 rails guesses a rail's slots in 32-bit floats, right to within one below 2^20 slices; rails whose costs
+    # are the same, and those of 370 ps and of none at all
+    rails = {"one": lambda: W.make_rails([2700], lat_ns=0), "alike": lambda: W.make_rails([65536] * 16, lat_ns=300),
+             "wide": lambda: W.make_rails(np.geomspace(2700, 4e6, 16).astype(np.int64), lat_ns=0)}[kind]()
+    w = contiguous_requests([5, most, 1000, 3, most // 3], 1, rails, 1)
+    assert largest_cost(rails, w.payload) * (most + 64) < 1 << 49
+    dispatch_and_compare(H, oracle, w, W.make_dispatch_params(4, gamma_q8=64, rr_start=(1 << 64) - 1))
+
+
+@pytest.mark.parametrize("over", [False, True])
+@pytest.mark.parametrize("kind", ["one", "alike", "apart"])
+def test_costs_as_large_as_the_chain_takes(H, oracle, over, kind):
+    # ... and holds a slot's key, slots x cost x 16 + rail, in a double: up to 2^53, which the largest costs here reach but for 2 %
+    bw = {"one": [50000], "alike": [50000] * 16, "apart": [50000] * 8 + [400000]}[kind]
+    lens = [5, 65536, 1000, 3, 20000]
+    lat = 0
+    for bit in reversed(range(32)):
+        if largest_cost(W.make_rails(bw, lat_ns=lat | 1 << bit), sum(lens)) * (65536 + 64) < 1 << 49:
+            lat |= 1 << bit
+    rails = W.make_rails(bw, lat_ns=lat + over)
+    if kind == "apart":
+        rails["lat_ns"][:4] //= 1000
+    assert (largest_cost(rails, sum(lens)) * (65536 + 64) < 1 << 49) != over
+    dispatch_and_compare(H, oracle, contiguous_requests(lens, 1, rails, 2), W.make_dispatch_params(4, gamma_q8=64, rr_start=7))
 
 
 @pytest.mark.parametrize("R", [4, 20])

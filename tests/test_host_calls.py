@@ -11,7 +11,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 MiB = 1 << 20
-LAUNCH, RECORD, WAIT, HOST_WAIT = 1, 2, 3, 4
+LAUNCH, RECORD, WAIT, HOST_WAIT, COPY = 1, 2, 3, 4, 5
 STREAM_A, STREAM_B = 0xA0, 0xB0                      # never dereferenced
 
 
@@ -511,6 +511,53 @@ def test_calls_stay_on_a_stream_with_a_priority_or_a_share_of_the_device(fake, p
     run(fake, "streams_with_terms", priority, mask)
 
 
+def dispatches_beside(n):
+    h = Host(slice_bytes=1 << 20)
+    T, W = h.T, h.W
+    rails, dp = W.make_rails([50000, 25000]), W.make_dispatch_params(1 << 18)
+    one, two = (T.tent_declare(h.ctx, *h.extents(n, 1 << 16)) for _ in range(2))
+    prio = np.arange(n, dtype=np.uint8) % 3
+    copied = n > 2048                                    # priorities that do not fit the kernel's arguments
+
+    def dispatch(b, info=False):
+        h.log()
+        h.hip.fake_answer_reports(int(info))
+        T.tent_plan_dispatch(h.ctx, b, rails, dp, prio, info, STREAM_A)
+        h.hip.fake_answer_reports(0)
+        log = h.log()
+        streams = {x[1] for x in log if x[0] in (LAUNCH, COPY)}
+        assert len(streams) == 1 and [x[0] for x in log].count(COPY) == int(copied)
+        first = [i for i, x in enumerate(log) if x[0] in (LAUNCH, COPY)][0]
+        return streams.pop(), {x[2] for x in log[:first] if x[0] == WAIT}
+
+    def execute(b):
+        h.log()
+        T.tent_execute(h.ctx, b, STREAM_A)
+        return [x[2] for x in h.log() if x[0] == RECORD]  # the bookkeeping's event, the copies' end
+
+    dispatch(one)
+    _, end = execute(one)
+    h.hip.fake_busy(1)
+    own, waits = dispatch(two)                           # a first plan beside another batch's copies
+    assert own != STREAM_A and not waits
+    execute(two)
+    T.tent_reset(h.ctx, one, STREAM_A)
+    stream, waits = dispatch(one)                        # rewrites what its own copies read
+    assert stream == own and waits == {end}
+    bookkeeping, end = execute(one)
+    stream, waits = dispatch(one)                        # what was deferred, behind the bookkeeping
+    assert (stream, waits) == ((own, {bookkeeping}) if n * 65536 >= 64 * MiB else (STREAM_A, set()))
+    execute(one)
+    assert dispatch(one, True)[0] == STREAM_A
+    T.tent_destroy(h.ctx)
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 2048, 2049])
+def test_dispatches_beside_copies(fake, n):
+    """As plans: a first one waits for the batch's own copies, a repeated one for their bookkeeping; one that reports stays."""
+    run(fake, "dispatches_beside", n)
+
+
 def test_tables_are_worked_on_beside_earlier_copies(fake):
     """A plan and a reset move no byte: while copies that they need not wait for run on the caller's stream they run on the
     context's own, behind the batch's own copies, and the batch's next call on the caller's stream waits for them."""
@@ -676,6 +723,34 @@ def capture_behind_beside():
 def test_a_capture_behind_work_beside_copies(fake):
     """A graph can wait for nothing outside it, and its caller cannot order it behind the context's own stream: the host waits."""
     run(fake, "capture_behind_beside")
+
+
+def dispatch_chains():
+    h = Host(slice_bytes=1)
+    T, W = h.T, h.W
+
+    def chain(slices, rails):
+        ptr, src, _, dst = h.extents(2, slices)
+        b = T.tent_declare(h.ctx, ptr, src, ptr, dst)
+        h.log()
+        T.tent_plan_dispatch(h.ctx, b, rails, W.make_dispatch_params(1), None, False, STREAM_A)
+        names = [x[2] for x in h.log() if x[0] == LAUNCH and "dispatch_chain" in x[2]]
+        T.tent_release(h.ctx, b)
+        return int(names[0].split("ILi")[1].split("E")[0])
+
+    near = lambda R: W.make_rails([4000000] * R, lat_ns=0)
+    assert chain(1000, near(16)) == 0 and chain(1000, near(17)) == 32
+    assert chain((1 << 20) - 1, near(16)) == 0 and chain(1 << 20, near(16)) == 16
+    # 4,032 slices: costs below 2^37 ps, of which the bytes make up 2,016
+    at = ((1 << 37) - 1 - 2016) // 1000
+    rails = lambda lat: W.make_rails([4000000] * 3, lat_ns=lat)
+    assert chain(4032, rails(at)) == 0 and chain(4032, rails(at + 1)) == 16
+    T.tent_destroy(h.ctx)
+
+
+def test_which_chain_a_dispatch_takes(fake):
+    """Up to 16 rails, below 2^20 slices a transfer, and below 2^49 for the largest cost times its slots."""
+    run(fake, "dispatch_chains")
 
 
 # The largest batches tent_declare_static accepts, in units of each kind: flags 0, no overlap check, bounded staging, both;
