@@ -21,14 +21,14 @@ def T():
     return binding
 
 
-def geometry(kind, total, g):
-    """CSR pointers and extents of both sides: transfers of a few pieces, source pieces in order, destination pieces shuffled."""
+def geometry(kind, total, g, per=7):
+    """CSR pointers and extents of both sides: transfers of `per` pieces, source pieces in order, destination pieces shuffled."""
     piece = 65536 if kind == "tiled" else 65000
     n = total // piece
     sizes = np.full(n, piece, dtype=np.int64)
     if kind == "ragged":
         sizes -= g.integers(0, 3000, size=n)
-    ptr = np.unique(np.concatenate([np.arange(0, n, 7), [n]])).astype(np.uint32)
+    ptr = np.unique(np.concatenate([np.arange(0, n, per), [n]])).astype(np.uint32)
     src = np.zeros(n, dtype=W.EXTENT_DTYPE)
     src["len"], src["off"] = sizes, np.concatenate([[0], np.cumsum(sizes)[:-1]])
     order = g.permutation(n)
@@ -79,8 +79,8 @@ def in_turn(T, kind, flags, wait):
             p.src.add_(turn + 1)                              # the program's own work on the stream, behind the copies of before
             T.tent_reset(p.ctx, b, p.stream); pause()
             if turn % 3 == 2:
-                st, info = T.tent_plan_dispatch(p.ctx, b, rails, W.make_dispatch_params(1 << 18, window=turn), None, True, p.stream)
-                told.append([info.n_mice, info.n_elephant, info.n_deferred] + list(info.plan.rail_bytes))
+                st, info = T.tent_plan_dispatch(p.ctx, b, rails, W.make_dispatch_params(1 << 18, window=turn), None, turn % 2 == 0, p.stream)
+                told.append([info.n_mice, info.n_elephant, info.n_deferred] + list(info.plan.rail_bytes) if info else [])
             else:
                 st, info = T.tent_plan(p.ctx, b, rails, turn % 3 == 1, p.stream)
                 told.append(list(info.rail_bytes) if info else [])
@@ -145,6 +145,48 @@ def test_windows_beside_their_own_copies(T, kind, flags):
         assert np.array_equal(a, b)
     for a, b in zip(with_waits[0], without[0]):
         assert torch.equal(a, b)
+
+
+def dispatches(T, flags, wait):
+    g = np.random.Generator(np.random.PCG64(6))
+    # 2,560 transfers, whose priorities travel by a copy, and 366, whose priorities travel with the kernel's arguments
+    pools = [Pools(T, geometry("tiled", 160 * MiB, g, per), 65536, flags, 6) for per in (1, 7)]
+    pause = torch.cuda.synchronize if wait else (lambda: None)
+    kept, told = [], []
+    try:
+        batches = [p.declare() for p in pools]
+        for turn in range(3):
+            for p, b in zip(pools, batches):
+                p.src.add_(1)
+                T.tent_reset(p.ctx, b, p.stream); pause()
+            for window in range(3):                               # what no slot takes is deferred, and planned again behind the copies
+                for p, b in zip(pools, batches) if turn != 1 else [(pools[0], batches[0])]:
+                    n = p.lists[0].shape[0] - 1
+                    rails = W.make_rails(g.integers(10000, 90000, size=6), queued=g.integers(0, 1 << 18, size=6), health=[0, 0, 2, 2, 2, 2])
+                    dp = W.make_dispatch_params(1 << 17, window=window + turn)
+                    st, info = T.tent_plan_dispatch(p.ctx, b, rails, dp, g.integers(0, 3, size=n).astype(np.uint8), (turn, window) == (2, 1), p.stream); pause()
+                    assert st == 0
+                    if info:
+                        told.append([info.n_mice, info.n_elephant, info.n_deferred] + list(info.plan.rail_bytes))
+                    slow_execute(T, p, b); pause()
+            told += [T.tent_poll(p.ctx, b, p.stream) for p, b in zip(pools, batches)] if turn else []
+            for p in pools:
+                kept += p.keep()
+        told += [T.tent_get_plan(p.ctx, b).tobytes() for p, b in zip(pools, batches)]
+        told += [T.tent_get_modes(p.ctx, b, p.lists[0].shape[0] - 1).tobytes() for p, b in zip(pools, batches)]
+        return kept, told
+    finally:
+        torch.cuda.synchronize()
+        for p in pools:
+            T.tent_destroy(p.ctx)
+
+
+@pytest.mark.parametrize("flags", [0, 1])
+def test_dispatches_beside_copies(T, flags):
+    with_waits, without = dispatches(T, flags, True), dispatches(T, flags, False)
+    assert with_waits[1] == without[1]
+    for k, (a, b) in enumerate(zip(with_waits[0], without[0])):
+        assert torch.equal(a, b), k
 
 
 def test_an_execute_recorded_behind_a_plan_beside_copies(T):
