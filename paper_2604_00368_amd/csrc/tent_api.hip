@@ -1774,8 +1774,8 @@ int tent_execute_bounded(tent_ctx* ctx, tent_batch_t batch, uint64_t chunk_bytes
     if (!b) return TENT_ERR_INVALID;
     if (!b->planned || b->broken || !(ctx->cfg.flags & TENT_FLAG_BOUNDED_STAGING)) return TENT_ERR_STATE;
     const BatchDev& d = b->dev;
-    // chunks are cut on 1 MiB boundaries so that the 256 consecutive tiles (or four consecutive 1 KiB
-    // ranges) of one workgroup never straddle two chunks
+    // chunks are cut on 1 MiB boundaries, so that the 256 consecutive tiles of a workgroup of the tables' kernels lie in one chunk and
+    // a chunk begins with a whole tile or range (a workgroup of bounded_ranges_kernel may reach into several chunks)
     if (chunk_bytes == 0 || (chunk_bytes & ((1ull << 20) - 1)) != 0 || slots < 1 || slots > 2) return TENT_ERR_INVALID;
     const uint64_t slot_bytes = chunk_bytes + 256ull * b->last_rails.n_rails;
     if (slot_bytes > ctx->cfg.staging_bytes / slots) return TENT_ERR_RANGE;
