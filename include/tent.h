@@ -481,7 +481,9 @@ int tent_get_plan(tent_ctx *ctx, tent_batch_t batch, tent_slice *host_out, uint6
  * Where one launch does the work of several stages its time stands under one of them: the first
  * plan of a small batch (at most 2048 extents a side, 2048 slices, and 16384 tiles if every slice
  * were a whole one; not bound serially) is a single launch under TENT_T_BIND and leaves EXTENT_SCAN, SLICE_SCAN and EXPAND at
- * 0; one-pass copies stand under TENT_T_GATHER and leave SCATTER at 0.
+ * 0; one-pass copies stand under TENT_T_GATHER and leave SCATTER at 0.  Apart from these a context with the flag launches the stages
+ * one by one, also where others write the slice table in one launch (up to 4096 extents a side and 3072 slices), and no call leaves
+ * its stream: the figures are those of the stages, not of what a plan takes without the flag.
  * `ms_out` and `launches_out` are host memory with TENT_T_COUNT entries each. */
 int tent_get_timings(tent_ctx *ctx, float *ms_out, uint32_t *launches_out);
 
